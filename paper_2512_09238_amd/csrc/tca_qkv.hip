@@ -2,17 +2,17 @@
 // the projections Q = X W_Q, K = X W_K, V = X W_V of Sec. III for all heads in one launch, written
 // straight into the layouts tca_select / tca_prefill (head-major) or tca_decode (token-major) read.
 //
-// bf16: a dense contraction, so it runs on the matrix cores.  One workgroup (8 waves, two per SIMD)
-// forms a 256-feature x 256-token tile of Y^T = W X^T with v_mfma_f32_32x32x16_bf16; a wave owns 128
-// features (one head for d = 128, two for d = 64) x 64 tokens = 4 x 2 accumulator blocks, so that a
-// k-step of 16 takes six fragment reads for eight MFMAs.  The hidden dimension is walked in stages of
-// 64; the W and X slices of a stage (32 KB each) go global -> LDS with the LDS modifier of the
-// buffer loads (no staging registers), XOR-swizzled so that the 16-byte fragment reads are free of
-// bank conflicts, two stages resident.  The one barrier of a stage sits in front of the stage's
-// last k-step, whose fragments are in registers by then: after it no wave reads the stage any more,
-// so the copies of the stage after next start there, and the first fragments of the next stage are
-// read under the last MFMAs.  Features are the rows of the MFMA result, so a lane ends up with four
-// consecutive features of one token: one 8-byte store each.
+// bf16: a dense contraction, so it runs on the matrix cores.  qkv_mfma_kernel forms tiles of Y^T = W X^T
+// with v_mfma_f32_32x32x16_bf16, 256 features x 256 tokens per workgroup for long calls (8 waves, two per SIMD,
+// a wave owning 128 features x 64 tokens = 4 x 2 accumulator blocks, so that a k-step of 16 takes six
+// fragment reads for eight MFMAs) down to 64 x 64 for short ones.  The hidden dimension is walked in stages of
+// 64; the W and X slices of a stage go global -> LDS with the LDS modifier of the buffer loads (no staging
+// registers), XOR-swizzled so that the 16-byte fragment reads are free of bank conflicts, two to six stages
+// resident.  The one barrier of a stage sits in front of the stage's last k-step, whose fragments are in
+// registers by then: after it no wave reads the stage any more, so the copies of a later stage start there, and
+// the first fragments of the next stage are read under the last MFMAs.  Features are the rows of the MFMA
+// result, so a lane ends up with four consecutive features of one token: one 8-byte store each.
+// qkv_skinny_kernel takes the calls of a few rows, which are one pass over the weights.
 //
 // fp32: one thread per output, fp32 multiply-adds in the order of the hidden index (small cases and
 // an independent check of the bf16 kernel's indexing).
@@ -29,8 +29,6 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
 
-constexpr int kPF = 256;                         // features per workgroup
-constexpr int kPT = 256;                         // tokens per workgroup
 constexpr int kPK = 64;                          // the hidden size must be a multiple of this
 
 // Where the projected rows go.  Part 0 = Q, 1 = K, 2 = V; feature f belongs to head f / d of the
@@ -52,81 +50,109 @@ __device__ __forceinline__ void copy16_to_lds(__amdgpu_buffer_rsrc_t rsrc, int l
 
 __device__ __forceinline__ int part_of_head(const QkvOut& o, int hg) { return hg < o.first_head[1] ? 0 : hg < o.first_head[2] ? 1 : 2; }
 
-// WT: tokens per wave (64: eight waves, two per SIMD; 128: four waves, one per SIMD, each fragment of W
-// feeding four MFMAs).  BK: hidden elements per stage (32 or 64); NST: stages resident in LDS.
-// grid: 8 * groups * 4 * n_ft workgroups (see the id map below); block 2 * (256 / WT) * 64.
-template <int WT, int BK, int NST>
-__global__ __launch_bounds__(2 * (kPT / WT) * 64) __attribute__((amdgpu_waves_per_eu(128 / WT, 128 / WT)))
+// Stores the blocks of 32 features (from fblk on) x TB * 32 tokens (from t0 on) of a wave: the lane holds token
+// column lrow of block tb; register 4 q4 + j is feature 8 q4 + 4 hh + j.
+template <int TB>
+__device__ __forceinline__ void store_block(const QkvOut& out, const uint16_t* __restrict__ bias, int64_t fblk, int n_feat,
+                                            int d, int64_t t0, int64_t n_tok, int lrow, int hh, const f32x16_t (&acc)[TB]) {
+  if (fblk >= n_feat) return;                                // n_feat is a multiple of d >= 64: whole blocks
+  const int hg = (int)(fblk / d), e0 = (int)(fblk - (int64_t)hg * d);
+  const int p = part_of_head(out, hg);
+  uint16_t* const hbase = (uint16_t*)out.base[p] + (int64_t)(hg - out.first_head[p]) * out.head_stride[p] + e0;
+  float bs[4][4];
+#pragma unroll
+  for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bs[q4][j] = bias ? bf16_to_f32(bias[fblk + 8 * q4 + 4 * hh + j]) : 0.f;
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) {
+    const int64_t t = t0 + tb * 32 + lrow;
+    if (t >= n_tok) continue;
+    uint16_t* const row = hbase + t * out.token_stride[p];
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      bf16x4_t pk;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) pk[j] = (__bf16)(acc[tb][4 * q4 + j] + bs[q4][j]);
+      *reinterpret_cast<bf16x4_t*>(row + 8 * q4 + 4 * hh) = pk;
+    }
+  }
+}
+
+// A workgroup of NWF x NWT waves forms a tile of NWF * FBW * 32 features x NWT * TBW * 32 tokens, a wave FBW x TBW
+// accumulator blocks of it; stages of 64 hidden elements, NST of them resident in LDS.
+// Which shape takes which call: see tca_qkv_project.
+template <int FBW, int TBW, int NWF, int NWT, int NST>
+__global__ __launch_bounds__(NWF * NWT * 64) __attribute__((amdgpu_waves_per_eu(NWF * NWT / 4, NWF * NWT / 4)))
 void qkv_mfma_kernel(const uint16_t* __restrict__ W, const uint16_t* __restrict__ X, const uint16_t* __restrict__ bias,
                      int n_feat, int64_t n_tok, int hidden, int d, QkvOut out, int n_ft, int n_tt) {
-  constexpr int ROWB = BK * 2;                   // bytes of a tile row
-  constexpr int CPR = ROWB / 16;                 // 16-byte chunks per tile row (8 or 4)
-  constexpr int TILEB = kPF * ROWB;              // one operand's slice of a stage (kPF == kPT)
-  constexpr int STAGEB = 2 * TILEB;
-  constexpr int KS = BK / 16;                    // k-steps per stage
-  constexpr int TB = WT / 32;                    // token blocks per wave
-  constexpr int NW = 2 * (kPT / WT);             // waves
-  constexpr int NL = TILEB / 1024 / NW;          // wave-loads per wave, per operand and stage
-  static_assert(NST * STAGEB <= 160 * 1024 && NL >= 1 && 2 * NL < 64, "shape");
+  constexpr int NW = NWF * NWT;
+  constexpr int PF = NWF * FBW * 32, PT = NWT * TBW * 32;
+  constexpr int BK = kPK, ROWB = BK * 2;         // a stage is one 128-byte line of every row
+  constexpr int CPR = ROWB / 16;                 // 16-byte chunks per tile row
+  constexpr int WB = PF * ROWB, XB = PT * ROWB, STAGEB = WB + XB;
+  constexpr int NLW = WB / 1024 / NW, NLX = XB / 1024 / NW, NL = NLW + NLX;      // wave-loads per wave and stage
+  static_assert(NST * STAGEB <= 160 * 1024 && NLW >= 1 && NLX >= 1, "shape");
   __shared__ __attribute__((aligned(16))) unsigned char lds[NST * STAGEB];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // Workgroup ids go round-robin over the 8 XCDs.  An XCD takes every eighth token tile; the 32
-  // workgroups it runs at a time are 8 feature tiles x 4 token tiles, which walk the hidden dimension
-  // side by side: their L2 sees each W slice four times and each X slice eight times.
-  const int x = blockIdx.x & 7, u = blockIdx.x >> 3;
-  const int per_group = 4 * n_ft;
-  const int grp = u / per_group, in = u - grp * per_group;
-  const int ft = in >> 2, tt = (grp * 4 + (in & 3)) * 8 + x;
-  if (tt >= n_tt) return;
-  const int wf = wv & 1, wt = wv >> 1;           // the wave's 128 features and WT tokens inside the tile
-  const int64_t f0 = (int64_t)ft * kPF, t0 = (int64_t)tt * kPT;
-  const int rows_w = n_feat - f0 < kPF ? (int)(n_feat - f0) : kPF;
-  const int rows_x = n_tok - t0 < kPT ? (int)(n_tok - t0) : kPT;
+  // Workgroup ids go round-robin over the 8 XCDs.  The tiles are walked in groups of four token tiles, feature
+  // tiles inside a group, and XCD x takes the x-th eighth of that sequence without holes: the 32 workgroups it
+  // runs at a time are 8 feature tiles x 4 token tiles, which go through the hidden dimension side by side, so
+  // that their L2 sees a W slice four times and an X slice eight times.  (Ids that return at once must not be
+  // spread among the others: an XCD deals its ids to its CUs in order.)
+  const int n_items = n_ft * n_tt, per_xcd = (n_items + 7) >> 3;
+  const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (item >= n_items) return;
+  const int grp = item / (4 * n_ft), in = item - grp * (4 * n_ft);
+  const int gw = n_tt - grp * 4 < 4 ? n_tt - grp * 4 : 4;          // token tiles of this group
+  const int ft = in / gw, tt = grp * 4 + (in - ft * gw);
+  const int wf = wv % NWF, wt = wv / NWF;        // the wave's place inside the tile
+  const int64_t f0 = (int64_t)ft * PF, t0 = (int64_t)tt * PT;
+  const int rows_w = n_feat - f0 < PF ? (int)(n_feat - f0) : PF;
+  const int rows_x = n_tok - t0 < PT ? (int)(n_tok - t0) : PT;
 
   // ---- copies.  Chunk c of tile row r sits at chunk position c ^ swz(r), where swz makes the 16 rows a
   // quarter-wave reads at one chunk column fall into distinct banks.  Rows past the end of W or X read
   // as zero (range check of the descriptor).
-  auto swz_of = [](int r) { return CPR == 8 ? (r >> 1) & 7 : (r >> 2) & 3; };
+  auto swz_of = [](int r) { return (r >> 1) & 7; };
   constexpr int kRsrcFlags = 0x00020000;         // raw buffer, 32-bit data format
   const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void*)(W + f0 * hidden), 0, rows_w * hidden * 2, kRsrcFlags);
   const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void*)(X + t0 * hidden), 0, rows_x * hidden * 2, kRsrcFlags);
-  int lo[NL];                                    // this lane's byte offset into the operand, per wave-load (same for W and X)
+  int low[NLW], lox[NLX];                        // this lane's byte offsets into the operands, per wave-load
+  auto lane_offset = [&](int q) {                // 16-byte chunk of the LDS tile this lane fills in wave-load q
+    const int cid = q * 64 + lane, r = cid / CPR, pch = cid % CPR;
+    return r * hidden * 2 + ((pch ^ swz_of(r)) << 4);
+  };
 #pragma unroll
-  for (int j = 0; j < NL; ++j) {
-    const int cid = (wv * NL + j) * 64 + lane;   // 16-byte chunk of the LDS tile this lane fills
-    const int r = cid / CPR, pch = cid % CPR;
-    lo[j] = r * hidden * 2 + ((pch ^ swz_of(r)) << 4);
-  }
-  auto issue = [&](int kt, int s) {
+  for (int j = 0; j < NLW; ++j) low[j] = lane_offset(wv * NLW + j);
 #pragma unroll
-    for (int j = 0; j < NL; ++j) {
-      unsigned char* dst = lds + s * STAGEB + (wv * NL + j) * 1024;
-      copy16_to_lds(rs_w, lo[j], kt * ROWB, dst);
-      copy16_to_lds(rs_x, lo[j], kt * ROWB, dst + TILEB);
-    }
+  for (int j = 0; j < NLX; ++j) lox[j] = lane_offset(wv * NLX + j);
+  // copy i of this wave's share of stage kt into place sp, the operands taking turns
+  constexpr int kBoth = NLW < NLX ? NLW : NLX;
+  auto issue_one = [&](int kt, int sp, int i) {
+    unsigned char* const dst = lds + sp * STAGEB;
+    const bool is_w = i < 2 * kBoth ? (i & 1) == 0 : NLW > NLX;
+    const int j = i < 2 * kBoth ? i >> 1 : i - kBoth;
+    if (is_w) copy16_to_lds(rs_w, low[j < NLW ? j : 0], kt * ROWB, dst + (wv * NLW + j) * 1024);
+    else copy16_to_lds(rs_x, lox[j < NLX ? j : 0], kt * ROWB, dst + WB + (wv * NLX + j) * 1024);
   };
 
   // ---- fragments: lane = (row lane & 31, k half lane >> 5) of a 32-row block
+  constexpr int KS = BK / 16;                    // k-steps per stage
   const int lrow = lane & 31, hh = lane >> 5;
   int fo[KS];                                    // byte offset inside a block of 32 rows, per k-step of a stage
 #pragma unroll
   for (int kk = 0; kk < KS; ++kk) fo[kk] = lrow * ROWB + (((kk * 2 + hh) ^ swz_of(lrow)) << 4);
-  const unsigned char* const wbase = lds + wf * (128 * ROWB);
-  const unsigned char* const xbase = lds + TILEB + wt * (WT * ROWB);
-  f32x16_t acc[4][TB];
+  const unsigned char* const wbase = lds + wf * (FBW * 32 * ROWB);
+  const unsigned char* const xbase = lds + WB + wt * (TBW * 32 * ROWB);
+  f32x16_t acc[FBW][TBW];
 #pragma unroll
-  for (int fb = 0; fb < 4; ++fb)
+  for (int fb = 0; fb < FBW; ++fb)
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb)
+    for (int tb = 0; tb < TBW; ++tb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[fb][tb][i] = 0.f;
-  auto mma = [&](const bf16x8_t (&a)[4], const bf16x8_t (&b)[TB]) {
-#pragma unroll
-    for (int fb = 0; fb < 4; ++fb)
-#pragma unroll
-      for (int tb = 0; tb < TB; ++tb) acc[fb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[fb], b[tb], acc[fb][tb], 0, 0, 0);
-  };
 
   // Stage kt lives in place kt % NST.  The loop is cut at the barriers: a stretch starts behind the
   // barrier of stage kt - 1 with that stage's last k-step (its fragments are in registers), under
@@ -136,98 +162,166 @@ void qkv_mfma_kernel(const uint16_t* __restrict__ W, const uint16_t* __restrict_
   // multiplies zeros for the stage that is not there, the last ones copy the last stage again instead
   // of stages that are not there), because every further copy of it costs registers the accumulators
   // need.  The order of a stretch's instructions is written out and fenced (sched_barrier): one MFMA,
-  // behind every second one a fragment read of the next k-step in the order of need, behind each of the
-  // stretch's first ones a copy.  Left to itself the compiler issues the copies in one burst and the
+  // behind it a fragment read of the next k-step in the order of need and, behind each of the stretch's first
+  // ones, a copy.  Left to itself the compiler issues the copies in one burst and the
   // fragment reads in clumps (5 % slower, as is an order merely suggested through sched_group_barrier).
+  // The barrier is the bare instruction behind a wait of our own: a __syncthreads() would wait for every
+  // copy in flight, whatever NST is.
   static_assert(KS == 4 && NST >= 2, "the stretch below is four k-steps");
   const int nk = hidden / BK;
-  constexpr int kGroup = 2 * NL;                 // loads of one stage, per wave
-  constexpr int kAhead = (NST - 2) * kGroup;     // loads that may still be in flight when the next stage must be in
+  constexpr int kAhead = (NST - 2) * NL;         // loads that may still be in flight when the next stage must be in
   static_assert(kAhead < 64, "vmcnt is six bits wide");
-  constexpr int kWaitNext = 0x0F70 | (kAhead & 15) | ((kAhead >> 4) << 14);   // vmcnt: bits [3:0] and [15:14]
-  bf16x8_t a0[4], b0[TB], a1[4], b1[TB];
+  // vmcnt(kAhead) (bits [3:0] and [15:14]); lgkmcnt(0): this wave's reads of the stage it leaves have returned
+  constexpr int kWaitNext = 0x0070 | (kAhead & 15) | ((kAhead >> 4) << 14);
+  bf16x8_t a0[FBW], b0[TBW], a1[FBW], b1[TBW];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
 #pragma unroll
-    for (int fb = 0; fb < 4; ++fb) a1[fb][i] = (__bf16)0.f;
+    for (int fb = 0; fb < FBW; ++fb) a1[fb][i] = (__bf16)0.f;
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) b1[tb][i] = (__bf16)0.f;
+    for (int tb = 0; tb < TBW; ++tb) b1[tb][i] = (__bf16)0.f;
   }
 #pragma unroll
-  for (int j = 0; j + 1 < NST; ++j) issue(j < nk ? j : nk - 1, j);
+  for (int j = 0; j + 1 < NST; ++j)
+#pragma unroll
+    for (int i = 0; i < NL; ++i) issue_one(j < nk ? j : nk - 1, j, i);
   __builtin_amdgcn_s_waitcnt(kWaitNext);         // stage 0 is in
-  __syncthreads();
+  __builtin_amdgcn_s_barrier();
   int s = 0;                                     // place of stage kt
   // fragment i of k-step kk of the stage in place sp, in the order the MFMAs need them: W block 0, the X
   // blocks, the other W blocks
-  auto read_one = [&](int sp, int kk, int i, bf16x8_t (&a)[4], bf16x8_t (&b)[TB]) {
+  auto read_one = [&](int sp, int kk, int i, bf16x8_t (&a)[FBW], bf16x8_t (&b)[TBW]) {
     if (i == 0) a[0] = *reinterpret_cast<const bf16x8_t*>(wbase + sp * STAGEB + fo[kk]);
-    else if (i <= TB) b[i - 1] = *reinterpret_cast<const bf16x8_t*>(xbase + sp * STAGEB + (i - 1) * (32 * ROWB) + fo[kk]);
-    else a[i - TB] = *reinterpret_cast<const bf16x8_t*>(wbase + sp * STAGEB + (i - TB) * (32 * ROWB) + fo[kk]);
+    else if (i <= TBW) b[i - 1] = *reinterpret_cast<const bf16x8_t*>(xbase + sp * STAGEB + (i - 1) * (32 * ROWB) + fo[kk]);
+    else a[i - TBW] = *reinterpret_cast<const bf16x8_t*>(wbase + sp * STAGEB + (i - TBW) * (32 * ROWB) + fo[kk]);
   };
-  // copy i of this wave's share of stage kt into place sp
-  auto issue_one = [&](int kt, int sp, int i) {
-    const int j = i >> 1;
-    unsigned char* dst = lds + sp * STAGEB + (wv * NL + j) * 1024;
-    if (i & 1) copy16_to_lds(rs_x, lo[j], kt * ROWB, dst + TILEB);
-    else copy16_to_lds(rs_w, lo[j], kt * ROWB, dst);
-  };
-  // one k-step: the MFMAs of the current fragments (ca, cb); the reads of the fragments (na, nb) of k-step
-  // kk of place sp; with COPY the copies of stage ckt into place cs
-  constexpr int NM = 4 * TB, NR = 4 + TB, RSTEP = NM / NR > 1 ? 2 : 1;
-  auto kstep = [&](const bf16x8_t (&ca)[4], const bf16x8_t (&cb)[TB], bf16x8_t (&na)[4], bf16x8_t (&nb)[TB], int sp, int kk,
-                   auto copy_tag, int ckt, int cs) {
-    constexpr bool COPY = decltype(copy_tag)::value;
+  // k-step number n of a stretch: the MFMAs of the current fragments (ca, cb); the reads of the fragments
+  // (na, nb) of k-step kk of place sp; this k-step's share of the copies of stage ckt into place cs
+  constexpr int NM = FBW * TBW, NR = FBW + TBW;
+  auto kstep = [&](const bf16x8_t (&ca)[FBW], const bf16x8_t (&cb)[TBW], bf16x8_t (&na)[FBW], bf16x8_t (&nb)[TBW], int sp, int kk,
+                   auto n_tag, int ckt, int cs) {
+    constexpr int N = decltype(n_tag)::value;
 #pragma unroll
     for (int j = 0; j < NM; ++j) {
-      const int fb = j / TB, tb = j % TB;
+      const int fb = j / TBW, tb = j % TBW;
       acc[fb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ca[fb], cb[tb], acc[fb][tb], 0, 0, 0);
-      if (j % RSTEP == 0 && j / RSTEP < NR) read_one(sp, kk, j / RSTEP, na, nb);
-      if (COPY && j < kGroup) issue_one(ckt, cs, j);
+#pragma unroll
+      for (int i = j; i < (j + 1 < NM ? j + 1 : NR); ++i)
+        if (i < NR) read_one(sp, kk, i, na, nb);
+      if (N * NM + j < NL) issue_one(ckt, cs, N * NM + j);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
+  static_assert(NL <= 4 * NM, "the copies of a stage fit its stretch");
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
   for (int kt = 0; kt < nk; ++kt) {
     const int s_prev = s == 0 ? NST - 1 : s - 1;
     const int ckt = kt + NST - 1 < nk ? kt + NST - 1 : nk - 1;
     __builtin_amdgcn_sched_barrier(0);
-    kstep(a1, b1, a0, b0, s, 0, std::true_type{}, ckt, s_prev);          // the last k-step of stage kt - 1
-    kstep(a0, b0, a1, b1, s, 1, std::false_type{}, 0, 0);
-    kstep(a1, b1, a0, b0, s, 2, std::false_type{}, 0, 0);
-    kstep(a0, b0, a1, b1, s, 3, std::false_type{}, 0, 0);
+    kstep(a1, b1, a0, b0, s, 0, I0{}, ckt, s_prev);          // the last k-step of stage kt - 1
+    kstep(a0, b0, a1, b1, s, 1, I1{}, ckt, s_prev);
+    kstep(a1, b1, a0, b0, s, 2, I2{}, ckt, s_prev);
+    kstep(a0, b0, a1, b1, s, 3, I3{}, ckt, s_prev);
     __builtin_amdgcn_s_waitcnt(kWaitNext);       // this wave's share of stage kt + 1 has landed
-    __syncthreads();                             // everyone's has, and nobody reads stage kt any more
+    __builtin_amdgcn_s_barrier();                // everyone's has, and nobody reads stage kt any more
     s = s + 1 == NST ? 0 : s + 1;
   }
-  mma(a1, b1);                                   // the last k-step of the last stage
+#pragma unroll
+  for (int fb = 0; fb < FBW; ++fb)               // the last k-step of the last stage
+#pragma unroll
+    for (int tb = 0; tb < TBW; ++tb) acc[fb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[fb], b1[tb], acc[fb][tb], 0, 0, 0);
   __builtin_amdgcn_s_waitcnt(0x0F70);            // no copy into this workgroup's LDS may outlive it
+#pragma unroll
+  for (int fb = 0; fb < FBW; ++fb)
+    store_block<TBW>(out, bias, f0 + wf * (FBW * 32) + fb * 32, n_feat, d, t0 + wt * (TBW * 32), n_tok, lrow, hh, acc[fb]);
+}
 
-  // ---- epilogue: lane holds token column lrow of block tb; register 4 q4 + j is feature 8 q4 + 4 hh + j of block fb
+// ---- calls of few rows (a decoding batch): bound by one pass over the weights
+//
+// One workgroup of eight waves forms FB * 16 features x TB * 16 tokens with v_mfma_f32_16x16x32_bf16.  The
+// waves split the hidden dimension in units of 64 elements (one 128-byte line of a weight row each),
+// interleaved, and load their fragments straight from global memory: nothing is reused inside a workgroup
+// that would pay for a stage in LDS, and a wave has U units of loads in flight at once, which is what keeps
+// HBM busy.  A lane's chunks of a unit are kb and kb + 4 (kb = lane / 16): the order of the hidden index
+// inside a unit does not matter as long as W and X agree.  The waves' fp32 sums are added through LDS in
+// wave order.
+template <int FB, int TB, int U>
+__global__ __launch_bounds__(512) void qkv_skinny_kernel(const uint16_t* __restrict__ W, const uint16_t* __restrict__ X,
+                                                         const uint16_t* __restrict__ bias, int64_t n_tok, int hidden,
+                                                         int d, QkvOut out) {
+  typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+  constexpr int NW = 8;
+  __shared__ __attribute__((aligned(16))) f32x4_t red[NW][FB * TB][64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, kb = lane >> 4;
+  const int f0 = blockIdx.x * (FB * 16);           // n_feat is a multiple of 64
+  const int64_t t0 = (int64_t)blockIdx.y * (TB * 16);
+  const uint16_t* wp[FB];
+  const uint16_t* xp[TB];
 #pragma unroll
-  for (int fb = 0; fb < 4; ++fb) {
-    const int64_t fblk = f0 + wf * 128 + fb * 32;            // first feature of the block (uniform)
-    if (fblk >= n_feat) continue;                            // n_feat is a multiple of d >= 64: whole blocks
-    const int hg = (int)(fblk / d), e0 = (int)(fblk - (int64_t)hg * d);
-    const int p = part_of_head(out, hg);
-    uint16_t* const hbase = (uint16_t*)out.base[p] + (int64_t)(hg - out.first_head[p]) * out.head_stride[p] + e0;
-    float bs[4][4];
+  for (int fb = 0; fb < FB; ++fb) wp[fb] = W + (size_t)(f0 + fb * 16 + r) * hidden + kb * 8;
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4)
+  for (int tb = 0; tb < TB; ++tb) {
+    const int64_t t = t0 + tb * 16 + r;
+    xp[tb] = X + (size_t)(t < n_tok ? t : n_tok - 1) * hidden + kb * 8;      // rows past the end repeat the last, never stored
+  }
+  f32x4_t acc[FB][TB];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) bs[q4][j] = bias ? bf16_to_f32(bias[fblk + 8 * q4 + 4 * hh + j]) : 0.f;
+  for (int fb = 0; fb < FB; ++fb)
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-      const int64_t t = t0 + wt * WT + tb * 32 + lrow;
-      if (t >= n_tok) continue;
-      uint16_t* const row = hbase + t * out.token_stride[p];
+    for (int tb = 0; tb < TB; ++tb) acc[fb][tb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int nu = hidden >> 6;
+  auto units = [&](int u0, auto n_tag) {           // units u0, u0 + 8, .. (N of them), all inside the hidden dimension
+    constexpr int N = decltype(n_tag)::value;
+    bf16x8_t w[N][2][FB], x[N][2][TB];
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        bf16x4_t pk;
+    for (int i = 0; i < N; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) pk[j] = (__bf16)(acc[fb][tb][4 * q4 + j] + bs[q4][j]);
-        *reinterpret_cast<bf16x4_t*>(row + 8 * q4 + 4 * hh) = pk;
+      for (int s = 0; s < 2; ++s) {
+        const int k = (u0 + i * NW) * 64 + s * 32;
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb) w[i][s][fb] = *reinterpret_cast<const bf16x8_t*>(wp[fb] + k);
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) x[i][s][tb] = *reinterpret_cast<const bf16x8_t*>(xp[tb] + k);
       }
-    }
+    __builtin_amdgcn_sched_barrier(0);             // all of them requested before the first is used
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+          for (int tb = 0; tb < TB; ++tb)
+            acc[fb][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i][s][fb], x[i][s][tb], acc[fb][tb], 0, 0, 0);
+  };
+  int u = wv;
+  for (; u + (U - 1) * NW < nu; u += U * NW) units(u, std::integral_constant<int, U>{});
+  for (; u < nu; u += NW) units(u, std::integral_constant<int, 1>{});
+#pragma unroll
+  for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) red[wv][fb * TB + tb][lane] = acc[fb][tb];
+  __syncthreads();
+  // lane (token r, kb) of a block holds the features 4 kb .. 4 kb + 3 of one token
+  for (int g = tid; g < FB * TB * 64; g += 512) {
+    const int blk = g >> 6, ln = g & 63;
+    f32x4_t s = red[0][blk][ln];
+#pragma unroll
+    for (int x = 1; x < NW; ++x) s += red[x][blk][ln];
+    const int f = f0 + (blk / TB) * 16 + 4 * (ln >> 4);
+    const int64_t t = t0 + (blk % TB) * 16 + (ln & 15);
+    if (t >= n_tok) continue;
+    const int hg = f / d, e0 = f - hg * d, p = part_of_head(out, hg);
+    uint16_t* const row = (uint16_t*)out.base[p] + (int64_t)(hg - out.first_head[p]) * out.head_stride[p] + t * out.token_stride[p] + e0;
+    bf16x4_t pk;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) pk[j] = (__bf16)(s[j] + (bias ? bf16_to_f32(bias[f + j]) : 0.f));
+    *reinterpret_cast<bf16x4_t*>(row) = pk;
   }
 }
 
@@ -253,11 +347,33 @@ __global__ __launch_bounds__(256) void qkv_rows_kernel(const T* __restrict__ W, 
 
 using namespace tca;
 
-// The shape in use: 64 tokens per wave (eight waves), stages of 64 hidden elements, two of them resident.
-// Measured at 131072 rows, hidden 4096, 6144 features: 128 tokens per wave (four waves, a third fewer
-// fragment reads) 8 % slower; stages of 32 elements, three to five resident (a copy has longer to
-// arrive, twice the barriers) 15 % slower.
-static constexpr int kWT = 64, kBK = 64, kNST = 2;
+namespace {
+constexpr int kCUs = 256;
+
+struct QkvCall {
+  const uint16_t *W, *X, *bias;
+  int n_feat;
+  int64_t n_tok;
+  int hidden, d;
+  QkvOut out;
+  hipStream_t st;
+};
+
+template <int FB, int TB, int U>
+void launch_skinny(const QkvCall& c) {
+  const dim3 grid((unsigned)(c.n_feat / (16 * FB)), (unsigned)((c.n_tok + 16 * TB - 1) / (16 * TB)));      // n_feat is a multiple of 64
+  hipLaunchKernelGGL((qkv_skinny_kernel<FB, TB, U>), grid, dim3(512), 0, c.st, c.W, c.X, c.bias, c.n_tok, c.hidden, c.d, c.out);
+}
+
+template <int FBW, int TBW, int NWF, int NWT, int NST>
+void launch_tiles(const QkvCall& c) {
+  constexpr int PF = NWF * FBW * 32, PT = NWT * TBW * 32;
+  const int n_ft = (c.n_feat + PF - 1) / PF, n_tt = (int)((c.n_tok + PT - 1) / PT);
+  const unsigned n_wg = 8u * (unsigned)(((int64_t)n_ft * n_tt + 7) / 8);
+  hipLaunchKernelGGL((qkv_mfma_kernel<FBW, TBW, NWF, NWT, NST>), dim3(n_wg), dim3(NWF * NWT * 64), 0, c.st, c.W, c.X, c.bias,
+                     c.n_feat, c.n_tok, c.hidden, c.d, c.out, n_ft, n_tt);
+}
+}  // namespace
 
 extern "C" int tca_qkv_project(const tca_params* prm, const void* X, int64_t n_tokens, int hidden, const void* W,
                                const void* bias, void* Q, int64_t q_token_stride, int64_t q_head_stride, void* K,
@@ -286,17 +402,48 @@ extern "C" int tca_qkv_project(const tca_params* prm, const void* X, int64_t n_t
                        (const float*)W, (const float*)X, (const float*)bias, n_feat, hidden, d, out);
   } else {
     if (hidden % kPK) return fail(TCA_ERR_UNSUPPORTED, "tca_qkv_project (bf16): hidden=%d is not a multiple of %d", hidden, kPK);
-    if ((int64_t)kPF * hidden * 2 > INT32_MAX) return fail(TCA_ERR_UNSUPPORTED, "tca_qkv_project (bf16): hidden=%d", hidden);
+    if ((int64_t)256 * hidden * 2 > INT32_MAX) return fail(TCA_ERR_UNSUPPORTED, "tca_qkv_project (bf16): hidden=%d", hidden);
     if ((q_token_stride | q_head_stride | kv_token_stride | kv_head_stride) & 3 || ((uintptr_t)Q | (uintptr_t)K | (uintptr_t)V) & 7 ||
         ((uintptr_t)X | (uintptr_t)W) & 15)
       return fail(TCA_ERR_INVALID, "tca_qkv_project (bf16): strides must be multiples of 4 elements, outputs 8-byte and inputs 16-byte aligned");
-    const int n_ft = (n_feat + kPF - 1) / kPF;
-    const int64_t n_tt = (n_tokens + kPT - 1) / kPT;
-    const int64_t groups = ((n_tt + 7) / 8 + 3) / 4;
-    const int64_t n_wg = 8 * groups * 4 * n_ft;
-    if (n_wg > INT32_MAX) return fail(TCA_ERR_UNSUPPORTED, "tca_qkv_project: n_tokens=%lld", (long long)n_tokens);
-    hipLaunchKernelGGL((qkv_mfma_kernel<kWT, kBK, kNST>), dim3((unsigned)n_wg), dim3(2 * (kPT / kWT) * 64), 0, st, (const uint16_t*)W, (const uint16_t*)X,
-                       (const uint16_t*)bias, n_feat, n_tokens, hidden, d, out, n_ft, (int)n_tt);
+    const QkvCall call{(const uint16_t*)W, (const uint16_t*)X, (const uint16_t*)bias, n_feat, n_tokens, hidden, d, out, st};
+    // Up to 32 rows one pass over the weights is all there is to do.  Measured at 6144 features, hidden 4096 (50 MB of
+    // weights): 16 rows 262 -> 15.8 us, 32 rows 265 -> 19.3 us (tiles of 256 x 256 before); 10240 features, hidden
+    // 8192: 16 rows 822 -> 44 us.  Four feature blocks per workgroup instead of two halve the reads of X and pay
+    // once two would make more workgroups than CUs (44 against 52 us there; 21.7 against 15.8 us at 6144).
+    const bool wide = n_feat / 32 > kCUs;
+    if (n_tokens <= 16) {
+      if (wide) launch_skinny<4, 1, 4>(call); else launch_skinny<2, 1, 4>(call);
+    } else if (n_tokens <= 32) {
+      if (wide) launch_skinny<4, 2, 2>(call); else launch_skinny<2, 2, 4>(call);
+    } else {
+      // Tiles.  What a workgroup waits for is the passage of its stages from L2 into LDS, about 24 bytes per clock and
+      // CU whatever the shape and however many stages are resident: a call takes (rounds of 256 workgroups) x
+      // (features + tokens of the tile), and the 256 x 256 tile, where the matrix pipe takes as long, 1.35 times that.
+      // The shape with the smallest product is taken (the larger tile if equal); us measured at 6144 features,
+      // hidden 4096 (64x64 / 64x128 / 128x128 / 128x256 / 256x256), the choice in brackets:
+      //   128 rows [23] 31 42 47 98;  256: 41 [31] 41 58 107;  413: 54 49 [36] 52 103;  1024: 119 84 80 [63] 106;
+      //   1500: 129 110 102 104 [91];  4096: 338 272 221 [185] 199;  8192: 687 574 459 379 [342]
+      // (256 x 256 alone, with ids that skipped CUs when the token tiles were not a multiple of 32, took 290 - 315
+      // us up to 1024 rows and 240 us at 2048).
+      constexpr int kTiles[5][2] = {{256, 256}, {128, 256}, {128, 128}, {64, 128}, {64, 64}};      // features, tokens
+      int best = -1;
+      int64_t best_cost = 0;
+      for (int i = 0; i < 5; ++i) {
+        const int64_t items = (int64_t)((n_feat + kTiles[i][0] - 1) / kTiles[i][0]) * ((n_tokens + kTiles[i][1] - 1) / kTiles[i][1]);
+        if (items > INT32_MAX - 8) continue;       // the grid, rounded up to a multiple of 8
+        const int64_t cost = (items + kCUs - 1) / kCUs * (i == 0 ? 690 : kTiles[i][0] + kTiles[i][1]);
+        if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
+      }
+      switch (best) {
+        case 0: launch_tiles<4, 2, 2, 4, 2>(call); break;
+        case 1: launch_tiles<2, 2, 2, 4, 3>(call); break;
+        case 2: launch_tiles<2, 1, 2, 4, 4>(call); break;
+        case 3: launch_tiles<1, 1, 2, 4, 4>(call); break;
+        case 4: launch_tiles<1, 1, 2, 2, 6>(call); break;
+        default: return fail(TCA_ERR_UNSUPPORTED, "tca_qkv_project: n_tokens=%lld", (long long)n_tokens);
+      }
+    }
   }
   TCA_HIP_CHECK(hipGetLastError());
   return TCA_OK;

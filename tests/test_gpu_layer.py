@@ -210,6 +210,26 @@ def test_qkv_project_random_shapes(tb, bufs, case):
     test_qkv_project_matches_oracle(tb, bufs, case)
 
 
+QKV_SHAPES = [
+    # every kernel and tile shape the bf16 call chooses between (by rows, and features times rows), at its edges
+    (4, 2, 128, 4160, 16, "bf16", True, "token", 2),      # up to 16 rows: 65 units over 8 waves, batches of four and a rest
+    (64, 8, 128, 320, 7, "bf16", True, "token", 0),       # the same, more than 8192 features
+    (4, 2, 128, 576, 32, "bf16", False, "token", 0),      # 17 to 32 rows
+    (64, 8, 128, 64, 17, "bf16", True, "head", 1),
+    (4, 2, 128, 448, 33, "bf16", True, "head", 0),        # 64 x 64 tiles, six stages resident, seven walked
+    (32, 8, 128, 128, 256, "bf16", True, "head", 0),      # 64 x 128, fewer stages than places
+    (32, 8, 128, 192, 413, "bf16", True, "head", 0),      # 128 x 128, last token tile ragged
+    (32, 8, 128, 320, 724, "bf16", False, "head", 0),     # 128 x 256
+    (32, 8, 128, 64, 3000, "bf16", True, "head", 0),      # 128 x 256, three groups of token tiles
+    (32, 8, 128, 256, 1500, "bf16", True, "head", 0),     # 256 x 256, a group of two token tiles behind one of four
+]
+
+
+@pytest.mark.parametrize("case", QKV_SHAPES, ids=lambda c: f"hq{c[0]}-hkv{c[1]}-d{c[2]}-hid{c[3]}-n{c[4]}-{c[5]}-{c[7]}")
+def test_qkv_project_every_tile_shape(tb, bufs, case):
+    test_qkv_project_matches_oracle(tb, bufs, case)
+
+
 def test_qkv_project_refuses_what_it_cannot_do(tb, bufs):
     prm = H.params_for(tb, 4, 2, 128, 16, 16, "bf16")
     x = wl.projection_inputs(4, 2, 128, 96, 8, "bf16", 5)
