@@ -57,7 +57,7 @@ static int prefill_checked(const tca_params* prm, const void* Q, int64_t q_pos0,
   if (offs[0] != 0) return fail(TCA_ERR_INVALID, "%s: offs[0] must be 0", who);
   for (int h = 0; h < sel_heads(prm); ++h)
     if (offs[h + 1] < offs[h]) return fail(TCA_ERR_INVALID, "%s: offs not ascending at %d", who, h);
-  const size_t need = tca_prefill_workspace_bytes(prm, n_queries, offs[sel_heads(prm)]);
+  const size_t need = prm->dtype == TCA_BF16 ? prefill_mfma_workspace_need(prm, n_queries, offs[sel_heads(prm)]) : 0;
   if (need && (!ws || ws_bytes < need || ((uintptr_t)ws & 255)))
     return fail(TCA_ERR_WORKSPACE, "%s: workspace needs %zu bytes, 256-byte aligned", who, need);
   if (n_queries == 0) return TCA_OK;
@@ -69,7 +69,7 @@ static int prefill_checked(const tca_params* prm, const void* Q, int64_t q_pos0,
   } else {
     rc = launch_prefill_mfma(prm, (const bf16_t*)Q, q_pos0, n_queries, (const bf16_t*)K, (const bf16_t*)V,
                              kv_stride, idx, (const bf16_t*)Kg, (const bf16_t*)Vg, offs, n_rows,
-                             (bf16_t*)O, lse, ws, st, part);
+                             (bf16_t*)O, lse, ws, ws_bytes, st, part);
   }
   if (rc) return rc;
   TCA_HIP_CHECK(hipGetLastError());

@@ -38,6 +38,7 @@
 // quotient is the same, and the common tile needs no maximum at all.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 #include <vector>
 
@@ -57,7 +58,20 @@ struct PrefillHeads {
   int64_t offs[TCA_MAX_HEADS + 1];      // row offsets of the heads' regions
   int32_t tile_off[TCA_MAX_HEADS + 1];  // V^T tile offsets of the heads' regions
   int32_t xcd_start[9];                 // the range of the (head, query tile) sequence each XCD works through
+  int32_t order;                        // how an XCD walks its range: see the ids in prefill_mfma_kernel
+  uint8_t perm[TCA_MAX_HEADS];          // order 1 and 2: the heads in the sequence
 };
+
+// Calls with too few query tiles for the chip: the tiles of a (head, query tile) item are cut into chunks of
+// `chunk` tiles, one workgroup each, whose unnormalised results merge_split_kernel combines.
+struct SplitPlan {
+  float* part;                          // per workgroup: the O^T accumulators, then m and l of its queries
+  int32_t chunk;                        // tiles per chunk, even
+  int32_t run;                          // consecutive workgroups that go to one XCD
+  int32_t item_start[TCA_MAX_HEADS + 1];  // head h's workgroups: [item_start[h], item_start[h + 1]), chunk-major, query tiles inside
+};
+struct NoSplit {};
+template <int D> constexpr size_t split_floats() { return 128 * (size_t)(D + 2); }      // per workgroup of 128 queries
 
 // position p (0..63) inside a stored V^T tile -> key (0..63) of the tile
 __host__ __device__ inline int vt_key_of_pos(int p) {
@@ -205,6 +219,13 @@ __device__ __forceinline__ void settle_acc(f32x16_t (&o)[N]) {
     asm volatile("s_nop 15\n\ts_nop 7" : "+a"(o[0]), "+a"(o[1]));
 }
 
+// Two four-wave workgroups share a CU, and an XCD deals its ids to its 32 CUs in turn: every second run of 32 ids is
+// taken backwards, so that of a sequence sorted by length the longest and the shortest meet on a CU.
+__device__ __forceinline__ int pair_up(int u, int n) {
+  const int b = u & ~31, len = n - b < 32 ? n - b : 32;
+  return (u & 32) ? b + len - 1 - (u - b) : u;
+}
+
 // Cross-half exchange: returns max over the two 32-lane halves, in every lane.
 __device__ __forceinline__ float half_max(float v) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -277,14 +298,16 @@ __device__ __forceinline__ void copy16_to_lds(__amdgpu_buffer_rsrc_t rsrc, int l
 // GATHER: no compacted K exists; the K rows of a region tile are fetched from the dense K through
 // idx (the position of every row is read one iteration ahead and becomes the lane's offset of the
 // tile copy); the V^T tiles were built through idx by the pre-pass.
-template <int D, int NW, int QB, bool GATHER>
+// SPLIT: the workgroup walks one chunk of the item's tiles and leaves its accumulators, m and l to the merge.
+template <int D, int NW, int QB, bool GATHER, bool SPLIT = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2 / QB, 2 / QB)))
 void prefill_mfma_kernel(
     const uint16_t* __restrict__ Q, int64_t q_pos0, int64_t n_queries, const uint16_t* __restrict__ K,
     int64_t kv_stride, const int32_t* __restrict__ idx, const uint16_t* __restrict__ Kg,
     const int32_t* __restrict__ n_rows, const uint16_t* __restrict__ Vgt, const uint16_t* __restrict__ Vt,
     int64_t dense_tile0, int dense_tiles, PrefillHeads ph, int Hq, int G, int GS, int w, float scale,
-    uint16_t* __restrict__ O, float* __restrict__ lse, unsigned long long* __restrict__ clk, int part) {
+    uint16_t* __restrict__ O, float* __restrict__ lse, unsigned long long* __restrict__ clk, int part,
+    std::conditional_t<SPLIT, SplitPlan, NoSplit> sp) {
   // part: TCA_PART_ALL, or one of the two key subsets alone (TCA_PART_WINDOW: the dense window;
   // TCA_PART_GLOBAL: the region), each normalised by itself, to be merged through lse
   constexpr int KK = D / 16;             // MFMA k-steps over the head dimension
@@ -318,19 +341,49 @@ void prefill_mfma_kernel(
   // sequence (head-major, a head's query tiles longest first) is cut instead into eight ranges of equal
   // estimated work (xcd_start, from the host).  An XCD takes the piece of the head its range ends in
   // first (that head's longest tiles) and the rest in order, so that it ends on a head's shortest tiles.
+  // That is order 0.  With few rounds of workgroups the order matters more than the L2: order 1 takes the query
+  // tiles longest first and the XCD's heads inside, order 2 the heads longest first (plan_xcds chooses).
   int h, qtile;
-  if ((Hq & 7) == 0) {
-    const int x = bid & 7, u = bid >> 3;           // XCD, position in the XCD's own sequence
+  int t_first = 0;                                 // the first tile this workgroup walks
+  [[maybe_unused]] int item = 0;
+  if constexpr (SPLIT) {
+    // The order is chunk-major inside a head, so that the query tiles that read the same keys are neighbours; runs
+    // of them are dealt to the XCDs in turn: a run shares an L2, and the chunks that are short or empty (where the
+    // queries see less than the longest one does) spread over all XCDs.
+    const int u = bid >> 3, turn = u / sp.run;
+    item = (turn * 8 + (bid & 7)) * sp.run + (u - turn * sp.run);
+    if (item >= sp.item_start[Hq]) return;
+    h = 0;
+    for (int step = 64; step > 0; step >>= 1)
+      if (h + step < Hq && sp.item_start[h + step] <= item) h += step;
+    const int in = item - sp.item_start[h], ch = in / n_qt;
+    qtile = in - ch * n_qt;
+    t_first = ch * sp.chunk;
+  } else if ((Hq & 7) == 0) {
+    const int x = bid & 7;                         // XCD
+    int u = bid >> 3;                              // position in the XCD's own sequence
     const int s = ph.xcd_start[x], e = ph.xcd_start[x + 1];
     if (u >= e - s) return;                        // the grid is sized for the longest range
-    const int he = e / n_qt * n_qt;                // where the head begins in which the range ends
-    const int len_e = he > s ? e - he : 0;
-    const int g = u < len_e ? he + u : s + (u - len_e);
-    h = g / n_qt;
-    qtile = n_qt - 1 - g % n_qt;
+    if (NW == 4 && ph.order == 1) u = pair_up(u, e - s);
+    if (ph.order == 0) {
+      const int he = e / n_qt * n_qt;              // where the head begins in which the range ends
+      const int len_e = he > s ? e - he : 0;
+      const int g = u < len_e ? he + u : s + (u - len_e);
+      h = g / n_qt;
+      qtile = n_qt - 1 - g % n_qt;
+    } else {                                       // whole heads per XCD, Hq / 8 each
+      const int nh = Hq >> 3, hp = ph.order == 1 ? u % nh : u / n_qt;
+      h = ph.perm[x * nh + hp];
+      qtile = n_qt - 1 - (ph.order == 1 ? u / nh : u - hp * n_qt);
+    }
   } else {
-    h = bid % Hq;
-    qtile = n_qt - 1 - bid / Hq;
+    // longest query tiles first, all heads of each; the heads are shifted from turn to turn so that an XCD (which
+    // gets every eighth id) does not always meet the same ones
+    const int x = bid & 7, mine = (n_qt * Hq - x + 7) >> 3;       // XCD, and how many ids it gets
+    const int g = NW == 4 ? pair_up(bid >> 3, mine) * 8 + x : bid;
+    const int k = g / Hq, period = 8 / ((Hq & 1) ? 1 : (Hq & 2) ? 2 : 4);
+    h = (g - k * Hq + k / period) % Hq;
+    qtile = n_qt - 1 - k;
   }
   const int kvh = h / G;
   const int64_t r0 = (int64_t)qtile * BM;          // first query row of the workgroup
@@ -358,20 +411,31 @@ void prefill_mfma_kernel(
   const int wg_last = (int)(q_pos0 + i64min(r0 + BM - 1, last_row));
   const int wg_first = (int)(q_pos0 + r0);
   const int last_pos = (int)(q_pos0 + last_row);
-  // Global rows visible to every query of the wave, to some query of the workgroup: two searches with
-  // wave-uniform bounds, done by the wave together (a workgroup has the CU to itself, so what its
-  // prologue waits for is lost; a binary search per lane was 17 dependent loads).  A lane's own count
-  // follows from the first: its query lies at most WQ - 1 positions behind the wave's first one, and
-  // positions are distinct and ascending, so only the next WQ rows can make the difference.
-  const int nv_wave_lo = __builtin_amdgcn_readfirstlane(count_le_wave(idx + base, nr, (int64_t)wave_first - w, lane));
-  const int nv_wg_hi = __builtin_amdgcn_readfirstlane(count_le_wave(idx + base, nr, (int64_t)wg_last - w, lane));
-  {
-    const int nxt = nv_wave_lo + lane < nr ? idx[base + nv_wave_lo + lane] : 0x7FFFFFFF;   // lane j: row nv_wave_lo + j
+  // Global rows visible to every query of the wave, to some query of the workgroup, to each lane's query.  A
+  // workgroup has the CU to itself (or shares it with one other), so what its prologue waits for is lost: one
+  // search with a wave-uniform bound, done by the wave together (three dependent loads for 2^18 rows; a binary
+  // search per lane was 17), then one round more: positions are distinct and ascending and the workgroup's last
+  // query lies at most BM - 1 behind the wave's first, so only the next BM rows can make the differences.
+  // While the window reaches back to the start there is nothing to count.
+  int nv_wave_lo = 0, nv_wg_hi = 0;
+#pragma unroll
+  for (int blk = 0; blk < QB; ++blk) nvis[blk] = 0;
+  if (wg_last >= w && nr > 0) {
+    nv_wave_lo = __builtin_amdgcn_readfirstlane(count_le_wave(idx + base, nr, (int64_t)wave_first - w, lane));
+    int nxt[BM / 64];                              // lane j of nxt[i]: the position of row nv_wave_lo + 64 i + j
+#pragma unroll
+    for (int i = 0; i < BM / 64; ++i) {
+      const int r = nv_wave_lo + i * 64 + lane;
+      nxt[i] = r < nr ? idx[base + r] : 0x7FFFFFFF;
+    }
+    nv_wg_hi = nv_wave_lo;
+#pragma unroll
+    for (int i = 0; i < BM / 64; ++i) nv_wg_hi += __builtin_popcountll(__ballot(nxt[i] <= wg_last - w));
 #pragma unroll
     for (int blk = 0; blk < QB; ++blk) nvis[blk] = nv_wave_lo;
 #pragma unroll
     for (int j = 0; j < WQ - 1; ++j) {
-      const int pj = __builtin_amdgcn_readlane(nxt, j);
+      const int pj = __builtin_amdgcn_readlane(nxt[0], j);
 #pragma unroll
       for (int blk = 0; blk < QB; ++blk) nvis[blk] += (int64_t)pj <= (int64_t)qpos[blk] - w;
     }
@@ -379,7 +443,15 @@ void prefill_mfma_kernel(
   const int n_gt = (nv_wg_hi + kBN - 1) / kBN;
   const int win_lo = wg_first - w + 1 > 0 ? wg_first - w + 1 : 0;
   const int wt0 = win_lo / kBN, wt1 = wg_last / kBN;                      // absolute dense tiles [wt0, wt1]
-  const int n_tiles = n_gt + (part == TCA_PART_GLOBAL ? 0 : wt1 - wt0 + 1);
+  int n_tiles = n_gt + (part == TCA_PART_GLOBAL ? 0 : wt1 - wt0 + 1);       // SPLIT: up to the end of the chunk
+  if constexpr (SPLIT) {
+    if (t_first >= n_tiles) {                      // nothing left for this chunk: the merge skips it by its l
+      float* const ml = sp.part + (size_t)item * split_floats<D>() + 128 * D;
+      if (tid < 128) { ml[tid] = -INFINITY; ml[128 + tid] = 0.f; }
+      return;
+    }
+    if (t_first + sp.chunk < n_tiles) n_tiles = t_first + sp.chunk;
+  }
   const int last = n_tiles - 1;
   if (n_tiles == 0) {                              // TCA_PART_GLOBAL with no visible global row: an empty part
 #pragma unroll
@@ -818,10 +890,10 @@ void prefill_mfma_kernel(
   f32x16_t sa[QB][2], sb[QB][2];
   {
     auto tile_or_last = [&](int t) { return t < last ? t : last; };
-    const CopyJob first = copy_job(0, 0, kring, vring, load_tile_rows(0));
+    const CopyJob first = copy_job(t_first, t_first, kring, vring, load_tile_rows(t_first));
 #pragma unroll
     for (int j = 0; j < Copy::N; ++j) copy_load(first, j);
-    const CopyJob second = copy_job(tile_or_last(1), 0, kring + KBYTES, vring, load_tile_rows(tile_or_last(1)));
+    const CopyJob second = copy_job(tile_or_last(t_first + 1), 0, kring + KBYTES, vring, load_tile_rows(tile_or_last(t_first + 1)));
 #pragma unroll
     for (int j = 0; j < Copy::NK; ++j) copy_load(second, j);
     if constexpr (RING == 3) {
@@ -830,7 +902,7 @@ void prefill_mfma_kernel(
 #pragma unroll
       for (int j = 0; j < Copy::N; ++j) copy_load(third, j);
     }
-    if constexpr (GATHER) rows_ahead = load_tile_rows(tile_or_last(RING));    // for the copies of step 0
+    if constexpr (GATHER) rows_ahead = load_tile_rows(tile_or_last(t_first + RING));    // for the copies of step 0
     // K(0), V^T(0) are in (GATHER: the positions just requested count among the newest as well)
     __builtin_amdgcn_s_waitcnt(0x0F70 | (Copy::NK + (RING - 2) * Copy::N + (GATHER ? Copy::NK : 0)));
     __syncthreads();
@@ -883,7 +955,7 @@ void prefill_mfma_kernel(
       if (it + 1 < n_tiles) step(it + 1, sb, sa, std::false_type{});
     }
   } else {
-    for (int it = 0; it < n_tiles; it += 2) {
+    for (int it = t_first; it < n_tiles; it += 2) {
       step(it, sa, sb, std::false_type{});
       if (it + 1 < n_tiles) step(it + 1, sb, sa, std::false_type{});
     }
@@ -893,7 +965,23 @@ void prefill_mfma_kernel(
     atomicAdd(clk, (unsigned long long)__builtin_readcyclecounter() - clk_c0);
     atomicAdd(clk + 1, (unsigned long long)__builtin_amdgcn_s_memrealtime() - clk_r0);
     atomicAdd(clk + 2, clk_loop - clk_c0);        // of which before the first step
-    atomicAdd(clk + 3, (unsigned long long)n_tiles);
+    atomicAdd(clk + 3, (unsigned long long)(n_tiles - t_first));
+  }
+
+  if constexpr (SPLIT) {                           // the lanes' accumulators as they lie: the merge reads them the same way
+    static_assert(NW == 4 && QB == 1, "128 queries per workgroup");
+    float* const po = sp.part + (size_t)item * split_floats<D>();
+    typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+#pragma unroll
+    for (int sl = 0; sl < DS; ++sl)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const f32x4_t v = {o[0][sl][4 * q4], o[0][sl][4 * q4 + 1], o[0][sl][4 * q4 + 2], o[0][sl][4 * q4 + 3]};
+        *reinterpret_cast<f32x4_t*>(po + (((sl * 4 + q4) * NW + wv) * 64 + lane) * 4) = v;
+      }
+    const float lt = half_sum(l[0]);
+    if (hh == 0) { po[128 * D + wv * 32 + c] = m[0]; po[128 * D + 128 + wv * 32 + c] = lt; }
+    return;
   }
 
   // ---- normalise and store
@@ -919,18 +1007,79 @@ void prefill_mfma_kernel(
   }
 }
 
+// Merge of the chunks of a split call: O = sum_s e^{m_s - M} O_s / sum_s e^{m_s - M} l_s per query (references m in
+// score units, as the kernel keeps them).  grid (query tiles, Hq, D / 32); block 256: wave = 32 queries, lane =
+// (half, query) with 4 x 4 of the D / 32 slice's columns, the layout the accumulators were left in: coalesced reads.
+template <int D>
+__global__ __launch_bounds__(256) void merge_split_kernel(SplitPlan sp, int64_t n_queries, float scale,
+                                                          uint16_t* __restrict__ O, float* __restrict__ lse) {
+  typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+  const int qtile = blockIdx.x, n_qt = gridDim.x, h = blockIdx.y, sl = blockIdx.z;
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, hh = lane >> 5, c = lane & 31;
+  const int n_ch = (sp.item_start[h + 1] - sp.item_start[h]) / n_qt;
+  const size_t stride = (size_t)n_qt * split_floats<D>();
+  const float* base = sp.part + (size_t)(sp.item_start[h] + qtile) * split_floats<D>();
+  const float sl2e = scale * 1.4426950408889634f;
+  const int q = wv * 32 + c;
+  float M = -INFINITY;
+#pragma unroll 8
+  for (int s = 0; s < n_ch; ++s) M = fmaxf(M, base[s * stride + 128 * D + q]);
+  f32x4_t acc[4];
+#pragma unroll
+  for (int q4 = 0; q4 < 4; ++q4) acc[q4] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  float L = 0.f;
+#pragma unroll 4
+  for (int s = 0; s < n_ch; ++s) {                 // no branch: the loads of several chunks are in flight at once
+    const float* po = base + s * stride;
+    const float l = po[128 * D + 128 + q];
+    const float wgt = l > 0.f ? __builtin_amdgcn_exp2f((po[128 * D + q] - M) * sl2e) : 0.f;
+    L += l * wgt;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const f32x4_t v = *reinterpret_cast<const f32x4_t*>(po + (((sl * 4 + q4) * 4 + wv) * 64 + lane) * 4);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[q4][j] += l > 0.f ? v[j] * wgt : 0.f;      // an empty chunk's accumulators were never written
+    }
+  }
+  const int64_t r = (int64_t)qtile * 128 + q;
+  if (r >= n_queries) return;
+  const float inv = L > 0.f ? 1.f / L : 0.f;
+  uint16_t* orow = O + ((size_t)h * n_queries + r) * D;
+#pragma unroll
+  for (int q4 = 0; q4 < 4; ++q4) {
+    bf16x4_t pk;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) pk[j] = (__bf16)(acc[q4][j] * inv);
+    *reinterpret_cast<bf16x4_t*>(orow + sl * 32 + 8 * q4 + 4 * hh) = pk;
+  }
+  if (lse && sl == 0 && hh == 0) lse[(size_t)h * n_queries + r] = L > 0.f ? M * scale + __logf(L) : -INFINITY;
+}
+
 // ------------------------------------------------------------------ host side --
 struct MfmaWs {
   unsigned long long* clk;   // sums over the workgroups of the last call: {shader-clock cycles, 100 MHz ticks, cycles before the first step, tiles}
   uint16_t* Vgt;       // [g_tiles][D][64]
   uint16_t* Vt;        // [Hkv][dense_tiles][D][64]
-  size_t bytes;
+  float* part;         // split calls: [workgroups][split_floats]; what lies behind it may be missing
+  size_t need;         // bytes without it: what a call must be given
+  size_t bytes;        // bytes with it
 };
 
 static int64_t max_region_tiles(int Hq, int64_t cap_rows) { return (cap_rows + kBN - 1) / kBN + Hq; }
 static int64_t max_dense_tiles(int64_t n_queries, int w) { return (n_queries + w) / kBN + 2; }
 
-static MfmaWs carve_mfma_ws(void* ws, const tca_params* prm, int64_t g_tiles, int64_t d_tiles) {
+// Workgroups of a split call, at most: two rounds of what the chip holds at a time, and no more than the tiles there
+// are in chunks of kMinChunk.  Grows with both arguments, so that a workspace sized for the largest call of a
+// program serves its smaller ones.
+constexpr int kSplitSlots = 512;       // four-wave workgroups the chip runs at a time: two per CU
+constexpr int kMinChunk = 8;           // tiles: below that a workgroup's prologue and its partial results outweigh the walk
+static int64_t max_split_items(const tca_params* prm, int64_t n_queries, int64_t cap_rows) {
+  const int64_t tiles = (cap_rows + kBN - 1) / kBN + max_dense_tiles(n_queries, prm->window);
+  const int64_t all = prm->n_q_heads * ((n_queries + 127) / 128) * ((tiles + kMinChunk - 1) / kMinChunk);
+  return all < 2 * kSplitSlots ? all : 2 * kSplitSlots;
+}
+
+static MfmaWs carve_mfma_ws(void* ws, const tca_params* prm, int64_t g_tiles, int64_t d_tiles, int64_t split_items) {
   MfmaWs m;
   char* b = (char*)ws;
   size_t off = 0;
@@ -938,13 +1087,22 @@ static MfmaWs carve_mfma_ws(void* ws, const tca_params* prm, int64_t g_tiles, in
   m.clk = (unsigned long long*)(b + off); off = align_up(off + 4 * sizeof(unsigned long long), 256);
   m.Vgt = (uint16_t*)(b + off); off = align_up(off + (size_t)g_tiles * tile_bytes, 256);
   m.Vt = (uint16_t*)(b + off);  off = align_up(off + (size_t)prm->n_kv_heads * d_tiles * tile_bytes, 256);
+  m.need = off;
+  m.part = (float*)(b + off);
+  off += (size_t)split_items * (prm->head_dim == 128 ? split_floats<128>() : split_floats<64>()) * sizeof(float);
   m.bytes = off;
   return m;
 }
 
+static MfmaWs mfma_ws(void* ws, const tca_params* prm, int64_t n_queries, int64_t cap_rows) {
+  return carve_mfma_ws(ws, prm, max_region_tiles(sel_heads(prm), cap_rows), max_dense_tiles(n_queries, prm->window),
+                       max_split_items(prm, n_queries, cap_rows));
+}
 size_t prefill_mfma_workspace_bytes(const tca_params* prm, int64_t n_queries, int64_t cap_rows) {
-  return carve_mfma_ws(nullptr, prm, max_region_tiles(sel_heads(prm), cap_rows),
-                       max_dense_tiles(n_queries, prm->window)).bytes;
+  return mfma_ws(nullptr, prm, n_queries, cap_rows).bytes;
+}
+size_t prefill_mfma_workspace_need(const tca_params* prm, int64_t n_queries, int64_t cap_rows) {
+  return mfma_ws(nullptr, prm, n_queries, cap_rows).need;
 }
 
 // Chooses the ranges of the (head, query tile) sequence, in the order the kernel walks it, that the eight
@@ -956,24 +1114,100 @@ size_t prefill_mfma_workspace_bytes(const tca_params* prm, int64_t n_queries, in
 // time per XCD, the next item to the first free slot) and the one that ends sooner is taken: with few
 // long items per slot a range of equal work but one item more than the slots divide costs a whole
 // round.  A poor estimate costs balance, never correctness.
+// Tile steps of query tile qt (BM queries) of a head with a region of cap rows: the dense tiles of the window,
+// exactly; the visible part of the region as if its rows were spread evenly over the positions seen so far (the
+// host does not know idx).
+static int64_t tile_steps(const tca_params* prm, int64_t cap, int64_t q_pos0, int64_t n_queries, int BM, int64_t qt, int part) {
+  const int w = prm->window;
+  const int64_t L_end = q_pos0 + n_queries;
+  const int64_t first = q_pos0 + qt * BM, lastq = first + BM - 1 < L_end - 1 ? first + BM - 1 : L_end - 1;
+  int64_t c = 0;
+  if (part != TCA_PART_GLOBAL) c += lastq / kBN - (first - w + 1 > 0 ? first - w + 1 : 0) / kBN + 1;
+  if (part != TCA_PART_WINDOW && lastq >= w && cap) c += (cap * (lastq - w + 1) / L_end + kBN - 1) / kBN;
+  return c;
+}
+
+// When the slowest of `slots` workgroup places of one XCD ends, items taken in order by the first free place.
+template <typename Cost>
+static int64_t play(int64_t n, int slots, Cost cost) {
+  int64_t heap[64], worst = 0;                     // when each place is free, a binary heap, smallest on top
+  for (int i = 0; i < slots; ++i) heap[i] = 0;
+  for (int64_t u = 0; u < n; ++u) {
+    const int64_t t = heap[0] + cost(u);
+    if (t > worst) worst = t;
+    int i = 0;
+    for (int k = 1; k < slots; k = 2 * i + 1) {
+      if (k + 1 < slots && heap[k + 1] < heap[k]) ++k;
+      if (heap[k] >= t) break;
+      heap[i] = heap[k];
+      i = k;
+    }
+    heap[i] = t;
+  }
+  return worst;
+}
+
+// Chooses which items an XCD takes and in which order (PrefillHeads: xcd_start, order, perm), and returns the
+// length of the longest range.  *makespan: the estimated end of the call in tile steps.
+// Candidates: the (head, query tile) sequence, a head at a time, cut into eight ranges of equal estimated work
+// (heads keep different numbers of rows) or of whole heads; and whole heads dealt out so that the XCDs' sums come
+// close, walked by query tile (longest first, the heads inside) or by head (longest first).  Where there are many
+// rounds of workgroups, equal work ends evenly by itself and one head at a time is the order that the L2 likes
+// (a late start of a long head costs little): no other is looked at from 16 rounds on.  Otherwise each is played
+// through (`slots` workgroups at a time per XCD, the next item to the first free slot) and the one that ends soonest
+// taken.  Measured with the first two candidates only, and with all: 2700 tokens, 64 heads, 283 -> 169 us; 4096
+// tokens, 32 heads, 212 -> 175 us; 4000 queries behind 64K tokens 1156 -> 1017 us.  The estimate is in tile steps (tile_steps), and a constant for what a workgroup does before and after its loop.  A poor
+// estimate costs balance, never correctness.
+constexpr int64_t kFixedSteps = 4;
 static int64_t plan_xcds(PrefillHeads& ph, const tca_params* prm, const int64_t* offs, int64_t q_pos0,
-                         int64_t n_queries, int BM, int part, int slots) {
-  const int Hq = prm->n_q_heads, GS = sel_group(prm), w = prm->window;
-  const int64_t n_qt = (n_queries + BM - 1) / BM, L_end = q_pos0 + n_queries, n_items = Hq * n_qt;
-  constexpr int64_t kFixedSteps = 4;
-  auto cost = [&](int64_t g) {                     // item g: head g / n_qt, its query tiles longest first
-    const int64_t h = g / n_qt, qt = n_qt - 1 - g % n_qt, cap = offs[h / GS + 1] - offs[h / GS];
-    const int64_t first = q_pos0 + qt * BM, lastq = first + BM - 1 < L_end - 1 ? first + BM - 1 : L_end - 1;
-    int64_t c = kFixedSteps;
-    if (part != TCA_PART_GLOBAL) c += lastq / kBN - (first - w + 1 > 0 ? first - w + 1 : 0) / kBN + 1;
-    if (part != TCA_PART_WINDOW && lastq >= w) c += (cap * (lastq - w + 1) / L_end + kBN - 1) / kBN;
-    return c;
-  };
-  std::vector<int32_t> c((size_t)n_items);
-  int64_t total = 0;
-  for (int64_t g = 0; g < n_items; ++g) total += c[g] = (int32_t)cost(g);
+                         int64_t n_queries, int BM, int part, int slots, int64_t* makespan = nullptr) {
+  const int Hq = prm->n_q_heads, GS = sel_group(prm), nh = Hq / 8;
+  const int64_t n_qt = (n_queries + BM - 1) / BM, n_items = Hq * n_qt;
+  ph.order = 0;
   int32_t by_head[9], by_work[9];
-  for (int x = 0; x <= 8; ++x) by_head[x] = (int32_t)(x * (Hq / 8) * n_qt);
+  for (int x = 0; x <= 8; ++x) by_head[x] = (int32_t)(x * nh * n_qt);
+  const bool few_rounds = n_items < (int64_t)8 * slots * 16;
+  if (few_rounds) {
+    // whole heads dealt out, the costliest (by its last query tile) first, each to the XCD with the smallest sum that
+    // has room; with a shared selection the heads stay with their group, whose tiles they share
+    int64_t last_cost[TCA_MAX_HEADS], sum[8] = {};
+    int by_cost[TCA_MAX_HEADS], have[8] = {};
+    for (int h = 0; h < Hq; ++h) {
+      ph.perm[h] = (uint8_t)h;
+      by_cost[h] = h;
+      last_cost[h] = h % GS ? last_cost[h - 1] : tile_steps(prm, offs[h / GS + 1] - offs[h / GS], q_pos0, n_queries, BM, n_qt - 1, part);
+    }
+    if (GS == 1) {
+      std::stable_sort(by_cost, by_cost + Hq, [&](int a, int b) { return last_cost[a] > last_cost[b]; });
+      for (int i = 0; i < Hq; ++i) {
+        int to = -1;
+        for (int xc = 0; xc < 8; ++xc)
+          if (have[xc] < nh && (to < 0 || sum[xc] < sum[to])) to = xc;
+        ph.perm[to * nh + have[to]++] = (uint8_t)by_cost[i];
+        sum[to] += last_cost[by_cost[i]];
+      }
+    }
+  }
+  if (!makespan && n_items <= (int64_t)8 * slots) {            // all at once: the order only decides who shares a CU
+    ph.order = 1;
+    for (int x = 0; x <= 8; ++x) ph.xcd_start[x] = by_head[x];
+    return nh * n_qt;
+  }
+  // item g of the sequence: head g / n_qt, its query tiles longest first
+  std::vector<int32_t> c((size_t)n_items);
+  std::vector<int64_t> head_cost((size_t)Hq, 0);
+  int64_t total = 0;
+  for (int h = 0; h < Hq; ++h) {
+    if (h % GS) {                                  // the heads of a shared selection cost the same
+      for (int64_t i = 0; i < n_qt; ++i) c[h * n_qt + i] = c[(h - 1) * n_qt + i];
+      head_cost[h] = head_cost[h - 1];
+    } else {
+      const int64_t cap = offs[h / GS + 1] - offs[h / GS];
+      for (int64_t i = 0; i < n_qt; ++i)
+        head_cost[h] += c[h * n_qt + i] = (int32_t)(kFixedSteps + tile_steps(prm, cap, q_pos0, n_queries, BM, n_qt - 1 - i, part));
+    }
+    total += head_cost[h];
+  }
   int64_t acc = 0;
   int x = 0;
   by_work[0] = 0;
@@ -982,31 +1216,116 @@ static int64_t plan_xcds(PrefillHeads& ph, const tca_params* prm, const int64_t*
     while (x < 7 && acc * 8 >= total * (x + 1)) by_work[++x] = (int32_t)(g + 1);
   }
   while (x < 8) by_work[++x] = (int32_t)n_items;
-  // when the slowest XCD ends, the kernel's own order inside a range: the piece of the head the range ends in first
-  auto makespan = [&](const int32_t* st) {
-    int64_t worst = 0, free_at[64];
-    for (int xc = 0; xc < 8; ++xc) {
-      const int64_t s = st[xc], e = st[xc + 1], he = e / n_qt * n_qt, len_e = he > s ? e - he : 0;
-      for (int i = 0; i < slots; ++i) free_at[i] = 0;
-      for (int64_t u = 0; u < e - s; ++u) {
-        int first = 0;
-        for (int i = 1; i < slots; ++i)
-          if (free_at[i] < free_at[first]) first = i;
-        free_at[first] += c[u < len_e ? he + u : s + (u - len_e)];
+  const int32_t* best = by_work;
+  if (few_rounds) {
+    int64_t best_t = -1;
+    auto better = [&](int64_t t) {
+      if (best_t >= 0 && t >= best_t) return false;
+      best_t = t;
+      return true;
+    };
+    for (const int32_t* st : {by_head, by_work}) {
+      int64_t t = 0;
+      for (int xc = 0; xc < 8; ++xc) {
+        const int64_t s = st[xc], e = st[xc + 1], he = e / n_qt * n_qt, len_e = he > s ? e - he : 0;
+        const int64_t tx = play(e - s, slots, [&](int64_t u) { return c[u < len_e ? he + u : s + (u - len_e)]; });
+        if (tx > t) t = tx;
       }
-      for (int i = 0; i < slots; ++i)
-        if (free_at[i] > worst) worst = free_at[i];
+      if (better(t)) best = st;
     }
-    return worst;
-  };
-  // with many rounds per slot the last, shortest items even the ends out and equal work wins
-  const bool few_rounds = n_items < (int64_t)8 * slots * 16;
-  const int32_t* best = !few_rounds || makespan(by_work) < makespan(by_head) ? by_work : by_head;
+    for (int order = 1; order <= 2; ++order) {
+      int64_t t = 0;
+      for (int xc = 0; xc < 8; ++xc) {
+        const uint8_t* p = ph.perm + xc * nh;
+        const int64_t tx = play(nh * n_qt, slots, [&](int64_t u) {
+          return order == 1 ? c[p[u % nh] * n_qt + u / nh] : c[p[u / n_qt] * n_qt + u % n_qt];
+        });
+        if (tx > t) t = tx;
+      }
+      if (better(t)) {
+        best = by_head;
+        ph.order = order;
+      }
+    }
+    if (makespan) *makespan = best_t;
+  } else if (makespan) {
+    *makespan = total / (8 * slots);
+  }
   int64_t longest = 0;
   for (x = 0; x <= 8; ++x) ph.xcd_start[x] = best[x];
   for (x = 0; x < 8; ++x)
     if (best[x + 1] - best[x] > longest) longest = best[x + 1] - best[x];
   return longest;
+}
+
+// Whether a call's items are cut into chunks, and how long: fills sp (all but part) and returns the number of
+// workgroups, or 0 for the plain launch.  plain_steps: when the plain launch would end, in tile steps (each slot
+// of the chip taken: with 256 workgroups or fewer a step takes 0.6 of the time).  Measured, whole and in chunks: 413
+// queries behind 64K tokens (32 heads) 539 -> 218 us, behind 112K 949 -> 344 us; 128 behind 16K 164 -> 62 us; 2048
+// behind 30K (4 heads, d = 64) 304 -> 93 us; from 512 items of equal length on nothing is gained.
+static int64_t plan_split(SplitPlan& sp, const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries,
+                          size_t ws_left, int64_t plain_steps) {
+  const int Hq = prm->n_q_heads, GS = sel_group(prm);
+  const int64_t n_qt = (n_queries + 127) / 128, n_items = Hq * n_qt;
+  const size_t item_bytes = (prm->head_dim == 128 ? split_floats<128>() : split_floats<64>()) * sizeof(float);
+  const int64_t fit = (int64_t)(ws_left / item_bytes);
+  const int64_t most = fit < 2 * kSplitSlots ? fit : 2 * kSplitSlots;
+  if (n_items >= most) return 0;
+  int64_t total = 0, longest = 0, bound[TCA_MAX_HEADS];
+  for (int h = 0; h < Hq; ++h) {
+    if (h % GS) {
+      bound[h] = bound[h - 1];
+    } else {
+      const int64_t cap = offs[h / GS + 1] - offs[h / GS];
+      bound[h] = 0;
+      for (int64_t qt = 0; qt < n_qt; ++qt) {
+        total += GS * tile_steps(prm, cap, q_pos0, n_queries, 128, qt, TCA_PART_ALL);
+        // an upper bound, wherever the region's rows lie: the chunks must cover every tile
+        const int64_t last = q_pos0 + (qt + 1 < n_qt ? qt * 128 + 127 : n_queries - 1);
+        const int64_t seen = last - prm->window + 1 < 0 ? 0 : last - prm->window + 1;
+        const int64_t b = tile_steps(prm, 0, q_pos0, n_queries, 128, qt, TCA_PART_ALL) + ((seen < cap ? seen : cap) + kBN - 1) / kBN;
+        if (b > bound[h]) bound[h] = b;
+      }
+    }
+    if (bound[h] > longest) longest = bound[h];
+  }
+  // Chunk lengths: the shortest that keeps one round of the chip, and two.  Their cost in us: a step takes 1.8 us (d =
+  // 128) or 1.1 us (64) with the chip full, 0.6 of that half full; the merge a launch, 0.3 us per chunk of an item, and
+  // the partial results written and read at 4 TB/s.
+  const double step = prm->head_dim == 128 ? 1.8 : 1.1;
+  const double occ_plain = n_items <= kSplitSlots / 2 ? 0.6 : 1.0;
+  const double plain = plain_steps * occ_plain * step;
+  double best = 0.9 * plain;
+  int64_t best_items = 0, best_chunk = 0;
+  for (const int64_t room : {(int64_t)kSplitSlots / 2, (int64_t)kSplitSlots, (int64_t)2 * kSplitSlots}) {
+    const int64_t lim = room < most ? room : most;
+    if (n_items > lim) continue;
+    int64_t chunk = (total + lim - 1) / lim, items = 0;
+    for (chunk = chunk < kMinChunk ? kMinChunk : chunk;; chunk += (chunk + 15) / 16) {
+      chunk = (chunk + 1) & ~(int64_t)1;
+      items = 0;
+      for (int h = 0; h < Hq; ++h) items += n_qt * ((bound[h] + chunk - 1) / chunk);
+      if (items <= lim) break;
+    }
+    const double walk = items <= kSplitSlots / 2 ? 0.6 * (chunk + kFixedSteps)
+                        : items <= kSplitSlots   ? (double)(chunk + kFixedSteps)
+                                                 : 1.1 * (total + kFixedSteps * items) / kSplitSlots + 0.3 * chunk;
+    const double t = walk * step + 5.0 + 0.3 * ((longest + chunk - 1) / chunk) + items * (double)item_bytes * 2e-6 / 4.0;
+    if (t < best) { best = t; best_items = items; best_chunk = chunk; }
+  }
+  if (!best_items) return 0;
+  int64_t run = 0;
+  for (int h = 0; h < Hq; ++h) {
+    sp.item_start[h] = (int32_t)run;
+    run += n_qt * ((bound[h] + best_chunk - 1) / best_chunk);
+  }
+  sp.item_start[Hq] = (int32_t)run;
+  sp.chunk = (int32_t)best_chunk;
+  // Few query tiles: an eighth of the sequence per XCD (64 heads, 413 queries behind 64K tokens: 423 us, against 468
+  // with runs of one chunk's query tiles).  Many: their chunks end at different places, and runs of 8 spread
+  // the short ones (4 heads, 17000 tokens: an eighth each left XCDs with a quarter of the others' work).
+  sp.run = n_qt <= 16 ? (int32_t)((run + 7) / 8) : 8;
+  return run;
 }
 
 // The workgroup shape of a call: waves, and blocks of 32 queries per wave.  The size of the call chooses
@@ -1025,7 +1344,7 @@ template <int D>
 static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, int64_t n_queries,
                      const uint16_t* K, const uint16_t* V, int64_t kv_stride, const int32_t* idx,
                      const uint16_t* Kg, const uint16_t* Vg, const int64_t* offs, const int32_t* n_rows,
-                     uint16_t* O, float* lse, void* ws, hipStream_t st, int part) {
+                     uint16_t* O, float* lse, void* ws, size_t ws_bytes, hipStream_t st, int part) {
   const int Hq = prm->n_q_heads, Hkv = prm->n_kv_heads, Hs = sel_heads(prm), w = prm->window;
   PrefillHeads ph;
   int32_t run = 0;
@@ -1042,7 +1361,7 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
   const int64_t win_lo = q_pos0 - w + 1 > 0 ? q_pos0 - w + 1 : 0;
   const int64_t dt0 = win_lo / kBN, dt1 = (q_pos0 + n_queries - 1) / kBN;
   const int d_tiles = (int)(dt1 - dt0 + 1);
-  MfmaWs mw = carve_mfma_ws(ws, prm, max_region_tiles(Hs, offs[Hs]), max_dense_tiles(n_queries, w));
+  MfmaWs mw = mfma_ws(ws, prm, n_queries, offs[Hs]);
   // cycle counters only when asked for (and not for a part: two parts may run side by side on one workspace,
   // where the window part touches only the dense V^T tiles and the global part only the regions')
   unsigned long long* clk = diag_prefill_clocks() && part == TCA_PART_ALL ? mw.clk : nullptr;
@@ -1070,6 +1389,42 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
   // queries (one wave per SIMD, every LDS fragment feeds two MFMAs, half the LDS reads) stay
   // selectable through the diagnostics switch: measured 5-8 % slower on 128K tokens, because a
   // lone wave cannot issue its vector, LDS and scalar instructions fast enough beside the MFMAs.
+  const WgShape sh = choose_shape(prm, n_queries, gather);
+  const int64_t n_qt128 = (n_queries + 127) / 128;
+  // Not for a part: the two parts may run side by side on one workspace, which has room for one call's chunks.
+  if (sh.nw == 4 && sh.qb == 1 && part == TCA_PART_ALL && prefill_variant() == 0 && (int64_t)n_qt128 * Hq < 2 * kSplitSlots) {
+    // when the plain launch would end: its longest item if it is all resident at once, else what the plan says
+    int64_t plain = 0;
+    if (n_qt128 * Hq <= kSplitSlots) {
+      for (int h = 0; h < Hq; h += sel_group(prm)) {
+        const int64_t c = kFixedSteps + tile_steps(prm, offs[h / sel_group(prm) + 1] - offs[h / sel_group(prm)], q_pos0, n_queries, 128,
+                                                   n_qt128 - 1, part);
+        if (c > plain) plain = c;
+      }
+    } else if ((Hq & 7) == 0) {
+      plan_xcds(ph, prm, offs, q_pos0, n_queries, 128, part, 64, &plain);
+    } else {
+      for (int h = 0; h < Hq; ++h)                 // no plan for such head counts: what the longest takes alone, at least
+        plain = std::max(plain, kFixedSteps + tile_steps(prm, offs[h / sel_group(prm) + 1] - offs[h / sel_group(prm)], q_pos0, n_queries,
+                                                         128, n_qt128 - 1, part));
+      plain = plain * 6 / 10;
+    }
+    SplitPlan sp;
+    const int64_t n_wg = plan_split(sp, prm, offs, q_pos0, n_queries, ws_bytes > mw.need ? ws_bytes - mw.need : 0, plain);
+    if (n_wg) {
+      sp.part = mw.part;
+      auto launch_split = [&](auto gather_tag) {
+        hipLaunchKernelGGL((prefill_mfma_kernel<D, 4, 1, decltype(gather_tag)::value, true>), dim3(8u * sp.run * (unsigned)((n_wg + 8 * sp.run - 1) / (8 * sp.run))),
+                           dim3(256), 0, st, Q, q_pos0, n_queries, K, kv_stride, idx, Kg, n_rows, mw.Vgt, mw.Vt, dt0,
+                           d_tiles, ph, Hq, Hq / Hkv, sel_group(prm), w, (float)logit_scale(prm), O, lse, clk, part, sp);
+      };
+      if (gather) launch_split(std::true_type{});
+      else launch_split(std::false_type{});
+      hipLaunchKernelGGL((merge_split_kernel<D>), dim3((unsigned)((n_queries + 127) / 128), Hq, D / 32), dim3(256), 0, st,
+                         sp, n_queries, (float)logit_scale(prm), O, lse);
+      return;
+    }
+  }
   auto launch = [&](auto nw_tag, auto qb_tag, auto gather_tag) {
     constexpr int NW = decltype(nw_tag)::value, QB = decltype(qb_tag)::value;
     constexpr bool GATHER = decltype(gather_tag)::value;
@@ -1080,13 +1435,12 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
                                         : (unsigned)n_qt * Hq;
     hipLaunchKernelGGL((prefill_mfma_kernel<D, NW, QB, GATHER>), dim3(n_wg), dim3(NW * 64), 0, st, Q,
                        q_pos0, n_queries, K, kv_stride, idx, Kg, n_rows, mw.Vgt, mw.Vt, dt0, d_tiles, ph, Hq,
-                       Hq / Hkv, sel_group(prm), w, (float)logit_scale(prm), O, lse, clk, part);
+                       Hq / Hkv, sel_group(prm), w, (float)logit_scale(prm), O, lse, clk, part, NoSplit{});
   };
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2>;
   using I4 = std::integral_constant<int, 4>;
   using I8 = std::integral_constant<int, 8>;
-  const WgShape sh = choose_shape(prm, n_queries, gather);
   if (gather) {
     if (sh.nw == 8) launch(I8{}, I1{}, std::true_type{});
     else launch(I4{}, I1{}, std::true_type{});
@@ -1109,7 +1463,7 @@ int64_t prefill_mfma_xcd_plan(const tca_params* prm, const int64_t* offs, int64_
 int launch_prefill_mfma(const tca_params* prm, const bf16_t* Q, int64_t q_pos0, int64_t n_queries,
                         const bf16_t* K, const bf16_t* V, int64_t kv_stride, const int32_t* idx,
                         const bf16_t* Kg, const bf16_t* Vg, const int64_t* offs, const int32_t* n_rows,
-                        bf16_t* O, float* lse, void* ws, hipStream_t st, int part) {
+                        bf16_t* O, float* lse, void* ws, size_t ws_bytes, hipStream_t st, int part) {
   // the kernel addresses tiles with 32-bit byte offsets inside each buffer
   const int64_t row_bytes = (int64_t)prm->head_dim * 2;
   int64_t max_rows = q_pos0 + n_queries + prm->window + 2 * kBN;
@@ -1121,10 +1475,10 @@ int launch_prefill_mfma(const tca_params* prm, const bf16_t* Q, int64_t q_pos0, 
   auto u = [](const bf16_t* p) { return reinterpret_cast<const uint16_t*>(p); };
   if (prm->head_dim == 128)
     run_mfma<128>(prm, u(Q), q_pos0, n_queries, u(K), u(V), kv_stride, idx, u(Kg), u(Vg), offs, n_rows,
-                  reinterpret_cast<uint16_t*>(O), lse, ws, st, part);
+                  reinterpret_cast<uint16_t*>(O), lse, ws, ws_bytes, st, part);
   else
     run_mfma<64>(prm, u(Q), q_pos0, n_queries, u(K), u(V), kv_stride, idx, u(Kg), u(Vg), offs, n_rows,
-                 reinterpret_cast<uint16_t*>(O), lse, ws, st, part);
+                 reinterpret_cast<uint16_t*>(O), lse, ws, ws_bytes, st, part);
   return TCA_OK;
 }
 

@@ -642,3 +642,62 @@ def test_large_logits_do_not_overflow(tb, bufs, dtype):
     for h in range(Hq):
         o, n = int(cache.offs[h]), int(cache.n_rows[0, h].item())
         assert np.array_equal(cache.idx[0, o:o + n].cpu().numpy(), ocache.S[h]), f"head {h} after decoding"
+
+
+SPLIT_CASES = [
+    # Hq, Hkv, d, queries, rows of each region lie ..., share, gather-free
+    (8, 2, 128, 1, "spread", False, False),        # one query: a query tile of which one row is stored
+    (8, 2, 128, 129, "front", False, False),       # every region row visible to every query: more tiles than an even spread
+    (16, 2, 64, 300, "back", True, False),         # rows inside the queries' windows: the last chunks are empty for some
+    (3, 1, 128, 130, "spread", False, True),       # a head count that is no multiple of 8; rows fetched through idx
+    (4, 4, 64, 2200, "spread", False, False),      # more than 16 query tiles: runs dealt to the XCDs in turn
+    (8, 8, 128, 64, "front", False, False),        # G = 1
+]
+
+
+@pytest.mark.parametrize("case", SPLIT_CASES, ids=lambda c: f"Hq{c[0]}-Hkv{c[1]}-d{c[2]}-n{c[3]}-{c[4]}-share{c[5]}-free{c[6]}")
+def test_few_queries_behind_a_long_context(tb, bufs, case):
+    """bf16 calls with few query tiles are cut into chunks of keys and merged: the chunks must cover every
+    tile wherever the region's rows lie, one head keeps no rows at all, and a workspace of the bare minimum
+    (no room for chunks) gives the same within the tolerance of both."""
+    Hq, Hkv, d, n, where, share, free = case
+    print("case", case, flush=True)
+    L, w, b, seed = 6000, 256, 64, 91
+    rng = np.random.default_rng(seed + n)
+    x = wl.prefill_inputs("lowrank", Hq, Hkv, d, L, "bf16", seed)
+    prm = H.params_for(tb, Hq, Hkv, d, b, w, "bf16", share=share)
+    Hs = Hkv if share else Hq
+    counts = [0 if h == 1 else int(rng.integers(1200, 2600)) for h in range(Hs)]
+    lo, hi = {"spread": (0, L), "front": (0, 2700), "back": (L - 2700, L)}[where]
+    S = [np.sort(rng.choice(np.arange(lo, hi), size=c, replace=False)) for c in counts]
+    gb = bufs.GlobalBuffers(prm, np.array(counts) + 5)
+    Qd, Kd, Vd = (bufs.to_device(x[k]) for k in ("Q", "K", "V"))
+    for h, s in enumerate(S):
+        o, at = int(gb.offs[h]), torch.from_numpy(s).cuda()
+        gb.idx[o:o + len(s)] = at.to(torch.int32)
+        gb.Kg[o:o + len(s)], gb.Vg[o:o + len(s)] = Kd[h // (Hs // Hkv), at], Vd[h // (Hs // Hkv), at]
+        gb.n_rows[h] = len(s)
+    Qt = Qd[:, L - n:].contiguous()
+    total = int(gb.offs[-1])
+    need = 256 + 512 * d + (total // 64 + Hs + 1 + Hkv * ((n + w) // 64 + 2)) * 128 * d      # clock counters, V^T tiles, rounding
+    Kg, Vg = (None, None) if free else (gb.Kg, gb.Vg)
+    outs = []
+    for ws in (bufs.workspace(tb.tca_prefill_workspace_bytes(prm, n, total)), bufs.workspace(need)):
+        O = torch.full_like(Qt, float("nan"))
+        lse = torch.full((Hq, n), float("nan"), dtype=torch.float32, device="cuda")
+        tb.tca_prefill(prm, Qt, L - n, n, Kd, Vd, L, gb.idx, Kg, Vg, gb.offs, gb.n_rows, O, lse, ws)
+        torch.cuda.synchronize()
+        outs.append((bufs.to_host_f64(O), lse.cpu().numpy()))
+    rows = sorted({0, 1, n // 2, n - 1, min(n - 1, 127), min(n - 1, 128)} & set(range(n)))
+    ref = H.oracle_rows(x, None, {"w": w}, S, np.array([L - n + r for r in rows]))
+    Qf, Kf = wl.to_f64(x["Q"]), wl.to_f64(x["K"])
+    for O, lse in outs:
+        assert not np.isnan(O).any() and not np.isnan(lse).any(), "some output rows were never written"
+        for h in range(Hq):
+            assert np.abs(O[h][rows] - ref[h]).max() <= H.TOL["bf16"], f"head {h}"
+            g, s = h // (Hq // Hkv), S[h // (Hq // Hs)]
+            i = L - 1
+            T = orc.visible_keys(i, s, w)
+            assert abs(lse[h, n - 1] - np.log(np.exp(Kf[g][T] @ Qf[h, i] / np.sqrt(d)).sum())) <= 5e-2
+    print("difference between the two workspaces:", np.abs(outs[0][0] - outs[1][0]).max(), flush=True)
+    assert np.abs(outs[0][0] - outs[1][0]).max() <= 2 * H.TOL["bf16"]
