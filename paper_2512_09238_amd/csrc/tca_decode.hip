@@ -65,32 +65,6 @@ static int global_slots(const tca_params* prm, int64_t max_head_rows) {
   return (int)((max_head_rows + chunk_rows(prm) - 1) / chunk_rows(prm));
 }
 
-// Number of entries <= bound among the ascending idx[0..n), found by a whole wave: every
-// round probes the last element of up to 64 equal chunks of the open range, so 2^18 rows take
-// three dependent loads instead of eighteen.  Result in every lane.
-__device__ __forceinline__ int count_le_wave(const int32_t* __restrict__ idx, int n, int64_t bound) {
-  const int lane = threadIdx.x & 63;
-  int lo = 0, hi = n;                       // the count lies in [lo, hi]
-  while (hi - lo > 64) {
-    const int len = hi - lo;
-    const int step = (len + 63) / 64;
-    const bool has = lane * step < len;     // lane's chunk: [lo + lane*step, lo + min((lane+1)*step, len))
-    const int last = lo + min((lane + 1) * step, len) - 1;
-    const bool le = has && (int64_t)idx[last] <= bound;
-    const int c = __popcll(__ballot(le));   // chunks that lie entirely at or below the bound (a prefix of them)
-    const int nch = (len + step - 1) / step;
-    if (c == nch) { lo = hi; break; }
-    const int lo2 = lo + c * step;
-    hi = lo + min((c + 1) * step, len) - 1; // the last element of chunk c is above the bound
-    lo = lo2;
-  }
-  if (hi > lo) {
-    const bool le = lane < hi - lo && (int64_t)idx[lo + lane] <= bound;
-    lo += __popcll(__ballot(le));
-  }
-  return lo;
-}
-
 // max over the 16 lanes of a row, result in every lane
 __device__ __forceinline__ float row16_max(float v) {
   v = fmaxf(v, dpp_f32<kDppXor1>(v));

@@ -8,11 +8,10 @@
 
 namespace tca {
 
-// One wavefront per query, fp32 arithmetic; any storage type.
-template <typename T>
-int launch_prefill_rows(const tca_params* prm, const T* Q, int64_t q_pos0, int64_t n_queries, const T* K,
-                        const T* V, int64_t kv_stride, const int32_t* idx, const T* Kg, const T* Vg,
-                        const int64_t* offs, const int32_t* n_rows, T* O, float* lse, hipStream_t st, int part);
+// fp32 storage: fp64 logits, fp32 exponentials and accumulation.
+int launch_prefill_f32(const tca_params* prm, const float* Q, int64_t q_pos0, int64_t n_queries, const float* K,
+                       const float* V, int64_t kv_stride, const int32_t* idx, const float* Kg, const float* Vg,
+                       const int64_t* offs, const int32_t* n_rows, float* O, float* lse, hipStream_t st, int part);
 
 // bf16 MFMA flash kernel.
 // _bytes: the workspace a caller is told to bring; _need: what a call must have.  The rest holds the partial results

@@ -63,9 +63,9 @@ static int prefill_checked(const tca_params* prm, const void* Q, int64_t q_pos0,
   if (n_queries == 0) return TCA_OK;
   hipStream_t st = (hipStream_t)stream;
   if (prm->dtype == TCA_F32) {
-    rc = launch_prefill_rows<float>(prm, (const float*)Q, q_pos0, n_queries, (const float*)K,
-                                    (const float*)V, kv_stride, idx, (const float*)Kg, (const float*)Vg,
-                                    offs, n_rows, (float*)O, lse, st, part);
+    rc = launch_prefill_f32(prm, (const float*)Q, q_pos0, n_queries, (const float*)K,
+                            (const float*)V, kv_stride, idx, (const float*)Kg, (const float*)Vg, offs, n_rows,
+                            (float*)O, lse, st, part);
   } else {
     rc = launch_prefill_mfma(prm, (const bf16_t*)Q, q_pos0, n_queries, (const bf16_t*)K, (const bf16_t*)V,
                              kv_stride, idx, (const bf16_t*)Kg, (const bf16_t*)Vg, offs, n_rows,

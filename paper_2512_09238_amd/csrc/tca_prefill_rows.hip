@@ -1,146 +1,285 @@
-// Row-wise prefill attention (Eq. 2; Alg. 2 line 7): one wavefront per query.
+// fp32 prefill attention (Eq. 2; Alg. 2 line 7): the TCA_F32 path.
 //
-// This is the fp32 path (TCA_F32) and the plain cross-check for the MFMA
-// kernel: every query walks its own key list - the head's visible global rows
-// (idx <= i-w) followed by its window (i-w, i] - with an online softmax.  A
-// wave is split into four 16-lane groups; a group owns every fourth key, each
-// lane a D/16 slice of the row, so the q.k reduction is a 4-step butterfly and
-// the P.V accumulation needs no communication.  Groups are merged at the end.
-// Logits and the running maximum are fp64 (the products of fp32 or bf16 inputs are
-// exact in it), so that the exponent x - max carries no cancellation error even
-// when the logits are in the hundreds; exponentials, sums and P.V are fp32.
+// Logits and the running maximum are fp64 (the products of fp32 inputs are exact in it), so that the exponent
+// x - max carries no cancellation error even when the logits are in the hundreds; exponentials, sums and P.V are
+// fp32.  Both products run on the matrix cores: S^T = K Q^T with v_mfma_f64_16x16x4_f64 on operands widened in
+// registers, O^T = V^T P^T with v_mfma_f32_16x16x4_f32.  The bound is the fp64 product: 64 cycles per 16 x 16 x 4
+// block and SIMD against 32 for the fp32 one.
+//
+// A wave owns 16 queries; lane (kb = lane / 16, c = lane % 16) holds, of every 16-key block, the scores of the
+// keys kb + 4 r (r = 0 .. 3) against query c, which is where P^T must lie as operand B of the second product if
+// its step r takes those keys: no exchange between the two.  The order of the head's elements inside the first
+// product is free as long as K and Q agree: lane kb takes the kb-th quarter of a row, so that K is read from LDS
+// 16 bytes at a time (chunk index xor row, conflict-free); in the second, row i of block s is element
+// (D / 16) i + s, so that V is too, and a lane ends up with D / 4 consecutive elements of its query.
+//
+// KG = 1: four waves (64 queries) share tiles of 16 keys.  KG = 4: the four waves take the same 16 queries and
+// every fourth tile each, and are merged at the end: four times the workgroups, for calls that would not
+// fill the chip.
 #include <hip/hip_runtime.h>
 
 #include "tca_common.h"
 #include "tca_device.h"
+#include "tca_prefill.h"
 
 namespace tca {
 
 constexpr int kRowThreads = 256;
 
-// count of entries <= bound in ascending idx[0..n)
-__device__ __forceinline__ int count_le(const int32_t* idx, int n, int64_t bound) {
-  int lo = 0, hi = n;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if ((int64_t)idx[mid] <= bound) lo = mid + 1; else hi = mid;
-  }
-  return lo;
-}
-
 struct HeadOffs { int64_t offs[TCA_MAX_HEADS + 1]; };
 
-template <typename T, int D>
-__global__ __launch_bounds__(kRowThreads) void prefill_rows_kernel(
-    const T* __restrict__ Q, int64_t q_pos0, int64_t n_queries, const T* __restrict__ K,
-    const T* __restrict__ V, int64_t kv_stride, const int32_t* __restrict__ idx,
-    const T* __restrict__ Kg, const T* __restrict__ Vg, HeadOffs ho,
-    const int32_t* __restrict__ n_rows, int G, int GS, int w, double scale, T* __restrict__ O,
+// grid (query tiles * Hq), longest query tiles first, heads inside; block 256
+template <int D, int KG>
+__global__ __launch_bounds__(kRowThreads, 2) void prefill_f32_kernel(
+    const float* __restrict__ Q, int64_t q_pos0, int64_t n_queries, const float* __restrict__ K,
+    const float* __restrict__ V, int64_t kv_stride, const int32_t* __restrict__ idx,
+    const float* __restrict__ Kg, const float* __restrict__ Vg, HeadOffs ho,
+    const int32_t* __restrict__ n_rows, int Hq, int G, int GS, int w, double scale, float* __restrict__ O,
     float* __restrict__ lse, int part) {
-  constexpr int EL = D / 16;                       // elements of a row per lane
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int grp = lane >> 4, sub = lane & 15;
-  const int h = blockIdx.y, kvh = h / G;
-  const int64_t r = (int64_t)blockIdx.x * (kRowThreads / kWave) + wv;
-  if (r >= n_queries) return;
-  const int64_t i = q_pos0 + r;                    // position of this query
-
-  double q[EL];
-#pragma unroll
-  for (int e = 0; e < EL; ++e) q[e] = (double)load_f32(Q + ((size_t)h * n_queries + r) * D + sub * EL + e);
-
-  const int hs = h / GS;                           // the selection this query head reads
+  typedef double f64x4_t __attribute__((ext_vector_type(4)));
+  typedef float f32x4_t __attribute__((ext_vector_type(4)));
+  constexpr int TK = 16;                           // keys per tile
+  constexpr int GW = 4 / KG, GT = GW * 64;         // waves, threads that share a tile
+  constexpr int QT = GW * 16;                      // queries per workgroup
+  constexpr int C4 = D / 4;                        // 16-byte chunks of a row
+  constexpr int SB = D / 16;                       // blocks of O^T; chunks of a quarter row
+  constexpr int NL = TK * C4 / GT;                 // chunks a thread stages, of K and of V
+  // KG = 4 shares nothing of V: at d = 128, where the registers are short, V goes from memory to its operands (at d = 64
+  // requesting it a tile ahead and keeping it in LDS is faster: 1024 tokens, 4 heads, 23 against 28 us).
+  constexpr bool kStageV = KG == 1 || D == 64;
+  __shared__ f32x4_t kt[KG][TK][C4], vt[kStageV ? KG : 1][TK][C4];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kb = lane >> 4, c = lane & 15;
+  const int grp = wv / GW, gt = tid - grp * GT;    // key group, thread inside it
+  const int h = blockIdx.x % Hq;
+  const int qtile = gridDim.x / Hq - 1 - blockIdx.x / Hq;
+  const int kvh = h / G, hs = h / GS;              // hs: the selection this query head reads
   const int64_t base = ho.offs[hs];
-  // part: both key subsets, or one of them alone (normalised by itself; merged later through lse)
-  const int n_glob = part == TCA_PART_WINDOW ? 0 : count_le(idx + base, n_rows[hs], i - w);
-  const int64_t win0 = i - w + 1 > 0 ? i - w + 1 : 0;
-  const int64_t n_keys = n_glob + (part == TCA_PART_GLOBAL ? 0 : i - win0 + 1);
+  const int64_t r0 = (int64_t)qtile * QT;
+  int64_t qrow = r0 + (wv - grp * GW) * 16 + c;    // this lane's query
+  const bool stored = qrow < n_queries;
+  if (!stored) qrow = n_queries - 1;               // computes a duplicate
+  const int qpos = (int)(q_pos0 + qrow);
+  const int wg_first = (int)(q_pos0 + r0);
+  const int wg_last = (int)(q_pos0 + (r0 + QT < n_queries ? r0 + QT : n_queries) - 1);
 
-  double m = -INFINITY;
-  float l = 0.f, acc[EL];
+  double q[D / 4];                                 // element kb D/4 + t of the query
 #pragma unroll
-  for (int e = 0; e < EL; ++e) acc[e] = 0.f;
+  for (int t = 0; t < SB; ++t) {
+    const f32x4_t v = *reinterpret_cast<const f32x4_t*>(Q + ((size_t)h * n_queries + qrow) * D + kb * (D / 4) + 4 * t);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) q[4 * t + e] = (double)v[e];
+  }
 
-  for (int64_t k0 = 0; k0 < n_keys; k0 += 4) {
-    const int64_t k = k0 + grp;
-    const bool ok = k < n_keys;
-    const T *kr = K, *vr = V;
-    if (ok) {
-      if (k < n_glob) {
-        if (Kg) {
-          kr = Kg + (size_t)(base + k) * D;
-          vr = Vg + (size_t)(base + k) * D;
-        } else {                                       // gather-free call: the kept rows are read where they lie
-          const size_t row = (size_t)kvh * kv_stride + idx[base + k];
-          kr = K + row * D;
-          vr = V + row * D;
-        }
-      } else {
-        const size_t row = (size_t)kvh * kv_stride + (win0 + (k - n_glob));
-        kr = K + row * D;
-        vr = V + row * D;
+  // rows of the region visible to some query of the workgroup, to this lane's query
+  // (part: both key subsets, or one of them alone, normalised by itself and merged later through lse)
+  const int nr = part == TCA_PART_WINDOW ? 0 : n_rows[hs];
+  int nv_hi = 0, nvis = 0;
+  if (nr > 0 && wg_last >= w) {
+    nv_hi = count_le_wave(idx + base, nr, (int64_t)wg_last - w);
+    // positions are distinct and ascending: the first query sees at most QT - 1 rows fewer
+    int lo = nv_hi - (QT - 1) > 0 ? nv_hi - (QT - 1) : 0, hi = nv_hi;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (idx[base + mid] <= qpos - w) lo = mid + 1; else hi = mid;
+    }
+    nvis = lo;
+  }
+  const int n_rt = (nv_hi + TK - 1) / TK;
+  const int win_lo = wg_first - w + 1 > 0 ? wg_first - w + 1 : 0;
+  const int n_tiles = n_rt + (part == TCA_PART_GLOBAL ? 0 : (wg_last - win_lo) / TK + 1);
+
+  // chunk ch of row r of tile t in src (gather-free call, Kg = NULL: the kept rows are read where they lie); zeros past
+  // the last key
+  const float* const k_reg = Kg ? Kg + base * D : K + (size_t)kvh * kv_stride * D;
+  const float* const v_reg = Kg ? Vg + base * D : V + (size_t)kvh * kv_stride * D;
+  const float* const k_win = K + ((size_t)kvh * kv_stride + win_lo) * D;
+  const float* const v_win = V + ((size_t)kvh * kv_stride + win_lo) * D;
+  const int32_t* const gather = Kg ? nullptr : idx + base;
+  auto load = [&](const float* reg, const float* win, int t, int r, int ch) {
+    f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+    if (t < n_rt) {
+      const int g = t * TK + r;
+      if (g < nv_hi) v = *reinterpret_cast<const f32x4_t*>(reg + (size_t)(gather ? gather[g] : g) * D + 4 * ch);
+    } else {
+      const int j = (t - n_rt) * TK + r;
+      if (j <= wg_last - win_lo) v = *reinterpret_cast<const f32x4_t*>(win + (size_t)j * D + 4 * ch);
+    }
+    return v;
+  };
+  // the next tile, on its way (where V is not staged: its K)
+  f32x4_t kr[NL], vr[kStageV ? NL : 1];
+  auto fetch = [&](int t) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int ci = i * GT + gt, r = ci / C4, ch = ci - r * C4;
+      kr[i] = load(k_reg, k_win, t, r, ch);
+      if constexpr (kStageV) vr[i] = load(v_reg, v_win, t, r, ch);
+    }
+  };
+  auto sync = [&] {                                // the threads that share a tile
+    if constexpr (KG == 1) {
+      __syncthreads();
+    } else {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+  };
+
+  double m = -INFINITY;                            // the same in the four lanes of a query
+  float l = 0.f;                                   // over this lane's keys
+  f32x4_t o[SB];
+#pragma unroll
+  for (int s = 0; s < SB; ++s) o[s] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  if (grp < n_tiles) fetch(grp);
+  for (int t = grp; t < n_tiles; t += KG) {
+    sync();                                        // the tile before has been consumed
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int ci = i * GT + gt, r = ci / C4, ch = ci - r * C4;
+      kt[grp][r][ch ^ (r & 15)] = kr[i];
+      if constexpr (kStageV) vt[grp][r][ch] = vr[i];
+    }
+    sync();
+    f32x4_t vd[kStageV ? 1 : 4][SB / 4];           // this lane's chunks of the rows kb + 4 r
+    if constexpr (!kStageV) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int u = 0; u < SB / 4; ++u) vd[r][u] = load(v_reg, v_win, t, kb + 4 * r, c * (SB / 4) + u);
+    }
+    if (t + KG < n_tiles) fetch(t + KG);
+
+    f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < SB; ++u) {
+      const f32x4_t kf = kt[grp][c][(kb * SB + u) ^ c];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)kf[e], q[4 * u + e], acc, 0, 0, 0);
+    }
+    // visible <=> lo <= key inside the tile < hi
+    int lo = 0, hi;
+    if (t < n_rt) {
+      hi = nvis - t * TK;
+    } else {
+      const int j0 = win_lo + (t - n_rt) * TK;
+      lo = qpos - w + 1 - j0;
+      hi = qpos + 1 - j0;
+    }
+    double x[4], mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int key = kb + 4 * r;
+      x[r] = key >= lo && key < hi ? acc[r] * scale : -INFINITY;
+      mx = fmax(mx, x[r]);
+    }
+    mx = fmax(mx, __shfl_xor(mx, 16, kWave));
+    mx = fmax(mx, __shfl_xor(mx, 32, kWave));
+    const double mn = fmax(m, mx);
+    const float corr = mn > m ? expf((float)(m - mn)) : 1.f;         // 0 on the first keys (m = -inf)
+    m = mn;
+    float p[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) p[r] = x[r] > -INFINITY ? expf((float)(x[r] - m)) : 0.f;
+    l = fmaf(l, corr, (p[0] + p[1]) + (p[2] + p[3]));
+    // The tile's part is summed from zero and added to the rest once: a quarter of the roundings at the size of the
+    // whole sum (error against 64 bits at 1500 tokens 2e-7; 4e-7 with every product added to the whole).
+    f32x4_t ot[SB];
+#pragma unroll
+    for (int s = 0; s < SB; ++s) ot[s] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+#pragma unroll
+      for (int u = 0; u < SB / 4; ++u) {
+        f32x4_t vf;
+        if constexpr (kStageV) vf = vt[grp][kb + 4 * r][c * (SB / 4) + u];
+        else vf = vd[r][u];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ot[4 * u + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e], p[r], ot[4 * u + e], 0, 0, 0);
       }
     }
-    double s = 0.0;
-    if (ok) {
 #pragma unroll
-      for (int e = 0; e < EL; ++e) s = fma(q[e], (double)load_f32(kr + sub * EL + e), s);
-    }
-    s = row16_sum(s) * scale;
-    if (ok) {
-      const double mn = fmax(m, s);
-      const float corr = expf((float)(m - mn)), pr = expf((float)(s - mn));   // m = -inf: corr = 0
-      l = l * corr + pr;
+    for (int s = 0; s < SB; ++s)
 #pragma unroll
-      for (int e = 0; e < EL; ++e) acc[e] = acc[e] * corr + pr * load_f32(vr + sub * EL + e);
-      m = mn;
-    }
+      for (int e = 0; e < 4; ++e) o[s][e] = fmaf(o[s][e], corr, ot[s][e]);
   }
-  // merge the four groups (lanes with equal `sub`)
-  for (int o = 16; o < 64; o <<= 1) {
-    const double mo = __shfl_xor(m, o, kWave);
-    const float lo = __shfl_xor(l, o, kWave);
-    const double mn = fmax(m, mo);
-    const float ca = (m == -INFINITY) ? 0.f : expf((float)(m - mn));
-    const float cb = (mo == -INFINITY) ? 0.f : expf((float)(mo - mn));
-    l = l * ca + lo * cb;
+  l += __shfl_xor(l, 16, kWave);
+  l += __shfl_xor(l, 32, kWave);
+
+  // o[s][r] is element SB (4 kb + r) + s of query c
+  if constexpr (KG == 1) {
+    if (!stored) return;
+    const float inv = l > 0.f ? 1.f / l : 0.f;     // an empty part: zeros, lse = -inf
+    float* orow = O + ((size_t)h * n_queries + qrow) * D + kb * (D / 4);
 #pragma unroll
-    for (int e = 0; e < EL; ++e) acc[e] = acc[e] * ca + __shfl_xor(acc[e], o, kWave) * cb;
-    m = mn;
-  }
-  if (grp == 0) {
-    const float inv = l > 0.f ? 1.f / l : 0.f;         // an empty part: zeros, lse = -inf
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-    for (int e = 0; e < EL; ++e) store_f32(O + ((size_t)h * n_queries + r) * D + sub * EL + e, acc[e] * inv);
-    if (lse && sub == 0) lse[(size_t)h * n_queries + r] = l > 0.f ? (float)(m + log((double)l)) : -INFINITY;
+      for (int u = 0; u < SB / 4; ++u) {
+        const f32x4_t v = {o[4 * u][r] * inv, o[4 * u + 1][r] * inv, o[4 * u + 2][r] * inv, o[4 * u + 3][r] * inv};
+        *reinterpret_cast<f32x4_t*>(orow + r * SB + 4 * u) = v;
+      }
+    if (lse && kb == 0) lse[(size_t)h * n_queries + qrow] = l > 0.f ? (float)(m + log((double)l)) : -INFINITY;
+  } else {
+    __shared__ double ms[KG][16];
+    __shared__ float ls[KG][16];
+    static_assert(sizeof(kt) >= sizeof(float) * KG * 16 * D, "the tiles' place holds the waves' results");
+    float* const po = reinterpret_cast<float*>(&kt[0][0][0]);        // [wave][query][D]
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int s = 0; s < SB; ++s) po[(wv * 16 + c) * D + kb * (D / 4) + r * SB + s] = o[s][r];
+    if (kb == 0) { ms[wv][c] = m; ls[wv][c] = l; }
+    __syncthreads();
+    const int qi = tid >> 4, sub = tid & 15;       // 16 threads per query, D / 16 elements each
+    if (r0 + qi >= n_queries) return;
+    double M = ms[0][qi];
+#pragma unroll
+    for (int g = 1; g < KG; ++g) M = fmax(M, ms[g][qi]);
+    float L = 0.f, a[SB];
+#pragma unroll
+    for (int e = 0; e < SB; ++e) a[e] = 0.f;
+#pragma unroll
+    for (int g = 0; g < KG; ++g) {
+      const float wgt = ls[g][qi] > 0.f ? expf((float)(ms[g][qi] - M)) : 0.f;
+      L += ls[g][qi] * wgt;
+#pragma unroll
+      for (int e = 0; e < SB; ++e) a[e] += po[(g * 16 + qi) * D + sub * SB + e] * wgt;
+    }
+    const float inv = L > 0.f ? 1.f / L : 0.f;
+    float* orow = O + ((size_t)h * n_queries + r0 + qi) * D + sub * SB;
+#pragma unroll
+    for (int u = 0; u < SB / 4; ++u) {
+      const f32x4_t v = {a[4 * u] * inv, a[4 * u + 1] * inv, a[4 * u + 2] * inv, a[4 * u + 3] * inv};
+      *reinterpret_cast<f32x4_t*>(orow + 4 * u) = v;
+    }
+    if (lse && sub == 0) lse[(size_t)h * n_queries + r0 + qi] = L > 0.f ? (float)(M + log((double)L)) : -INFINITY;
   }
 }
 
-template <typename T>
-int launch_prefill_rows(const tca_params* prm, const T* Q, int64_t q_pos0, int64_t n_queries, const T* K,
-                        const T* V, int64_t kv_stride, const int32_t* idx, const T* Kg, const T* Vg,
-                        const int64_t* offs, const int32_t* n_rows, T* O, float* lse, hipStream_t st, int part) {
+int launch_prefill_f32(const tca_params* prm, const float* Q, int64_t q_pos0, int64_t n_queries, const float* K,
+                       const float* V, int64_t kv_stride, const int32_t* idx, const float* Kg, const float* Vg,
+                       const int64_t* offs, const int32_t* n_rows, float* O, float* lse, hipStream_t st, int part) {
   HeadOffs ho;
   for (int h = 0; h <= sel_heads(prm); ++h) ho.offs[h] = offs[h];
-  const int GS = sel_group(prm);
-  const int G = prm->n_q_heads / prm->n_kv_heads;
-  dim3 grid((unsigned)((n_queries + 3) / 4), prm->n_q_heads);
+  const int Hq = prm->n_q_heads;
   const double scale = logit_scale(prm);
-  if (prm->head_dim == 128)
-    hipLaunchKernelGGL((prefill_rows_kernel<T, 128>), grid, dim3(kRowThreads), 0, st, Q, q_pos0, n_queries,
-                       K, V, kv_stride, idx, Kg, Vg, ho, n_rows, G, GS, prm->window, scale, O, lse, part);
-  else
-    hipLaunchKernelGGL((prefill_rows_kernel<T, 64>), grid, dim3(kRowThreads), 0, st, Q, q_pos0, n_queries,
-                       K, V, kv_stride, idx, Kg, Vg, ho, n_rows, G, GS, prm->window, scale, O, lse, part);
+  // Few workgroups of 64 queries for 256 CUs: 16 each.  us with 64 / with 16: 4 heads, 4096 tokens (256 workgroups of
+  // 64) 241 / 117; 32 heads, 700 tokens (352) 145 / 123; 64 heads, 500 tokens (512) 119 / 141; 32 heads, 1500 tokens
+  // (768) 359 / 461.  (One wave per query, keys read from L2 by each, took 95 us at 4 heads and 1024 tokens where this
+  // takes 23, and 7.1 ms at 32 heads and 3315 tokens where this takes 1.5.)
+  const bool few = (n_queries + 63) / 64 * Hq < 400;
+  const int64_t n_wg = (n_queries + (few ? 15 : 63)) / (few ? 16 : 64) * Hq;
+  if (n_wg > INT32_MAX) return fail(TCA_ERR_UNSUPPORTED, "tca_prefill (fp32): %lld queries", (long long)n_queries);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n_wg), dim3(kRowThreads), 0, st, Q, q_pos0, n_queries, K, V, kv_stride, idx,
+                       Kg, Vg, ho, n_rows, Hq, Hq / prm->n_kv_heads, sel_group(prm), prm->window, scale, O, lse, part);
+  };
+  if (prm->head_dim == 128) { if (few) launch(prefill_f32_kernel<128, 4>); else launch(prefill_f32_kernel<128, 1>); }
+  else { if (few) launch(prefill_f32_kernel<64, 4>); else launch(prefill_f32_kernel<64, 1>); }
   return TCA_OK;
 }
-
-template int launch_prefill_rows<float>(const tca_params*, const float*, int64_t, int64_t, const float*,
-                                        const float*, int64_t, const int32_t*, const float*, const float*,
-                                        const int64_t*, const int32_t*, float*, float*, hipStream_t, int);
-template int launch_prefill_rows<bf16_t>(const tca_params*, const bf16_t*, int64_t, int64_t, const bf16_t*,
-                                         const bf16_t*, int64_t, const int32_t*, const bf16_t*,
-                                         const bf16_t*, const int64_t*, const int32_t*, bf16_t*, float*,
-                                         hipStream_t, int);
 
 }  // namespace tca

@@ -701,3 +701,40 @@ def test_few_queries_behind_a_long_context(tb, bufs, case):
             assert abs(lse[h, n - 1] - np.log(np.exp(Kf[g][T] @ Qf[h, i] / np.sqrt(d)).sum())) <= 5e-2
     print("difference between the two workspaces:", np.abs(outs[0][0] - outs[1][0]).max(), flush=True)
     assert np.abs(outs[0][0] - outs[1][0]).max() <= 2 * H.TOL["bf16"]
+
+
+F32_CASES = [
+    # Hq, Hkv, d, L, q0, w, share, gather-free: both key splits of the fp32 kernel, at the edges of its tiles
+    (4, 1, 64, 1300, 1283, 128, False, False),     # 17 queries: a second tile of one row, keys dealt to four waves
+    (2, 2, 128, 700, 0, 64, False, True),          # rows through idx; 16 queries per workgroup, ragged last tile
+    (16, 2, 64, 1700, 1, 96, True, False),         # 64 queries per workgroup (27 tiles x 16 heads), shared selection
+    (24, 3, 128, 1100, 3, 512, False, False),
+]
+
+
+@pytest.mark.parametrize("case", F32_CASES, ids=lambda c: f"Hq{c[0]}-Hkv{c[1]}-d{c[2]}-L{c[3]}-q{c[4]}-w{c[5]}-share{c[6]}-free{c[7]}")
+def test_fp32_prefill_both_key_splits(tb, bufs, case):
+    """Against the oracle on rows at the tiles' edges.  The bound is fp32's: the terms and the weighted sum of up to L
+    of them carry 2^-24 each against values of up to ~5, so 1e-5 absolute leaves a factor of ten."""
+    Hq, Hkv, d, L, q0, w, share, free = case
+    print("case", case, flush=True)
+    x = wl.prefill_inputs("lowrank", Hq, Hkv, d, L, "f32", 41)
+    b = 32
+    prm = H.params_for(tb, Hq, Hkv, d, b, w, "f32", share=share)
+    Hs = Hkv if share else Hq
+    P, _ = budgets_to_configs(tb, b, wl.budget_fractions(42, Hs))
+    gb, Qd, Kd, Vd = H.gpu_select(tb, bufs, prm, x, P)
+    n = L - q0
+    Qt = Qd[:, q0:].contiguous()
+    O = torch.full_like(Qt, float("nan"))
+    lse = torch.full((Hq, n), float("nan"), dtype=torch.float32, device="cuda")
+    Kg, Vg = (None, None) if free else (gb.Kg, gb.Vg)
+    tb.tca_prefill(prm, Qt, q0, n, Kd, Vd, L, gb.idx, Kg, Vg, gb.offs, gb.n_rows, O, lse, None)
+    torch.cuda.synchronize()
+    Og = bufs.to_host_f64(O)
+    assert not np.isnan(Og).any() and not torch.isnan(lse).any()
+    rows = np.array(sorted({0, 1, 15, 16, 63, 64, n // 2, n - 2, n - 1} & set(range(n))))
+    ref = H.oracle_rows(x, None, {"w": w}, [H.head_indices(gb, h) for h in range(Hs)], q0 + rows)
+    worst = max(np.abs(Og[h][rows] - ref[h]).max() for h in range(Hq))
+    print("max abs err", worst, flush=True)
+    assert worst <= 1e-5
