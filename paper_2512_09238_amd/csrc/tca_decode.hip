@@ -1,26 +1,26 @@
 // Single-token decode over the compacted KV cache, and selection of blocks
 // completed while decoding (Sec. IV-B, "Online Token Selection in Decoding Stage").
 //
-// One step = four launches on the caller's stream:
-//   prep    : write the new K/V row into the ring; per head, count the global
-//             rows that have left the window (idx <= T-w; idx is ascending so
-//             this is a prefix, found by a 64-way search of one wave).
-//   partial : split-K attention.  grid (slot, selection head, sequence); a slot is
-//             a chunk of kChunk rows of the head's global region or of the ring.
-//             The 256 threads form sixteen 16-lane groups, each streaming whole
-//             rows with 16-byte loads and keeping its own online softmax; groups
-//             are merged into one (max, sum, acc[D]) partial per slot and query
-//             head.  HBM-bound: every K/V row is read once per selection head -
-//             once per query head, or, when the group shares one selection, once
-//             per KV head with every row scored against the group's G queries.
-//   merge   : log-sum-exp merge of a head's partials -> O.  If the new token
-//             completes a block, the same workgroup scores the block's b rows
-//             with this step's query in fp64 (Eq. 5 restricted to the block),
-//             ranks them and appends the top t = floor(sum k p_k) to the head's
-//             global region in position order.  Shared selection: the group's
-//             first workgroup ranks by the sum over the group's heads of their
-//             block-normalised scores and appends once per KV head.
-//   advance : length += 1.
+// One step = two launches on the caller's stream:
+//   partial : split-K attention.  grid (unit, sequence); a unit is a chunk of rows of one
+//             head's global region, or of one KV head's ring, and there is one for every chunk
+//             that exists (heads keep different numbers of rows; a grid of heads x longest head
+//             had two workgroups of three find nothing to do).  The rows that have left the
+//             window (idx <= T-w; idx is ascending, so a prefix of the chunk) are found by a
+//             64-way search, one load as a rule.  The unit that holds the new row's ring slot
+//             writes the row there first.  The 256 threads form sixteen 16-lane groups, each
+//             streaming whole rows with 16-byte loads and keeping its own online softmax;
+//             groups are merged into one (max, sum, acc[D]) partial per unit and query head.
+//             HBM-bound: every K/V row is read once per selection head - once per query head,
+//             or, when the group shares one selection, once per KV head with every row scored
+//             against the group's G queries.
+//   merge   : log-sum-exp merge of a head's partials -> O.  If the new token completes a
+//             block, the same workgroup scores the block's b rows with this step's query in
+//             fp64 (Eq. 5 restricted to the block), ranks them and appends the top t =
+//             floor(sum k p_k) to the head's global region in position order.  Shared
+//             selection: the group's first workgroup ranks by the sum over the group's heads
+//             of their block-normalised scores and appends once per KV head.  The last
+//             workgroup of a sequence advances its length.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -33,36 +33,64 @@ namespace tca {
 
 constexpr int kPartThreads = 256;                 // threads of a split-K workgroup (64 with 256-row slots measured 8-14 % slower)
 constexpr int kPartWaves = kPartThreads / 64;
-constexpr int kChunk = 4 * kPartThreads;          // rows per split-K slot: 64 per 16-lane group
+constexpr int kChunk = 4 * kPartThreads;          // rows per split-K unit of a long step: 64 per 16-lane group
 constexpr int kChunkShared = 2048;                // the same when every row is scored against a group of queries (1024: 507, 2048: 480, 4096: 540 us per step)
+constexpr int kMinChunk = 128;                    // of a short step: see choose_chunk
 constexpr int kDecThreads = 256;                  // the other kernels
-constexpr int kMaxSlots = 4096;       // split-K slots per head the merge kernel can weigh (4M rows per head)
+constexpr int kMaxSlots = 4096;       // split-K units per head the merge kernel can weigh (4M rows per head)
 
 struct DecodeHeads {
   int64_t offs[TCA_MAX_HEADS + 1];
   int32_t t_dec[TCA_MAX_HEADS];
+  int32_t unit0[TCA_MAX_HEADS + 1];   // first unit of each head's region; unit0[Hs]: the first ring unit
+  int32_t chunk;                      // rows per unit
+  int32_t ring_units;                 // units of one ring
 };
 
+// Partials of a sequence: region [selection head][its query heads][its units], then ring [query head][ring_units];
+// D + 2 floats each.
 struct DecodeWs {
-  int32_t* n_vis;    // [B][Hs]
-  float* part;       // [B][Hq][n_slots][D+2]
+  int32_t* done;     // [B] workgroups of the merge that have finished (cleared by the partial kernel)
+  float* part;
   size_t bytes;
 };
 
-static DecodeWs carve_decode_ws(void* ws, int B, int Hq, int D, int n_slots) {
+static DecodeWs carve_decode_ws(void* ws, int B, int Hq, int D, int64_t partials_per_seq) {
   DecodeWs w;
   char* base = (char*)ws;
   size_t off = 0;
-  w.n_vis = (int32_t*)(base + off); off = align_up(off + (size_t)B * Hq * sizeof(int32_t), 256);   // sized for Hs = Hq
-  w.part = (float*)(base + off);    off = align_up(off + (size_t)B * Hq * n_slots * (D + 2) * sizeof(float), 256);
+  w.done = (int32_t*)(base + off); off = align_up(off + (size_t)B * Hq * sizeof(int32_t), 256);
+  w.part = (float*)(base + off);   off = align_up(off + (size_t)B * partials_per_seq * (D + 2) * sizeof(float), 256);
   w.bytes = off;
   return w;
 }
 
-static int chunk_rows(const tca_params* prm) { return sel_group(prm) > 1 ? kChunkShared : kChunk; }
-static int window_slots(const tca_params* prm) { return (prm->window + chunk_rows(prm) - 1) / chunk_rows(prm); }
-static int global_slots(const tca_params* prm, int64_t max_head_rows) {
-  return (int)((max_head_rows + chunk_rows(prm) - 1) / chunk_rows(prm));
+static int long_chunk(const tca_params* prm) { return sel_group(prm) > 1 ? kChunkShared : kChunk; }
+static int64_t chunks_of(int64_t rows, int chunk) { return (rows + chunk - 1) / chunk; }
+
+// Bytes every call must have: the partials of chunks of the full length, every head as long as the longest.
+static size_t decode_ws_need(const tca_params* prm, int batch, int64_t max_head_rows) {
+  const int c = long_chunk(prm);
+  return carve_decode_ws(nullptr, batch, prm->n_q_heads, prm->head_dim,
+                         prm->n_q_heads * (chunks_of(max_head_rows, c) + chunks_of(prm->window, c))).bytes;
+}
+
+// A step whose chunks of full length would leave CUs without work takes shorter ones, down to kMinChunk rows, as long as
+// they come to at most this many workgroups.  us per step (32 query heads, one selection each, d = 128, bf16) with full chunks,
+// and up to 512 / 1536 / 3072 / 4096 workgroups: 1 x 8000 tokens 44 / 18 / 19 / 18 / 17; 4 x 30000 95 / 96 / 87 / 84 /
+// 83; 8 x 30011 fp8 107 / 108 / 112 / 95 / 93; shared selection 4 x 30000 107 / 66 / 53 / 59 / 59, 64 heads 3 x 110000 128 / 127
+// / 118 / 125 / 125 (2048: 115).
+static int64_t short_units(const tca_params* prm) { return sel_group(prm) > 1 ? 2048 : 3072; }
+// Bytes a caller is told to bring: the same, or what a step of short chunks can need (each unit serves at most a
+// group of queries).
+static size_t decode_ws_bytes(const tca_params* prm, int batch, int64_t max_head_rows) {
+  const int G = prm->n_q_heads / prm->n_kv_heads;
+  int64_t few = (int64_t)batch * prm->n_q_heads * (chunks_of(max_head_rows, kMinChunk) + chunks_of(prm->window, kMinChunk));
+  if (few > short_units(prm) * G) few = short_units(prm) * G;
+  const size_t need = decode_ws_need(prm, batch, max_head_rows);
+  const size_t with_short = carve_decode_ws(nullptr, batch, prm->n_q_heads, prm->head_dim, 0).bytes +
+                            align_up((size_t)few * (prm->head_dim + 2) * sizeof(float), 256);
+  return need > with_short ? need : with_short;
 }
 
 // max over the 16 lanes of a row, result in every lane
@@ -95,43 +123,31 @@ __device__ __forceinline__ void store_cache_slice(const float (&x)[EL], KV* dst_
   if (sub == 0) *scale_slot = scale;
 }
 
-// grid (B, ceil(Hs/4)); block 256: one wave per selection head; the workgroups with blockIdx.y = 0
-// also write the new row into the ring (KV = T: as it is; KV = fp8_t: as codes and a scale)
+// Writes the new row (k_new, v_new: D elements each) into row `row` of the ring; called by a whole workgroup, which may
+// read it back after the barrier inside (KV = T: the row as it is; KV = fp8_t: as codes and a scale).
 template <typename T, typename KV, int D>
-__global__ __launch_bounds__(256) void decode_prep_kernel(tca_cache c, DecodeHeads dh, int Hs, int Hkv, int w,
-                                                          const T* __restrict__ k_new, const T* __restrict__ v_new,
-                                                          int32_t* __restrict__ n_vis) {
-  const int s = blockIdx.x;
-  const int64_t Tpos = c.length[s];
-  if (blockIdx.y == 0) {
-    const int slot = (int)(Tpos % w);
-    KV* rk = (KV*)c.ringK;
-    KV* rv = (KV*)c.ringV;
+__device__ __forceinline__ void store_new_row(const tca_cache& c, size_t row, const T* __restrict__ k_new, const T* __restrict__ v_new) {
+  if (threadIdx.x < 32) {                              // one 16-lane group for K, one for V
+    constexpr int EL = D / 16;
+    const int sub = threadIdx.x & 15;
+    const bool is_v = threadIdx.x >= 16;
+    const T* src = (is_v ? v_new : k_new) + sub * EL;
+    KV* dst = (KV*)(is_v ? c.ringV : c.ringK) + row * D;
     if constexpr (std::is_same<T, KV>::value) {
-      for (int e = threadIdx.x; e < Hkv * D; e += blockDim.x) {
-        const int kvh = e / D, dd = e - kvh * D;
-        const size_t dst = (((size_t)s * Hkv + kvh) * w + slot) * D + dd;
-        rk[dst] = k_new[(size_t)s * Hkv * D + e];
-        rv[dst] = v_new[(size_t)s * Hkv * D + e];
-      }
+      RawSlice<T, EL> x;
+      x.load(src);
+      uint32_t* out = reinterpret_cast<uint32_t*>(dst + sub * EL);
+#pragma unroll
+      for (int i = 0; i < RawSlice<T, EL>::W; ++i) out[i] = x.w[i];
     } else {
-      constexpr int EL = D / 16;
-      const int grp = threadIdx.x >> 4, sub = threadIdx.x & 15;       // one 16-lane group per (KV head, K or V)
-      for (int job = grp; job < 2 * Hkv; job += 16) {
-        const int kvh = job >> 1;
-        const T* src = ((job & 1) ? v_new : k_new) + ((size_t)s * Hkv + kvh) * D + sub * EL;
-        float x[EL];
-        load_slice<T, EL>(src, x);
-        const size_t row = ((size_t)s * Hkv + kvh) * w + slot;
-        store_cache_slice<KV, EL>(x, ((job & 1) ? rv : rk) + row * D, ((job & 1) ? c.ringV_scale : c.ringK_scale) + row, sub);
-      }
+      float x[EL];
+      load_slice<T, EL>(src, x);
+      store_cache_slice<KV, EL>(x, dst, (is_v ? c.ringV_scale : c.ringK_scale) + row, sub);
     }
+    __threadfence_block();
+    __builtin_amdgcn_s_waitcnt(0x0F70);                // the stores have reached the cache the workgroup reads through
   }
-  const int h = blockIdx.y * 4 + (threadIdx.x >> 6);
-  if (h >= Hs) return;
-  const int32_t* ix = c.idx + (size_t)s * c.cap_rows + dh.offs[h];
-  const int nv = count_le_wave(ix, c.n_rows[s * Hs + h], Tpos - w);
-  if ((threadIdx.x & 63) == 0) n_vis[s * Hs + h] = nv;
+  __syncthreads();
 }
 
 // Tail of the split-K kernels: every 16-lane group of the workgroup holds, for each of NQ
@@ -487,33 +503,38 @@ __device__ __forceinline__ void partial_rows_mfma(const bf16_t* __restrict__ kba
   merge_partials<D, NQ>(m, l, acc, out, out_head, red);
 }
 
-// grid (n_slots, Hs, B); block kPartThreads.  Selection head hs = blockIdx.y serves the GQ query
-// heads hs*GQ .. hs*GQ+GQ-1 (GQ = 1: one selection per query head).  Slots below g_slots are
-// chunks of the head's global region, the others chunks of the ring.  The ring belongs to the KV
-// head, so with GW > GQ (one selection per query head, GW = G heads per KV head) the workgroup
-// of the group's first head scores each ring row against all GW queries and the others skip it.
+// grid (units, B); block kPartThreads.  Selection head hs serves the GQ query heads hs*GQ .. hs*GQ+GQ-1 (GQ = 1: one
+// selection per query head).  Units below unit0[Hs] are chunks of a head's global region, the others chunks of a
+// ring.  The ring belongs to the KV head, so its units score each row against all GW query heads of the group.
 template <typename T, typename KV, int D, int GQ, int GW>
 __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
-    tca_cache c, DecodeHeads dh, int Hq, int Hkv, int w, int g_slots, int n_slots, double scale,
-    const T* __restrict__ q, const int32_t* __restrict__ n_vis, float* __restrict__ part) {
+    tca_cache c, DecodeHeads dh, int Hq, int Hkv, int w, double scale, const T* __restrict__ q,
+    const T* __restrict__ k_new, const T* __restrict__ v_new, int32_t* __restrict__ done, float* __restrict__ part) {
   constexpr int EL = D / 16;
-  constexpr int CH = GQ > 1 ? kChunkShared : kChunk;  // rows per slot
   constexpr int NMAX = GQ > GW ? GQ : GW;
   __shared__ float red[kPartWaves * 16 * NMAX * (EL + 2)];
   constexpr bool kMfma = sizeof(KV) == 2 && D == 128;  // rows that partial_rows_mfma takes
   __shared__ __attribute__((aligned(16))) unsigned char tiles[kMfma && NMAX > 1 ? kPartWaves * kMfmaTileBytes + NMAX * 256 : 16];
-  const int slot = blockIdx.x, hs = blockIdx.y, s = blockIdx.z;
-  const int Hs = Hq / GQ, h0 = hs * GQ, kvh = h0 / (Hq / Hkv);
-  float* out = part + (((size_t)s * Hq + h0) * n_slots + slot) * (D + 2);   // head h0 + g: + g * n_slots * (D+2)
-  const size_t out_head = (size_t)n_slots * (D + 2);
+  const int unit = blockIdx.x, s = blockIdx.y;
+  const int Hs = Hq / GQ;
   const int64_t Tpos = c.length[s];
-  const T* q0 = q + ((size_t)s * Hq + h0) * D;
+  const int region_units = dh.unit0[Hs];
+  float* const seq_part = part + (size_t)s * ((size_t)GQ * region_units + (size_t)Hq * dh.ring_units) * (D + 2);
+  if (unit == 0 && threadIdx.x == 0) done[s] = 0;      // for the merge that follows
 
-  if (slot < g_slots) {
-    const int nv = n_vis[s * Hs + hs];
-    const int r_begin = slot * CH;
-    const int r_end = min(nv, r_begin + CH);
+  if (unit < region_units) {
+    int hs = 0;
+    for (int step = 64; step > 0; step >>= 1)
+      if (hs + step < Hs && dh.unit0[hs + step] <= unit) hs += step;
+    const int ns = dh.unit0[hs + 1] - dh.unit0[hs], slot = unit - dh.unit0[hs];
+    const int r_begin = slot * dh.chunk;
     const size_t base = (size_t)s * c.cap_rows + dh.offs[hs];
+    int len = c.n_rows[s * Hs + hs] - r_begin;
+    if (len > dh.chunk) len = dh.chunk;
+    const int r_end = r_begin + (len > 0 ? count_le_wave(c.idx + base + r_begin, len, Tpos - w) : 0);
+    float* out = seq_part + ((size_t)GQ * dh.unit0[hs] + slot) * (D + 2);    // query g: + g * ns * (D+2)
+    const size_t out_head = (size_t)ns * (D + 2);
+    const T* q0 = q + ((size_t)s * Hq + hs * GQ) * D;
     if constexpr (kMfma && GQ > 1)
       partial_rows_mfma<GQ>((const T*)c.Kg + base * D, (const T*)c.Vg + base * D, r_begin, r_end, q0, scale, out,
                             out_head, red, tiles);
@@ -521,13 +542,19 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
       partial_rows<T, KV, D, GQ>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base,
                                  c.Vg_scale + base, r_begin, r_end, q0, scale, out, out_head, red);
   } else {
-    if (GW != GQ && h0 % GW != 0) return;              // this head's ring partial is written by the group's first head
+    const int v = unit - region_units, kvh = v / dh.ring_units, slot = v - kvh * dh.ring_units, h0 = kvh * GW;
+    const int r_begin = slot * dh.chunk;
+    const size_t base = ((size_t)s * Hkv + kvh) * w;
     // Slot r of the ring holds the latest position congruent to r mod w that is <= Tpos.  Once
     // Tpos >= w every slot is filled; before that only slots 0 .. Tpos are.
     const int filled = Tpos >= w ? w : (int)Tpos + 1;
-    const int r_begin = (slot - g_slots) * CH;
-    const int r_end = min(filled, r_begin + CH);
-    const size_t base = ((size_t)s * Hkv + kvh) * w;
+    const int r_end = min(filled, r_begin + dh.chunk);
+    const int newest = (int)(Tpos % w);
+    if (newest >= r_begin && newest < r_begin + dh.chunk)
+      store_new_row<T, KV, D>(c, base + newest, k_new + ((size_t)s * Hkv + kvh) * D, v_new + ((size_t)s * Hkv + kvh) * D);
+    float* out = seq_part + ((size_t)GQ * region_units + (size_t)h0 * dh.ring_units + slot) * (D + 2);
+    const size_t out_head = (size_t)dh.ring_units * (D + 2);
+    const T* q0 = q + ((size_t)s * Hq + h0) * D;
     if constexpr (kMfma && GW > 1)
       partial_rows_mfma<GW>((const T*)c.ringK + base * D, (const T*)c.ringV + base * D, r_begin, r_end, q0, scale,
                             out, out_head, red, tiles);
@@ -540,8 +567,8 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
 // grid (Hq, B); block 256
 template <typename T, typename KV, int D>
 __global__ __launch_bounds__(kDecThreads) void decode_merge_kernel(
-    tca_cache c, DecodeHeads dh, int Hq, int Hkv, int GS, int w, int b, int n_slots, double scale,
-    const T* __restrict__ q, const float* __restrict__ part, T* __restrict__ O) {
+    tca_cache c, DecodeHeads dh, int Hq, int Hkv, int GS, int w, int b, double scale,
+    const T* __restrict__ q, const float* __restrict__ part, int32_t* __restrict__ done, T* __restrict__ O) {
   constexpr int EL = D / 16;
   __shared__ double xs[256];
   __shared__ double gred[kDecThreads / kWave];
@@ -550,7 +577,19 @@ __global__ __launch_bounds__(kDecThreads) void decode_merge_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int h = blockIdx.x, s = blockIdx.y;
   const int G = Hq / Hkv, kvh = h / G;
-  const float* pp = part + ((size_t)s * Hq + h) * n_slots * (D + 2);
+  const int hs = h / GS, Hs = Hq / GS;
+  // the head's partials: those of its region, then those of its ring
+  const int ns = dh.unit0[hs + 1] - dh.unit0[hs], n_slots = ns + dh.ring_units;
+  const float* const seq_part = part + (size_t)s * ((size_t)GS * dh.unit0[Hs] + (size_t)Hq * dh.ring_units) * (D + 2);
+  const float* const p_region = seq_part + ((size_t)GS * dh.unit0[hs] + (size_t)(h - hs * GS) * ns) * (D + 2);
+  const float* const p_ring = seq_part + ((size_t)GS * dh.unit0[Hs] + (size_t)h * dh.ring_units) * (D + 2);
+  auto partial_at = [&](int x) { return x < ns ? p_region + (size_t)x * (D + 2) : p_ring + (size_t)(x - ns) * (D + 2); };
+  const int64_t Tpos = c.length[s];
+  // the last workgroup of the sequence to finish advances its length; every one has read it before
+  auto finish = [&] {
+    __syncthreads();
+    if (threadIdx.x == 0 && atomicAdd(&done[s], 1) == Hq - 1) c.length[s] = Tpos + 1;
+  };
 
   // log-sum-exp merge of the head's partials: slot weights first (one thread per
   // slot), then every thread sums four output columns over a share of the slots
@@ -559,8 +598,10 @@ __global__ __launch_bounds__(kDecThreads) void decode_merge_kernel(
   __shared__ float lsum[kDecThreads / kWave];
   {
     float M = -INFINITY;
-    for (int x = tid; x < n_slots; x += kDecThreads)
-      if (pp[(size_t)x * (D + 2) + 1] > 0.f) M = fmaxf(M, pp[(size_t)x * (D + 2)]);
+    for (int x = tid; x < n_slots; x += kDecThreads) {
+      const float* px = partial_at(x);
+      if (px[1] > 0.f) M = fmaxf(M, px[0]);
+    }
     M = group_max(M, kWave);
     if (lane == 0) lsum[wv] = M;
     __syncthreads();
@@ -568,8 +609,9 @@ __global__ __launch_bounds__(kDecThreads) void decode_merge_kernel(
     __syncthreads();
     float lpart = 0.f;
     for (int x = tid; x < n_slots; x += kDecThreads) {
-      const float lx = pp[(size_t)x * (D + 2) + 1];
-      const float wx = lx > 0.f ? __builtin_amdgcn_exp2f(pp[(size_t)x * (D + 2)] - M) : 0.f;   // references are in base-2 units
+      const float* px = partial_at(x);
+      const float lx = px[1];
+      const float wx = lx > 0.f ? __builtin_amdgcn_exp2f(px[0] - M) : 0.f;   // references are in base-2 units
       wgt[x] = wx;
       lpart += lx * wx;
     }
@@ -585,7 +627,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_merge_kernel(
     for (int x = part; x < n_slots; x += SPLIT) {
       const float wx = wgt[x];                           // an empty slot's columns were never written
       if (wx != 0.f) {
-        const float* src = pp + (size_t)x * (D + 2) + 2 + 4 * cq;      // 8-byte aligned
+        const float* src = partial_at(x) + 2 + 4 * cq;   // 8-byte aligned
         const float2 lo = *reinterpret_cast<const float2*>(src), hi = *reinterpret_cast<const float2*>(src + 2);
         a0 += lo.x * wx; a1 += lo.y * wx; a2 += hi.x * wx; a3 += hi.y * wx;
       }
@@ -602,10 +644,11 @@ __global__ __launch_bounds__(kDecThreads) void decode_merge_kernel(
   }
 
   // block completed by this token?
-  const int64_t Tpos = c.length[s];
-  if ((Tpos + 1) % b != 0) return;
-  if (h % GS != 0) return;                             // one workgroup per selection head ranks the block
-  const int hs = h / GS, Hs = Hq / GS;
+  // (one workgroup per selection head ranks the block)
+  if ((Tpos + 1) % b != 0 || h % GS != 0) {
+    finish();
+    return;
+  }
   const int64_t p0 = Tpos + 1 - b;                     // first position of the block
   const int slot0 = (int)(p0 % w);                     // contiguous in the ring: w is a multiple of b
   const size_t ring_row0 = ((size_t)s * Hkv + kvh) * w + slot0;
@@ -698,11 +741,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_merge_kernel(
     int64_t nf = (int64_t)fill + t;
     c.n_rows[s * Hs + hs] = (int32_t)(nf > cap ? cap : nf);
   }
-}
-
-__global__ void decode_advance_kernel(int64_t* length, int B) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s < B) length[s] += 1;
+  finish();
 }
 
 // grid (ceil(rows/16), Hkv); block 256: one 16-lane group per row
@@ -776,26 +815,52 @@ static int check_cache(const tca_params* prm, const tca_cache* c) {
   return TCA_OK;
 }
 
+// Fills dh.chunk, dh.ring_units and dh.unit0 for chunks of `chunk` rows; the workgroups per sequence.
+static int64_t set_chunk(DecodeHeads& dh, const tca_params* prm, int chunk) {
+  const int Hs = sel_heads(prm);
+  int64_t run = 0;
+  for (int h = 0; h < Hs; ++h) {
+    dh.unit0[h] = (int32_t)run;
+    run += chunks_of(dh.offs[h + 1] - dh.offs[h], chunk);
+  }
+  dh.unit0[Hs] = (int32_t)run;
+  dh.chunk = chunk;
+  dh.ring_units = (int32_t)chunks_of(prm->window, chunk);
+  return run + (int64_t)prm->n_kv_heads * dh.ring_units;
+}
+
+static size_t ws_of(const DecodeHeads& dh, const tca_params* prm, int batch) {
+  return carve_decode_ws(nullptr, batch, prm->n_q_heads, prm->head_dim,
+                         (int64_t)sel_group(prm) * dh.unit0[sel_heads(prm)] + (int64_t)prm->n_q_heads * dh.ring_units).bytes;
+}
+
+// The chunk length of a step: the shortest that stays within short_units workgroups (and the workspace), the full one
+// from there on.
+static int64_t choose_chunk(DecodeHeads& dh, const tca_params* prm, int batch, size_t ws_bytes) {
+  for (int c = kMinChunk; c < long_chunk(prm); c *= 2) {
+    const int64_t units = set_chunk(dh, prm, c);
+    if (units * batch <= short_units(prm) && ws_of(dh, prm, batch) <= ws_bytes) return units;
+  }
+  return set_chunk(dh, prm, long_chunk(prm));
+}
+
 template <typename T, typename KV, int D>
-static int run_decode(const tca_params* prm, const tca_cache* c, const DecodeHeads& dh, int64_t max_rows,
-                      const T* q, const T* k_new, const T* v_new, T* O, void* ws, hipStream_t st) {
+static int run_decode(const tca_params* prm, const tca_cache* c, const DecodeHeads& dh, int64_t units, const T* q,
+                      const T* k_new, const T* v_new, T* O, void* ws, hipStream_t st) {
   const int Hq = prm->n_q_heads, Hkv = prm->n_kv_heads, B = c->batch, w = prm->window;
-  const int Hs = sel_heads(prm), GS = sel_group(prm);
-  const int g_slots = global_slots(prm, max_rows), n_slots = g_slots + window_slots(prm);
-  DecodeWs dw = carve_decode_ws(ws, B, Hq, D, n_slots);
-  hipLaunchKernelGGL((decode_prep_kernel<T, KV, D>), dim3(B, (Hs + 3) / 4), dim3(256), 0, st, *c, dh, Hs, Hkv, w, k_new,
-                     v_new, dw.n_vis);
+  const int GS = sel_group(prm);
+  const DecodeWs dw = carve_decode_ws(ws, B, Hq, D, 0);
   const double sc = logit_scale(prm);
   // (queries per region row, queries per ring row): (G, G) for a shared selection, else (1, G)
   const int G = Hq / Hkv;
 #define TCA_PARTIAL_CASE(GG)                                                                                    \
   case GG:                                                                                                      \
     if (GS > 1)                                                                                                 \
-      hipLaunchKernelGGL((decode_partial_kernel<T, KV, D, GG, GG>), dim3(n_slots, Hs, B), dim3(kPartThreads), 0, st, \
-                         *c, dh, Hq, Hkv, w, g_slots, n_slots, sc, q, dw.n_vis, dw.part);                       \
+      hipLaunchKernelGGL((decode_partial_kernel<T, KV, D, GG, GG>), dim3((unsigned)units, B), dim3(kPartThreads), 0, st, \
+                         *c, dh, Hq, Hkv, w, sc, q, k_new, v_new, dw.done, dw.part);                            \
     else                                                                                                        \
-      hipLaunchKernelGGL((decode_partial_kernel<T, KV, D, 1, GG>), dim3(n_slots, Hs, B), dim3(kPartThreads), 0, st, \
-                         *c, dh, Hq, Hkv, w, g_slots, n_slots, sc, q, dw.n_vis, dw.part);                       \
+      hipLaunchKernelGGL((decode_partial_kernel<T, KV, D, 1, GG>), dim3((unsigned)units, B), dim3(kPartThreads), 0, st, \
+                         *c, dh, Hq, Hkv, w, sc, q, k_new, v_new, dw.done, dw.part);                            \
     break;
   switch (G) {
     TCA_PARTIAL_CASE(1) TCA_PARTIAL_CASE(2) TCA_PARTIAL_CASE(3) TCA_PARTIAL_CASE(4)
@@ -803,8 +868,7 @@ static int run_decode(const tca_params* prm, const tca_cache* c, const DecodeHea
   }
 #undef TCA_PARTIAL_CASE
   hipLaunchKernelGGL((decode_merge_kernel<T, KV, D>), dim3(Hq, B), dim3(kDecThreads), 0, st, *c, dh, Hq, Hkv, GS, w,
-                     prm->block, n_slots, logit_scale(prm), q, dw.part, O);
-  hipLaunchKernelGGL(decode_advance_kernel, dim3((B + 63) / 64), dim3(64), 0, st, c->length, B);
+                     prm->block, sc, q, dw.part, dw.done, O);
   return TCA_OK;
 }
 
@@ -814,8 +878,7 @@ using namespace tca;
 
 extern "C" size_t tca_decode_workspace_bytes(const tca_params* prm, int batch, int64_t max_head_rows) {
   if (check_params(prm) != TCA_OK || batch < 1 || max_head_rows < 0) return 0;
-  const int n_slots = global_slots(prm, max_head_rows) + window_slots(prm);
-  return carve_decode_ws(nullptr, batch, prm->n_q_heads, prm->head_dim, n_slots).bytes;
+  return decode_ws_bytes(prm, batch, max_head_rows);
 }
 
 extern "C" int tca_cache_load_window(const tca_params* prm, const tca_cache* cache, int seq, const void* K,
@@ -877,7 +940,7 @@ extern "C" int tca_cache_load_global(const tca_params* prm, const tca_cache* cac
   return TCA_OK;
 }
 
-// Argument checks and the four launches of a step, on a caller-visible scratch buffer.
+// Argument checks and the two launches of a step, on a caller-visible scratch buffer.
 static int decode_step(const tca_params* prm, const tca_cache* cache, const int64_t* offs, const void* q,
                        const void* k_new, const void* v_new, const double* p, void* O, void* ws, size_t ws_bytes,
                        void* stream, const char* who) {
@@ -902,17 +965,19 @@ static int decode_step(const tca_params* prm, const tca_cache* cache, const int6
     dh.t_dec[h] = tca_decode_budget(b, p + (size_t)h * nk);
   }
   dh.offs[Hs] = offs[Hs];
-  if (global_slots(prm, max_rows) + window_slots(prm) > kMaxSlots)
+  if (chunks_of(max_rows, long_chunk(prm)) + chunks_of(prm->window, long_chunk(prm)) > kMaxSlots)
     return fail(TCA_ERR_UNSUPPORTED, "%s: more than %d split-K slots per head", who, kMaxSlots);
-  const size_t need = tca_decode_workspace_bytes(prm, cache->batch, max_rows);
+  const size_t need = decode_ws_need(prm, cache->batch, max_rows);
   if (ws_bytes < need || ((uintptr_t)ws & 255))
     return fail(TCA_ERR_WORKSPACE, "%s: scratch needs %zu bytes, 256-byte aligned; %zu available", who, need,
                 ws_bytes);
+  const int64_t units = choose_chunk(dh, prm, cache->batch, ws_bytes);
+  if (units > INT32_MAX || cache->batch > 65535) return fail(TCA_ERR_UNSUPPORTED, "%s: batch=%d", who, cache->batch);
   hipStream_t st = (hipStream_t)stream;
 #define TCA_RUN_DECODE(TT, KK)                                                                                         \
   (prm->head_dim == 128                                                                                                \
-       ? run_decode<TT, KK, 128>(prm, cache, dh, max_rows, (const TT*)q, (const TT*)k_new, (const TT*)v_new, (TT*)O, ws, st) \
-       : run_decode<TT, KK, 64>(prm, cache, dh, max_rows, (const TT*)q, (const TT*)k_new, (const TT*)v_new, (TT*)O, ws, st))
+       ? run_decode<TT, KK, 128>(prm, cache, dh, units, (const TT*)q, (const TT*)k_new, (const TT*)v_new, (TT*)O, ws, st) \
+       : run_decode<TT, KK, 64>(prm, cache, dh, units, (const TT*)q, (const TT*)k_new, (const TT*)v_new, (TT*)O, ws, st))
   if (cache->kv_format == TCA_KV_FP8) rc = TCA_RUN_DECODE(bf16_t, fp8_t);
   else if (prm->dtype == TCA_BF16) rc = TCA_RUN_DECODE(bf16_t, bf16_t);
   else rc = TCA_RUN_DECODE(float, float);

@@ -738,3 +738,77 @@ def test_fp32_prefill_both_key_splits(tb, bufs, case):
     worst = max(np.abs(Og[h][rows] - ref[h]).max() for h in range(Hq))
     print("max abs err", worst, flush=True)
     assert worst <= 1e-5
+
+
+CHUNK_CASES = [
+    # Hq, Hkv, d, dtype, w, rows of the heads' regions, tokens seen, share, kv
+    (4, 2, 128, "bf16", 256, (0, 1, 128, 129), 700, False, "native"),        # no unit, one row, a full unit, one more
+    (4, 1, 64, "f32", 128, (127, 300, 0, 5), 128, False, "native"),          # nothing has left the window yet but position 0
+    (16, 2, 128, "bf16", 384, (1000, 257), 2000, True, "native"),            # G = 8, shared
+    (8, 2, 128, "bf16", 512, (40, 700, 0, 0, 513, 1, 2, 3), 3000, False, "fp8"),
+    (2, 2, 64, "bf16", 64, (90, 200), 40, False, "native"),                  # ring not full
+]
+
+
+@pytest.mark.parametrize("case", CHUNK_CASES, ids=lambda c: f"Hq{c[0]}-Hkv{c[1]}-d{c[2]}-{c[3]}-w{c[4]}-T{c[6]}-share{c[7]}-{c[8]}")
+def test_decode_units_at_their_edges(tb, bufs, case):
+    """One step on caches whose regions are ragged at the edges of the short units (128 rows), with the workspace the
+    library asks for (short units) and with the smallest it takes (full ones): both give the same rows in the cache,
+    and outputs that agree to the storage type's rounding."""
+    Hq, Hkv, d, dtype, w, rows, T, share, kv = case
+    print("case", case, flush=True)
+    prm = H.params_for(tb, Hq, Hkv, d, 32, w, dtype, share=share)
+    Hs = Hkv if share else Hq
+    P, _ = budgets_to_configs(tb, 32, [0.3] * Hs)
+    B = 2
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    G = Hq // Hkv
+    chunk = 2048 if share and G > 1 else 1024
+    need = -(-B * Hq * 4 // 256) * 256 + -(-B * Hq * (-(-max(rows) // chunk) + -(-w // chunk)) * (d + 2) * 4 // 256) * 256
+    got = []
+    for full in (False, True):
+        g = torch.Generator(device="cuda").manual_seed(5)
+        cache = bufs.DecodeCache(prm, B, list(rows), kv_format=tb.TCA_KV_FP8 if kv == "fp8" else tb.TCA_KV_NATIVE)
+        n_used = torch.tensor([max(0, r - 3) for r in rows], dtype=torch.int32, device="cuda")
+        src = bufs.GlobalBuffers(prm, list(rows))
+        src.Kg[:] = torch.randn(src.Kg.shape, generator=g, device="cuda").to(dt)
+        src.Vg[:] = torch.randn(src.Vg.shape, generator=g, device="cuda").to(dt)
+        src.n_rows[:] = n_used
+        idx = np.zeros(max(int(src.offs[-1]), 1), np.int32)
+        for h, n in enumerate(n_used.tolist()):                     # ascending, some of them still inside the window
+            idx[src.offs[h]:src.offs[h] + n] = np.linspace(0, max(T - 1, n), n, endpoint=False).astype(np.int32)
+        src.idx[:] = torch.from_numpy(idx).cuda()
+        K, V = (torch.randn(Hkv, max(T, 1), d, generator=g, device="cuda").to(dt) for _ in range(2))
+        for s in range(B):
+            tb.tca_cache_load_window(prm, cache.view, s, K, V, T, T - s)
+            tb.tca_cache_load_global(prm, cache.view, s, src.idx, src.Kg, src.Vg, src.offs, src.n_rows)
+        q = torch.randn(B, Hq, d, generator=g, device="cuda").to(dt)
+        kn, vn = (torch.randn(B, Hkv, d, generator=g, device="cuda").to(dt) for _ in range(2))
+        O = torch.full_like(q, float("nan"))
+        ws = bufs.workspace(need if full else tb.tca_decode_workspace_bytes(prm, B, max(rows)))
+        tb.tca_decode(prm, cache.view, cache.offs, q, kn, vn, P, O, ws)
+        torch.cuda.synchronize()
+        assert cache.length.tolist() == [T + 1, T]
+        got.append((O.double(), cache, (q, kn, vn, K, V, src, idx, n_used)))
+    for name in ("ringK", "ringV", "Kg", "Vg", "idx", "n_rows"):
+        assert torch.equal(getattr(got[0][1], name), getattr(got[1][1], name)), name
+    # against the definition, in fp64, on the rows as the cache holds them
+    O, c, (q, kn, vn, K, V, src, idx, n_used) = got[0]
+
+    def rows64(name, s):
+        x = getattr(c, name)[s].reshape(-1, d)
+        if kv == "fp8":
+            return x.view(torch.float8_e4m3fn).double() * getattr(c, name + "_scale")[s].reshape(-1, 1).double()
+        return x.double()
+    for s in range(B):
+        Ts = T - s                                                  # position of the new row
+        for h in range(Hq):
+            hs, kvh = h // (Hq // Hs), h // G
+            o, n = int(src.offs[hs]), int((torch.from_numpy(idx[src.offs[hs]:src.offs[hs] + int(n_used[hs])]) <= Ts - w).sum())
+            r0, r1 = kvh * w, kvh * w + min(w, Ts + 1)
+            keys = torch.cat([rows64("Kg", s)[o:o + n], rows64("ringK", s)[r0:r1]])
+            vals = torch.cat([rows64("Vg", s)[o:o + n], rows64("ringV", s)[r0:r1]])
+            x = (keys @ q[s, h].double()) / d ** 0.5
+            ref = torch.softmax(x, 0) @ vals
+            for Ox in (got[0][0], got[1][0]):
+                assert (Ox[s, h] - ref).abs().max().item() <= H.TOL[dtype], (s, h)
