@@ -1,21 +1,23 @@
 // Offline head-specific sparsity determination (Alg. 1; Eq. 3, Eq. 4).
 //
-// Runs once per model, so everything is fp64 and written for exactness, not
-// speed: the decisions a_i >= tau then agree with an fp64 reference except at
-// exact ties.  The dense causal attention matrix A is never materialised:
-//   rowstats  : per query row j, max and sum of exp of the causal logits        (softmax denominators)
-//   colmeans  : per key column k, sum_{j>=k} exp(x_jk - max_j) / sum_j, divided
+// Runs once per model, and everything is fp64: the decisions a_i >= tau then agree with an fp64 reference
+// except at exact ties.  The dense causal attention matrix A is never materialised:
+//   rows      : per query row j, max and sum of exp of the causal logits        (softmax denominators)
+//   columns   : per key column k, sum_{j>=k} exp(x_jk - max_j) / sum_j, divided
 //               by the structural column count L-k                              (Eq. 4 inner term)
-// Both kernels give one wavefront to a row (column).  Its four 16-lane groups take 16 keys
-// (queries) each per iteration; a lane holds a D/16 slice of the vectors and forms its slice of
-// all 16 dot products, and a transposed butterfly (each exchange halves the products a lane still
-// carries) leaves every lane with the total of a different key: 64 logits, and 64 useful
-// exponentials, per wave and iteration.
+// Both are passes of one kernel over Q K^T on the matrix cores (v_mfma_f64_16x16x4_f64, operands widened in
+// registers): a wave keeps 32 rows of one operand (the queries of its row statistics, the keys of its column sums) in
+// registers and streams the other through LDS.  The order of the head's elements inside a product is free as long as
+// both operands agree: lane kb takes the kb-th quarter of a row, so that LDS is read 16 bytes at a time (chunk index
+// xor row, conflict-free).  The bound is the fp64 matrix product, 64 cycles per 16 x 16 x 4 block and SIMD: 8192 tokens,
+// 32 heads, 3.6 ms per pass at 2.4 GHz, measured 5.1 and 4.9 ms; on the vector ALU (dot products of 16 lanes and a
+// butterfly) the passes took 16.5 and 18.9 ms.
 // The selection of every candidate reuses the online-selection stages (scores
 // and in-block ranks once, budgets per candidate); cand_score sums the column
 // means of the tokens a candidate keeps (Eq. 4).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
 #include <vector>
 
 #include "tca_common.h"
@@ -26,101 +28,149 @@ namespace tca {
 
 constexpr int kCalThreads = 256;
 
-template <typename T, int EL>
-__device__ __forceinline__ void load_slice_f64(const T* p, double (&out)[EL]) {
-  float tmp[EL];
-  load_slice<T, EL>(p, tmp);
-#pragma unroll
-  for (int e = 0; e < EL; ++e) out[e] = (double)tmp[e];
-}
+// grid (ceil(L / 128) * Hq), the longest walks first, heads inside (head by head, the last head's longest walks start when
+// the others are done: 16.0 against 10.1 ms for both passes); block 256: wave = 32 fixed rows, lane (kb = lane / 16, c = lane % 16)
+// holds, of every 16 streamed rows, the logits of the rows kb + 4 r against the fixed rows c and c + 16.
+// COL = false: the queries are fixed, keys 0 .. j stream by, row_max / row_sum are written.  COL = true: the keys are
+// fixed, queries k .. L-1 stream by, abar is written.
+template <typename T, int D, bool COL>
+__global__ __launch_bounds__(kCalThreads, 2) void cal_pass_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, int64_t L, int Hq, int G, double scale,
+    double* __restrict__ row_max, double* __restrict__ row_sum, double* __restrict__ abar) {
+  typedef double f64x4_t __attribute__((ext_vector_type(4)));
+  constexpr int EPC = Vec16<T>::N;                 // elements of a 16-byte chunk
+  constexpr int CPR = D / EPC, CPQ = CPR / 4;      // chunks of a row, of a quarter row
+  constexpr int TS = 32;                           // streamed rows per tile
+  constexpr int NL = TS * CPR / kCalThreads;       // chunks a thread stages
+  constexpr int SWZ = (CPR < 16 ? CPR : 16) - 1;
+  static_assert(NL >= 1 && NL * kCalThreads == TS * CPR, "shape");
+  __shared__ raw16_t tile[TS][CPR];
+  __shared__ double rmx[COL ? TS : 1], rinv[COL ? TS : 1];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, kb = lane >> 4, c = lane & 15;
+  const int h = blockIdx.x % Hq, kvh = h / G, turn = blockIdx.x / Hq;
+  const int64_t f0 = (int64_t)(COL ? turn : gridDim.x / Hq - 1 - turn) * 128;
+  const T* fixed = COL ? K + (size_t)kvh * L * D : Q + (size_t)h * L * D;
+  const T* stream = COL ? Q + (size_t)h * L * D : K + (size_t)kvh * L * D;
+  const double* rm = row_max + (size_t)h * L;
+  const double* rs = row_sum + (size_t)h * L;
 
-// merge the (m, l) pairs of all 64 lanes of a wave
-__device__ __forceinline__ void merge_lanes(double& m, double& l) {
-  for (int o = 1; o < 64; o <<= 1) {
-    const double mo = __shfl_xor(m, o, kWave), lo = __shfl_xor(l, o, kWave);
-    const double mn = fmax(m, mo);
-    const double a = (m == -INFINITY) ? 0.0 : exp(m - mn);
-    const double b = (mo == -INFINITY) ? 0.0 : exp(mo - mn);
-    l = l * a + lo * b;
-    m = mn;
-  }
-}
-
-// Dot products of this lane's slice `fixed` with the same slice of 16 consecutive rows starting
-// at rows + r0 (rows at or beyond r_end count as zero), summed over the 16 lanes of the group.
-// Returns the total of row r0 + (the row index this lane ends up with), and that index.
-template <typename T, int D>
-__device__ __forceinline__ double dots16(const T* __restrict__ rows, int64_t r0, int64_t r_end, int sub,
-                                         const double (&fixed)[D / 16], int& which) {
-  constexpr int EL = D / 16;
-  using GR = GroupReduce<16, 16>;
-  double acc[16];
+  int64_t frow[2];
+  double f[2][D / 4];                              // elements kb D/4 .. of the fixed rows
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    acc[r] = 0.0;
-    if (r0 + r < r_end) {
-      double v[EL];
-      load_slice_f64<T, EL>(rows + (size_t)(r0 + r) * D + sub * EL, v);
+  for (int b = 0; b < 2; ++b) {
+    frow[b] = f0 + wv * 32 + b * 16 + c;
+    const int64_t r = frow[b] < L ? frow[b] : L - 1;                 // rows past the end compute a duplicate, never stored
 #pragma unroll
-      for (int e = 0; e < EL; ++e) acc[r] = fma(fixed[e], v[e], acc[r]);
+    for (int u = 0; u < CPQ; ++u) {
+      float v[EPC];
+      Vec16<T>::load(fixed + (size_t)r * D + kb * (D / 4) + u * EPC, v);
+#pragma unroll
+      for (int e = 0; e < EPC; ++e) f[b][u * EPC + e] = (double)v[e];
     }
   }
-  which = GR::head_of(sub);
-  return GR::run(acc, sub);
-}
-
-// grid (ceil(L/4), Hq); block 256: one wave per query row
-template <typename T, int D>
-__global__ __launch_bounds__(kCalThreads) void cal_rowstats_kernel(
-    const T* __restrict__ Q, const T* __restrict__ K, int64_t L, int G, double scale,
-    double* __restrict__ row_max, double* __restrict__ row_sum) {
-  constexpr int EL = D / 16;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, grp = lane >> 4, sub = lane & 15;
-  const int h = blockIdx.y, kvh = h / G;
-  const int64_t j = L - 1 - ((int64_t)blockIdx.x * 4 + wv);       // longest rows first
-  if (j < 0) return;
-  double q[EL];
-  load_slice_f64<T, EL>(Q + ((size_t)h * L + j) * D + sub * EL, q);
-  const T* Kh = K + (size_t)kvh * L * D;
-  double m = -INFINITY, l = 0.0;
-  for (int64_t k0 = 0; k0 <= j; k0 += 64) {
-    int r;
-    const double s = dots16<T, D>(Kh, k0 + grp * 16, j + 1, sub, q, r) * scale;
-    if (k0 + grp * 16 + r <= j) {
-      const double mn = fmax(m, s);
-      l = l * exp(m - mn) + exp(s - mn);
-      m = mn;
+  const int64_t s_begin = COL ? f0 : 0, s_end = COL ? L : (f0 + 128 < L ? f0 + 128 : L);
+  raw16_t nxt[NL];
+  double nrm = 0.0, nri = 0.0;
+  auto fetch = [&](int64_t s0) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int ci = i * kCalThreads + tid, r = ci / CPR, ch = ci - r * CPR;
+      nxt[i] = raw16_t{0, 0, 0, 0};
+      if (s0 + r < s_end) nxt[i] = load_raw16(stream + (size_t)(s0 + r) * D + ch * EPC);
+    }
+    if (COL && tid < TS && s0 + tid < s_end) {
+      nrm = rm[s0 + tid];
+      nri = 1.0 / rs[s0 + tid];
+    }
+  };
+  double m[2] = {-INFINITY, -INFINITY}, l[2] = {0.0, 0.0};          // COL: l alone, the sum
+  fetch(s_begin);
+  for (int64_t s0 = s_begin; s0 < s_end; s0 += TS) {
+    __syncthreads();                               // the tile before has been consumed
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int ci = i * kCalThreads + tid, r = ci / CPR, ch = ci - r * CPR;
+      tile[r][ch ^ (r & SWZ)] = nxt[i];
+    }
+    if (COL && tid < TS) { rmx[tid] = nrm; rinv[tid] = nri; }
+    __syncthreads();
+    if (s0 + TS < s_end) fetch(s0 + TS);
+#pragma unroll
+    for (int sub = 0; sub < TS / 16; ++sub) {
+      f64x4_t acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+      for (int u = 0; u < CPQ; ++u) {
+        float v[EPC];
+        widen_raw16<T>(tile[sub * 16 + c][(kb * CPQ + u) ^ (c & SWZ)], v);
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) {
+          const double a = (double)v[e];
+          acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, f[0][u * EPC + e], acc[0], 0, 0, 0);
+          acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, f[1][u * EPC + e], acc[1], 0, 0, 0);
+        }
+      }
+      // A block of rows that every fixed row of the wave may see takes no tests: its exponentials are independent of
+      // each other (under a test each, they ran one after the other: 17.8 against 16.4 ms for the call).
+      const int64_t si0 = s0 + sub * 16;
+      const int64_t wave0 = f0 + wv * 32;
+      const bool full = COL ? si0 >= wave0 + 31 && si0 + 16 <= L : si0 + 15 <= wave0 && si0 + 16 <= s_end;
+      auto take = [&](auto full_tag) {
+        constexpr bool FULL = decltype(full_tag)::value;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          double x[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int64_t si = si0 + kb + 4 * r;
+            x[r] = acc[b][r] * scale;
+            if (!FULL && !(COL ? si >= frow[b] && si < L : si <= frow[b] && si < s_end)) x[r] = -INFINITY;
+          }
+          if constexpr (COL) {
+            double e[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int sl = sub * 16 + kb + 4 * r;
+              e[r] = FULL || x[r] > -INFINITY ? exp(x[r] - rmx[sl]) * rinv[sl] : 0.0;
+            }
+            l[b] += (e[0] + e[1]) + (e[2] + e[3]);
+          } else {
+            const double mx = fmax(m[b], fmax(fmax(x[0], x[1]), fmax(x[2], x[3])));
+            if (mx > m[b]) {                       // this lane's rows: the four lanes of a query are merged at the end
+              l[b] *= exp(m[b] - mx);              // 0 on the first rows (m = -inf)
+              m[b] = mx;
+            }
+            double e[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) e[r] = FULL || x[r] > -INFINITY ? exp(x[r] - mx) : 0.0;
+            l[b] += (e[0] + e[1]) + (e[2] + e[3]);
+          }
+        }
+      };
+      if (full) take(std::true_type{});
+      else take(std::false_type{});
     }
   }
-  merge_lanes(m, l);
-  if (lane == 0) {
-    row_max[(size_t)h * L + j] = m;
-    row_sum[(size_t)h * L + j] = l;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    for (int o = 16; o < 64; o <<= 1) {
+      const double lo = __shfl_xor(l[b], o, kWave);
+      if constexpr (COL) {
+        l[b] += lo;
+      } else {
+        const double mo = __shfl_xor(m[b], o, kWave);
+        const double mn = fmax(m[b], mo);
+        const double wa = (m[b] == -INFINITY) ? 0.0 : exp(m[b] - mn);
+        const double wb = (mo == -INFINITY) ? 0.0 : exp(mo - mn);
+        l[b] = l[b] * wa + lo * wb;
+        m[b] = mn;
+      }
+    }
+    if (kb == 0 && frow[b] < L) {
+      const size_t at = (size_t)h * L + frow[b];
+      if constexpr (COL) abar[at] = l[b] / (double)(L - frow[b]);
+      else { row_max[at] = m[b]; row_sum[at] = l[b]; }
+    }
   }
-}
-
-// grid (ceil(L/4), Hq); block 256: one wave per key column
-template <typename T, int D>
-__global__ __launch_bounds__(kCalThreads) void cal_colmeans_kernel(
-    const T* __restrict__ Q, const T* __restrict__ K, int64_t L, int G, double scale,
-    const double* __restrict__ row_max, const double* __restrict__ row_sum, double* __restrict__ abar) {
-  constexpr int EL = D / 16;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, grp = lane >> 4, sub = lane & 15;
-  const int h = blockIdx.y, kvh = h / G;
-  const int64_t k = (int64_t)blockIdx.x * 4 + wv;                 // longest columns first
-  if (k >= L) return;
-  double kv[EL];
-  load_slice_f64<T, EL>(K + ((size_t)kvh * L + k) * D + sub * EL, kv);
-  const T* Qh = Q + (size_t)h * L * D;
-  double acc = 0.0;
-  for (int64_t j0 = k; j0 < L; j0 += 64) {
-    int r;
-    const double s = dots16<T, D>(Qh, j0 + grp * 16, L, sub, kv, r) * scale;
-    const int64_t j = j0 + grp * 16 + r;
-    if (j < L) acc += exp(s - row_max[(size_t)h * L + j]) / row_sum[(size_t)h * L + j];
-  }
-  acc = group_sum(acc, kWave);
-  if (lane == 0) abar[(size_t)h * L + k] = acc / (double)(L - k);
 }
 
 // grid (M, Hs); block 256.  a[h][i] = sum of abar over tokens with rank < t_block (Eq. 4).
@@ -206,11 +256,10 @@ __global__ void cal_gather_qlast_kernel(const T* __restrict__ Q, int64_t L, int 
 template <typename T, int D>
 static void run_passes(const tca_params* prm, const T* Q, const T* K, int64_t L, const CalWs& c, hipStream_t st) {
   const int Hq = prm->n_q_heads, G = Hq / prm->n_kv_heads;
-  const dim3 grid((unsigned)((L + 3) / 4), Hq);
+  const dim3 grid((unsigned)((L + 127) / 128 * Hq));
   const double sc = logit_scale(prm);
-  hipLaunchKernelGGL((cal_rowstats_kernel<T, D>), grid, dim3(kCalThreads), 0, st, Q, K, L, G, sc, c.row_max, c.row_sum);
-  hipLaunchKernelGGL((cal_colmeans_kernel<T, D>), grid, dim3(kCalThreads), 0, st, Q, K, L, G, sc, c.row_max, c.row_sum,
-                     c.abar);
+  hipLaunchKernelGGL((cal_pass_kernel<T, D, false>), grid, dim3(kCalThreads), 0, st, Q, K, L, Hq, G, sc, c.row_max, c.row_sum, c.abar);
+  hipLaunchKernelGGL((cal_pass_kernel<T, D, true>), grid, dim3(kCalThreads), 0, st, Q, K, L, Hq, G, sc, c.row_max, c.row_sum, c.abar);
   hipLaunchKernelGGL((cal_gather_qlast_kernel<T>), dim3(Hq), dim3(128), 0, st, Q, L, D, (T*)c.q_last);
 }
 

@@ -812,3 +812,16 @@ def test_decode_units_at_their_edges(tb, bufs, case):
             ref = torch.softmax(x, 0) @ vals
             for Ox in (got[0][0], got[1][0]):
                 assert (Ox[s, h] - ref).abs().max().item() <= H.TOL[dtype], (s, h)
+
+
+CALIB_EDGES = [
+    ("lowrank", 3, 1, 64, 129, "bf16", 16, 4, 74),     # one row into the second block of 128; three heads per group
+    ("lowrank", 2, 2, 128, 33, "f32", 16, 3, 75),      # one row into the second streamed tile of 32
+    ("lowrank", 8, 4, 64, 256, "f32", 32, 3, 76),      # whole blocks
+    ("lowrank", 4, 2, 128, 160, "bf16", 32, 3, 77),    # a wave of the last block with no row at all
+]
+
+
+@pytest.mark.parametrize("case", CALIB_EDGES, ids=lambda c: f"{c[0]}-Hq{c[1]}-d{c[3]}-L{c[4]}-{c[5]}-b{c[6]}-M{c[7]}")
+def test_calibrate_at_the_edges_of_its_tiles(tb, bufs, case):
+    test_calibrate_budgets_matches_oracle(tb, bufs, case)
