@@ -12,7 +12,7 @@
 //                   ranks and writes 1 byte per (head, token); for selection the
 //                   ranking is left to gather_kernel, which is bound by HBM and
 //                   has the vector ALU to spare.
-//   assign_kernel : one workgroup per query head.  Global softmax normaliser,
+//   assign_kernel : one workgroup per head (one to sixteen waves).  Global softmax normaliser,
 //                   h_j (Eq. 6), rank of every block, t_j = Psi[rank] (Eq. 7),
 //                   exclusive scan of t_j -> destination row of every block.
 //   gather_kernel : one workgroup per (head, block).  Ranks the block's tokens by
@@ -34,7 +34,6 @@
 namespace tca {
 
 constexpr int kScoreThreads = 256;
-constexpr int kAssignThreads = 1024;
 constexpr int kGatherThreads = 256;
 constexpr int kGatherRows = 2;        // rows per thread in flight in the copy loop (4 measured the same)
 constexpr int kHeadsPerLaunch = 32;
@@ -302,47 +301,49 @@ struct AssignArgs {
   int64_t cap[kHeadsPerLaunch];                   // capacity of the head's region
 };
 
-__device__ __forceinline__ double block_reduce_max(double v, double* red) {
-  v = group_max(v, kWave);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) red[wv] = v;
-  __syncthreads();
-  double r = red[0];
-  for (int i = 1; i < kAssignThreads / kWave; ++i) r = fmax(r, red[i]);
-  return r;
-}
-__device__ __forceinline__ double block_reduce_sum(double v, double* red) {
-  v = group_sum(v, kWave);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) red[wv] = v;
-  __syncthreads();
-  double r = 0.0;
-  for (int i = 0; i < kAssignThreads / kWave; ++i) r += red[i];
-  return r;
+// max / sum over the NT threads of the workgroup, result in every thread; red: one double per wave
+template <int NT, bool MAX>
+__device__ __forceinline__ double block_reduce(double v, double* red) {
+  v = MAX ? group_max(v, kWave) : group_sum(v, kWave);
+  if constexpr (NT > kWave) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    __syncthreads();
+    if (lane == 0) red[wv] = v;
+    __syncthreads();
+    v = red[0];
+    for (int i = 1; i < NT / kWave; ++i) v = MAX ? fmax(v, red[i]) : v + red[i];
+  }
+  return v;
 }
 
-// grid (heads in this launch); block 1024.
-__global__ __launch_bounds__(kAssignThreads) void assign_kernel(
+// does (ha, ja) come after (hb, jb) in the order: ascending h, ties by lower block
+__device__ __forceinline__ bool comes_after(double ha, int ja, double hb, int jb) { return ha > hb || (ha == hb && ja > jb); }
+
+// grid (heads in this launch); block NT, R blocks per thread, m <= NT * R.  Everything is latency: the sort keeps its
+// pairs in registers, exchanges at distances below 64 are lane shuffles, those between waves go through LDS
+// (barriers), those at NT and beyond stay inside the thread.
+template <int NT, int R>
+__global__ __launch_bounds__(NT) void assign_kernel(
     AssignArgs args, int head0, int nk, int m, int nbt, int b, double alpha, int metric,
     const double* __restrict__ stats, int32_t* __restrict__ n_rows,
     int32_t* __restrict__ blk_t, int32_t* __restrict__ blk_dst) {
-  __shared__ double hs[TCA_MAX_BLOCKS];
-  __shared__ uint16_t ts[TCA_MAX_BLOCKS];
-  __shared__ uint16_t js[TCA_MAX_BLOCKS];
-  __shared__ double red[kAssignThreads / kWave];
-  __shared__ int32_t scan[kAssignThreads];
-  const int tid = threadIdx.x;
+  constexpr int P = NT * R;
+  __shared__ double hs[NT > kWave ? P : 1];
+  __shared__ uint16_t js[NT > kWave ? P : 1];
+  __shared__ uint16_t ts[P];
+  __shared__ double red[NT / kWave];
+  __shared__ int32_t wave_sum[NT / kWave];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int hl = blockIdx.x, h = head0 + hl;
   const double* st = stats + (size_t)h * nbt * kBlockStats;
+  const int32_t fill = n_rows[h];
 
-  // the statistics of this thread's blocks (block j = tid + k * 1024, tail block included), read once
-  constexpr int KMAX = TCA_MAX_BLOCKS / kAssignThreads + 1;
+  // the statistics of this thread's blocks (block j = tid + k * NT, tail block included), read once
+  constexpr int KMAX = R + 1;
   double bM[KMAX], bE1[KMAX], bE2[KMAX];              // bE2: the statistic the chosen index needs
 #pragma unroll
   for (int k = 0; k < KMAX; ++k) {
-    const int j = tid + k * kAssignThreads;
+    const int j = tid + k * NT;
     const bool in = j < nbt;
     bM[k] = in ? st[j * kBlockStats] : -INFINITY;
     bE1[k] = in ? st[j * kBlockStats + 1] : 0.0;
@@ -352,19 +353,23 @@ __global__ __launch_bounds__(kAssignThreads) void assign_kernel(
   double mx = -INFINITY;
 #pragma unroll
   for (int k = 0; k < KMAX; ++k) mx = fmax(mx, bM[k]);
-  mx = block_reduce_max(mx, red);
+  mx = block_reduce<NT, true>(mx, red);
   double z = 0.0;
 #pragma unroll
   for (int k = 0; k < KMAX; ++k) {
-    bM[k] = tid + k * kAssignThreads < nbt ? bE1[k] * exp(bM[k] - mx) : 0.0;   // block mass before normalisation
+    bM[k] = tid + k * NT < nbt ? bE1[k] * exp(bM[k] - mx) : 0.0;   // block mass before normalisation
     z += bM[k];
   }
-  z = block_reduce_sum(z, red);
+  z = block_reduce<NT, false>(z, red);
 
   // Eq. 6
+  double key[R];
+  int blk[R];
 #pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
-    const int j = tid + k * kAssignThreads;
+  for (int k = 0; k < R; ++k) {
+    const int j = tid + k * NT;
+    key[k] = INFINITY;                                 // padding sorts last
+    blk[k] = j;
     if (j < m) {
       const double mass = bM[k] / z;
       // HHI of the block (Eq. 6), or the entropy of the scores renormalised inside it:
@@ -372,78 +377,105 @@ __global__ __launch_bounds__(kAssignThreads) void assign_kernel(
       const double spread = metric == TCA_METRIC_ENTROPY
                                 ? (log(bE1[k]) - bE2[k] / bE1[k]) / log((double)b)
                                 : 1.0 - bE2[k] / (bE1[k] * bE1[k]);
-      hs[j] = (1.0 - alpha) * mass + alpha * spread;
+      key[k] = (1.0 - alpha) * mass + alpha * spread;
     }
   }
-  __syncthreads();
 
-  // order the blocks by ascending h (ties: lower block first) with a bitonic sort
-  // of (h, block) pairs in LDS, then Eq. 7: the block at sorted position r gets Psi[r]
-  int P = 1;
-  while (P < m) P <<= 1;
-  for (int e = tid; e < P; e += kAssignThreads) {
-    js[e] = (uint16_t)e;
-    if (e >= m) hs[e] = INFINITY;                      // padding sorts last
-  }
-  __syncthreads();
-  for (int k = 2; k <= P; k <<= 1) {
-    for (int jj = k >> 1; jj > 0; jj >>= 1) {
-      for (int e = tid; e < P; e += kAssignThreads) {
-        const int pr = e ^ jj;
-        if (pr > e) {
-          const double ha = hs[e], hb = hs[pr];
-          const uint16_t ja = js[e], jb = js[pr];
-          const bool a_after_b = (ha > hb) || (ha == hb && ja > jb);
-          const bool ascending = (e & k) == 0;
-          if (a_after_b == ascending) {
-            hs[e] = hb; hs[pr] = ha;
-            js[e] = jb; js[pr] = ja;
+  // order the blocks by ascending h (ties: lower block first) with a bitonic sort of (h, block) pairs,
+  // then Eq. 7: the block at sorted position r gets Psi[r].  Element e = tid + k * NT.
+  int top = 2;
+  while (top < m) top <<= 1;                           // what lies beyond is padding, in order already
+  for (int kk = 2; kk <= top; kk <<= 1) {
+    for (int jj = kk >> 1; jj > 0; jj >>= 1) {
+      if (jj >= NT) {
+        if constexpr (R > 1) {
+          const int dr = jj / NT;
+#pragma unroll
+          for (int k = 0; k < R; ++k) {
+#pragma unroll
+            for (int d = 1; d < R; d <<= 1) {          // partners k and k + d, d known to the compiler
+              if (d == dr && (k & d) == 0 && k + d < R) {
+                const bool ascending = ((tid + k * NT) & kk) == 0;
+                if (comes_after(key[k], blk[k], key[k + d], blk[k + d]) == ascending) {
+                  const double tk = key[k]; key[k] = key[k + d]; key[k + d] = tk;
+                  const int tb = blk[k]; blk[k] = blk[k + d]; blk[k + d] = tb;
+                }
+              }
+            }
           }
         }
+      } else if (jj >= kWave) {
+        if constexpr (NT > kWave) {
+          __syncthreads();                             // the exchange before has been read
+#pragma unroll
+          for (int k = 0; k < R; ++k) { hs[tid + k * NT] = key[k]; js[tid + k * NT] = (uint16_t)blk[k]; }
+          __syncthreads();
+#pragma unroll
+          for (int k = 0; k < R; ++k) {
+            const int e = tid + k * NT, pr = e ^ jj;
+            const double ho = hs[pr];
+            const int jo = js[pr];
+            const bool lower = (e & jj) == 0, ascending = (e & kk) == 0;
+            // the lower element of an ascending pair keeps the smaller
+            if (comes_after(key[k], blk[k], ho, jo) == (lower == ascending)) { key[k] = ho; blk[k] = jo; }
+          }
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+          const int e = tid + k * NT;
+          const double ho = __shfl_xor(key[k], jj, kWave);
+          const int jo = __shfl_xor(blk[k], jj, kWave);
+          const bool lower = (e & jj) == 0, ascending = (e & kk) == 0;
+          if (comes_after(key[k], blk[k], ho, jo) == (lower == ascending)) { key[k] = ho; blk[k] = jo; }
+        }
       }
-      // Element e is always handled by the wave that owns its aligned group of 64,
-      // so a stage with partner distance < 64 touches only the wave's own
-      // elements.  A workgroup barrier is needed only when this stage or the next
-      // one pairs elements of different waves; otherwise the wave's own LDS
-      // accesses are already ordered.
-      const int next_jj = jj > 1 ? (jj >> 1) : k;        // distance of the following stage
-      if (jj >= kWave || next_jj >= kWave) __syncthreads();
-      else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int r = tid + k * NT;
+    if (r < m) {
+      int e = 0;
+      while (e < nk - 1 && r >= args.cum[hl][e]) ++e;
+      ts[blk[k]] = (uint16_t)(1 << e);
     }
   }
   __syncthreads();
-  for (int r = tid; r < m; r += kAssignThreads) {
-    int e = 0;
-    while (e < nk - 1 && r >= args.cum[hl][e]) ++e;
-    ts[js[r]] = (uint16_t)(1 << e);
-  }
-  __syncthreads();
 
-  // exclusive scan of t_j in block order: thread t owns a run of `per` blocks
-  const int per = (m + kAssignThreads - 1) / kAssignThreads;
-  const int j0 = tid * per;
-  int local = 0;
-  for (int j = j0; j < j0 + per && j < m; ++j) local += ts[j];
-  scan[tid] = local;
-  __syncthreads();
-  for (int o = 1; o < kAssignThreads; o <<= 1) {
-    int v = tid >= o ? scan[tid - o] : 0;
-    __syncthreads();
-    scan[tid] += v;
-    __syncthreads();
+  // exclusive scan of t_j in block order: thread t owns blocks t * R .. t * R + R - 1
+  int own[R], local = 0;
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    own[k] = tid * R + k < m ? ts[tid * R + k] : 0;
+    local += own[k];
   }
-  const int32_t fill = n_rows[h];
-  int run = fill + scan[tid] - local;
-  for (int j = j0; j < j0 + per && j < m; ++j) {
-    blk_t[(size_t)h * m + j] = ts[j];
-    blk_dst[(size_t)h * m + j] = run;
-    run += ts[j];
+  int incl = local;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int v = __shfl_up(incl, o, kWave);
+    if (lane >= o) incl += v;
   }
+  if (lane == kWave - 1) wave_sum[wv] = incl;
   __syncthreads();
-  if (tid == kAssignThreads - 1) {
-    int64_t total = (int64_t)fill + scan[tid];
-    if (total > args.cap[hl]) total = args.cap[hl];
-    n_rows[h] = (int32_t)total;
+  int before = 0, all = 0;
+  for (int i = 0; i < NT / kWave; ++i) {
+    if (i < wv) before += wave_sum[i];
+    all += wave_sum[i];
+  }
+  int run = fill + before + incl - local;
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int j = tid * R + k;
+    if (j < m) {
+      blk_t[(size_t)h * m + j] = own[k];
+      blk_dst[(size_t)h * m + j] = run;
+      run += own[k];
+    }
+  }
+  if (tid == 0) {
+    const int64_t total = (int64_t)fill + all;
+    n_rows[h] = (int32_t)(total > args.cap[hl] ? args.cap[hl] : total);
   }
 }
 
@@ -635,8 +667,17 @@ void select_assign_stage(const tca_params* prm, int64_t n_tokens, const double* 
       for (int e = 0; e < nk; ++e) { run += c[e]; aa.cum[hl][e] = (int32_t)run; }
       aa.cap[hl] = cap[h0 + hl];
     }
-    hipLaunchKernelGGL(assign_kernel, dim3(nh), dim3(kAssignThreads), 0, st, aa, h0, nk, (int)nb,
-                       (int)nbt, b, prm->alpha, prm->metric, stats, n_rows, blk_t, blk_dst);
+    // One wave where it can hold all blocks (no barrier at all), then four, then sixteen, whose threads take four blocks
+    // each at most.  us per launch, 32 heads: 64 blocks 12.5 -> 8.6, 3 blocks 8.5 -> 5.3, 1024 blocks 28.3 -> 20.3
+    // (one shape of 1024 threads, the sort and the scan in LDS, before).
+    auto launch = [&](auto kernel, int threads) {
+      hipLaunchKernelGGL(kernel, dim3(nh), dim3(threads), 0, st, aa, h0, nk, (int)nb, (int)nbt, b, prm->alpha, prm->metric,
+                         stats, n_rows, blk_t, blk_dst);
+    };
+    if (nb <= 64) launch(assign_kernel<64, 1>, 64);
+    else if (nb <= 256) launch(assign_kernel<256, 1>, 256);
+    else if (nb <= 1024) launch(assign_kernel<1024, 1>, 1024);
+    else launch(assign_kernel<1024, 4>, 1024);
   }
 }
 
