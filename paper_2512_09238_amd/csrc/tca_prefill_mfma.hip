@@ -81,60 +81,79 @@ __host__ __device__ inline int vt_key_of_pos(int p) {
 }
 
 // ---------------------------------------------------------------- pre-pass --
-// Transposes 64-row tiles of a row-major [rows, D] bf16 matrix into
-// [D][64] tiles (keys permuted by vt_key_of_pos); rows >= n_valid become zero.
-// grid (tiles, groups); block 256.
+// Transposes 64-row tiles of row-major [rows, D] bf16 matrices into [D][64] tiles (keys permuted by
+// vt_key_of_pos); rows past the last become zero, tiles past it are left alone (nobody reads them).  HBM-bound: no
+// LDS, a thread loads 16 bytes of the eight keys of one output chunk, transposes the 8 x 8 block in registers and
+// stores eight 16-byte chunks; of a wave's loads and stores every eight lanes cover 128 consecutive bytes.
+// (Staged through LDS and read back two bytes at a time: 2.7 TB/s; this 5.1 TB/s: 64 heads, 4.4 M
+// rows, 800 -> 440 us.)
+// The first region_tiles tiles are those of the regions (head by ph.tile_off; gather_idx != NULL: row r of a region
+// is row gather_idx[ph.offs[g] + r] of the dense matrix of KV head g / sel_per_kv, no compacted copy exists), the
+// others dense rows (tiles_per_group per KV head, from row first_row on, valid below valid_all).
+// grid (ceil(tiles / (256 / D))): D threads per tile; block 256.
 template <int D>
 __global__ __launch_bounds__(256) void transpose_tiles_kernel(
-    const uint16_t* __restrict__ src, int64_t group_stride_rows, const int32_t* group_valid,
-    int64_t valid_all, int64_t first_row, uint16_t* __restrict__ dst, int tiles_per_group,
-    PrefillHeads ph, int mode, unsigned long long* clk, const int32_t* __restrict__ gather_idx, int sel_per_kv) {
-  // mode 0: global regions (group = selection head; rows from ph.offs, valid rows from group_valid).
-  //         gather_idx != NULL: src is the dense [KV head][group_stride_rows][D] matrix and row r of the
-  //         region is its row gather_idx[ph.offs[g] + r] of KV head g / sel_per_kv (no compacted copy exists)
-  // mode 1: dense K/V (group = KV head; absolute rows first_row + 64*tile, valid while < valid_all)
-  __shared__ uint16_t tile[kBN][D + 8];
-  const int g = blockIdx.y, t = blockIdx.x, tid = threadIdx.x;
-  if (clk && g == 0 && t == 0 && tid < 4) clk[tid] = 0;      // the attention kernel that follows accumulates here
-  int64_t row0;
-  int64_t n_valid;
-  size_t out_tile;
-  if (mode == 0) {
-    const int64_t cap = ph.offs[g + 1] - ph.offs[g];
-    const int ntile = (int)((cap + kBN - 1) / kBN);
-    if (t >= ntile) return;
-    row0 = ph.offs[g] + (int64_t)t * kBN;
-    n_valid = (int64_t)group_valid[g] - (int64_t)t * kBN;
-    out_tile = (size_t)ph.tile_off[g] + t;
-  } else {
-    row0 = (int64_t)g * group_stride_rows + first_row + (int64_t)t * kBN;
-    n_valid = valid_all - (first_row + (int64_t)t * kBN);
-    out_tile = (size_t)g * tiles_per_group + t;
-  }
-  constexpr int CPR = D / 8;                       // 16-byte chunks per row
-  for (int c = tid; c < kBN * CPR; c += 256) {
-    const int r = c / CPR, part = c - r * CPR;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (r < n_valid) {
-      size_t row = (size_t)(row0 + r);
-      if (mode == 0 && gather_idx) row = (size_t)(g / sel_per_kv) * group_stride_rows + gather_idx[row0 + r];
-      v = *reinterpret_cast<const uint4*>(src + row * D + part * 8);
+    const uint16_t* __restrict__ Vg, const uint16_t* __restrict__ V, int64_t kv_stride, const int32_t* __restrict__ n_rows,
+    const int32_t* __restrict__ gather_idx, int sel_per_kv, int Hs, int region_tiles, int tiles, int tiles_per_group,
+    int64_t first_row, int64_t valid_all, uint16_t* __restrict__ region_dst, uint16_t* __restrict__ dense_dst,
+    PrefillHeads ph, unsigned long long* clk) {
+  constexpr int TPT = D;                           // threads per tile: 8 chunks of keys x D / 8 chunks of columns
+  const int tid = threadIdx.x;
+  if (clk && blockIdx.x == 0 && tid < 4) clk[tid] = 0;       // the attention kernel that follows accumulates here
+  const int t = __builtin_amdgcn_readfirstlane(blockIdx.x * (256 / TPT) + tid / TPT);      // uniform: a wave has one tile
+  if (t >= tiles) return;
+  const int in = tid % TPT;
+  const int part = (in >> 3) & 7, cg = (in & 7) + 8 * (in >> 6);       // chunk of keys, chunk of columns
+  const uint16_t* src;
+  const int32_t* gi = nullptr;
+  int64_t row0, n_valid;
+  uint16_t* out;
+  if (t < region_tiles) {
+    int g = 0;
+    for (int step = 64; step > 0; step >>= 1)
+      if (g + step < Hs && ph.tile_off[g + step] <= t) g += step;
+    const int64_t r = (int64_t)(t - ph.tile_off[g]) * kBN;
+    n_valid = n_rows[g] - r;
+    row0 = r;
+    if (gather_idx) {
+      gi = gather_idx + ph.offs[g] + r;
+      src = V + (size_t)(g / sel_per_kv) * kv_stride * D;
+    } else {
+      src = Vg + (size_t)ph.offs[g] * D;
     }
-    *reinterpret_cast<uint4*>(&tile[r][part * 8]) = v;
+    out = region_dst + (size_t)t * (D * kBN);
+  } else {
+    const int dt = t - region_tiles, g = dt / tiles_per_group;
+    row0 = first_row + (int64_t)(dt - g * tiles_per_group) * kBN;
+    n_valid = valid_all - row0;
+    src = V + (size_t)g * kv_stride * D;
+    out = dense_dst + (size_t)dt * (D * kBN);
   }
-  __syncthreads();
-  uint16_t* out = dst + out_tile * (size_t)(D * kBN);
-  for (int c = tid; c < D * (kBN / 8); c += 256) {
-    const int dd = c / (kBN / 8), part = c - dd * (kBN / 8);
-    uint16_t v[8];
+  if (n_valid <= 0) return;
+  uint4 v[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = tile[vt_key_of_pos(part * 8 + e)][dd];
-    uint4 pk;
-    pk.x = v[0] | ((uint32_t)v[1] << 16);
-    pk.y = v[2] | ((uint32_t)v[3] << 16);
-    pk.z = v[4] | ((uint32_t)v[5] << 16);
-    pk.w = v[6] | ((uint32_t)v[7] << 16);
-    *reinterpret_cast<uint4*>(out + (size_t)dd * kBN + part * 8) = pk;
+  for (int e = 0; e < 8; ++e) {
+    const int k = vt_key_of_pos(part * 8 + e);
+    v[e] = make_uint4(0, 0, 0, 0);
+    if (k < n_valid) {
+      const size_t row = gi ? (size_t)gi[k] : (size_t)(row0 + k);
+      v[e] = *reinterpret_cast<const uint4*>(src + row * D + cg * 8);
+    }
+  }
+  const uint32_t* w = reinterpret_cast<const uint32_t*>(v);            // [key][pair of columns]
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    uint4 lo, hi;                                  // columns 2 j and 2 j + 1 over the eight keys
+    uint32_t* l = reinterpret_cast<uint32_t*>(&lo);
+    uint32_t* h = reinterpret_cast<uint32_t*>(&hi);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      l[k] = __builtin_amdgcn_perm(w[(2 * k + 1) * 4 + j], w[2 * k * 4 + j], 0x05040100u);
+      h[k] = __builtin_amdgcn_perm(w[(2 * k + 1) * 4 + j], w[2 * k * 4 + j], 0x07060302u);
+    }
+    uint16_t* o = out + (size_t)(cg * 8 + 2 * j) * kBN + part * 8;
+    *reinterpret_cast<uint4*>(o) = lo;
+    *reinterpret_cast<uint4*>(o + kBN) = hi;
   }
 }
 
@@ -1348,13 +1367,11 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
   const int Hq = prm->n_q_heads, Hkv = prm->n_kv_heads, Hs = sel_heads(prm), w = prm->window;
   PrefillHeads ph;
   int32_t run = 0;
-  int max_tiles = 0;
   for (int h = 0; h < Hs; ++h) {
     ph.offs[h] = offs[h];
     ph.tile_off[h] = run;
     const int nt = (int)((offs[h + 1] - offs[h] + kBN - 1) / kBN);
     run += nt;
-    if (nt > max_tiles) max_tiles = nt;
   }
   ph.offs[Hs] = offs[Hs];
   ph.tile_off[Hs] = run;
@@ -1369,19 +1386,14 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
   // gather-free call (no compacted copy of the kept rows): V^T tiles of the regions are built from the
   // dense V through idx, and the attention kernel fetches the K rows of its region tiles the same way
   const bool gather = Kg == nullptr;
-  if (max_tiles > 0 && part != TCA_PART_WINDOW) {
-    if (gather)
-      hipLaunchKernelGGL((transpose_tiles_kernel<D>), dim3(max_tiles, Hs), dim3(256), 0, st, V, kv_stride, n_rows,
-                         (int64_t)0, (int64_t)0, mw.Vgt, 0, ph, 0, (unsigned long long*)nullptr, idx, Hs / Hkv);
-    else
-      hipLaunchKernelGGL((transpose_tiles_kernel<D>), dim3(max_tiles, Hs), dim3(256), 0, st, Vg, (int64_t)0, n_rows,
-                         (int64_t)0, (int64_t)0, mw.Vgt, 0, ph, 0, (unsigned long long*)nullptr,
-                         (const int32_t*)nullptr, 1);
+  {
+    const int region_tiles = part == TCA_PART_WINDOW ? 0 : run;
+    const int tiles = region_tiles + (part == TCA_PART_GLOBAL ? 0 : d_tiles * Hkv);
+    if (tiles > 0)
+      hipLaunchKernelGGL((transpose_tiles_kernel<D>), dim3((unsigned)((tiles + 256 / D - 1) / (256 / D))), dim3(256), 0, st, Vg, V,
+                         kv_stride, n_rows, gather ? idx : (const int32_t*)nullptr, Hs / Hkv, Hs, region_tiles, tiles, d_tiles,
+                         dt0 * kBN, q_pos0 + n_queries, mw.Vgt, mw.Vt, ph, clk);
   }
-  if (part != TCA_PART_GLOBAL)
-    hipLaunchKernelGGL((transpose_tiles_kernel<D>), dim3(d_tiles, Hkv), dim3(256), 0, st, V, kv_stride,
-                       (const int32_t*)nullptr, q_pos0 + n_queries, dt0 * kBN, mw.Vt, d_tiles, ph, 1, clk,
-                       (const int32_t*)nullptr, 1);
 
   // Shape of a workgroup.  Long calls: eight waves of 32 queries (256 queries, one workgroup per CU,
   // two waves per SIMD).  Calls with few query tiles: four waves of 32 queries
