@@ -744,59 +744,127 @@ __global__ __launch_bounds__(kDecThreads) void decode_merge_kernel(
   finish();
 }
 
-// grid (ceil(rows/16), Hkv); block 256: one 16-lane group per row
-template <typename T, typename KV, int D>
+// Copies a row of T into a cache row of storage type KV: as stored, or as codes and a scale (called by the 16 lanes of a
+// group).  ALIGNED: slices of up to 16 bytes at a time; otherwise element by element.
+template <typename T, typename KV, int D, bool ALIGNED>
+struct RowCopy {
+  static constexpr int EL = D / 16;
+  static constexpr bool kSame = std::is_same<T, KV>::value;
+  RawSlice<T, EL> raw;
+  __device__ __forceinline__ void load(const T* row, int sub) {
+    if constexpr (ALIGNED) {
+      raw.load(row + sub * EL);
+    } else if constexpr (sizeof(T) == 2) {
+      const uint16_t* p = reinterpret_cast<const uint16_t*>(row) + sub * EL;
+#pragma unroll
+      for (int i = 0; i < EL / 2; ++i) raw.w[i] = p[2 * i] | ((uint32_t)p[2 * i + 1] << 16);
+    } else {
+      const uint32_t* p = reinterpret_cast<const uint32_t*>(row) + sub * EL;
+#pragma unroll
+      for (int i = 0; i < EL; ++i) raw.w[i] = p[i];
+    }
+  }
+  __device__ __forceinline__ void store(KV* row, float* scale_slot, int sub) const {
+    if constexpr (!kSame) {
+      float x[EL];
+      raw.widen(x);
+      store_cache_slice<KV, EL>(x, row, scale_slot, sub);
+    } else if constexpr (ALIGNED) {
+      constexpr int W = RawSlice<T, EL>::W;
+      if constexpr (W == 2) {
+        *reinterpret_cast<uint2*>(row + sub * EL) = make_uint2(raw.w[0], raw.w[1]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < W / 4; ++i)
+          reinterpret_cast<uint4*>(row + sub * EL)[i] = make_uint4(raw.w[4 * i], raw.w[4 * i + 1], raw.w[4 * i + 2], raw.w[4 * i + 3]);
+      }
+    } else if constexpr (sizeof(T) == 2) {
+      uint16_t* p = reinterpret_cast<uint16_t*>(row) + sub * EL;
+#pragma unroll
+      for (int i = 0; i < EL; ++i) p[i] = (uint16_t)(raw.w[i >> 1] >> (16 * (i & 1)));
+    } else {
+      uint32_t* p = reinterpret_cast<uint32_t*>(row) + sub * EL;
+#pragma unroll
+      for (int i = 0; i < EL; ++i) p[i] = raw.w[i];
+    }
+  }
+};
+
+// Both handover kernels are HBM-bound copies: one 16-lane group per row, kCopyRows (kWinRows) rows of K and of V per
+// group requested before the first is stored.  32768 tokens, 32 heads, into the FP8 cache (147 MB): 47.5 -> 44.7 us for the
+// two kernels; with bf16 rows, which went two bytes per lane, 62 -> 42 us.
+// (Four rows of the regions: 40 and 37 us against 36 and 35; of the window, of which there is little: 10.8 against 8.3.)
+constexpr int kCopyRows = 2, kWinRows = 1;
+
+// grid (ceil(rows / (16 kWinRows)), Hkv); block 256
+template <typename T, typename KV, int D, bool ALIGNED>
 __global__ __launch_bounds__(256) void load_window_kernel(tca_cache c, int seq, int Hkv, int w, const T* __restrict__ K,
                                                           const T* __restrict__ V, int64_t kv_stride, int64_t L) {
-  constexpr int EL = D / 16;
   const int kvh = blockIdx.y, sub = threadIdx.x & 15;
   const int64_t first = L - w > 0 ? L - w : 0;
-  const int64_t pos = first + (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) c.length[seq] = L;
-  if (pos >= L) return;
-  const int slot = (int)(pos % w);
-  const T* ks = K + ((size_t)kvh * kv_stride + pos) * D;
-  const T* vs = V + ((size_t)kvh * kv_stride + pos) * D;
-  const size_t row = ((size_t)seq * Hkv + kvh) * w + slot;
-  KV* kd = (KV*)c.ringK + row * D;
-  KV* vd = (KV*)c.ringV + row * D;
-  if constexpr (std::is_same<T, KV>::value) {
-    for (int e = sub; e < D; e += 16) { kd[e] = ks[e]; vd[e] = vs[e]; }
-  } else {
-    float x[EL];
-    load_slice<T, EL>(ks + sub * EL, x);
-    store_cache_slice<KV, EL>(x, kd, c.ringK_scale + row, sub);
-    load_slice<T, EL>(vs + sub * EL, x);
-    store_cache_slice<KV, EL>(x, vd, c.ringV_scale + row, sub);
+  const int64_t pos0 = first + (int64_t)blockIdx.x * (16 * kWinRows) + (threadIdx.x >> 4);
+  RowCopy<T, KV, D, ALIGNED> k[kWinRows], v[kWinRows];
+#pragma unroll
+  for (int u = 0; u < kWinRows; ++u) {
+    const int64_t pos = pos0 + u * 16;
+    if (pos < L) {
+      k[u].load(K + ((size_t)kvh * kv_stride + pos) * D, sub);
+      v[u].load(V + ((size_t)kvh * kv_stride + pos) * D, sub);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kWinRows; ++u) {
+    const int64_t pos = pos0 + u * 16;
+    if (pos < L) {                                     // (all 16 lanes of a group alike)
+      const size_t row = ((size_t)seq * Hkv + kvh) * w + (int)(pos % w);
+      k[u].store((KV*)c.ringK + row * D, c.ringK_scale + row, sub);
+      v[u].store((KV*)c.ringV + row * D, c.ringV_scale + row, sub);
+    }
   }
 }
 
-// grid (ceil(cap_rows/16)); block 256: one 16-lane group per row of the flat global buffer
-template <typename T, typename KV, int D>
+// grid (ceil(cap_rows / (16 kCopyRows))); block 256
+template <typename T, typename KV, int D, bool ALIGNED>
 __global__ __launch_bounds__(256) void load_global_kernel(tca_cache c, int seq, DecodeHeads dh, int Hs,
                                                           const int32_t* __restrict__ idx, const T* __restrict__ Kg,
                                                           const T* __restrict__ Vg, const int32_t* __restrict__ n_rows) {
-  constexpr int EL = D / 16;
   const int sub = threadIdx.x & 15;
-  const int64_t r = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
   if (blockIdx.x == 0 && threadIdx.x < Hs) c.n_rows[(size_t)seq * Hs + threadIdx.x] = n_rows[threadIdx.x];
-  if (r >= c.cap_rows) return;
-  int h = 0;
-  while (h + 1 < Hs && dh.offs[h + 1] <= r) ++h;                 // the head whose region holds row r
-  if (r - dh.offs[h] >= n_rows[h]) return;                      // capacity beyond the filled rows
-  const size_t dst = (size_t)seq * c.cap_rows + r;
-  if (sub == 0) c.idx[dst] = idx[r];
-  KV* kd = (KV*)c.Kg + dst * D;
-  KV* vd = (KV*)c.Vg + dst * D;
-  if constexpr (std::is_same<T, KV>::value) {
-    for (int e = sub; e < D; e += 16) { kd[e] = Kg[(size_t)r * D + e]; vd[e] = Vg[(size_t)r * D + e]; }
-  } else {
-    float x[EL];
-    load_slice<T, EL>(Kg + (size_t)r * D + sub * EL, x);
-    store_cache_slice<KV, EL>(x, kd, c.Kg_scale + dst, sub);
-    load_slice<T, EL>(Vg + (size_t)r * D + sub * EL, x);
-    store_cache_slice<KV, EL>(x, vd, c.Vg_scale + dst, sub);
+  // the head whose region holds the workgroup's first row; its other rows lie a head or more further at most
+  const int64_t first = (int64_t)blockIdx.x * (16 * kCopyRows);
+  int h0 = 0;
+  for (int step = 64; step > 0; step >>= 1)
+    if (h0 + step < Hs && dh.offs[h0 + step] <= first) h0 += step;
+  RowCopy<T, KV, D, ALIGNED> k[kCopyRows], v[kCopyRows];
+  int32_t at[kCopyRows];
+  bool ok[kCopyRows];
+#pragma unroll
+  for (int u = 0; u < kCopyRows; ++u) {
+    const int64_t r = first + u * 16 + (threadIdx.x >> 4);
+    int h = h0;
+    while (h + 1 < Hs && dh.offs[h + 1] <= r) ++h;
+    ok[u] = r < c.cap_rows && r - dh.offs[h] < n_rows[h];            // not the capacity beyond the filled rows
+    if (ok[u]) {
+      at[u] = idx[r];
+      k[u].load(Kg + (size_t)r * D, sub);
+      v[u].load(Vg + (size_t)r * D, sub);
+    }
   }
+#pragma unroll
+  for (int u = 0; u < kCopyRows; ++u) {
+    if (ok[u]) {
+      const size_t dst = (size_t)seq * c.cap_rows + first + u * 16 + (threadIdx.x >> 4);
+      if (sub == 0) c.idx[dst] = at[u];
+      k[u].store((KV*)c.Kg + dst * D, c.Kg_scale + dst, sub);
+      v[u].store((KV*)c.Vg + dst * D, c.Vg_scale + dst, sub);
+    }
+  }
+}
+
+// May rows be copied 16 bytes at a time?  (rows are multiples of 64 bytes)
+static bool aligned16(const void* a, const void* b, const void* c, const void* d) {
+  return (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)d) & 15) == 0;
 }
 
 static int check_cache(const tca_params* prm, const tca_cache* c) {
@@ -892,12 +960,20 @@ extern "C" int tca_cache_load_window(const tca_params* prm, const tca_cache* cac
                 (long long)kv_stride);
   const int w = prm->window;
   const int64_t rows = L < w ? L : w;
-  dim3 grid((unsigned)((rows + 15) / 16 > 0 ? (rows + 15) / 16 : 1), prm->n_kv_heads);
+  const int64_t blocks = (rows + 16 * kWinRows - 1) / (16 * kWinRows);
+  dim3 grid((unsigned)(blocks > 0 ? blocks : 1), prm->n_kv_heads);
+  const bool wide = aligned16(K, V, cache->ringK, cache->ringV);
   hipStream_t st = (hipStream_t)stream;
   const bool d128 = prm->head_dim == 128;
-#define TCA_LOAD_WINDOW(TT, KK, DD)                                                                            \
-  hipLaunchKernelGGL((load_window_kernel<TT, KK, DD>), grid, dim3(256), 0, st, *cache, seq, prm->n_kv_heads, w, \
-                     (const TT*)K, (const TT*)V, kv_stride, L)
+  auto go = [&](auto kernel, auto tag) {
+    using TT = decltype(tag);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, *cache, seq, prm->n_kv_heads, w, (const TT*)K, (const TT*)V, kv_stride, L);
+  };
+#define TCA_LOAD_WINDOW(TT, KK, DD)                                      \
+  do {                                                                   \
+    if (wide) go(load_window_kernel<TT, KK, DD, true>, TT{});            \
+    else go(load_window_kernel<TT, KK, DD, false>, TT{});                \
+  } while (0)
   if (cache->kv_format == TCA_KV_FP8) { if (d128) TCA_LOAD_WINDOW(bf16_t, fp8_t, 128); else TCA_LOAD_WINDOW(bf16_t, fp8_t, 64); }
   else if (prm->dtype == TCA_BF16) { if (d128) TCA_LOAD_WINDOW(bf16_t, bf16_t, 128); else TCA_LOAD_WINDOW(bf16_t, bf16_t, 64); }
   else { if (d128) TCA_LOAD_WINDOW(float, float, 128); else TCA_LOAD_WINDOW(float, float, 64); }
@@ -927,11 +1003,18 @@ extern "C" int tca_cache_load_global(const tca_params* prm, const tca_cache* cac
   dh.offs[Hs] = offs[Hs];
   if (cache->cap_rows == 0) return TCA_OK;
   hipStream_t st = (hipStream_t)stream;
-  dim3 grid((unsigned)((cache->cap_rows + 15) / 16));
+  dim3 grid((unsigned)((cache->cap_rows + 16 * kCopyRows - 1) / (16 * kCopyRows)));
+  const bool wide = aligned16(Kg, Vg, cache->Kg, cache->Vg);
   const bool d128 = prm->head_dim == 128;
-#define TCA_LOAD_GLOBAL(TT, KK, DD)                                                                      \
-  hipLaunchKernelGGL((load_global_kernel<TT, KK, DD>), grid, dim3(256), 0, st, *cache, seq, dh, Hs, idx, \
-                     (const TT*)Kg, (const TT*)Vg, n_rows)
+  auto go = [&](auto kernel, auto tag) {
+    using TT = decltype(tag);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, *cache, seq, dh, Hs, idx, (const TT*)Kg, (const TT*)Vg, n_rows);
+  };
+#define TCA_LOAD_GLOBAL(TT, KK, DD)                                      \
+  do {                                                                   \
+    if (wide) go(load_global_kernel<TT, KK, DD, true>, TT{});            \
+    else go(load_global_kernel<TT, KK, DD, false>, TT{});                \
+  } while (0)
   if (cache->kv_format == TCA_KV_FP8) { if (d128) TCA_LOAD_GLOBAL(bf16_t, fp8_t, 128); else TCA_LOAD_GLOBAL(bf16_t, fp8_t, 64); }
   else if (prm->dtype == TCA_BF16) { if (d128) TCA_LOAD_GLOBAL(bf16_t, bf16_t, 128); else TCA_LOAD_GLOBAL(bf16_t, bf16_t, 64); }
   else { if (d128) TCA_LOAD_GLOBAL(float, float, 128); else TCA_LOAD_GLOBAL(float, float, 64); }

@@ -245,3 +245,66 @@ def test_qkv_project_refuses_what_it_cannot_do(tb, bufs):
     tb.tca_qkv_project(prm, Xd, 0, 64, Wd, None, Q, 128, 8 * 128, K, V, 128, 8 * 128)      # nothing to do
     torch.cuda.synchronize()
     assert float(Q.abs().sum()) == 0.0
+
+
+@pytest.mark.parametrize("pairing", ["half", "interleaved"])
+@pytest.mark.parametrize("dtype,d,nh,n", [("bf16", 128, 33, 1), ("bf16", 64, 2, 6), ("f32", 128, 5, 3), ("f32", 64, 17, 9)])
+def test_rope_of_a_buffer_that_is_not_16_byte_aligned(tb, bufs, pairing, dtype, d, nh, n):
+    """The rows of a buffer that starts one element past a 16-byte boundary (read and written element by element)
+    come out as those of an aligned one, bit for bit, and nothing around them is touched; the aligned call itself is
+    compared with the oracle (rows below and above a multiple of the four a workgroup takes, more items than a turn)."""
+    code = tb.TCA_ROPE_HALF if pairing == "half" else tb.TCA_ROPE_INTERLEAVED
+    x = wl.prefill_inputs("lowrank", nh, nh, d, n, dtype, 85)["Q"]
+    prm = H.params_for(tb, nh, nh, d, 16, 16, dtype)
+    A = bufs.to_device(x)
+    flat = torch.full((A.numel() + 2,), 7.0, dtype=A.dtype, device="cuda")
+    flat[1:-1] = A.flatten()
+    tb.tca_rope(prm, A, nh, n, 70001, 500000.0, code)
+    tb.tca_rope(prm, flat[1:-1], nh, n, 70001, 500000.0, code)
+    torch.cuda.synchronize()
+    assert torch.equal(flat[1:-1], A.flatten()) and flat[0] == 7.0 and flat[-1] == 7.0
+    ref = _storage_round(orc.rope_rotate(wl.to_f64(x), 70001 + np.arange(n), base=500000.0, pairing=pairing), dtype)
+    ulp = np.abs(ref) * (2.0 ** -7 if dtype == "bf16" else 2.0 ** -23) + 1e-30
+    assert np.all(np.abs(bufs.to_host_f64(A) - ref) <= ulp)
+
+
+@pytest.mark.parametrize("dtype,kv,d", [("bf16", "native", 128), ("bf16", "native", 64), ("f32", "native", 128), ("bf16", "fp8", 64)])
+def test_handover_of_rows_that_are_not_16_byte_aligned(tb, bufs, dtype, kv, d):
+    """Window and global rows copied from buffers one element past a 16-byte boundary equal those copied from
+    aligned ones; 70 rows of region and 130 of window leave ragged groups of rows, one head keeps none."""
+    Hq, Hkv, w, L = 4, 2, 64, 130
+    prm = H.params_for(tb, Hq, Hkv, d, 16, w, dtype)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    cap = np.array([70, 3, 1, 65])
+    src = bufs.GlobalBuffers(prm, cap)
+    src.n_rows[:] = torch.tensor([70, 0, 1, 60], dtype=torch.int32)
+    src.idx[:] = torch.arange(len(src.idx), dtype=torch.int32)
+    caches = []
+    for shift in (0, 1):
+        g.manual_seed(3)
+
+        def rows(*shape):
+            n = int(np.prod(shape))
+            t = torch.empty(n + 8, dtype=dt, device="cuda")[shift:shift + n]
+            t.copy_(torch.randn(n, generator=g, device="cuda").to(dt))
+            return t
+        K, V, Kg, Vg = rows(Hkv, L, d), rows(Hkv, L, d), rows(int(cap.sum()), d), rows(int(cap.sum()), d)
+        assert (K.data_ptr() & 15 == 0) == (shift == 0)
+        c = bufs.DecodeCache(prm, 2, cap, kv_format=tb.TCA_KV_FP8 if kv == "fp8" else tb.TCA_KV_NATIVE)
+        tb.tca_cache_load_window(prm, c.view, 1, K, V, L, L)
+        tb.tca_cache_load_global(prm, c.view, 1, src.idx, Kg, Vg, src.offs, src.n_rows)
+        torch.cuda.synchronize()
+        caches.append((c, K, V, Kg, Vg))
+    (a, K, V, Kg, Vg), b = caches[0], caches[1][0]
+    for name in ("ringK", "ringV", "Kg", "Vg", "idx", "n_rows", "length") + (("ringK_scale", "Kg_scale") if kv == "fp8" else ()):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
+    assert a.length.tolist() == [0, L] and a.n_rows[1].tolist() == [70, 0, 1, 60] and not a.n_rows[0].any()
+    if kv == "native":
+        pos = torch.arange(L - w, L, device="cuda")
+        assert torch.equal(a.ringK[1][:, pos % w], K.view(Hkv, L, d)[:, pos])
+        assert torch.equal(a.ringV[1][:, pos % w], V.view(Hkv, L, d)[:, pos])
+        kept = torch.cat([torch.arange(0, 70), torch.tensor([73]), torch.arange(74, 134)]).cuda()
+        assert torch.equal(a.Kg[1, kept], Kg.view(-1, d)[kept]) and torch.equal(a.Vg[1, kept], Vg.view(-1, d)[kept])
+        rest = torch.tensor([70, 71, 72] + list(range(134, 139)), device="cuda")
+        assert not a.Kg[1, rest].any() and not a.idx[1, rest].any()
