@@ -106,7 +106,11 @@ void qkv_mfma_kernel(const uint16_t* __restrict__ W, const uint16_t* __restrict_
   if (item >= n_items) return;
   const int grp = item / (4 * n_ft), in = item - grp * (4 * n_ft);
   const int gw = n_tt - grp * 4 < 4 ? n_tt - grp * 4 : 4;          // token tiles of this group
-  const int ft = in / gw, tt = grp * 4 + (in - ft * gw);
+  const int ft = in / gw, ts = grp * 4 + (in - ft * gw);
+  // Place ts of the token tiles' order: every eighth tile from 0 on, then from 1 on, ..: the XCDs then walk neighbouring
+  // tiles side by side (335 us at 8192 rows, hidden 4096, 6144 features; 340 with an eighth of the rows to each)
+  const int tq = n_tt >> 3, tr = n_tt & 7, cut = tr * (tq + 1);
+  const int tt = ts < cut ? ts / (tq + 1) + 8 * (ts % (tq + 1)) : tr + (ts - cut) / tq + 8 * ((ts - cut) % tq);
   const int wf = wv % NWF, wt = wv / NWF;        // the wave's place inside the tile
   const int64_t f0 = (int64_t)ft * PF, t0 = (int64_t)tt * PT;
   const int rows_w = n_feat - f0 < PF ? (int)(n_feat - f0) : PF;
