@@ -14,8 +14,8 @@
 // result, so a lane ends up with four consecutive features of one token: one 8-byte store each.
 // qkv_skinny_kernel takes the calls of a few rows, which are one pass over the weights.
 //
-// fp32: one thread per output, fp32 multiply-adds in the order of the hidden index (small cases and
-// an independent check of the bf16 kernel's indexing).
+// fp32 (qkv_f32_kernel): fp32 multiply-adds in the order of the hidden index (small cases and an independent check of
+// the bf16 kernels' indexing).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -329,22 +329,107 @@ __global__ __launch_bounds__(512) void qkv_skinny_kernel(const uint16_t* __restr
   }
 }
 
-// grid (ceil(n_feat / 256), n_tok); block 256: thread = one feature of one token.
-template <typename T>
-__global__ __launch_bounds__(256) void qkv_rows_kernel(const T* __restrict__ W, const T* __restrict__ X,
-                                                       const T* __restrict__ bias, int n_feat, int hidden, int d,
-                                                       QkvOut out) {
-  const int f = blockIdx.x * 256 + threadIdx.x;
-  const int64_t t = blockIdx.y;
-  if (f >= n_feat) return;
-  const T* w = W + (size_t)f * hidden;
-  const T* xr = X + (size_t)t * hidden;
-  float acc = 0.f;
-  for (int c = 0; c < hidden; ++c) acc = fmaf(load_f32(xr + c), load_f32(w + c), acc);
-  if (bias) acc += load_f32(bias + f);
-  const int hg = f / d, e = f - hg * d;
-  const int p = part_of_head(out, hg);
-  store_f32((T*)out.base[p] + (int64_t)(hg - out.first_head[p]) * out.head_stride[p] + t * out.token_stride[p] + e, acc);
+// fp32: a workgroup takes FT features x TT tokens, a thread RF x RT of them, each summed over the hidden index in
+// order: fused multiply-adds onto one accumulator, the same bits whatever the tile.  The vector ALU and, for a few
+// rows, the reads of the weights bound it: KC columns of both operands sit in LDS (rows padded by 16 bytes, so that
+// the 16-byte reads of neighbouring features fall on different banks), the next KC are on their way into registers
+// meanwhile.  Lanes run over the features, so that the tokens' reads are broadcasts and the stores are contiguous.
+// ALIGNED: hidden % 4 == 0 and 16-byte operands.
+// grid (ceil(n_feat / FT), ceil(n_tok / TT)); block 256.
+template <int FT, int TT, int RF, int RT, int KC, bool ALIGNED>
+__global__ __launch_bounds__(256) void qkv_f32_kernel(const float* __restrict__ W, const float* __restrict__ X,
+                                                      const float* __restrict__ bias, int n_feat, int64_t n_tok, int hidden,
+                                                      int d, QkvOut out) {
+  constexpr int LF = FT / RF, LS = KC + 4, C4 = KC / 4, NL = (FT + TT) * C4 / 256;
+  static_assert(LF * (TT / RT) == 256 && (FT + TT) * C4 % 256 == 0, "256 threads");
+  __shared__ __align__(16) float lds[(FT + TT) * LS];           // FT rows of W, then TT rows of X
+  const int tid = threadIdx.x, lf = tid % LF, lt = tid / LF;
+  const int f0 = blockIdx.x * FT;
+  const int64_t t0 = (int64_t)blockIdx.y * TT;
+
+  const float* row[NL];                                         // rows past the end repeat the last one
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    const int r = (tid + i * 256) / C4;
+    row[i] = r < FT ? W + (size_t)min(f0 + r, n_feat - 1) * hidden : X + (size_t)min(t0 + (r - FT), n_tok - 1) * hidden;
+  }
+  float4 next[NL];
+  auto fetch = [&](int c0) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int c = c0 + ((tid + i * 256) % C4) * 4;
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if constexpr (ALIGNED) {
+        if (c < hidden) v = *reinterpret_cast<const float4*>(row[i] + c);
+      } else {
+        if (c < hidden) v.x = row[i][c];
+        if (c + 1 < hidden) v.y = row[i][c + 1];
+        if (c + 2 < hidden) v.z = row[i][c + 2];
+        if (c + 3 < hidden) v.w = row[i][c + 3];
+      }
+      next[i] = v;
+    }
+  };
+
+  float acc[RF][RT];
+#pragma unroll
+  for (int a = 0; a < RF; ++a)
+#pragma unroll
+    for (int b = 0; b < RT; ++b) acc[a][b] = 0.f;
+
+  fetch(0);
+  for (int c0 = 0; c0 < hidden; c0 += KC) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NL; ++i)
+      *reinterpret_cast<float4*>(lds + ((tid + i * 256) / C4) * LS + ((tid + i * 256) % C4) * 4) = next[i];
+    __syncthreads();
+    if (c0 + KC < hidden) fetch(c0 + KC);
+    const int n = min(KC, hidden - c0);
+    auto step4 = [&](int c) {
+      float4 w[RF], x[RT];
+#pragma unroll
+      for (int a = 0; a < RF; ++a) w[a] = *reinterpret_cast<const float4*>(lds + (lf + a * LF) * LS + c);
+#pragma unroll
+      for (int b = 0; b < RT; ++b) x[b] = *reinterpret_cast<const float4*>(lds + (FT + lt * RT + b) * LS + c);
+#pragma unroll
+      for (int a = 0; a < RF; ++a)
+#pragma unroll
+        for (int b = 0; b < RT; ++b) {
+          acc[a][b] = fmaf(x[b].x, w[a].x, acc[a][b]);
+          acc[a][b] = fmaf(x[b].y, w[a].y, acc[a][b]);
+          acc[a][b] = fmaf(x[b].z, w[a].z, acc[a][b]);
+          acc[a][b] = fmaf(x[b].w, w[a].w, acc[a][b]);
+        }
+    };
+    if (n == KC) {
+#pragma unroll 8
+      for (int c = 0; c < KC; c += 4) step4(c);
+    } else {
+      int c = 0;
+      for (; c + 4 <= n; c += 4) step4(c);
+      for (; c < n; ++c)                                        // no product with the padding: it would turn -0 into +0
+#pragma unroll
+        for (int a = 0; a < RF; ++a)
+#pragma unroll
+          for (int b = 0; b < RT; ++b)
+            acc[a][b] = fmaf(lds[(FT + lt * RT + b) * LS + c], lds[(lf + a * LF) * LS + c], acc[a][b]);
+    }
+  }
+
+#pragma unroll
+  for (int a = 0; a < RF; ++a) {
+    const int f = f0 + lf + a * LF;
+    if (f >= n_feat) continue;
+    const int hg = f / d, e = f - hg * d, p = part_of_head(out, hg);
+    float* const o = (float*)out.base[p] + (int64_t)(hg - out.first_head[p]) * out.head_stride[p] + e;
+    const float bf = bias ? bias[f] : 0.f;
+#pragma unroll
+    for (int b = 0; b < RT; ++b) {
+      const int64_t t = t0 + lt * RT + b;
+      if (t < n_tok) o[t * out.token_stride[p]] = bias ? acc[a][b] + bf : acc[a][b];
+    }
+  }
 }
 
 }  // namespace tca
@@ -377,6 +462,23 @@ void launch_tiles(const QkvCall& c) {
   hipLaunchKernelGGL((qkv_mfma_kernel<FBW, TBW, NWF, NWT, NST>), dim3(n_wg), dim3(NWF * NWT * 64), 0, c.st, c.W, c.X, c.bias,
                      c.n_feat, c.n_tok, c.hidden, c.d, c.out, n_ft, n_tt);
 }
+
+struct F32Call {
+  const float *W, *X, *bias;
+  int n_feat;
+  int64_t n_tok;
+  int hidden, d;
+  QkvOut out;
+  hipStream_t st;
+};
+
+template <int FT, int TT, int RF, int RT, int KC>
+void launch_f32(const F32Call& c) {
+  const dim3 grid((unsigned)((c.n_feat + FT - 1) / FT), (unsigned)((c.n_tok + TT - 1) / TT));
+  const bool aligned = c.hidden % 4 == 0 && !(((uintptr_t)c.W | (uintptr_t)c.X) & 15);
+  auto* const kernel = aligned ? qkv_f32_kernel<FT, TT, RF, RT, KC, true> : qkv_f32_kernel<FT, TT, RF, RT, KC, false>;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, c.st, c.W, c.X, c.bias, c.n_feat, c.n_tok, c.hidden, c.d, c.out);
+}
 }  // namespace
 
 extern "C" int tca_qkv_project(const tca_params* prm, const void* X, int64_t n_tokens, int hidden, const void* W,
@@ -402,8 +504,15 @@ extern "C" int tca_qkv_project(const tca_params* prm, const void* X, int64_t n_t
   hipStream_t st = (hipStream_t)stream;
   if (prm->dtype == TCA_F32) {
     if (n_tokens > 65535) return fail(TCA_ERR_UNSUPPORTED, "tca_qkv_project (fp32): more than 65535 rows per call");
-    hipLaunchKernelGGL((qkv_rows_kernel<float>), dim3((n_feat + 255) / 256, (unsigned)n_tokens), dim3(256), 0, st,
-                       (const float*)W, (const float*)X, (const float*)bias, n_feat, hidden, d, out);
+    // Fewer rows, smaller tiles: more workgroups and no work for missing rows; 64 x 64 once that gives every CU one.
+    // us, one thread per output before -> now, hidden 4096 and 6144 features: 2 rows 493 -> 48, 16: 1275 -> 72,
+    // 17: 1532 -> 97, 100: 10444 -> 156, 256: 23389 -> 292 (22 T multiply-adds a second, of about 36 that the vector
+    // ALU has); hidden 1024, 384 features: 2 rows 117 -> 14, 256: 254 -> 27.
+    const F32Call call{(const float*)W, (const float*)X, (const float*)bias, n_feat, n_tokens, hidden, d, out, st};
+    if (n_tokens <= 8) launch_f32<32, 8, 1, 1, 128>(call);
+    else if (n_tokens <= 16) launch_f32<32, 16, 1, 2, 64>(call);
+    else if ((int64_t)((n_feat + 63) / 64) * ((n_tokens + 63) / 64) < kCUs) launch_f32<32, 32, 2, 2, 64>(call);
+    else launch_f32<64, 64, 4, 4, 64>(call);
   } else {
     if (hidden % kPK) return fail(TCA_ERR_UNSUPPORTED, "tca_qkv_project (bf16): hidden=%d is not a multiple of %d", hidden, kPK);
     if ((int64_t)256 * hidden * 2 > INT32_MAX) return fail(TCA_ERR_UNSUPPORTED, "tca_qkv_project (bf16): hidden=%d", hidden);

@@ -225,6 +225,19 @@ QKV_SHAPES = [
 ]
 
 
+QKV_SHAPES += [
+    # fp32: each tile at its edges, with operands that 16-byte loads can read and without
+    (4, 1, 64, 132, 1, "f32", True, "head", 0),           # 32 x 8, a last stage of four columns
+    (4, 1, 64, 127, 8, "f32", False, "token", 0),
+    (2, 1, 64, 64, 9, "f32", True, "head", 1),            # 32 x 16
+    (2, 1, 64, 193, 16, "f32", True, "token", 0),
+    (4, 2, 128, 68, 17, "f32", False, "head", 0),         # 32 x 32
+    (4, 2, 128, 3, 45, "f32", True, "head", 2),
+    (32, 8, 128, 196, 161, "f32", True, "head", 0),       # 64 x 64, last token tile ragged
+    (32, 8, 128, 66, 192, "f32", False, "token", 0),
+]
+
+
 @pytest.mark.parametrize("case", QKV_SHAPES, ids=lambda c: f"hq{c[0]}-hkv{c[1]}-d{c[2]}-hid{c[3]}-n{c[4]}-{c[5]}-{c[7]}")
 def test_qkv_project_every_tile_shape(tb, bufs, case):
     test_qkv_project_matches_oracle(tb, bufs, case)
