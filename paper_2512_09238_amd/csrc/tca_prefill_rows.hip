@@ -269,7 +269,7 @@ int launch_prefill_f32(const tca_params* prm, const float* Q, int64_t q_pos0, in
   // Few workgroups of 64 queries for 256 CUs: 16 each.  us with 64 / with 16: 4 heads, 4096 tokens (256 workgroups of
   // 64) 241 / 117; 32 heads, 700 tokens (352) 145 / 123; 64 heads, 500 tokens (512) 119 / 141; 32 heads, 1500 tokens
   // (768) 359 / 461.  (One wave per query, keys read from L2 by each, took 95 us at 4 heads and 1024 tokens where this
-  // takes 23, and 7.1 ms at 32 heads and 3315 tokens where this takes 1.5.)
+  // takes 23, and 7.3 ms at 32 heads and 3315 tokens where the call now takes 1.6.)
   const bool few = (n_queries + 63) / 64 * Hq < 400;
   const int64_t n_wg = (n_queries + (few ? 15 : 63)) / (few ? 16 : 64) * Hq;
   if (n_wg > INT32_MAX) return fail(TCA_ERR_UNSUPPORTED, "tca_prefill (fp32): %lld queries", (long long)n_queries);
