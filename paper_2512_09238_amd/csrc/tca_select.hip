@@ -377,7 +377,10 @@ __global__ __launch_bounds__(NT) void assign_kernel(
       const double spread = metric == TCA_METRIC_ENTROPY
                                 ? (log(bE1[k]) - bE2[k] / bE1[k]) / log((double)b)
                                 : 1.0 - bE2[k] / (bE1[k] * bE1[k]);
-      key[k] = (1.0 - alpha) * mass + alpha * spread;
+      const double hj = (1.0 - alpha) * mass + alpha * spread;
+      // A row that is not finite makes every h of its head NaN.  Both sides of a pair decide for themselves below, which
+      // leaves the blocks a permutation only in a total order: NaN takes the last place, ties by block as ever.
+      if (hj == hj) key[k] = hj;
     }
   }
 
@@ -517,7 +520,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
       kvh = h / G;
     }
   }
-  const int t = blk_t[(size_t)h * n_blocks + j];
+  const int t = min(blk_t[(size_t)h * n_blocks + j], b);               // sel below has room for b rows, whatever it is told
   const int64_t base = oa.offs[h], cap = oa.offs[h + 1] - base;
   const int64_t dst0 = blk_dst[(size_t)h * n_blocks + j];
 
