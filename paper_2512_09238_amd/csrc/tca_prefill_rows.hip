@@ -168,11 +168,11 @@ __global__ __launch_bounds__(kRowThreads, 2) void prefill_f32_kernel(
       lo = qpos - w + 1 - j0;
       hi = qpos + 1 - j0;
     }
+    auto seen = [&](int r) { return kb + 4 * r >= lo && kb + 4 * r < hi; };
     double x[4], mx = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int key = kb + 4 * r;
-      x[r] = key >= lo && key < hi ? acc[r] * scale : -INFINITY;
+      x[r] = seen(r) ? acc[r] * scale : -INFINITY;
       mx = fmax(mx, x[r]);
     }
     mx = fmax(mx, __shfl_xor(mx, 16, kWave));
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void prefill_f32_kernel(
     m = mn;
     float p[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) p[r] = x[r] > -INFINITY ? expf((float)(x[r] - m)) : 0.f;
+    for (int r = 0; r < 4; ++r) p[r] = seen(r) ? expf((float)(x[r] - m)) : 0.f;       // by the mask: a NaN logit is no masked key
     l = fmaf(l, corr, (p[0] + p[1]) + (p[2] + p[3]));
     // The tile's part is summed from zero and added to the rest once: a quarter of the roundings at the size of the
     // whole sum (error against 64 bits at 1500 tokens 2e-7; 4e-7 with every product added to the whole).
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void prefill_f32_kernel(
     for (int e = 0; e < SB; ++e) a[e] = 0.f;
 #pragma unroll
     for (int g = 0; g < KG; ++g) {
-      const float wgt = ls[g][qi] > 0.f ? expf((float)(ms[g][qi] - M)) : 0.f;
+      const float wgt = ms[g][qi] == -INFINITY ? 0.f : expf((float)(ms[g][qi] - M));      // no keys: a sum of 0 (or of NaN, which stays)
       L += ls[g][qi] * wgt;
 #pragma unroll
       for (int e = 0; e < SB; ++e) a[e] += po[(g * 16 + qi) * D + sub * SB + e] * wgt;

@@ -70,3 +70,73 @@ def test_select_keeps_valid_rows_whatever_the_scores(tb, bufs, case, free):
             assert torch.equal(gb.Kg[o:o + len(got)].view(torch.int32), Kd[h // (Hs // Hkv), at].view(torch.int32))
         if h >= Hs // Hkv:                                           # the KV head without the bad row
             assert np.array_equal(got, H.head_indices(clean, h))
+
+
+def prefill_call(tb, bufs, Hq, Hkv, d, L, w, dtype, S, Qd, Kd, Vd, free=False, ws_bytes=None, b=16, q0=0):
+    """tca_prefill of the queries q0 .. L-1 with the kept positions S (one list per query head): O [Hq, L - q0, d], lse, in float64."""
+    prm = H.params_for(tb, Hq, Hkv, d, b, w, dtype)
+    gb = bufs.GlobalBuffers(prm, np.array([len(s) for s in S]) + 3)
+    for h, s in enumerate(S):
+        o, at = int(gb.offs[h]), torch.from_numpy(np.asarray(s, np.int64)).cuda()
+        gb.idx[o:o + len(s)] = at.to(torch.int32)
+        gb.Kg[o:o + len(s)], gb.Vg[o:o + len(s)] = Kd[h * Hkv // Hq, at], Vd[h * Hkv // Hq, at]
+        gb.n_rows[h] = len(s)
+    Qt = Qd[:, q0:].contiguous()
+    O = torch.full_like(Qt, 7.0)
+    lse = torch.full(Qt.shape[:2], 7.0, dtype=torch.float32, device="cuda")
+    if ws_bytes is None:
+        ws_bytes = tb.tca_prefill_workspace_bytes(prm, L - q0, int(gb.offs[-1]))
+    ws = bufs.workspace(ws_bytes)
+    tb.tca_prefill(prm, Qt, q0, L - q0, Kd, Vd, L, gb.idx, None if free else gb.Kg, None if free else gb.Vg, gb.offs,
+                   gb.n_rows, O, lse, ws)
+    torch.cuda.synchronize()
+    return O.double().cpu().numpy(), lse.double().cpu().numpy()
+
+
+def who_sees(Hq, Hkv, L, w, S, kvh, j):
+    """[Hq, L] true where query i of head h attends to row j of KV head kvh: in its window, or kept and behind it."""
+    i = np.arange(L)
+    out = np.zeros((Hq, L), bool)
+    for h in range(Hq):
+        if h * Hkv // Hq == kvh:
+            out[h] = ((i - w < j) & (j <= i)) | ((j <= i - w) & bool(np.isin(j, S[h])))
+    return out
+
+
+F32_CASES = [
+    # Hq, Hkv, d, L, w, gather-free, row: 64 queries per workgroup (432 and more), and 16
+    (16, 2, 64, 1700, 96, False, 803),
+    (32, 4, 128, 900, 64, True, 450),
+    (4, 2, 64, 333, 48, False, 100),
+    (2, 1, 128, 290, 32, True, 77),
+]
+
+
+def f32_inputs(bufs, case):
+    Hq, Hkv, d, L, w, free, j = case
+    x = wl.prefill_inputs("lowrank", Hq, Hkv, d, L, "f32", 62)
+    rng = np.random.default_rng(63)
+    S = [np.unique(np.append(np.setdiff1d(rng.choice(L, L // 3, replace=False), j), [j] if h % 2 == 0 else [])).astype(np.int64)
+         for h in range(Hq)]                                         # every other head keeps row j
+    return (S,) + tuple(bufs.to_device(x[k]) for k in ("Q", "K", "V"))
+
+
+@pytest.mark.parametrize("what", ["key", "query"])
+@pytest.mark.parametrize("case", F32_CASES, ids=lambda c: f"Hq{c[0]}-d{c[2]}-L{c[3]}-free{c[5]}")
+def test_fp32_prefill_shows_a_nan_where_it_is_seen(tb, bufs, case, what):
+    """A NaN in a key row makes the outputs of the queries that see it NaN, one in a query row that query's; all others
+    keep every bit."""
+    Hq, Hkv, d, L, w, free, j = case
+    print("case", case, what, flush=True)
+    S, Qd, Kd, Vd = f32_inputs(bufs, case)
+    clean, clean_lse = prefill_call(tb, bufs, Hq, Hkv, d, L, w, "f32", S, Qd, Kd, Vd, free)
+    if what == "key":
+        Kd[1 % Hkv, j, 5] = float("nan")
+        bad = who_sees(Hq, Hkv, L, w, S, 1 % Hkv, j)
+    else:
+        Qd[1, j, 5] = float("nan")
+        bad = np.zeros((Hq, L), bool)
+        bad[1, j] = True
+    O, lse = prefill_call(tb, bufs, Hq, Hkv, d, L, w, "f32", S, Qd, Kd, Vd, free)
+    assert np.isnan(O[bad]).all()
+    assert np.array_equal(O[~bad], clean[~bad]) and np.array_equal(lse[~bad], clean_lse[~bad])
