@@ -18,6 +18,8 @@
 // fill the chip.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "tca_common.h"
 #include "tca_device.h"
 #include "tca_prefill.h"
@@ -30,7 +32,7 @@ struct HeadOffs { int64_t offs[TCA_MAX_HEADS + 1]; };
 
 // grid (query tiles * Hq), longest query tiles first, heads inside; block 256
 template <int D, int KG>
-__global__ __launch_bounds__(kRowThreads, 2) void prefill_f32_kernel(
+__global__ __launch_bounds__(kRowThreads, D == 64 && KG == 1 ? 4 : 2) void prefill_f32_kernel(
     const float* __restrict__ Q, int64_t q_pos0, int64_t n_queries, const float* __restrict__ K,
     const float* __restrict__ V, int64_t kv_stride, const int32_t* __restrict__ idx,
     const float* __restrict__ Kg, const float* __restrict__ Vg, HeadOffs ho,
@@ -127,84 +129,123 @@ __global__ __launch_bounds__(kRowThreads, 2) void prefill_f32_kernel(
     }
   };
 
-  double m = -INFINITY;                            // the same in the four lanes of a query
-  float l = 0.f;                                   // over this lane's keys
+  double m;                                        // the same in the four lanes of a query
+  float l;                                         // over this lane's keys
   f32x4_t o[SB];
+  // The product gives a masked key the weight 0, which an infinity or a NaN in its V row turns into NaN for queries that do
+  // not see the row.  Such a value always shows in the sums of all queries of the wave: where it does, the walk is made again
+  // with PLAIN = false, which adds V key by key to the queries that see the key.  (Looking for it per tile, with the second
+  // way of adding beside the first: 43 against 31 us at 4 heads and 1024 tokens.)
+  auto walk = [&](auto plain_tag) {
+    constexpr bool PLAIN = decltype(plain_tag)::value;
+    m = -INFINITY;
+    l = 0.f;
 #pragma unroll
-  for (int s = 0; s < SB; ++s) o[s] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-  if (grp < n_tiles) fetch(grp);
-  for (int t = grp; t < n_tiles; t += KG) {
-    sync();                                        // the tile before has been consumed
+    for (int s = 0; s < SB; ++s) o[s] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if (grp < n_tiles) fetch(grp);
+    for (int t = grp; t < n_tiles; t += KG) {
+      sync();                                        // the tile before has been consumed
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int ci = i * GT + gt, r = ci / C4, ch = ci - r * C4;
-      kt[grp][r][ch ^ (r & 15)] = kr[i];
-      if constexpr (kStageV) vt[grp][r][ch] = vr[i];
-    }
-    sync();
-    f32x4_t vd[kStageV ? 1 : 4][SB / 4];           // this lane's chunks of the rows kb + 4 r
-    if constexpr (!kStageV) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int u = 0; u < SB / 4; ++u) vd[r][u] = load(v_reg, v_win, t, kb + 4 * r, c * (SB / 4) + u);
-    }
-    if (t + KG < n_tiles) fetch(t + KG);
-
-    f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int u = 0; u < SB; ++u) {
-      const f32x4_t kf = kt[grp][c][(kb * SB + u) ^ c];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)kf[e], q[4 * u + e], acc, 0, 0, 0);
-    }
-    // visible <=> lo <= key inside the tile < hi
-    int lo = 0, hi;
-    if (t < n_rt) {
-      hi = nvis - t * TK;
-    } else {
-      const int j0 = win_lo + (t - n_rt) * TK;
-      lo = qpos - w + 1 - j0;
-      hi = qpos + 1 - j0;
-    }
-    auto seen = [&](int r) { return kb + 4 * r >= lo && kb + 4 * r < hi; };
-    double x[4], mx = -INFINITY;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      x[r] = seen(r) ? acc[r] * scale : -INFINITY;
-      mx = fmax(mx, x[r]);
-    }
-    mx = fmax(mx, __shfl_xor(mx, 16, kWave));
-    mx = fmax(mx, __shfl_xor(mx, 32, kWave));
-    const double mn = fmax(m, mx);
-    const float corr = mn > m ? expf((float)(m - mn)) : 1.f;         // 0 on the first keys (m = -inf)
-    m = mn;
-    float p[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) p[r] = seen(r) ? expf((float)(x[r] - m)) : 0.f;       // by the mask: a NaN logit is no masked key
-    l = fmaf(l, corr, (p[0] + p[1]) + (p[2] + p[3]));
-    // The tile's part is summed from zero and added to the rest once: a quarter of the roundings at the size of the
-    // whole sum (error against 64 bits at 1500 tokens 2e-7; 4e-7 with every product added to the whole).
-    f32x4_t ot[SB];
-#pragma unroll
-    for (int s = 0; s < SB; ++s) ot[s] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-#pragma unroll
-      for (int u = 0; u < SB / 4; ++u) {
-        f32x4_t vf;
-        if constexpr (kStageV) vf = vt[grp][kb + 4 * r][c * (SB / 4) + u];
-        else vf = vd[r][u];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) ot[4 * u + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e], p[r], ot[4 * u + e], 0, 0, 0);
+      for (int i = 0; i < NL; ++i) {
+        const int ci = i * GT + gt, r = ci / C4, ch = ci - r * C4;
+        kt[grp][r][ch ^ (r & 15)] = kr[i];
+        if constexpr (kStageV) vt[grp][r][ch] = vr[i];
       }
+      sync();
+      f32x4_t vd[kStageV ? 1 : 4][SB / 4];           // this lane's chunks of the rows kb + 4 r
+      if constexpr (!kStageV) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int u = 0; u < SB / 4; ++u) vd[r][u] = load(v_reg, v_win, t, kb + 4 * r, c * (SB / 4) + u);
+      }
+      if (t + KG < n_tiles) fetch(t + KG);
+
+      f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int u = 0; u < SB; ++u) {
+        const f32x4_t kf = kt[grp][c][(kb * SB + u) ^ c];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)kf[e], q[4 * u + e], acc, 0, 0, 0);
+      }
+      // visible <=> lo <= key inside the tile < hi
+      int lo = 0, hi;
+      if (t < n_rt) {
+        hi = nvis - t * TK;
+      } else {
+        const int j0 = win_lo + (t - n_rt) * TK;
+        lo = qpos - w + 1 - j0;
+        hi = qpos + 1 - j0;
+      }
+      auto seen = [&](int r) { return kb + 4 * r >= lo && kb + 4 * r < hi; };
+      double x[4], mx = -INFINITY;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        x[r] = seen(r) ? acc[r] * scale : -INFINITY;
+        mx = fmax(mx, x[r]);
+      }
+      mx = fmax(mx, __shfl_xor(mx, 16, kWave));
+      mx = fmax(mx, __shfl_xor(mx, 32, kWave));
+      const double mn = fmax(m, mx);
+      const float corr = mn > m ? expf((float)(m - mn)) : 1.f;         // 0 on the first keys (m = -inf)
+      m = mn;
+      float p[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) p[r] = seen(r) ? expf((float)(x[r] - m)) : 0.f;       // by the mask: a NaN logit is no masked key
+      l = fmaf(l, corr, (p[0] + p[1]) + (p[2] + p[3]));
+      // The tile's part is summed from zero and added to the rest once: a quarter of the roundings at the size of the
+      // whole sum (error against 64 bits at 1500 tokens 2e-7; 4e-7 with every product added to the whole).
+      f32x4_t ot[SB];
+#pragma unroll
+      for (int s = 0; s < SB; ++s) ot[s] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      if constexpr (PLAIN) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll
+          for (int u = 0; u < SB / 4; ++u) {
+            f32x4_t vf;
+            if constexpr (kStageV) vf = vt[grp][kb + 4 * r][c * (SB / 4) + u];
+            else vf = vd[r][u];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ot[4 * u + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e], p[r], ot[4 * u + e], 0, 0, 0);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll 1
+          for (int k = 0; k < 4; ++k) {
+            const int from = k * 16, key = k + 4 * r;                // the lanes that hold the key
+            const float pk = __shfl(p[r], from + c, kWave);          // its weight for this lane's query
+            const bool sees = key >= lo && key < hi;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+              for (int u = 0; u < SB / 4; ++u)                       // elements SB (4 kb + j) + 4 u ..
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  float v;
+                  if constexpr (kStageV) v = vt[grp][key][(4 * kb + j) * (SB / 4) + u][e];
+                  else v = __shfl(vd[r][u][e], from + 4 * kb + j, kWave);
+                  if (sees) ot[4 * u + e][j] = fmaf(pk, v, ot[4 * u + e][j]);
+                }
+          }
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < SB; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[s][e] = fmaf(o[s][e], corr, ot[s][e]);
     }
+  };
+  walk(std::true_type{});
+  float odd = 0.f;                                 // 0 times every sum: not 0 if one is an infinity or a NaN
 #pragma unroll
-    for (int s = 0; s < SB; ++s)
+  for (int s = 0; s < SB; ++s)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[s][e] = fmaf(o[s][e], corr, ot[s][e]);
-  }
+    for (int e = 0; e < 4; ++e) odd = fmaf(o[s][e], 0.f, odd);
+  // (a wave of KG = 4 shares nothing with the others; with KG = 1 the barriers of the walk are the whole workgroup's)
+  if (KG == 1 ? __syncthreads_or(odd != 0.f) : __any(odd != 0.f)) walk(std::false_type{});
   l += __shfl_xor(l, 16, kWave);
   l += __shfl_xor(l, 32, kWave);
 

@@ -140,3 +140,22 @@ def test_fp32_prefill_shows_a_nan_where_it_is_seen(tb, bufs, case, what):
     O, lse = prefill_call(tb, bufs, Hq, Hkv, d, L, w, "f32", S, Qd, Kd, Vd, free)
     assert np.isnan(O[bad]).all()
     assert np.array_equal(O[~bad], clean[~bad]) and np.array_equal(lse[~bad], clean_lse[~bad])
+
+
+@pytest.mark.parametrize("value", ["inf", "nan"])
+@pytest.mark.parametrize("case", F32_CASES, ids=lambda c: f"Hq{c[0]}-d{c[2]}-L{c[3]}-free{c[5]}")
+def test_fp32_prefill_keeps_a_value_row_from_those_who_do_not_see_it(tb, bufs, case, value):
+    """An infinity or a NaN in a V row: that element of the queries that see the row is not finite, every other element
+    and every other query is what it is without (up to the order of a tile's sum: 1e-5 as in the oracle comparison)."""
+    Hq, Hkv, d, L, w, free, j = case
+    print("case", case, value, flush=True)
+    S, Qd, Kd, Vd = f32_inputs(bufs, case)
+    clean, clean_lse = prefill_call(tb, bufs, Hq, Hkv, d, L, w, "f32", S, Qd, Kd, Vd, free)
+    kvh, e = 1 % Hkv, 37
+    Vd[kvh, j, e] = float(value)
+    bad = np.zeros((Hq, L, d), bool)
+    bad[:, :, e] = who_sees(Hq, Hkv, L, w, S, kvh, j)
+    O, lse = prefill_call(tb, bufs, Hq, Hkv, d, L, w, "f32", S, Qd, Kd, Vd, free)
+    assert not np.isfinite(O[bad]).any()
+    assert np.isfinite(O[~bad]).all() and np.abs(O[~bad] - clean[~bad]).max() <= 1e-5
+    assert np.array_equal(lse, clean_lse)
