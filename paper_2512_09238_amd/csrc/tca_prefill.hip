@@ -37,6 +37,65 @@ __global__ __launch_bounds__(256) void merge_parts_kernel(T* __restrict__ Oa, co
   if (lse_out && lane == 0) lse_out[r] = mx + logf(wa + wb);
 }
 
+// Merge of the chunks of a split call: O = sum_s e^{m_s - M} O_s / sum_s e^{m_s - M} l_s per query (references m in
+// score units, as the kernel keeps them).  grid (query tiles, Hq, D / 32); block 256: wave = 32 queries, lane =
+// (half, query) with 4 x 4 of the D / 32 slice's columns, the layout the accumulators were left in: coalesced reads.
+// A chunk is empty if its sum l is 0; one whose sum is NaN (a key or a query that is not finite) takes part.  (The file of
+// the attention kernel is compiled without regard for NaN, this one is not.)
+template <int D>
+__global__ __launch_bounds__(256) void merge_split_kernel(SplitPlan sp, int64_t n_queries, float scale,
+                                                          uint16_t* __restrict__ O, float* __restrict__ lse) {
+  typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+  typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
+  const int qtile = blockIdx.x, n_qt = gridDim.x, h = blockIdx.y, sl = blockIdx.z;
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, hh = lane >> 5, c = lane & 31;
+  const int n_ch = (sp.item_start[h + 1] - sp.item_start[h]) / n_qt;
+  const size_t stride = (size_t)n_qt * split_floats<D>();
+  const float* base = sp.part + (size_t)(sp.item_start[h] + qtile) * split_floats<D>();
+  const float sl2e = scale * 1.4426950408889634f;
+  const int q = wv * 32 + c;
+  float M = -INFINITY;
+#pragma unroll 8
+  for (int s = 0; s < n_ch; ++s) M = fmaxf(M, base[s * stride + 128 * D + q]);
+  f32x4_t acc[4];
+#pragma unroll
+  for (int q4 = 0; q4 < 4; ++q4) acc[q4] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  float L = 0.f;
+#pragma unroll 4
+  for (int s = 0; s < n_ch; ++s) {                 // no branch: the loads of several chunks are in flight at once
+    const float* po = base + s * stride;
+    const float l = po[128 * D + 128 + q];
+    const float wgt = l != 0.f ? __builtin_amdgcn_exp2f((po[128 * D + q] - M) * sl2e) : 0.f;
+    L += l * wgt;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const f32x4_t v = *reinterpret_cast<const f32x4_t*>(po + (((sl * 4 + q4) * 4 + wv) * 64 + lane) * 4);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[q4][j] += l != 0.f ? v[j] * wgt : 0.f;     // an empty chunk's accumulators were never written
+    }
+  }
+  const int64_t r = (int64_t)qtile * 128 + q;
+  if (r >= n_queries) return;
+  const float inv = L != 0.f ? 1.f / L : 0.f;
+  uint16_t* orow = O + ((size_t)h * n_queries + r) * D;
+#pragma unroll
+  for (int q4 = 0; q4 < 4; ++q4) {
+    bf16x4_t pk;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) pk[j] = (__bf16)(acc[q4][j] * inv);
+    *reinterpret_cast<bf16x4_t*>(orow + sl * 32 + 8 * q4 + 4 * hh) = pk;
+  }
+  if (lse && sl == 0 && hh == 0) lse[(size_t)h * n_queries + r] = L > 0.f ? M * scale + __logf(L) : -INFINITY;
+}
+
+void launch_merge_split(const tca_params* prm, const SplitPlan& sp, int64_t n_queries, uint16_t* O, float* lse, hipStream_t st) {
+  const int D = prm->head_dim;
+  const dim3 grid((unsigned)((n_queries + 127) / 128), prm->n_q_heads, D / 32);
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, sp, n_queries, (float)logit_scale(prm), O, lse); };
+  if (D == 128) launch(merge_split_kernel<128>);
+  else launch(merge_split_kernel<64>);
+}
+
 static int prefill_checked(const tca_params* prm, const void* Q, int64_t q_pos0, int64_t n_queries, const void* K,
                            const void* V, int64_t kv_stride, const int32_t* idx, const void* Kg, const void* Vg,
                            const int64_t* offs, const int32_t* n_rows, void* O, float* lse, void* ws,

@@ -62,16 +62,7 @@ struct PrefillHeads {
   uint8_t perm[TCA_MAX_HEADS];          // order 1 and 2: the heads in the sequence
 };
 
-// Calls with too few query tiles for the chip: the tiles of a (head, query tile) item are cut into chunks of
-// `chunk` tiles, one workgroup each, whose unnormalised results merge_split_kernel combines.
-struct SplitPlan {
-  float* part;                          // per workgroup: the O^T accumulators, then m and l of its queries
-  int32_t chunk;                        // tiles per chunk, even
-  int32_t run;                          // consecutive workgroups that go to one XCD
-  int32_t item_start[TCA_MAX_HEADS + 1];  // head h's workgroups: [item_start[h], item_start[h + 1]), chunk-major, query tiles inside
-};
 struct NoSplit {};
-template <int D> constexpr size_t split_floats() { return 128 * (size_t)(D + 2); }      // per workgroup of 128 queries
 
 // position p (0..63) inside a stored V^T tile -> key (0..63) of the tile
 __host__ __device__ inline int vt_key_of_pos(int p) {
@@ -1026,54 +1017,6 @@ void prefill_mfma_kernel(
   }
 }
 
-// Merge of the chunks of a split call: O = sum_s e^{m_s - M} O_s / sum_s e^{m_s - M} l_s per query (references m in
-// score units, as the kernel keeps them).  grid (query tiles, Hq, D / 32); block 256: wave = 32 queries, lane =
-// (half, query) with 4 x 4 of the D / 32 slice's columns, the layout the accumulators were left in: coalesced reads.
-template <int D>
-__global__ __launch_bounds__(256) void merge_split_kernel(SplitPlan sp, int64_t n_queries, float scale,
-                                                          uint16_t* __restrict__ O, float* __restrict__ lse) {
-  typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
-  const int qtile = blockIdx.x, n_qt = gridDim.x, h = blockIdx.y, sl = blockIdx.z;
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, hh = lane >> 5, c = lane & 31;
-  const int n_ch = (sp.item_start[h + 1] - sp.item_start[h]) / n_qt;
-  const size_t stride = (size_t)n_qt * split_floats<D>();
-  const float* base = sp.part + (size_t)(sp.item_start[h] + qtile) * split_floats<D>();
-  const float sl2e = scale * 1.4426950408889634f;
-  const int q = wv * 32 + c;
-  float M = -INFINITY;
-#pragma unroll 8
-  for (int s = 0; s < n_ch; ++s) M = fmaxf(M, base[s * stride + 128 * D + q]);
-  f32x4_t acc[4];
-#pragma unroll
-  for (int q4 = 0; q4 < 4; ++q4) acc[q4] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  float L = 0.f;
-#pragma unroll 4
-  for (int s = 0; s < n_ch; ++s) {                 // no branch: the loads of several chunks are in flight at once
-    const float* po = base + s * stride;
-    const float l = po[128 * D + 128 + q];
-    const float wgt = l > 0.f ? __builtin_amdgcn_exp2f((po[128 * D + q] - M) * sl2e) : 0.f;
-    L += l * wgt;
-#pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const f32x4_t v = *reinterpret_cast<const f32x4_t*>(po + (((sl * 4 + q4) * 4 + wv) * 64 + lane) * 4);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[q4][j] += l > 0.f ? v[j] * wgt : 0.f;      // an empty chunk's accumulators were never written
-    }
-  }
-  const int64_t r = (int64_t)qtile * 128 + q;
-  if (r >= n_queries) return;
-  const float inv = L > 0.f ? 1.f / L : 0.f;
-  uint16_t* orow = O + ((size_t)h * n_queries + r) * D;
-#pragma unroll
-  for (int q4 = 0; q4 < 4; ++q4) {
-    bf16x4_t pk;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) pk[j] = (__bf16)(acc[q4][j] * inv);
-    *reinterpret_cast<bf16x4_t*>(orow + sl * 32 + 8 * q4 + 4 * hh) = pk;
-  }
-  if (lse && sl == 0 && hh == 0) lse[(size_t)h * n_queries + r] = L > 0.f ? M * scale + __logf(L) : -INFINITY;
-}
-
 // ------------------------------------------------------------------ host side --
 struct MfmaWs {
   unsigned long long* clk;   // sums over the workgroups of the last call: {shader-clock cycles, 100 MHz ticks, cycles before the first step, tiles}
@@ -1432,8 +1375,7 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
       };
       if (gather) launch_split(std::true_type{});
       else launch_split(std::false_type{});
-      hipLaunchKernelGGL((merge_split_kernel<D>), dim3((unsigned)((n_queries + 127) / 128), Hq, D / 32), dim3(256), 0, st,
-                         sp, n_queries, (float)logit_scale(prm), O, lse);
+      launch_merge_split(prm, sp, n_queries, O, lse, st);
       return;
     }
   }

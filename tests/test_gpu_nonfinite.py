@@ -159,3 +159,40 @@ def test_fp32_prefill_keeps_a_value_row_from_those_who_do_not_see_it(tb, bufs, c
     assert not np.isfinite(O[bad]).any()
     assert np.isfinite(O[~bad]).all() and np.abs(O[~bad] - clean[~bad]).max() <= 1e-5
     assert np.array_equal(lse, clean_lse)
+
+
+SPLIT_CASES = [
+    # Hq, Hkv, d, queries, gather-free, row that is not finite (kept by every other head) or query
+    (8, 2, 128, 130, False, 900),
+    (16, 2, 64, 300, True, 2500),
+    (3, 1, 128, 1, False, 2990),                                     # in the window
+    (4, 4, 64, 200, False, "query"),
+]
+
+
+@pytest.mark.parametrize("case", SPLIT_CASES, ids=lambda c: f"Hq{c[0]}-d{c[2]}-n{c[3]}-free{c[4]}-{c[5]}")
+def test_prefill_in_chunks_shows_a_nan_where_it_is_seen(tb, bufs, case):
+    """A bf16 call cut into chunks of keys and one with the smallest workspace, which is not, are NaN in the same places:
+    where a query sees the key row that is NaN, or is NaN itself."""
+    Hq, Hkv, d, n, free, j = case
+    print("case", case, flush=True)
+    L, w = 3000, 256
+    x = wl.prefill_inputs("lowrank", Hq, Hkv, d, L, "bf16", 64)
+    rng = np.random.default_rng(65)
+    at = j if j != "query" else -1
+    S = [np.unique(np.append(np.setdiff1d(rng.choice(L - 300, 1500, replace=False), at), [at] if h % 2 == 0 and at >= 0 else [])).astype(np.int64)
+         for h in range(Hq)]
+    Qd, Kd, Vd = (bufs.to_device(x[k]) for k in ("Q", "K", "V"))
+    bad = np.zeros((Hq, L), bool)
+    if at >= 0:
+        Kd[Hkv - 1, at, 5] = float("nan")
+        bad = who_sees(Hq, Hkv, L, w, S, Hkv - 1, at)
+    else:
+        Qd[Hq - 1, L - 7, 5] = float("nan")
+        bad[Hq - 1, L - 7] = True
+    total = sum(len(s) + 3 for s in S)
+    need = 256 + 512 * d + (total // 64 + Hq + 1 + Hkv * ((n + w) // 64 + 2)) * 128 * d      # clock counters, V^T tiles, rounding
+    for ws_bytes in (None, need):
+        O, _ = prefill_call(tb, bufs, Hq, Hkv, d, L, w, "bf16", S, Qd, Kd, Vd, free, ws_bytes, q0=L - n)
+        assert bad[:, L - n:].any()
+        assert np.array_equal(np.isnan(O).all(axis=2), bad[:, L - n:]) and np.array_equal(np.isnan(O).any(axis=2), bad[:, L - n:])
