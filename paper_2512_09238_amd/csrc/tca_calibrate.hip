@@ -118,19 +118,19 @@ __global__ __launch_bounds__(kCalThreads, 2) void cal_pass_kernel(
         constexpr bool FULL = decltype(full_tag)::value;
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
+          auto sees = [&](int r) {                 // by position, not by the logit: a NaN is no masked one
+            const int64_t si = si0 + kb + 4 * r;
+            return FULL || (COL ? si >= frow[b] && si < L : si <= frow[b] && si < s_end);
+          };
           double x[4];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int64_t si = si0 + kb + 4 * r;
-            x[r] = acc[b][r] * scale;
-            if (!FULL && !(COL ? si >= frow[b] && si < L : si <= frow[b] && si < s_end)) x[r] = -INFINITY;
-          }
+          for (int r = 0; r < 4; ++r) x[r] = sees(r) ? acc[b][r] * scale : -INFINITY;
           if constexpr (COL) {
             double e[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
               const int sl = sub * 16 + kb + 4 * r;
-              e[r] = FULL || x[r] > -INFINITY ? exp(x[r] - rmx[sl]) * rinv[sl] : 0.0;
+              e[r] = sees(r) ? exp(x[r] - rmx[sl]) * rinv[sl] : 0.0;
             }
             l[b] += (e[0] + e[1]) + (e[2] + e[3]);
           } else {
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(kCalThreads, 2) void cal_pass_kernel(
             }
             double e[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) e[r] = FULL || x[r] > -INFINITY ? exp(x[r] - mx) : 0.0;
+            for (int r = 0; r < 4; ++r) e[r] = sees(r) ? exp(x[r] - mx) : 0.0;
             l[b] += (e[0] + e[1]) + (e[2] + e[3]);
           }
         }

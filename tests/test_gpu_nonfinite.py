@@ -196,3 +196,23 @@ def test_prefill_in_chunks_shows_a_nan_where_it_is_seen(tb, bufs, case):
         O, _ = prefill_call(tb, bufs, Hq, Hkv, d, L, w, "bf16", S, Qd, Kd, Vd, free, ws_bytes, q0=L - n)
         assert bad[:, L - n:].any()
         assert np.array_equal(np.isnan(O).all(axis=2), bad[:, L - n:]) and np.array_equal(np.isnan(O).any(axis=2), bad[:, L - n:])
+
+
+@pytest.mark.parametrize("L", [129, 160, 333])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 128)])
+def test_calibration_shows_a_nan_key(tb, bufs, dtype, d, L):
+    """The last key row is seen by the last query alone, but every column mean counts that query: the heads of its KV head
+    have no coverage to compare and fall back, the others' results keep every bit."""
+    print("case", dtype, d, L, flush=True)
+    Hq, Hkv, b, M = 4, 2, 16, 4
+    x = wl.prefill_inputs("lowrank", Hq, Hkv, d, L, dtype, 66)
+    prm = H.params_for(tb, Hq, Hkv, d, b, b, dtype)
+    Qd, Kd = bufs.to_device(x["Q"]), bufs.to_device(x["K"])
+    ws = bufs.workspace(tb.tca_calibrate_workspace_bytes(prm, L, M))
+    clean = tb.tca_calibrate_budgets(prm, Qd, Kd, L, M, 1.0, 0.5, ws)
+    Kd[0, L - 1, 5] = float("nan")
+    got = tb.tca_calibrate_budgets(prm, Qd, Kd, L, M, 1.0, 0.5, ws)
+    assert np.isnan(got["a"][:2]).all() and got["fallback"][:2].all()
+    for name in ("a", "cand_idx", "p_star", "fallback"):
+        assert np.array_equal(got[name][2:], clean[name][2:]), name
+    assert np.array_equal(got["n"], clean["n"])
