@@ -123,27 +123,69 @@ __device__ __forceinline__ void store_cache_slice(const float (&x)[EL], KV* dst_
   if (sub == 0) *scale_slot = scale;
 }
 
+// Copies a row of T into a cache row of storage type KV: as stored, or as codes and a scale (called by the 16 lanes of a
+// group).  ALIGNED: slices of up to 16 bytes at a time; otherwise element by element.
+template <typename T, typename KV, int D, bool ALIGNED>
+struct RowCopy {
+  static constexpr int EL = D / 16;
+  static constexpr bool kSame = std::is_same<T, KV>::value;
+  RawSlice<T, EL> raw;
+  __device__ __forceinline__ void load(const T* row, int sub) {
+    if constexpr (ALIGNED) {
+      raw.load(row + sub * EL);
+    } else if constexpr (sizeof(T) == 2) {
+      const uint16_t* p = reinterpret_cast<const uint16_t*>(row) + sub * EL;
+#pragma unroll
+      for (int i = 0; i < EL / 2; ++i) raw.w[i] = p[2 * i] | ((uint32_t)p[2 * i + 1] << 16);
+    } else {
+      const uint32_t* p = reinterpret_cast<const uint32_t*>(row) + sub * EL;
+#pragma unroll
+      for (int i = 0; i < EL; ++i) raw.w[i] = p[i];
+    }
+  }
+  __device__ __forceinline__ void store(KV* row, float* scale_slot, int sub) const {
+    if constexpr (!kSame) {
+      float x[EL];
+      raw.widen(x);
+      store_cache_slice<KV, EL>(x, row, scale_slot, sub);
+    } else if constexpr (ALIGNED) {
+      constexpr int W = RawSlice<T, EL>::W;
+      if constexpr (W == 2) {
+        *reinterpret_cast<uint2*>(row + sub * EL) = make_uint2(raw.w[0], raw.w[1]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < W / 4; ++i)
+          reinterpret_cast<uint4*>(row + sub * EL)[i] = make_uint4(raw.w[4 * i], raw.w[4 * i + 1], raw.w[4 * i + 2], raw.w[4 * i + 3]);
+      }
+    } else if constexpr (sizeof(T) == 2) {
+      uint16_t* p = reinterpret_cast<uint16_t*>(row) + sub * EL;
+#pragma unroll
+      for (int i = 0; i < EL; ++i) p[i] = (uint16_t)(raw.w[i >> 1] >> (16 * (i & 1)));
+    } else {
+      uint32_t* p = reinterpret_cast<uint32_t*>(row) + sub * EL;
+#pragma unroll
+      for (int i = 0; i < EL; ++i) p[i] = raw.w[i];
+    }
+  }
+};
+
 // Writes the new row (k_new, v_new: D elements each) into row `row` of the ring; called by a whole workgroup, which may
 // read it back after the barrier inside (KV = T: the row as it is; KV = fp8_t: as codes and a scale).
 template <typename T, typename KV, int D>
 __device__ __forceinline__ void store_new_row(const tca_cache& c, size_t row, const T* __restrict__ k_new, const T* __restrict__ v_new) {
   if (threadIdx.x < 32) {                              // one 16-lane group for K, one for V
-    constexpr int EL = D / 16;
     const int sub = threadIdx.x & 15;
     const bool is_v = threadIdx.x >= 16;
-    const T* src = (is_v ? v_new : k_new) + sub * EL;
-    KV* dst = (KV*)(is_v ? c.ringV : c.ringK) + row * D;
-    if constexpr (std::is_same<T, KV>::value) {
-      RawSlice<T, EL> x;
-      x.load(src);
-      uint32_t* out = reinterpret_cast<uint32_t*>(dst + sub * EL);
-#pragma unroll
-      for (int i = 0; i < RawSlice<T, EL>::W; ++i) out[i] = x.w[i];
-    } else {
-      float x[EL];
-      load_slice<T, EL>(src, x);
-      store_cache_slice<KV, EL>(x, dst, (is_v ? c.ringV_scale : c.ringK_scale) + row, sub);
+    const T* src = is_v ? v_new : k_new;
+    RowCopy<T, KV, D, true> x;
+    if ((((uintptr_t)k_new | (uintptr_t)v_new) & 15) == 0) {
+      x.load(src, sub);
+    } else {                                           // the caller's rows may start at any element
+      RowCopy<T, KV, D, false> y;
+      y.load(src, sub);
+      x.raw = y.raw;
     }
+    x.store((KV*)(is_v ? c.ringV : c.ringK) + row * D, (is_v ? c.ringV_scale : c.ringK_scale) + row, sub);
     __threadfence_block();
     __builtin_amdgcn_s_waitcnt(0x0F70);                // the stores have reached the cache the workgroup reads through
   }
@@ -743,52 +785,6 @@ __global__ __launch_bounds__(kDecThreads) void decode_merge_kernel(
   }
   finish();
 }
-
-// Copies a row of T into a cache row of storage type KV: as stored, or as codes and a scale (called by the 16 lanes of a
-// group).  ALIGNED: slices of up to 16 bytes at a time; otherwise element by element.
-template <typename T, typename KV, int D, bool ALIGNED>
-struct RowCopy {
-  static constexpr int EL = D / 16;
-  static constexpr bool kSame = std::is_same<T, KV>::value;
-  RawSlice<T, EL> raw;
-  __device__ __forceinline__ void load(const T* row, int sub) {
-    if constexpr (ALIGNED) {
-      raw.load(row + sub * EL);
-    } else if constexpr (sizeof(T) == 2) {
-      const uint16_t* p = reinterpret_cast<const uint16_t*>(row) + sub * EL;
-#pragma unroll
-      for (int i = 0; i < EL / 2; ++i) raw.w[i] = p[2 * i] | ((uint32_t)p[2 * i + 1] << 16);
-    } else {
-      const uint32_t* p = reinterpret_cast<const uint32_t*>(row) + sub * EL;
-#pragma unroll
-      for (int i = 0; i < EL; ++i) raw.w[i] = p[i];
-    }
-  }
-  __device__ __forceinline__ void store(KV* row, float* scale_slot, int sub) const {
-    if constexpr (!kSame) {
-      float x[EL];
-      raw.widen(x);
-      store_cache_slice<KV, EL>(x, row, scale_slot, sub);
-    } else if constexpr (ALIGNED) {
-      constexpr int W = RawSlice<T, EL>::W;
-      if constexpr (W == 2) {
-        *reinterpret_cast<uint2*>(row + sub * EL) = make_uint2(raw.w[0], raw.w[1]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < W / 4; ++i)
-          reinterpret_cast<uint4*>(row + sub * EL)[i] = make_uint4(raw.w[4 * i], raw.w[4 * i + 1], raw.w[4 * i + 2], raw.w[4 * i + 3]);
-      }
-    } else if constexpr (sizeof(T) == 2) {
-      uint16_t* p = reinterpret_cast<uint16_t*>(row) + sub * EL;
-#pragma unroll
-      for (int i = 0; i < EL; ++i) p[i] = (uint16_t)(raw.w[i >> 1] >> (16 * (i & 1)));
-    } else {
-      uint32_t* p = reinterpret_cast<uint32_t*>(row) + sub * EL;
-#pragma unroll
-      for (int i = 0; i < EL; ++i) p[i] = raw.w[i];
-    }
-  }
-};
 
 // Both handover kernels are HBM-bound copies: one 16-lane group per row, kCopyRows (kWinRows) rows of K and of V per
 // group requested before the first is stored.  32768 tokens, 32 heads, into the FP8 cache (147 MB): 47.5 -> 44.7 us for the

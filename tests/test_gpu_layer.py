@@ -321,3 +321,38 @@ def test_handover_of_rows_that_are_not_16_byte_aligned(tb, bufs, dtype, kv, d):
         assert torch.equal(a.Kg[1, kept], Kg.view(-1, d)[kept]) and torch.equal(a.Vg[1, kept], Vg.view(-1, d)[kept])
         rest = torch.tensor([70, 71, 72] + list(range(134, 139)), device="cuda")
         assert not a.Kg[1, rest].any() and not a.idx[1, rest].any()
+
+
+@pytest.mark.parametrize("dtype,kv,d", [("bf16", "native", 128), ("bf16", "native", 64), ("f32", "native", 64), ("bf16", "fp8", 128)])
+def test_decode_step_from_rows_that_are_not_16_byte_aligned(tb, bufs, dtype, kv, d):
+    """New key and value rows that start one element past a 16-byte boundary: the ring and the outputs are those of
+    aligned ones, bit for bit."""
+    Hq, Hkv, w, T, b = 4, 2, 64, 90, 16
+    print("case", dtype, kv, d, flush=True)
+    prm = H.params_for(tb, Hq, Hkv, d, b, w, dtype)
+    P = np.stack([tb.tca_config_from_budget(b, 1.0, 0.3) for _ in range(Hq)])
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    got = []
+    for shift in (0, 1):
+        g = torch.Generator(device="cuda").manual_seed(4)
+        cache = bufs.DecodeCache(prm, 2, [20] * Hq, kv_format=tb.TCA_KV_FP8 if kv == "fp8" else tb.TCA_KV_NATIVE)
+        K, V = (torch.randn(Hkv, T, d, generator=g, device="cuda").to(dt) for _ in range(2))
+        q = torch.randn(2, Hq, d, generator=g, device="cuda").to(dt)
+        new = []
+        for _ in range(2):
+            t = torch.empty(2 * Hkv * d + 8, dtype=dt, device="cuda")[shift:shift + 2 * Hkv * d]
+            t.copy_(torch.randn(2 * Hkv * d, generator=g, device="cuda").to(dt))
+            assert (t.data_ptr() & 15 == 0) == (shift == 0)
+            new.append(t)
+        for s in range(2):
+            tb.tca_cache_load_window(prm, cache.view, s, K, V, T, T - 11 * s)
+        O = torch.full_like(q, 7.0)
+        tb.tca_decode(prm, cache.view, cache.offs, q, *new, P, O, bufs.workspace(tb.tca_decode_workspace_bytes(prm, 2, 20)))
+        torch.cuda.synchronize()
+        got.append((cache, O, new))
+    (a, Oa, new), (c, Oc, _) = got
+    for name in ("ringK", "ringV", "length") + (("ringK_scale", "ringV_scale") if kv == "fp8" else ()):
+        assert torch.equal(getattr(a, name), getattr(c, name)), name
+    assert torch.equal(Oa, Oc) and not torch.isnan(Oa.float()).any()
+    if kv == "native":
+        assert torch.equal(a.ringK[0, :, T % w], new[0].view(2, Hkv, d)[0]) and torch.equal(a.ringV[1, :, (T - 11) % w], new[1].view(2, Hkv, d)[1])
