@@ -80,8 +80,12 @@ __global__ __launch_bounds__(kRowThreads, D == 64 && KG == 1 ? 4 : 2) void prefi
   int nv_hi = 0, nvis = 0;
   if (nr > 0 && wg_last >= w) {
     nv_hi = count_le_wave(idx + base, nr, (int64_t)wg_last - w);
-    // positions are distinct and ascending: the first query sees at most QT - 1 rows fewer
+    // positions ascend, as a rule strictly: the first query then sees at most QT - 1 rows fewer
     int lo = nv_hi - (QT - 1) > 0 ? nv_hi - (QT - 1) : 0, hi = nv_hi;
+    if (lo > 0 && idx[base + lo - 1] > qpos - w) {                   // a position held more than once
+      hi = lo - 1;
+      lo = 0;
+    }
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
       if (idx[base + mid] <= qpos - w) lo = mid + 1; else hi = mid;

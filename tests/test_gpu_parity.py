@@ -825,3 +825,34 @@ CALIB_EDGES = [
 @pytest.mark.parametrize("case", CALIB_EDGES, ids=lambda c: f"{c[0]}-Hq{c[1]}-d{c[3]}-L{c[4]}-{c[5]}-b{c[6]}-M{c[7]}")
 def test_calibrate_at_the_edges_of_its_tiles(tb, bufs, case):
     test_calibrate_budgets_matches_oracle(tb, bufs, case)
+
+
+@pytest.mark.parametrize("case", [(2, 1, 64, 300, 32, 40), (16, 4, 128, 1700, 96, 150)], ids=["16-queries", "64-queries"])
+def test_fp32_prefill_counts_a_position_held_more_than_once(tb, bufs, case):
+    """Positions ascend but need not be distinct: a row held `times` times has that many keys, hidden from the first
+    queries of a workgroup and visible to its last.  1e-5 as for the other fp32 comparisons."""
+    Hq, Hkv, d, L, w, times = case
+    print("case", case, flush=True)
+    x = wl.prefill_inputs("lowrank", Hq, Hkv, d, L, "f32", 43)
+    prm = H.params_for(tb, Hq, Hkv, d, 16, w, "f32")
+    at = 137
+    S = np.sort(np.concatenate([np.arange(0, L // 2, 3), np.full(times, at)]))
+    gb = bufs.GlobalBuffers(prm, [len(S)] * Hq)
+    Qd, Kd, Vd = (bufs.to_device(x[k]) for k in ("Q", "K", "V"))
+    for h in range(Hq):
+        o, rows = int(gb.offs[h]), torch.from_numpy(S).cuda()
+        gb.idx[o:o + len(S)] = rows.to(torch.int32)
+        gb.Kg[o:o + len(S)], gb.Vg[o:o + len(S)] = Kd[h * Hkv // Hq, rows], Vd[h * Hkv // Hq, rows]
+        gb.n_rows[h] = len(S)
+    O = torch.full_like(Qd, float("nan"))
+    tb.tca_prefill(prm, Qd, 0, L, Kd, Vd, L, gb.idx, gb.Kg, gb.Vg, gb.offs, gb.n_rows, O, None, None)
+    torch.cuda.synchronize()
+    Of = bufs.to_host_f64(O)
+    Qf, Kf, Vf = (wl.to_f64(x[k]) for k in ("Q", "K", "V"))
+    for i in range(at + w - 70, at + w + 70):
+        keys = np.concatenate([S[S <= i - w], np.arange(max(0, i - w + 1), i + 1)])
+        for h in (0, Hq - 1):
+            g = h * Hkv // Hq
+            s = Kf[g][keys] @ Qf[h, i] / np.sqrt(d)
+            p = np.exp(s - s.max())
+            assert np.abs(Of[h, i] - p @ Vf[g][keys] / p.sum()).max() <= 1e-5, (h, i)
