@@ -249,7 +249,7 @@ __global__ __launch_bounds__(kRowThreads, D == 64 && KG == 1 ? 4 : 2) void prefi
 #pragma unroll
     for (int e = 0; e < 4; ++e) odd = fmaf(o[s][e], 0.f, odd);
   // (a wave of KG = 4 shares nothing with the others; with KG = 1 the barriers of the walk are the whole workgroup's)
-  if (KG == 1 ? __syncthreads_or(odd != 0.f) : __any(odd != 0.f)) walk(std::false_type{});
+  if (__builtin_expect(KG == 1 ? __syncthreads_or(odd != 0.f) : __any(odd != 0.f), 0)) walk(std::false_type{});
   l += __shfl_xor(l, 16, kWave);
   l += __shfl_xor(l, 32, kWave);
 
