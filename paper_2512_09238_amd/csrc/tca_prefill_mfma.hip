@@ -1116,10 +1116,16 @@ static int64_t play(int64_t n, int slots, Cost cost) {
 // close, walked by query tile (longest first, the heads inside) or by head (longest first).  Where there are many
 // rounds of workgroups, equal work ends evenly by itself and one head at a time is the order that the L2 likes
 // (a late start of a long head costs little): no other is looked at from 16 rounds on.  Otherwise each is played
-// through (`slots` workgroups at a time per XCD, the next item to the first free slot) and the one that ends soonest
-// taken.  Measured with the first two candidates only, and with all: 2700 tokens, 64 heads, 283 -> 169 us; 4096
-// tokens, 32 heads, 212 -> 175 us; 4000 queries behind 64K tokens 1156 -> 1017 us.  The estimate is in tile steps (tile_steps), and a constant for what a workgroup does before and after its loop.  A poor
-// estimate costs balance, never correctness.
+// through (`slots` workgroups at a time per XCD, the next item to the first free slot).  The estimate is in tile steps
+// (tile_steps), and a constant for what a workgroup does before and after its loop; a poor one costs balance, never
+// correctness.  It knows nothing of what the order costs besides: several heads at a time (by query tile) share the L2
+// where one had it alone, and heads dealt by cost leave their KV group.  So by head must promise 2.5 % more than the
+// ranges and by query tile 5 % more than either.  Estimated and measured end against the better of the two ranges (calls
+// on inputs in turn; 32 or 64 heads):
+//   by head        8192 behind 112K .988 -> 1.008, .960 -> .986; 8192 behind 64K .968 -> .992; 4096 behind 64K .890 -> .967;
+//                  4000 behind 64K .805 -> .907; 3000 behind 40K .792 -> .928; 12000 tokens .985 -> 1.004
+//   by query tile  4096 tokens .844 -> .925; 2700 .844 -> .937; 5000 .890 -> .962; 8192 .949 -> 1.000 and .961 -> 1.010;
+//                  12000 .954 -> 1.024; 16000 .976 -> 1.040; 20000 .965 -> 1.104; 32000 .993 -> 1.096
 constexpr int64_t kFixedSteps = 4;
 static int64_t plan_xcds(PrefillHeads& ph, const tca_params* prm, const int64_t* offs, int64_t q_pos0,
                          int64_t n_queries, int BM, int part, int slots, int64_t* makespan = nullptr) {
@@ -1180,36 +1186,34 @@ static int64_t plan_xcds(PrefillHeads& ph, const tca_params* prm, const int64_t*
   while (x < 8) by_work[++x] = (int32_t)n_items;
   const int32_t* best = by_work;
   if (few_rounds) {
-    int64_t best_t = -1;
-    auto better = [&](int64_t t) {
-      if (best_t >= 0 && t >= best_t) return false;
-      best_t = t;
-      return true;
-    };
-    for (const int32_t* st : {by_head, by_work}) {
+    auto ranges = [&](const int32_t* st) {
       int64_t t = 0;
       for (int xc = 0; xc < 8; ++xc) {
         const int64_t s = st[xc], e = st[xc + 1], he = e / n_qt * n_qt, len_e = he > s ? e - he : 0;
-        const int64_t tx = play(e - s, slots, [&](int64_t u) { return c[u < len_e ? he + u : s + (u - len_e)]; });
-        if (tx > t) t = tx;
+        t = std::max(t, play(e - s, slots, [&](int64_t u) { return c[u < len_e ? he + u : s + (u - len_e)]; }));
       }
-      if (better(t)) best = st;
-    }
-    for (int order = 1; order <= 2; ++order) {
+      return t;
+    };
+    auto dealt = [&](int order) {
       int64_t t = 0;
       for (int xc = 0; xc < 8; ++xc) {
         const uint8_t* p = ph.perm + xc * nh;
-        const int64_t tx = play(nh * n_qt, slots, [&](int64_t u) {
+        t = std::max(t, play(nh * n_qt, slots, [&](int64_t u) {
           return order == 1 ? c[p[u % nh] * n_qt + u / nh] : c[p[u / n_qt] * n_qt + u % n_qt];
-        });
-        if (tx > t) t = tx;
+        }));
       }
-      if (better(t)) {
-        best = by_head;
-        ph.order = order;
-      }
+      return t;
+    };
+    const int64_t t_head = ranges(by_head), t_work = ranges(by_work), t_one = dealt(1), t_two = dealt(2);
+    int64_t t = std::min(t_head, t_work);
+    best = t_head <= t_work ? by_head : by_work;
+    if (t_two * 40 < t * 39) {
+      t = t_two;
+      ph.order = 2;
     }
-    if (makespan) *makespan = best_t;
+    if (t_one * 20 < t * 19) ph.order = 1;
+    if (ph.order) best = by_head;
+    if (makespan) *makespan = std::min(std::min(t_head, t_work), std::min(t_one, t_two));
   } else if (makespan) {
     *makespan = total / (8 * slots);
   }
