@@ -76,8 +76,10 @@ __host__ __device__ inline int vt_key_of_pos(int p) {
 // vt_key_of_pos); rows past the last become zero, tiles past it are left alone (nobody reads them).  HBM-bound: no
 // LDS, a thread loads 16 bytes of the eight keys of one output chunk, transposes the 8 x 8 block in registers and
 // stores eight 16-byte chunks; of a wave's loads and stores every eight lanes cover 128 consecutive bytes.
-// (Staged through LDS and read back two bytes at a time: 2.7 TB/s; this 5.1 TB/s: 64 heads, 4.4 M
-// rows, 800 -> 440 us.)
+// The loads are non-temporal: nothing else reads these rows, and what they would push out of the caches is what the
+// attention kernel starts with.  us per call, staged through LDS in two launches / plain loads / this: 64 heads behind 112K
+// tokens (2.4 GB moved) 420 / 438 / 417, 32 heads and 128K tokens 326 / 341 / 314, 64 heads behind 64K 159 / 165 / 151,
+// 5446 tokens 14.3 / 11.1 / 11.0.  (Non-temporal stores, or a wave over whole rows and half the keys: 459 and 500 at 112K.)
 // The first region_tiles tiles are those of the regions (head by ph.tile_off; gather_idx != NULL: row r of a region
 // is row gather_idx[ph.offs[g] + r] of the dense matrix of KV head g / sel_per_kv, no compacted copy exists), the
 // others dense rows (tiles_per_group per KV head, from row first_row on, valid below valid_all).
@@ -128,7 +130,8 @@ __global__ __launch_bounds__(256) void transpose_tiles_kernel(
     v[e] = make_uint4(0, 0, 0, 0);
     if (k < n_valid) {
       const size_t row = gi ? (size_t)gi[k] : (size_t)(row0 + k);
-      v[e] = *reinterpret_cast<const uint4*>(src + row * D + cg * 8);
+      const raw16_t x = __builtin_nontemporal_load(reinterpret_cast<const raw16_t*>(src + row * D + cg * 8));
+      v[e] = make_uint4(x.x, x.y, x.z, x.w);
     }
   }
   const uint32_t* w = reinterpret_cast<const uint32_t*>(v);            // [key][pair of columns]
