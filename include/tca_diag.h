@@ -36,15 +36,26 @@ void tca_diag_prefill_clocks(int enable);
  * feeds two MFMAs); 3 = 8 waves x 32 queries.  All shapes compute the same result. */
 int tca_diag_prefill_variant(int variant);
 
-/* How a TCA_BF16 tca_prefill call with these sizes spreads its work over the chip (host only, nothing is
- * launched): the kernel walks the (head, query tile) items head by head, a head's query tiles from the
- * last to the first, and XCD x takes the items [start_out[x], start_out[x + 1]).
+/* How a TCA_BF16 tca_prefill call with these sizes spreads its (head, query tile) items over the chip (host only,
+ * nothing is launched).  Where tca_diag_prefill_walk below returns 0 the kernel walks the items head by head, a head's
+ * query tiles from the last to the first, and XCD x takes the items [start_out[x], start_out[x + 1]).  Where it returns 1
+ * or 2 every XCD takes whole heads, those that call names; start_out then holds the counts alone.
  *   offs : host [Hs + 1], as for tca_prefill;  part : TCA_PART_ALL / _WINDOW / _GLOBAL;
  *   gather_free != 0 : the call would have Kg = Vg = NULL;  start_out : host int32 [9]
- * Returns the number of workgroups of the attention kernel, or -1 (not a bf16 call, head count not a
- * multiple of 8, invalid sizes). */
+ * Returns the number of workgroups of the attention kernel of a call that is not cut into chunks of keys, or -1 (not a
+ * bf16 call, head count not a multiple of 8, invalid sizes). */
 int64_t tca_diag_prefill_xcd_plan(const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries,
                                   int part, int gather_free, int32_t* start_out);
+
+/* The order an XCD works its items off in, and whether the call is cut into chunks of keys (host only).  Arguments as
+ * above, and ws_bytes, the size of the workspace the call would be given.
+ *   heads_out : host int32 [Hq] or NULL: entries x Hq / 8 .. (x + 1) Hq / 8 - 1 are the heads of XCD x (orders 1 and 2)
+ *   chunks_out : host int64 or NULL: the workgroups of a call that is cut into chunks of keys, 0 where it is not
+ * Returns 0 (head by head, the ranges above), 1 (by query tile, longest first, the XCD's heads inside), 2 (its heads one
+ * at a time, the longest first), or -1 (as above, chunks_out is set all the same if only the head count is the reason).
+ * The order does not count for a call that is cut into chunks. */
+int tca_diag_prefill_walk(const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries, int part,
+                          int gather_free, size_t ws_bytes, int32_t* heads_out, int64_t* chunks_out);
 
 #ifdef __cplusplus
 }

@@ -103,6 +103,8 @@ EXPORTS = {
     "tca_diag_prefill_clocks": (None, [C.c_int]),
     "tca_diag_prefill_variant": (C.c_int, [C.c_int]),
     "tca_diag_prefill_xcd_plan": (C.c_int64, [_P(tca_params), C.c_void_p, C.c_int64, C.c_int64, C.c_int, C.c_int, C.c_void_p]),
+    "tca_diag_prefill_walk": (C.c_int, [_P(tca_params), C.c_void_p, C.c_int64, C.c_int64, C.c_int, C.c_int, C.c_size_t,
+                                        C.c_void_p, C.c_void_p]),
     "tca_calibrate_layers": (C.c_int, [_P(tca_params), C.c_int, _P(C.c_void_p), _P(C.c_void_p), C.c_int64, C.c_int,
                                        C.c_double, C.c_double, _dbl_p, _i32_p, _dbl_p, _i64_p, _i32_p,
                                        C.c_void_p, C.c_size_t, C.c_void_p]),
@@ -375,6 +377,19 @@ def tca_diag_prefill_xcd_plan(prm, offs, q_pos0: int, n_queries: int, part: int 
     if n < 0:
         raise ValueError("tca_diag_prefill_xcd_plan: not a bf16 call with a head count that is a multiple of 8")
     return start, int(n)
+
+
+def tca_diag_prefill_walk(prm, offs, q_pos0: int, n_queries: int, ws_bytes: int, part: int = 0, gather_free: bool = False):
+    """Returns (order, heads[Hq], chunks): the order an XCD works in (-1: none for such head counts), the heads in it, and
+    the workgroups of a call cut into chunks of keys (0: not cut)."""
+    offs = np.ascontiguousarray(offs, dtype=np.int64)
+    heads = np.zeros(prm.n_q_heads, dtype=np.int32)
+    chunks = C.c_int64(-1)
+    order = lib.tca_diag_prefill_walk(C.byref(prm), offs.ctypes.data_as(C.c_void_p), q_pos0, n_queries, part,
+                                      int(bool(gather_free)), ws_bytes, heads.ctypes.data_as(C.c_void_p), C.byref(chunks))
+    if order < 0 and chunks.value < 0:
+        raise ValueError("tca_diag_prefill_walk: not a bf16 call, or invalid sizes")
+    return int(order), heads, int(chunks.value)
 
 
 def prefill_shader_clock_ghz(ws) -> float:

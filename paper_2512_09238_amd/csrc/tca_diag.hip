@@ -75,6 +75,13 @@ extern "C" int64_t tca_diag_prefill_xcd_plan(const tca_params* prm, const int64_
   return prefill_mfma_xcd_plan(prm, offs, q_pos0, n_queries, part, gather_free != 0, start_out);
 }
 
+extern "C" int tca_diag_prefill_walk(const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries, int part,
+                                     int gather_free, size_t ws_bytes, int32_t* heads_out, int64_t* chunks_out) {
+  if (check_params(prm) != TCA_OK || prm->dtype != TCA_BF16 || !offs || q_pos0 < 0 || n_queries < 1) return -1;
+  if (part != TCA_PART_ALL && part != TCA_PART_WINDOW && part != TCA_PART_GLOBAL) return -1;
+  return prefill_mfma_walk(prm, offs, q_pos0, n_queries, part, gather_free != 0, ws_bytes, heads_out, chunks_out);
+}
+
 extern "C" size_t tca_probe_workspace_bytes(void) { return (size_t)kProbeBlocks * 3 * sizeof(unsigned long long); }
 
 extern "C" int tca_probe_mfma(int random_operands, int iters, double* tflops, double* shader_ghz, void* ws,

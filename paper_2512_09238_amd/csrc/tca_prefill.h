@@ -37,5 +37,8 @@ void launch_merge_split(const tca_params* prm, const SplitPlan& sp, int64_t n_qu
 // (start_out[9]); returns the number of workgroups launched, -1 if the head count is not a multiple of 8.
 int64_t prefill_mfma_xcd_plan(const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries, int part,
                               bool gather, int32_t* start_out);
+// What tca_diag_prefill_walk returns.
+int prefill_mfma_walk(const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries, int part, bool gather,
+                      size_t ws_bytes, int32_t* heads_out, int64_t* chunks_out);
 
 }  // namespace tca

@@ -1070,15 +1070,6 @@ size_t prefill_mfma_workspace_need(const tca_params* prm, int64_t n_queries, int
   return mfma_ws(nullptr, prm, n_queries, cap_rows).need;
 }
 
-// Chooses the ranges of the (head, query tile) sequence, in the order the kernel walks it, that the eight
-// XCDs work through, and returns the length of the longest.  Two candidates: whole heads per XCD, and
-// eight ranges of equal estimated work (heads keep different numbers of rows).  The estimate is in tile
-// steps: the dense tiles of the window, exactly; the visible part of a head's region as if its rows
-// were spread evenly over the positions seen so far (the host does not know idx); a constant for what a
-// workgroup does before and after its loop.  Each candidate is played through (`slots` workgroups at a
-// time per XCD, the next item to the first free slot) and the one that ends sooner is taken: with few
-// long items per slot a range of equal work but one item more than the slots divide costs a whole
-// round.  A poor estimate costs balance, never correctness.
 // Tile steps of query tile qt (BM queries) of a head with a region of cap rows: the dense tiles of the window,
 // exactly; the visible part of the region as if its rows were spread evenly over the positions seen so far (the
 // host does not know idx).
@@ -1300,6 +1291,8 @@ static int64_t plan_split(SplitPlan& sp, const tca_params* prm, const int64_t* o
 // The workgroup shape of a call: waves, and blocks of 32 queries per wave.  The size of the call chooses
 // between eight and four waves of 32 queries; the diagnostics switch can force a shape.
 struct WgShape { int nw, qb; };
+// workgroups of it an XCD runs at a time: 32 CUs, one eight-wave workgroup, one of four waves with a SIMD each, or two of four waves
+static int xcd_slots(WgShape sh) { return sh.nw == 8 || sh.qb == 2 ? 32 : 64; }
 static WgShape choose_shape(const tca_params* prm, int64_t n_queries, bool gather) {
   const int variant = prefill_variant();
   const bool many = ((n_queries + 255) / 256) * prm->n_q_heads >= 1024;
@@ -1307,6 +1300,26 @@ static WgShape choose_shape(const tca_params* prm, int64_t n_queries, bool gathe
   if (variant == 3 || (variant == 0 && many)) return {8, 1};
   if (variant == 2) return {4, 2};
   return {4, 1};
+}
+
+// The chunks of a call (plan_split), or 0.  Not for a part: the two parts may run side by side on one workspace, which has
+// room for one call's chunks.
+static int64_t choose_split(SplitPlan& sp, const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries, int part,
+                            WgShape sh, size_t ws_left) {
+  const int Hq = prm->n_q_heads, GS = sel_group(prm);
+  const int64_t n_qt = (n_queries + 127) / 128;
+  if (sh.nw != 4 || sh.qb != 1 || part != TCA_PART_ALL || prefill_variant() != 0 || n_qt * Hq >= 2 * kSplitSlots) return 0;
+  // when the plain launch would end: its longest item if it is all resident at once, else what the plan says
+  int64_t plain = 0;
+  if (n_qt * Hq > kSplitSlots && (Hq & 7) == 0) {
+    PrefillHeads ph;
+    plan_xcds(ph, prm, offs, q_pos0, n_queries, 128, part, 64, &plain);
+  } else {
+    for (int h = 0; h < Hq; h += GS)
+      plain = std::max(plain, kFixedSteps + tile_steps(prm, offs[h / GS + 1] - offs[h / GS], q_pos0, n_queries, 128, n_qt - 1, part));
+    if (n_qt * Hq > kSplitSlots) plain = plain * 6 / 10;           // no plan for such head counts: what the longest takes alone, at least
+  }
+  return plan_split(sp, prm, offs, q_pos0, n_queries, ws_left, plain);
 }
 
 template <int D>
@@ -1352,27 +1365,9 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
   // selectable through the diagnostics switch: measured 5-8 % slower on 128K tokens, because a
   // lone wave cannot issue its vector, LDS and scalar instructions fast enough beside the MFMAs.
   const WgShape sh = choose_shape(prm, n_queries, gather);
-  const int64_t n_qt128 = (n_queries + 127) / 128;
-  // Not for a part: the two parts may run side by side on one workspace, which has room for one call's chunks.
-  if (sh.nw == 4 && sh.qb == 1 && part == TCA_PART_ALL && prefill_variant() == 0 && (int64_t)n_qt128 * Hq < 2 * kSplitSlots) {
-    // when the plain launch would end: its longest item if it is all resident at once, else what the plan says
-    int64_t plain = 0;
-    if (n_qt128 * Hq <= kSplitSlots) {
-      for (int h = 0; h < Hq; h += sel_group(prm)) {
-        const int64_t c = kFixedSteps + tile_steps(prm, offs[h / sel_group(prm) + 1] - offs[h / sel_group(prm)], q_pos0, n_queries, 128,
-                                                   n_qt128 - 1, part);
-        if (c > plain) plain = c;
-      }
-    } else if ((Hq & 7) == 0) {
-      plan_xcds(ph, prm, offs, q_pos0, n_queries, 128, part, 64, &plain);
-    } else {
-      for (int h = 0; h < Hq; ++h)                 // no plan for such head counts: what the longest takes alone, at least
-        plain = std::max(plain, kFixedSteps + tile_steps(prm, offs[h / sel_group(prm) + 1] - offs[h / sel_group(prm)], q_pos0, n_queries,
-                                                         128, n_qt128 - 1, part));
-      plain = plain * 6 / 10;
-    }
-    SplitPlan sp;
-    const int64_t n_wg = plan_split(sp, prm, offs, q_pos0, n_queries, ws_bytes > mw.need ? ws_bytes - mw.need : 0, plain);
+  SplitPlan sp;
+  {
+    const int64_t n_wg = choose_split(sp, prm, offs, q_pos0, n_queries, part, sh, ws_bytes > mw.need ? ws_bytes - mw.need : 0);
     if (n_wg) {
       sp.part = mw.part;
       auto launch_split = [&](auto gather_tag) {
@@ -1390,9 +1385,7 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
     constexpr int NW = decltype(nw_tag)::value, QB = decltype(qb_tag)::value;
     constexpr bool GATHER = decltype(gather_tag)::value;
     const int n_qt = (int)((n_queries + NW * QB * 32 - 1) / (NW * QB * 32));
-    // workgroups an XCD runs at a time: 32 CUs, one eight-wave workgroup or two four-wave ones each
-    const unsigned n_wg = (Hq & 7) == 0 ? 8u * (unsigned)plan_xcds(ph, prm, offs, q_pos0, n_queries, NW * QB * 32, part,
-                                                                   NW == 8 || QB == 2 ? 32 : 64)
+    const unsigned n_wg = (Hq & 7) == 0 ? 8u * (unsigned)plan_xcds(ph, prm, offs, q_pos0, n_queries, NW * QB * 32, part, xcd_slots(sh))
                                         : (unsigned)n_qt * Hq;
     hipLaunchKernelGGL((prefill_mfma_kernel<D, NW, QB, GATHER>), dim3(n_wg), dim3(NW * 64), 0, st, Q,
                        q_pos0, n_queries, K, kv_stride, idx, Kg, n_rows, mw.Vgt, mw.Vt, dt0, d_tiles, ph, Hq,
@@ -1415,10 +1408,23 @@ int64_t prefill_mfma_xcd_plan(const tca_params* prm, const int64_t* offs, int64_
   if ((prm->n_q_heads & 7) != 0) return -1;
   const WgShape sh = choose_shape(prm, n_queries, gather);
   PrefillHeads ph;
-  const int64_t longest = plan_xcds(ph, prm, offs, q_pos0, n_queries, sh.nw * sh.qb * 32, part,
-                                    sh.nw == 8 || sh.qb == 2 ? 32 : 64);
+  const int64_t longest = plan_xcds(ph, prm, offs, q_pos0, n_queries, sh.nw * sh.qb * 32, part, xcd_slots(sh));
   for (int x = 0; x <= 8; ++x) start_out[x] = ph.xcd_start[x];
   return 8 * longest;
+}
+
+int prefill_mfma_walk(const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries, int part, bool gather,
+                      size_t ws_bytes, int32_t* heads_out, int64_t* chunks_out) {
+  const WgShape sh = choose_shape(prm, n_queries, gather);
+  const size_t need = prefill_mfma_workspace_need(prm, n_queries, offs[sel_heads(prm)]);
+  SplitPlan sp;
+  const int64_t chunks = choose_split(sp, prm, offs, q_pos0, n_queries, part, sh, ws_bytes > need ? ws_bytes - need : 0);
+  if (chunks_out) *chunks_out = chunks;
+  if ((prm->n_q_heads & 7) != 0) return -1;
+  PrefillHeads ph;
+  plan_xcds(ph, prm, offs, q_pos0, n_queries, sh.nw * sh.qb * 32, part, xcd_slots(sh));
+  for (int h = 0; heads_out && h < prm->n_q_heads; ++h) heads_out[h] = ph.order ? ph.perm[h] : h;
+  return ph.order;
 }
 
 int launch_prefill_mfma(const tca_params* prm, const bf16_t* Q, int64_t q_pos0, int64_t n_queries,

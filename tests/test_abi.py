@@ -174,6 +174,32 @@ def test_prefill_of_ten_rounds_keeps_a_head_at_a_time():
     n_qt = -(-L // 256)
     assert start[0] == 0 and start[8] == Hq * n_qt and n_wg == 8 * int(np.diff(start).max())
     assert not np.array_equal(start, np.arange(9) * 4 * n_qt)
+    assert tb.tca_diag_prefill_walk(prm, offs, 0, L, 1 << 30)[::2] == (0, 0)
+
+
+def test_prefill_order_and_chunks_of_a_call():
+    """The other orders, where they promise enough: by query tile for one window's length, by head for a late chunk whose
+    heads keep different numbers of rows; every head is on one XCD.  A call of few query tiles is cut into chunks if its
+    workspace has room for them, a part never."""
+    import paper_2512_09238_amd.binding as tb
+    Hq, w = 32, 4096
+    prm = tb.make_params(Hq, 8, 128, 128, w, tb.TCA_BF16, 0.5, 0.0)
+    rows = np.random.default_rng(5).permutation(np.linspace(0.03, 0.3, Hq)) * 65536
+    offs = np.concatenate([[0], np.cumsum(rows.astype(np.int64))])
+    order, heads, chunks = tb.tca_diag_prefill_walk(prm, np.arange(Hq + 1, dtype=np.int64) * 100, 0, w, 1 << 30)
+    assert (order, chunks) == (1, 0) and sorted(heads) == list(range(Hq))
+    order, heads, chunks = tb.tca_diag_prefill_walk(prm, offs, 65536, 8192, 1 << 30)
+    assert (order, chunks) == (2, 0) and sorted(heads) == list(range(Hq))
+    sums = [rows[heads[4 * x:4 * x + 4]].sum() for x in range(8)]
+    assert max(sums) / min(sums) < 1.1 and all((np.diff(rows[heads[4 * x:4 * x + 4]]) <= 0).all() for x in range(8))
+    full = tb.tca_prefill_workspace_bytes(prm, 300, int(offs[-1]))
+    assert 96 < tb.tca_diag_prefill_walk(prm, offs, 65536, 300, full)[2] <= 1024
+    assert tb.tca_diag_prefill_walk(prm, offs, 65536, 300, 0)[2] == 0
+    for part in (tb.TCA_PART_WINDOW, tb.TCA_PART_GLOBAL):
+        assert tb.tca_diag_prefill_walk(prm, offs, 65536, 300, full, part=part)[2] == 0
+    assert tb.tca_diag_prefill_walk(tb.make_params(12, 4, 128, 128, w, tb.TCA_BF16, 0.5, 0.0), offs[:13], 65536, 300, full)[0::2] >= (-1, 1)
+    with pytest.raises(ValueError):
+        tb.tca_diag_prefill_walk(tb.make_params(Hq, 8, 128, 128, w, tb.TCA_F32, 0.5, 0.0), offs, 0, w, 0)
 
 
 

@@ -192,6 +192,11 @@ def test_prefill_in_chunks_shows_a_nan_where_it_is_seen(tb, bufs, case):
         bad[Hq - 1, L - 7] = True
     total = sum(len(s) + 3 for s in S)
     need = 256 + 512 * d + (total // 64 + Hq + 1 + Hkv * ((n + w) // 64 + 2)) * 128 * d      # clock counters, V^T tiles, rounding
+    offs = np.concatenate([[0], np.cumsum([len(s) + 3 for s in S])])
+    prm = H.params_for(tb, Hq, Hkv, d, 16, w, "bf16")
+    cut = [tb.tca_diag_prefill_walk(prm, offs, L - n, n, size, gather_free=free)[2]
+           for size in (tb.tca_prefill_workspace_bytes(prm, n, total), need)]
+    assert cut[0] > 0 and cut[1] == 0
     for ws_bytes in (None, need):
         O, _ = prefill_call(tb, bufs, Hq, Hkv, d, L, w, "bf16", S, Qd, Kd, Vd, free, ws_bytes, q0=L - n)
         assert bad[:, L - n:].any()

@@ -681,13 +681,18 @@ def test_few_queries_behind_a_long_context(tb, bufs, case):
     total = int(gb.offs[-1])
     need = 256 + 512 * d + (total // 64 + Hs + 1 + Hkv * ((n + w) // 64 + 2)) * 128 * d      # clock counters, V^T tiles, rounding
     Kg, Vg = (None, None) if free else (gb.Kg, gb.Vg)
+    full = tb.tca_prefill_workspace_bytes(prm, n, total)
+    assert tb.tca_diag_prefill_walk(prm, gb.offs, L - n, n, full, gather_free=free)[2] > 0, "this call is not cut into chunks"
+    assert tb.tca_diag_prefill_walk(prm, gb.offs, L - n, n, need, gather_free=free)[2] == 0, "nor is this one whole"
     outs = []
-    for ws in (bufs.workspace(tb.tca_prefill_workspace_bytes(prm, n, total)), bufs.workspace(need)):
+    for ws in (bufs.workspace(full), bufs.workspace(full), bufs.workspace(need)):
         O = torch.full_like(Qt, float("nan"))
         lse = torch.full((Hq, n), float("nan"), dtype=torch.float32, device="cuda")
         tb.tca_prefill(prm, Qt, L - n, n, Kd, Vd, L, gb.idx, Kg, Vg, gb.offs, gb.n_rows, O, lse, ws)
         torch.cuda.synchronize()
         outs.append((bufs.to_host_f64(O), lse.cpu().numpy()))
+    again = outs.pop(0)
+    assert np.array_equal(again[0], outs[0][0]) and np.array_equal(again[1], outs[0][1]), "the same call twice"
     rows = sorted({0, 1, n // 2, n - 1, min(n - 1, 127), min(n - 1, 128)} & set(range(n)))
     ref = H.oracle_rows(x, None, {"w": w}, S, np.array([L - n + r for r in rows]))
     Qf, Kf = wl.to_f64(x["Q"]), wl.to_f64(x["K"])
