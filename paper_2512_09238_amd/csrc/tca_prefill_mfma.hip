@@ -154,33 +154,6 @@ __global__ __launch_bounds__(256) void transpose_tiles_kernel(
 // ------------------------------------------------------------- main kernel --
 __device__ __forceinline__ int64_t i64min(int64_t a, int64_t b) { return a < b ? a : b; }
 
-__device__ __forceinline__ int count_le_i32(const int32_t* idx, int n, int64_t bound) {
-  int lo = 0, hi = n;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if ((int64_t)idx[mid] <= bound) lo = mid + 1; else hi = mid;
-  }
-  return lo;
-}
-
-// The same count for a bound all 64 lanes share, found by the wave together: every round probes 64
-// evenly spaced elements of the remaining range at once, so 2^18 elements take three dependent loads
-// instead of eighteen.  n, bound: wave-uniform; the result is uniform as well.
-__device__ __forceinline__ int count_le_wave(const int32_t* idx, int n, int64_t bound, int lane) {
-  int lo = 0, len = n;                               // the count lies in [lo, lo + len]
-  while (len > 0) {
-    const int step = (len + 63) >> 6;
-    const int p = lo + (lane + 1) * step - 1;        // ascending probes: the lanes that pass form a prefix
-    const bool le = p < lo + len && (int64_t)idx[p] <= bound;
-    const int k = __builtin_popcountll(__ballot(le));
-    lo += k * step;
-    const int left = n - lo;                         // elements from lo to the end of the array
-    len = k == 64 ? 0 : (step - 1 < left ? step - 1 : left);
-    if (k == 64) lo = lo < n ? lo : n;
-  }
-  return lo;
-}
-
 // O^T += V^T P^T step.  With two query blocks per wave the O^T accumulators (128 registers for
 // d = 128) are pinned to the accumulation registers, which only the matrix pipe touches, so that
 // the scores and the exponentials' terms keep the vector registers.  The instruction is written
@@ -434,7 +407,7 @@ void prefill_mfma_kernel(
 #pragma unroll
   for (int blk = 0; blk < QB; ++blk) nvis[blk] = 0;
   if (wg_last >= w && nr > 0) {
-    nv_wave_lo = __builtin_amdgcn_readfirstlane(count_le_wave(idx + base, nr, (int64_t)wave_first - w, lane));
+    nv_wave_lo = __builtin_amdgcn_readfirstlane(count_le_wave(idx + base, nr, (int64_t)wave_first - w));
     int nxt[BM / 64];                              // lane j of nxt[i]: the position of row nv_wave_lo + 64 i + j
 #pragma unroll
     for (int i = 0; i < BM / 64; ++i) {

@@ -521,8 +521,8 @@ extern "C" int tca_qkv_project(const tca_params* prm, const void* X, int64_t n_t
       return fail(TCA_ERR_INVALID, "tca_qkv_project (bf16): strides must be multiples of 4 elements, outputs 8-byte and inputs 16-byte aligned");
     const QkvCall call{(const uint16_t*)W, (const uint16_t*)X, (const uint16_t*)bias, n_feat, n_tokens, hidden, d, out, st};
     // Up to 32 rows one pass over the weights is all there is to do.  Measured at 6144 features, hidden 4096 (50 MB of
-    // weights): 16 rows 262 -> 15.8 us, 32 rows 265 -> 19.3 us (tiles of 256 x 256 before); 10240 features, hidden
-    // 8192: 16 rows 822 -> 44 us.  Four feature blocks per workgroup instead of two halve the reads of X and pay
+    // weights): 16 rows 208 -> 15.6 us, 32 rows 196 -> 18.1 us (tiles of 256 x 256 before); 10240 features, hidden
+    // 8192: 16 rows 806 -> 44 us.  Four feature blocks per workgroup instead of two halve the reads of X and pay
     // once two would make more workgroups than CUs (44 against 52 us there; 21.7 against 15.8 us at 6144).
     const bool wide = n_feat / 32 > kCUs;
     if (n_tokens <= 16) {
@@ -537,8 +537,8 @@ extern "C" int tca_qkv_project(const tca_params* prm, const void* X, int64_t n_t
       // hidden 4096 (64x64 / 64x128 / 128x128 / 128x256 / 256x256), the choice in brackets:
       //   128 rows [23] 31 42 47 98;  256: 41 [31] 41 58 107;  413: 54 49 [36] 52 103;  1024: 119 84 80 [63] 106;
       //   1500: 129 110 102 104 [91];  4096: 338 272 221 [185] 199;  8192: 687 574 459 379 [342]
-      // (256 x 256 alone, with ids that skipped CUs when the token tiles were not a multiple of 32, took 290 - 315
-      // us up to 1024 rows and 240 us at 2048).
+      // (256 x 256 alone, with ids that skipped CUs when the token tiles were not a multiple of 32, took 196 - 221
+      // us up to 1500 rows, 230 us at 2048 and 295 at 4096).
       constexpr int kTiles[5][2] = {{256, 256}, {128, 256}, {128, 128}, {64, 128}, {64, 64}};      // features, tokens
       int best = -1;
       int64_t best_cost = 0;
