@@ -15,6 +15,10 @@
  *     ordinary CPU memory owned by the caller.  The library never allocates or
  *     frees device memory.  Scratch comes in through (ws, ws_bytes); query the
  *     size with the matching tca_*_workspace_bytes().  ws must be 256-byte aligned.
+ *     tca_prefill and tca_decode also take less, down to a size that
+ *     tca_last_error() names after TCA_ERR_WORKSPACE: what they leave out is room to
+ *     cut a call of few workgroups into more of them.  Such a call is slower, and as
+ *     its sums are formed in another order its results may differ in the last bits.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     All work is enqueued on it; only tca_calibrate_budgets waits for it.
  *   - Tensors are dense, row-major, innermost dimension head_dim:
@@ -33,7 +37,8 @@
  *     offs[n] .. offs[n] + n_rows[n] - 1 of a flat buffer (offs = capacity prefix
  *     sums, host array of Hs+1 entries; the heads' rows share one flat buffer
  *     addressed through precomputed offsets, the layout of App. C).  idx is the
- *     absolute token position of each row, ascending within a head.
+ *     absolute token position of each row, ascending within a head.  tca_select
+ *     keeps a position once, and the bf16 prefill counts on that.
  *   - Positions are 0-based.  The local subset of the query at position i is the
  *     window (i-w, i]; a global row at position j is visible to it iff j <= i-w,
  *     so no key is counted twice (Sec. IV, "no overlap").
@@ -130,7 +135,9 @@ int64_t tca_select_rows(const tca_params* prm, int64_t n_blocks, const double* p
 int tca_decode_budget(int b, const double* p);
 
 size_t tca_select_workspace_bytes(const tca_params* prm, int64_t n_tokens);
-/* cap_rows: total rows of the flat global buffer (offs[Hs]). */
+/* cap_rows: total rows of the flat global buffer (offs[Hs]).  Includes up to 68 MB for the partial results
+ * of calls cut into chunks of keys, also where the call asked about would not be cut itself: the size grows
+ * with both arguments, so that a workspace for the longest call of a program serves its short ones. */
 size_t tca_prefill_workspace_bytes(const tca_params* prm, int64_t n_queries, int64_t cap_rows);
 /* max_head_rows: the largest capacity of one head's region, max_h (offs[h+1]-offs[h]). */
 size_t tca_decode_workspace_bytes(const tca_params* prm, int batch, int64_t max_head_rows);
@@ -309,8 +316,8 @@ int tca_decode(const tca_params* prm, const tca_cache* cache, const int64_t* off
 
 /* tca_decode for callers that cannot allocate or hand over scratch memory: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, checks, kernels
- * and results as tca_decode, minus (ws, ws_bytes): the split-K partials go to an array of
- * TCA_DECODE_STATIC_BYTES bytes that is part of the library itself (each GPU the library runs on
+ * and results as tca_decode with a workspace of tca_decode_workspace_bytes(), minus (ws, ws_bytes):
+ * the split-K partials go to an array of TCA_DECODE_STATIC_BYTES bytes that is part of the library itself (each GPU the library runs on
  * holds it until the process ends).  The call allocates and frees nothing.  A step whose
  * tca_decode_workspace_bytes() exceeds TCA_DECODE_STATIC_BYTES is rejected with
  * TCA_ERR_WORKSPACE and nothing is launched (32 MiB covers batch 16 x 32 query heads x 128K
