@@ -25,7 +25,9 @@
 //             workgroup of a sequence advances its length.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
+#include <functional>
 #include <type_traits>
 
 #include "tca_common.h"
@@ -44,7 +46,9 @@ constexpr int kMaxSlots = 4096;       // split-K units per head the merge kernel
 struct DecodeHeads {
   int64_t offs[TCA_MAX_HEADS + 1];
   int32_t t_dec[TCA_MAX_HEADS];
-  int32_t unit0[TCA_MAX_HEADS + 1];   // first unit of each head's region; unit0[Hs]: the first ring unit
+  int32_t unit0[TCA_MAX_HEADS + 1];   // first unit of each head's region; unit0[Hs]: their number
+  int32_t first[TCA_MAX_HEADS];       // the order of the regions' workgroups: see order_units
+  uint8_t by_units[TCA_MAX_HEADS];    // the heads, those with the most units first
   int32_t chunk;                      // rows per unit
   int32_t ring_units;                 // units of one ring
 };
@@ -548,10 +552,16 @@ __device__ __forceinline__ void partial_rows_mfma(const bf16_t* __restrict__ kba
 }
 
 // grid (units, B); block kPartThreads.  Selection head hs serves the GQ query heads hs*GQ .. hs*GQ+GQ-1 (GQ = 1: one
-// selection per query head).  Units below unit0[Hs] are chunks of a head's global region, the others chunks of a
-// ring.  The ring belongs to the KV head, so its units score each row against all GW query heads of the group.
+// selection per query head).  The ring belongs to the KV head, so its units score each row against all GW query heads of
+// the group.  The rings' units come first, then the regions', all heads' first chunks, then all heads' second ones, ..: in
+// a cache with room to spare those that hold rows are neighbours, which the chip deals to its XCDs and CUs in turn, and the
+// empty ones follow.  (Head after head, the first chunks of all heads may be on one or two XCDs.  us per step of 32 heads with
+// room for 40000 rows each, head after head / this: 4 sequences of 1500 rows 91 / 53, 16 of 1500 286 / 162, 16 of 10000 618 /
+// 518, 16 of 3000 with a shared selection 222 / 135; full caches, 16 x 128K tokens 1088 / 1066, 5 x 112K 790 / 768.)
+// (The bound on the FP8 rows of 128 and groups of 4, which sit at 128 registers: with 132, a wave fewer per SIMD, 93.5 against
+// 92.4 us at 8 sequences of 30K tokens.)
 template <typename T, typename KV, int D, int GQ, int GW>
-__global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
+__global__ __launch_bounds__(kPartThreads, sizeof(KV) == 1 && D == 128 && GW == 4 ? 4 : 1) void decode_partial_kernel(
     tca_cache c, DecodeHeads dh, int Hq, int Hkv, int w, double scale, const T* __restrict__ q,
     const T* __restrict__ k_new, const T* __restrict__ v_new, int32_t* __restrict__ done, float* __restrict__ part) {
   constexpr int EL = D / 16;
@@ -559,24 +569,39 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
   __shared__ float red[kPartWaves * 16 * NMAX * (EL + 2)];
   constexpr bool kMfma = sizeof(KV) == 2 && D == 128;  // rows that partial_rows_mfma takes
   __shared__ __attribute__((aligned(16))) unsigned char tiles[kMfma && NMAX > 1 ? kPartWaves * kMfmaTileBytes + NMAX * 256 : 16];
-  const int unit = blockIdx.x, s = blockIdx.y;
+  const int id = blockIdx.x, s = blockIdx.y;
   const int Hs = Hq / GQ;
   const int64_t Tpos = c.length[s];
-  const int region_units = dh.unit0[Hs];
+  const int region_units = dh.unit0[Hs], all_ring_units = Hkv * dh.ring_units;
   float* const seq_part = part + (size_t)s * ((size_t)GQ * region_units + (size_t)Hq * dh.ring_units) * (D + 2);
-  if (unit == 0 && threadIdx.x == 0) done[s] = 0;      // for the merge that follows
+  if (id == 0 && threadIdx.x == 0) done[s] = 0;        // for the merge that follows
 
-  if (unit < region_units) {
-    int hs = 0;
-    for (int step = 64; step > 0; step >>= 1)
-      if (hs + step < Hs && dh.unit0[hs + step] <= unit) hs += step;
-    const int ns = dh.unit0[hs + 1] - dh.unit0[hs], slot = unit - dh.unit0[hs];
+  if (id >= all_ring_units) {
+    // The lanes read the tables at once and they are looked up in registers: in memory, one lookup behind the other and each
+    // line a miss at first, it cost the smallest steps 0.6 us of 17.
+    const int r = id - all_ring_units, lane = threadIdx.x & 63;
+    auto in_regs = [&](auto table) {
+      const int lo = lane < Hs ? table(lane) : INT32_MAX, hi = lane + 64 < Hs ? table(lane + 64) : INT32_MAX;
+      return [=](int i) { return i < 64 ? __builtin_amdgcn_readlane(lo, i) : __builtin_amdgcn_readlane(hi, i - 64); };
+    };
+    const int f0 = lane < Hs ? dh.first[lane] : INT32_MAX, f1 = lane + 64 < Hs ? dh.first[lane + 64] : INT32_MAX;
+    const auto by_units = in_regs([&](int i) { return (int)dh.by_units[i]; });
+    const auto unit0 = in_regs([&](int i) { return dh.unit0[i]; });
+    const auto unit1 = in_regs([&](int i) { return dh.unit0[i + 1]; });
+    const auto rows = in_regs([&](int i) { return c.n_rows[s * Hs + i]; });
+    // 2^32 / heads rounded up: its high product with a number below 2^25 is the quotient (heads <= 128; 1 has no such number)
+    const auto magic = in_regs([&](int i) { return (int)(0xFFFFFFFFu / (uint32_t)(Hs - i) + 1); });
+    const int i = __popcll(__ballot(f0 <= r)) + __popcll(__ballot(f1 <= r)) - 1, heads = Hs - i;
+    const int in = r - (i < 64 ? __builtin_amdgcn_readlane(f0, i) : __builtin_amdgcn_readlane(f1, i - 64));
+    const int turn = heads == 1 ? in : (int)__umulhi((uint32_t)in, (uint32_t)magic(i));
+    const int hs = by_units(in - turn * heads), above = by_units(i ? heads : 0);
+    const int u0 = unit0(hs), ns = unit1(hs) - u0, slot = turn + (i ? unit1(above) - unit0(above) : 0);
     const int r_begin = slot * dh.chunk;
     const size_t base = (size_t)s * c.cap_rows + dh.offs[hs];
-    int len = c.n_rows[s * Hs + hs] - r_begin;
+    int len = rows(hs) - r_begin;
     if (len > dh.chunk) len = dh.chunk;
     const int r_end = r_begin + (len > 0 ? count_le_wave(c.idx + base + r_begin, len, Tpos - w) : 0);
-    float* out = seq_part + ((size_t)GQ * dh.unit0[hs] + slot) * (D + 2);    // query g: + g * ns * (D+2)
+    float* out = seq_part + ((size_t)GQ * u0 + slot) * (D + 2);              // query g: + g * ns * (D+2)
     const size_t out_head = (size_t)ns * (D + 2);
     const T* q0 = q + ((size_t)s * Hq + hs * GQ) * D;
     if constexpr (kMfma && GQ > 1)
@@ -586,7 +611,7 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
       partial_rows<T, KV, D, GQ>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base,
                                  c.Vg_scale + base, r_begin, r_end, q0, scale, out, out_head, red);
   } else {
-    const int v = unit - region_units, kvh = v / dh.ring_units, slot = v - kvh * dh.ring_units, h0 = kvh * GW;
+    const int kvh = id / dh.ring_units, slot = id - kvh * dh.ring_units, h0 = kvh * GW;
     const int r_begin = slot * dh.chunk;
     const size_t base = ((size_t)s * Hkv + kvh) * w;
     // Slot r of the ring holds the latest position congruent to r mod w that is <= Tpos.  Once
@@ -910,6 +935,25 @@ static int64_t choose_chunk(DecodeHeads& dh, const tca_params* prm, int batch, s
   return set_chunk(dh, prm, long_chunk(prm));
 }
 
+// The order of the regions' workgroups, all heads' first chunks first: heads sorted by their number of units, most first; the
+// chunks in which the same heads take part form a piece.  Piece i holds the first Hs - i heads, and the chunks from the
+// number of units of head Hs - i of that order (0 for i = 0) to that of the one before it; its workgroups start at number
+// first[i], chunk by chunk.
+static void order_units(DecodeHeads& dh, int Hs) {
+  auto units = [&](int h) { return dh.unit0[h + 1] - dh.unit0[h]; };
+  uint32_t key[TCA_MAX_HEADS];                         // units, then the head (there are at most kMaxSlots units per head)
+  for (int h = 0; h < Hs; ++h) key[h] = (uint32_t)units(h) << 8 | (uint32_t)(255 - h);
+  std::sort(key, key + Hs, std::greater<uint32_t>());
+  for (int h = 0; h < Hs; ++h) dh.by_units[h] = (uint8_t)(255 - (key[h] & 255u));
+  int32_t run = 0, before = 0;
+  for (int i = 0; i < Hs; ++i) {
+    const int32_t upto = units(dh.by_units[Hs - 1 - i]);
+    dh.first[i] = run;
+    run += (upto - before) * (Hs - i);
+    before = upto;
+  }
+}
+
 template <typename T, typename KV, int D>
 static int run_decode(const tca_params* prm, const tca_cache* c, const DecodeHeads& dh, int64_t units, const T* q,
                       const T* k_new, const T* v_new, T* O, void* ws, hipStream_t st) {
@@ -1053,6 +1097,7 @@ static int decode_step(const tca_params* prm, const tca_cache* cache, const int6
     return fail(TCA_ERR_WORKSPACE, "%s: scratch needs %zu bytes, 256-byte aligned; %zu available", who, need,
                 ws_bytes);
   const int64_t units = choose_chunk(dh, prm, cache->batch, ws_bytes);
+  order_units(dh, Hs);
   if (units > INT32_MAX || cache->batch > 65535) return fail(TCA_ERR_UNSUPPORTED, "%s: batch=%d", who, cache->batch);
   hipStream_t st = (hipStream_t)stream;
 #define TCA_RUN_DECODE(TT, KK)                                                                                         \

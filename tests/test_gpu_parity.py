@@ -819,6 +819,53 @@ def test_decode_units_at_their_edges(tb, bufs, case):
                 assert (Ox[s, h] - ref).abs().max().item() <= H.TOL[dtype], (s, h)
 
 
+ROOMY_CASES = [
+    # Hq, Hkv, d, dtype, share: more heads than a wave has lanes, a number of heads that is odd, one head, units of one length
+    (128, 16, 64, "bf16", False),
+    (72, 9, 64, "f32", False),
+    (7, 1, 128, "bf16", False),
+    (8, 1, 128, "bf16", True),
+]
+
+
+@pytest.mark.parametrize("case", ROOMY_CASES, ids=lambda c: f"Hq{c[0]}-Hkv{c[1]}-d{c[2]}-{c[3]}-share{c[4]}")
+def test_decode_in_a_cache_with_room_to_spare(tb, bufs, case):
+    """Heads with room for 0 to 900 rows that hold any part of it: every unit of every head is walked once, whatever the
+    order of the workgroups (the definition in fp64, on every head)."""
+    Hq, Hkv, d, dtype, share = case
+    print("case", case, flush=True)
+    w, T = 64, 5000
+    prm = H.params_for(tb, Hq, Hkv, d, 32, w, dtype, share=share)
+    Hs = Hkv if share else Hq
+    rng = np.random.default_rng(Hq)
+    cap = np.array([[0, 128, int(rng.integers(1, 900)), 384][h % 4] if Hs > 1 else 700 for h in range(Hs)])
+    used = np.array([int(rng.integers(0, c + 1)) for c in cap])
+    P = np.stack([tb.tca_config_from_budget(32, 1.0, 0.3) for _ in range(Hs)])
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    cache = bufs.DecodeCache(prm, 2, cap)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    for name in ("Kg", "Vg", "ringK", "ringV"):
+        x = getattr(cache, name)
+        x.copy_(torch.randn(x.shape, generator=g, device="cuda").to(dt))
+    cache.n_rows[:] = torch.from_numpy(used.astype(np.int32)).cuda()
+    for h in range(Hs):
+        cache.idx[:, cache.offs[h]:cache.offs[h] + used[h]] = torch.arange(int(used[h]), dtype=torch.int32, device="cuda") * 5
+    cache.length[:] = T
+    q = torch.randn(2, Hq, d, generator=g, device="cuda").to(dt)
+    kn, vn = (torch.randn(2, Hkv, d, generator=g, device="cuda").to(dt) for _ in range(2))
+    O = torch.full_like(q, float("nan"))
+    tb.tca_decode(prm, cache.view, cache.offs, q, kn, vn, P, O, bufs.workspace(tb.tca_decode_workspace_bytes(prm, 2, int(cap.max()))))
+    torch.cuda.synchronize()
+    for s in range(2):
+        for h in range(Hq):
+            hs, kvh, o = h // (Hq // Hs), h // (Hq // Hkv), int(cache.offs[h // (Hq // Hs)])
+            n = int((np.arange(used[hs]) * 5 <= T - w).sum())
+            keys = torch.cat([cache.Kg[s, o:o + n], cache.ringK[s, kvh]]).double()
+            vals = torch.cat([cache.Vg[s, o:o + n], cache.ringV[s, kvh]]).double()
+            ref = torch.softmax((keys @ q[s, h].double()) / d ** 0.5, 0) @ vals
+            assert (O[s, h].double() - ref).abs().max().item() <= H.TOL[dtype], (s, h)
+
+
 CALIB_EDGES = [
     ("lowrank", 3, 1, 64, 129, "bf16", 16, 4, 74),     # one row into the second block of 128; three heads per group
     ("lowrank", 2, 2, 128, 33, "f32", 16, 3, 75),      # one row into the second streamed tile of 32
