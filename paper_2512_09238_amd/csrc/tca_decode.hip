@@ -256,19 +256,15 @@ __device__ __forceinline__ void merge_partials(float (&m)[NQ], float (&l)[NQ], f
 // kPartWaves * 16 * NQ * (D/16 + 2) floats.  Called by a whole workgroup.
 // T: type of the queries; KV: storage type of the rows (T itself, or fp8_t with one float scale per
 // row in kscale / vscale, indexed like the rows).
-template <typename T, typename KV, int D, int NQ>
+template <typename T, typename KV, int D, int NQ, typename Visible>
 __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const KV* __restrict__ vbase,
                                              const float* __restrict__ kscale, const float* __restrict__ vscale,
-                                             int r_begin, int r_end, const T* __restrict__ q0, double scale,
+                                             int r_begin, int r_cap, Visible visible, const T* __restrict__ q0, double scale,
                                              float* __restrict__ out, size_t out_head, float* red) {
   constexpr int EL = D / 16;
   const int tid = threadIdx.x;
   const int grp = tid >> 4, sub = tid & 15;           // groups of 16 lanes
-  if (r_begin >= r_end) {
-    if (tid < NQ) { out[tid * out_head] = -INFINITY; out[tid * out_head + 1] = 0.f; }
-    return;
-  }
-
+  int r_end = r_cap;                                  // until the first rows are requested
   // logits are carried in base-2 units (scale * log2 e) so that the exponential is one v_exp_f32.
   // bf16 storage: q.k over a lane's slice is EL/2 two-element bf16 dot products with fp32
   // accumulation straight from the loaded words, and the factor is applied to the row's sum.
@@ -326,6 +322,13 @@ __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const
     }
   };
   fetch(r_begin, kr, vr, ksc, vsc, ok);
+  r_end = visible();
+  if (r_begin >= r_end) {
+    if (tid < NQ) { out[tid * out_head] = -INFINITY; out[tid * out_head + 1] = 0.f; }
+    return;
+  }
+#pragma unroll
+  for (int u = 0; u < kUnr; ++u) ok[u] = r_begin + u * (kPartThreads / 16) + grp < r_end;
   for (int r0 = r_begin; r0 < r_end; r0 += (kPartThreads / 16) * kUnr) {
     Raw kn[kUnr], vn[kUnr];
     float ksn[kUnr], vsn[kUnr];
@@ -395,9 +398,9 @@ constexpr int kMfmaTileBytes = 16 * 256 + 16 * 8 * 4;
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 dec_bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float dec_f32x4_t;
 
-template <int NQ>
+template <int NQ, typename Visible>
 __device__ __forceinline__ void partial_rows_mfma(const bf16_t* __restrict__ kbase, const bf16_t* __restrict__ vbase,
-                                                  int r_begin, int r_end, const bf16_t* __restrict__ q0, double scale,
+                                                  int r_begin, int r_cap, Visible visible, const bf16_t* __restrict__ q0, double scale,
                                                   float* __restrict__ out, size_t out_head, float* red,
                                                   unsigned char* tiles) {
   constexpr int D = 128, EL = 8;
@@ -405,10 +408,7 @@ __device__ __forceinline__ void partial_rows_mfma(const bf16_t* __restrict__ kba
   constexpr float kSlack = 8.f;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int kb = lane >> 4, n = lane & 15;            // group inside the wave; lane inside the group
-  if (r_begin >= r_end) {
-    if (tid < NQ) { out[tid * out_head] = -INFINITY; out[tid * out_head + 1] = 0.f; }
-    return;
-  }
+  int r_end = r_cap;                                  // until the first rows are requested
   unsigned char* kt = tiles + wv * kMfmaTileBytes;    // [16 rows][16 chunks of 16 B], chunk index xor row
   float* pt = reinterpret_cast<float*>(kt + 16 * 256); // [16 rows][8 queries]: scores, then terms p
   const bool holder = n < NQ;                         // this lane owns the scores of query n
@@ -456,6 +456,13 @@ __device__ __forceinline__ void partial_rows_mfma(const bf16_t* __restrict__ kba
   };
   fetch_k(r_begin);
   fetch_v(r_begin);
+  r_end = visible();
+  if (r_begin >= r_end) {
+    if (tid < NQ) { out[tid * out_head] = -INFINITY; out[tid * out_head + 1] = 0.f; }
+    return;
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) okk[u] = okv[u] = r_begin + 16 * wv + 4 * kb + u < r_end;
   for (int r0 = r_begin; r0 < r_end; r0 += 16 * kPartWaves) {
     // this iteration's K rows into the tile, the next ones requested
 #pragma unroll
@@ -600,16 +607,17 @@ __global__ __launch_bounds__(kPartThreads, sizeof(KV) == 1 && D == 128 && GW == 
     const size_t base = (size_t)s * c.cap_rows + dh.offs[hs];
     int len = rows(hs) - r_begin;
     if (len > dh.chunk) len = dh.chunk;
-    const int r_end = r_begin + (len > 0 ? count_le_wave(c.idx + base + r_begin, len, Tpos - w) : 0);
+    // the rows that have left the window: looked up while the first ones are on their way
+    auto visible = [&] { return r_begin + (len > 0 ? count_le_wave(c.idx + base + r_begin, len, Tpos - w) : 0); };
     float* out = seq_part + ((size_t)GQ * u0 + slot) * (D + 2);              // query g: + g * ns * (D+2)
     const size_t out_head = (size_t)ns * (D + 2);
     const T* q0 = q + ((size_t)s * Hq + hs * GQ) * D;
     if constexpr (kMfma && GQ > 1)
-      partial_rows_mfma<GQ>((const T*)c.Kg + base * D, (const T*)c.Vg + base * D, r_begin, r_end, q0, scale, out,
+      partial_rows_mfma<GQ>((const T*)c.Kg + base * D, (const T*)c.Vg + base * D, r_begin, r_begin + len, visible, q0, scale, out,
                             out_head, red, tiles);
     else
       partial_rows<T, KV, D, GQ>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base,
-                                 c.Vg_scale + base, r_begin, r_end, q0, scale, out, out_head, red);
+                                 c.Vg_scale + base, r_begin, r_begin + len, visible, q0, scale, out, out_head, red);
   } else {
     const int kvh = id / dh.ring_units, slot = id - kvh * dh.ring_units, h0 = kvh * GW;
     const int r_begin = slot * dh.chunk;
@@ -618,6 +626,7 @@ __global__ __launch_bounds__(kPartThreads, sizeof(KV) == 1 && D == 128 && GW == 
     // Tpos >= w every slot is filled; before that only slots 0 .. Tpos are.
     const int filled = Tpos >= w ? w : (int)Tpos + 1;
     const int r_end = min(filled, r_begin + dh.chunk);
+    auto visible = [&] { return r_end; };
     const int newest = (int)(Tpos % w);
     if (newest >= r_begin && newest < r_begin + dh.chunk)
       store_new_row<T, KV, D>(c, base + newest, k_new + ((size_t)s * Hkv + kvh) * D, v_new + ((size_t)s * Hkv + kvh) * D);
@@ -625,11 +634,11 @@ __global__ __launch_bounds__(kPartThreads, sizeof(KV) == 1 && D == 128 && GW == 
     const size_t out_head = (size_t)dh.ring_units * (D + 2);
     const T* q0 = q + ((size_t)s * Hq + h0) * D;
     if constexpr (kMfma && GW > 1)
-      partial_rows_mfma<GW>((const T*)c.ringK + base * D, (const T*)c.ringV + base * D, r_begin, r_end, q0, scale,
+      partial_rows_mfma<GW>((const T*)c.ringK + base * D, (const T*)c.ringV + base * D, r_begin, r_end, visible, q0, scale,
                             out, out_head, red, tiles);
     else
       partial_rows<T, KV, D, GW>((const KV*)c.ringK + base * D, (const KV*)c.ringV + base * D, c.ringK_scale + base,
-                                 c.ringV_scale + base, r_begin, r_end, q0, scale, out, out_head, red);
+                                 c.ringV_scale + base, r_begin, r_end, visible, q0, scale, out, out_head, red);
   }
 }
 
