@@ -245,29 +245,33 @@ void qkv_mfma_kernel(const uint16_t* __restrict__ W, const uint16_t* __restrict_
 
 // ---- calls of few rows (a decoding batch): bound by one pass over the weights
 //
-// One workgroup of eight waves forms FB * 16 features x TB * 16 tokens with v_mfma_f32_16x16x32_bf16.  The
-// waves split the hidden dimension in units of 64 elements (one 128-byte line of a weight row each),
-// interleaved, and load their fragments straight from global memory: nothing is reused inside a workgroup
-// that would pay for a stage in LDS, and a wave has U units of loads in flight at once, which is what keeps
-// HBM busy.  A lane's chunks of a unit are kb and kb + 4 (kb = lane / 16): the order of the hidden index
+// One workgroup of sixteen waves forms nf features (FB blocks of 16, the last of them not always full) x TB * 16
+// tokens with v_mfma_f32_16x16x32_bf16.  The waves split the hidden dimension in units of 64 elements (one 128-byte
+// line of a weight row each), interleaved, and load their fragments straight from global memory: nothing is reused
+// inside a workgroup that would pay for a stage in LDS, and a wave has U units of loads in flight at once, which is
+// what keeps HBM busy.  A lane's chunks of a unit are kb and kb + 4 (kb = lane / 16): the order of the hidden index
 // inside a unit does not matter as long as W and X agree.  The waves' fp32 sums are added through LDS in
 // wave order.
+// Every workgroup reads the whole of X, and one CU takes in weights only so fast: the features are dealt out so that
+// every CU has one workgroup (nf: see launch_skinny).  Sixteen waves with U units instead of eight with four or two
+// make no difference up to 32 features a workgroup and 5 % at 40; eight units in flight, non-temporal loads of W
+// (14.1 against 12.2 us at 16 rows) or another first unit per workgroup gain nothing.
 template <int FB, int TB, int U>
-__global__ __launch_bounds__(512) void qkv_skinny_kernel(const uint16_t* __restrict__ W, const uint16_t* __restrict__ X,
-                                                         const uint16_t* __restrict__ bias, int64_t n_tok, int hidden,
-                                                         int d, QkvOut out) {
+__global__ __launch_bounds__(1024) void qkv_skinny_kernel(const uint16_t* __restrict__ W, const uint16_t* __restrict__ X,
+                                                          const uint16_t* __restrict__ bias, int n_feat, int nf, int64_t n_tok,
+                                                          int hidden, int d, QkvOut out) {
   typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
-  constexpr int NW = 8;
+  constexpr int NW = 16;
   __shared__ __attribute__((aligned(16))) f32x4_t red[NW][FB * TB][64];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, kb = lane >> 4;
-  const int f0 = blockIdx.x * (FB * 16);           // n_feat is a multiple of 64
+  const int f0 = blockIdx.x * nf, mine = min(nf, n_feat - f0);       // multiples of 4
   const int64_t t0 = (int64_t)blockIdx.y * (TB * 16);
   const uint16_t* wp[FB];
   const uint16_t* xp[TB];
 #pragma unroll
-  for (int fb = 0; fb < FB; ++fb) wp[fb] = W + (size_t)(f0 + fb * 16 + r) * hidden + kb * 8;
+  for (int fb = 0; fb < FB; ++fb) wp[fb] = W + (size_t)(f0 + min(fb * 16 + r, mine - 1)) * hidden + kb * 8;     // (as the tokens' below)
 #pragma unroll
   for (int tb = 0; tb < TB; ++tb) {
     const int64_t t = t0 + tb * 16 + r;
@@ -279,7 +283,7 @@ __global__ __launch_bounds__(512) void qkv_skinny_kernel(const uint16_t* __restr
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) acc[fb][tb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int nu = hidden >> 6;
-  auto units = [&](int u0, auto n_tag) {           // units u0, u0 + 8, .. (N of them), all inside the hidden dimension
+  auto units = [&](int u0, auto n_tag) {           // units u0, u0 + NW, .. (N of them), all inside the hidden dimension
     constexpr int N = decltype(n_tag)::value;
     bf16x8_t w[N][2][FB], x[N][2][TB];
 #pragma unroll
@@ -312,14 +316,14 @@ __global__ __launch_bounds__(512) void qkv_skinny_kernel(const uint16_t* __restr
     for (int tb = 0; tb < TB; ++tb) red[wv][fb * TB + tb][lane] = acc[fb][tb];
   __syncthreads();
   // lane (token r, kb) of a block holds the features 4 kb .. 4 kb + 3 of one token
-  for (int g = tid; g < FB * TB * 64; g += 512) {
+  for (int g = tid; g < FB * TB * 64; g += NW * 64) {
     const int blk = g >> 6, ln = g & 63;
     f32x4_t s = red[0][blk][ln];
 #pragma unroll
     for (int x = 1; x < NW; ++x) s += red[x][blk][ln];
     const int f = f0 + (blk / TB) * 16 + 4 * (ln >> 4);
     const int64_t t = t0 + (blk % TB) * 16 + (ln & 15);
-    if (t >= n_tok) continue;
+    if (t >= n_tok || f - f0 >= mine) continue;
     const int hg = f / d, e0 = f - hg * d, p = part_of_head(out, hg);
     uint16_t* const row = (uint16_t*)out.base[p] + (int64_t)(hg - out.first_head[p]) * out.head_stride[p] + t * out.token_stride[p] + e0;
     bf16x4_t pk;
@@ -448,10 +452,23 @@ struct QkvCall {
   hipStream_t st;
 };
 
-template <int FB, int TB, int U>
+template <int FB, int TB>
+void launch_skinny(const QkvCall& c, int nf) {
+  constexpr int U = 4 / (FB * TB) > 1 ? 4 / (FB * TB) : 1;
+  const dim3 grid((unsigned)((c.n_feat + nf - 1) / nf), (unsigned)((c.n_tok + 16 * TB - 1) / (16 * TB)));
+  hipLaunchKernelGGL((qkv_skinny_kernel<FB, TB, U>), grid, dim3(1024), 0, c.st, c.W, c.X, c.bias, c.n_feat, nf, c.n_tok, c.hidden,
+                     c.d, c.out);
+}
+
+template <int TB>
 void launch_skinny(const QkvCall& c) {
-  const dim3 grid((unsigned)(c.n_feat / (16 * FB)), (unsigned)((c.n_tok + 16 * TB - 1) / (16 * TB)));      // n_feat is a multiple of 64
-  hipLaunchKernelGGL((qkv_skinny_kernel<FB, TB, U>), grid, dim3(512), 0, c.st, c.W, c.X, c.bias, c.n_tok, c.hidden, c.d, c.out);
+  // Features per workgroup: as many as give each CU one (the same number of) workgroups, in fours (a store) and 16 at least.
+  const int rounds = (c.n_feat + 64 * kCUs - 1) / (64 * kCUs), share = (c.n_feat + rounds * kCUs - 1) / (rounds * kCUs);
+  const int nf = share <= 16 ? 16 : (share + 3) / 4 * 4;
+  if (nf <= 16) launch_skinny<1, TB>(c, nf);
+  else if (nf <= 32) launch_skinny<2, TB>(c, nf);
+  else if (nf <= 48) launch_skinny<3, TB>(c, nf);
+  else launch_skinny<4, TB>(c, nf);
 }
 
 template <int FBW, int TBW, int NWF, int NWT, int NST>
@@ -521,14 +538,13 @@ extern "C" int tca_qkv_project(const tca_params* prm, const void* X, int64_t n_t
       return fail(TCA_ERR_INVALID, "tca_qkv_project (bf16): strides must be multiples of 4 elements, outputs 8-byte and inputs 16-byte aligned");
     const QkvCall call{(const uint16_t*)W, (const uint16_t*)X, (const uint16_t*)bias, n_feat, n_tokens, hidden, d, out, st};
     // Up to 32 rows one pass over the weights is all there is to do.  Measured at 6144 features, hidden 4096 (50 MB of
-    // weights): 16 rows 208 -> 15.6 us, 32 rows 196 -> 18.1 us (tiles of 256 x 256 before); 10240 features, hidden
-    // 8192: 16 rows 806 -> 44 us.  Four feature blocks per workgroup instead of two halve the reads of X and pay
-    // once two would make more workgroups than CUs (44 against 52 us there; 21.7 against 15.8 us at 6144).
-    const bool wide = n_feat / 32 > kCUs;
+    // weights), with 256 x 256 tiles / 32 features per workgroup / an equal share of 24 per CU: 1 row 196 / 13.8 / 10.5 us,
+    // 16 rows 208 / 15.8 / 12.2, 30 rows 196 / 18.1 / 15.4; 10240 features, hidden 8192 (168 MB), 64 / 40 per workgroup:
+    // 1 row 40.7 / 32.3, 16 rows 44.5 / 32.1, 30 rows 51.9 / 38.8.
     if (n_tokens <= 16) {
-      if (wide) launch_skinny<4, 1, 4>(call); else launch_skinny<2, 1, 4>(call);
+      launch_skinny<1>(call);
     } else if (n_tokens <= 32) {
-      if (wide) launch_skinny<4, 2, 2>(call); else launch_skinny<2, 2, 4>(call);
+      launch_skinny<2>(call);
     } else {
       // Tiles.  What a workgroup waits for is the passage of its stages from L2 into LDS, about 24 bytes per clock and
       // CU whatever the shape and however many stages are resident: a call takes (rounds of 256 workgroups) x

@@ -212,7 +212,7 @@ def test_qkv_project_random_shapes(tb, bufs, case):
 
 QKV_SHAPES = [
     # every kernel and tile shape the bf16 call chooses between (by rows, and features times rows), at its edges
-    (4, 2, 128, 4160, 16, "bf16", True, "token", 2),      # up to 16 rows: 65 units over 8 waves, batches of four and a rest
+    (4, 2, 128, 4160, 16, "bf16", True, "token", 2),      # up to 16 rows: 65 units over 16 waves, batches of four and a rest
     (64, 8, 128, 320, 7, "bf16", True, "token", 0),       # the same, more than 8192 features
     (4, 2, 128, 576, 32, "bf16", False, "token", 0),      # 17 to 32 rows
     (64, 8, 128, 64, 17, "bf16", True, "head", 1),
@@ -222,6 +222,16 @@ QKV_SHAPES = [
     (32, 8, 128, 320, 724, "bf16", False, "head", 0),     # 128 x 256
     (32, 8, 128, 64, 3000, "bf16", True, "head", 0),      # 128 x 256, three groups of token tiles
     (32, 8, 128, 256, 1500, "bf16", True, "head", 0),     # 256 x 256, a group of two token tiles behind one of four
+]
+
+
+QKV_SHAPES += [
+    # up to 32 rows, by the features that fall to a workgroup
+    (56, 8, 64, 1088, 16, "bf16", True, "token", 0),      # 20 of 4608: four in the second block, eight in the last workgroup
+    (32, 8, 128, 2112, 1, "bf16", True, "head", 1),       # 24, one row, 33 units over 16 waves, two in flight
+    (64, 8, 128, 1024, 32, "bf16", False, "token", 0),    # 40, three blocks
+    (96, 12, 128, 128, 19, "bf16", True, "token", 0),     # 60, four blocks
+    (128, 16, 128, 192, 5, "bf16", True, "token", 0),     # 40 in two rounds
 ]
 
 
