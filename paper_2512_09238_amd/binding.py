@@ -58,47 +58,50 @@ class tca_cache(C.Structure):
 
 _P = C.POINTER
 _dbl_p, _i64_p, _i32_p = _P(C.c_double), _P(C.c_int64), _P(C.c_int32)
+# How host arrays are declared below: an address (see _np), which costs half a microsecond less to make than a typed
+# pointer; typed pointers and byref() are taken as well.
+_dbls = _i64s = _i32s = C.c_void_p
 
 EXPORTS = {
     "tca_selection_heads": (C.c_int, [_P(tca_params)]),
     "tca_num_counts": (C.c_int, [C.c_int]),
-    "tca_make_candidates": (C.c_int, [C.c_int, C.c_int, C.c_double, _dbl_p]),
-    "tca_config_from_budget": (C.c_int, [C.c_int, C.c_double, C.c_double, _dbl_p]),
-    "tca_psi_counts": (C.c_int, [C.c_int, C.c_int64, _dbl_p, _i64_p]),
-    "tca_select_rows": (C.c_int64, [_P(tca_params), C.c_int64, _dbl_p, _i64_p]),
-    "tca_decode_budget": (C.c_int, [C.c_int, _dbl_p]),
+    "tca_make_candidates": (C.c_int, [C.c_int, C.c_int, C.c_double, _dbls]),
+    "tca_config_from_budget": (C.c_int, [C.c_int, C.c_double, C.c_double, _dbls]),
+    "tca_psi_counts": (C.c_int, [C.c_int, C.c_int64, _dbls, _i64s]),
+    "tca_select_rows": (C.c_int64, [_P(tca_params), C.c_int64, _dbls, _i64s]),
+    "tca_decode_budget": (C.c_int, [C.c_int, _dbls]),
     "tca_select_workspace_bytes": (C.c_size_t, [_P(tca_params), C.c_int64]),
     "tca_prefill_workspace_bytes": (C.c_size_t, [_P(tca_params), C.c_int64, C.c_int64]),
     "tca_decode_workspace_bytes": (C.c_size_t, [_P(tca_params), C.c_int, C.c_int64]),
     "tca_calibrate_workspace_bytes": (C.c_size_t, [_P(tca_params), C.c_int64, C.c_int]),
     "tca_probe_workspace_bytes": (C.c_size_t, []),
-    "tca_probe_mfma": (C.c_int, [C.c_int, C.c_int, _dbl_p, _dbl_p, C.c_void_p, C.c_size_t, C.c_void_p]),
+    "tca_probe_mfma": (C.c_int, [C.c_int, C.c_int, _dbls, _dbls, C.c_void_p, C.c_size_t, C.c_void_p]),
     "tca_select": (C.c_int, [_P(tca_params), C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_int64,
-                             C.c_int64, _dbl_p, _i64_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
+                             C.c_int64, _dbls, _i64s, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                              C.c_void_p, C.c_size_t, C.c_void_p]),
     "tca_prefill": (C.c_int, [_P(tca_params), C.c_void_p, C.c_int64, C.c_int64, C.c_void_p, C.c_void_p,
-                              C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, _i64_p, C.c_void_p,
+                              C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, _i64s, C.c_void_p,
                               C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
     "tca_prefill_part": (C.c_int, [_P(tca_params), C.c_int, C.c_void_p, C.c_int64, C.c_int64, C.c_void_p, C.c_void_p,
-                                   C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, _i64_p, C.c_void_p,
+                                   C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, _i64s, C.c_void_p,
                                    C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
     "tca_prefill_merge": (C.c_int, [_P(tca_params), C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                                     C.c_void_p, C.c_void_p]),
     "tca_select_prefill_overlapped": (C.c_int, [_P(tca_params), C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
-                                                C.c_int64, C.c_int64, C.c_int64, _dbl_p, _i64_p, C.c_void_p,
+                                                C.c_int64, C.c_int64, C.c_int64, _dbls, _i64s, C.c_void_p,
                                                 C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                                                 C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p, C.c_size_t,
                                                 C.c_void_p, C.c_void_p]),
     "tca_cache_load_window": (C.c_int, [_P(tca_params), _P(tca_cache), C.c_int, C.c_void_p, C.c_void_p,
                                         C.c_int64, C.c_int64, C.c_void_p]),
     "tca_cache_load_global": (C.c_int, [_P(tca_params), _P(tca_cache), C.c_int, C.c_void_p, C.c_void_p, C.c_void_p,
-                                        _i64_p, C.c_void_p, C.c_void_p]),
-    "tca_decode": (C.c_int, [_P(tca_params), _P(tca_cache), _i64_p, C.c_void_p, C.c_void_p, C.c_void_p,
-                             _dbl_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
-    "tca_decode_static": (C.c_int, [_P(tca_params), _P(tca_cache), _i64_p, C.c_void_p, C.c_void_p, C.c_void_p,
-                                    _dbl_p, C.c_void_p, C.c_void_p]),
+                                        _i64s, C.c_void_p, C.c_void_p]),
+    "tca_decode": (C.c_int, [_P(tca_params), _P(tca_cache), _i64s, C.c_void_p, C.c_void_p, C.c_void_p,
+                             _dbls, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
+    "tca_decode_static": (C.c_int, [_P(tca_params), _P(tca_cache), _i64s, C.c_void_p, C.c_void_p, C.c_void_p,
+                                    _dbls, C.c_void_p, C.c_void_p]),
     "tca_calibrate_budgets": (C.c_int, [_P(tca_params), C.c_void_p, C.c_void_p, C.c_int64, C.c_int,
-                                        C.c_double, C.c_double, _dbl_p, _i32_p, _dbl_p, _i64_p, _i32_p,
+                                        C.c_double, C.c_double, _dbls, _i32s, _dbls, _i64s, _i32s,
                                         C.c_void_p, C.c_size_t, C.c_void_p]),
     "tca_diag_prefill_clocks": (None, [C.c_int]),
     "tca_diag_prefill_variant": (C.c_int, [C.c_int]),
@@ -106,7 +109,7 @@ EXPORTS = {
     "tca_diag_prefill_walk": (C.c_int, [_P(tca_params), C.c_void_p, C.c_int64, C.c_int64, C.c_int, C.c_int, C.c_size_t,
                                         C.c_void_p, C.c_void_p]),
     "tca_calibrate_layers": (C.c_int, [_P(tca_params), C.c_int, _P(C.c_void_p), _P(C.c_void_p), C.c_int64, C.c_int,
-                                       C.c_double, C.c_double, _dbl_p, _i32_p, _dbl_p, _i64_p, _i32_p,
+                                       C.c_double, C.c_double, _dbls, _i32s, _dbls, _i64s, _i32s,
                                        C.c_void_p, C.c_size_t, C.c_void_p]),
     "tca_rope": (C.c_int, [_P(tca_params), C.c_void_p, C.c_int, C.c_int64, C.c_int64, C.c_double, C.c_int, C.c_void_p]),
     "tca_qkv_project": (C.c_int, [_P(tca_params), C.c_void_p, C.c_int64, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p,
@@ -133,23 +136,28 @@ def _check(rc: int) -> int:
 
 def _dp(t):
     """Device pointer of a torch tensor (None -> NULL; an int is taken as a device address)."""
-    if t is None:
-        return None
-    if isinstance(t, int):                      # a device address (a row inside a caller's buffer)
-        return C.c_void_p(t)
+    if t is None or isinstance(t, int):         # a device address (a row inside a caller's buffer)
+        return t
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("device arguments must be contiguous CUDA tensors")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _host(a, dtype):
     return np.ascontiguousarray(a, dtype=dtype)
 
 
+def _np(a):
+    """Address of a host array's first element; the caller keeps the array until the call has returned."""
+    return a.__array_interface__["data"][0]
+
+
 def _stream(stream):
+    """The stream handle to launch on: the given one, or torch's current one.  The handle is asked for directly: a
+    torch.cuda.Stream object around it costs 3 us, as much as a launch, on every call of a decoding step."""
     if stream is not None:
-        return C.c_void_p(int(stream))
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return int(stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def make_params(n_q_heads, n_kv_heads, head_dim, block, window, dtype, alpha=0.5, scale=0.0,
@@ -168,33 +176,33 @@ def tca_num_counts(b: int) -> int:
 
 def tca_make_candidates(b: int, M: int, sigma: float) -> np.ndarray:
     out = np.empty((M, tca_num_counts(b)), np.float64)
-    _check(lib.tca_make_candidates(b, M, sigma, out.ctypes.data_as(_dbl_p)))
+    _check(lib.tca_make_candidates(b, M, sigma, _np(out)))
     return out
 
 
 def tca_config_from_budget(b: int, sigma: float, frac: float) -> np.ndarray:
     out = np.empty(tca_num_counts(b), np.float64)
-    _check(lib.tca_config_from_budget(b, sigma, frac, out.ctypes.data_as(_dbl_p)))
+    _check(lib.tca_config_from_budget(b, sigma, frac, _np(out)))
     return out
 
 
 def tca_psi_counts(b: int, m: int, p) -> np.ndarray:
     p = _host(p, np.float64)
     out = np.empty(tca_num_counts(b), np.int64)
-    _check(lib.tca_psi_counts(b, m, p.ctypes.data_as(_dbl_p), out.ctypes.data_as(_i64_p)))
+    _check(lib.tca_psi_counts(b, m, _np(p), _np(out)))
     return out
 
 
 def tca_select_rows(prm: tca_params, n_blocks: int, p):
     p = _host(p, np.float64)
     rows = np.empty(tca_selection_heads(prm), np.int64)
-    total = _check(lib.tca_select_rows(C.byref(prm), n_blocks, p.ctypes.data_as(_dbl_p), rows.ctypes.data_as(_i64_p)))
+    total = _check(lib.tca_select_rows(C.byref(prm), n_blocks, _np(p), _np(rows)))
     return total, rows
 
 
 def tca_decode_budget(b: int, p) -> int:
     p = _host(p, np.float64)
-    return _check(lib.tca_decode_budget(b, p.ctypes.data_as(_dbl_p)))
+    return _check(lib.tca_decode_budget(b, _np(p)))
 
 
 def tca_select_workspace_bytes(prm, n_tokens: int) -> int:
@@ -225,7 +233,7 @@ def tca_select(prm, q_last, K, V, kv_stride, pos0, n_tokens, p, offs, n_rows, id
     offs = _host(offs, np.int64)
     wsp, wsb = _ws_args(ws)
     _check(lib.tca_select(C.byref(prm), _dp(q_last), _dp(K), _dp(V), kv_stride, pos0, n_tokens,
-                          p.ctypes.data_as(_dbl_p), offs.ctypes.data_as(_i64_p), _dp(n_rows), _dp(idx),
+                          _np(p), _np(offs), _dp(n_rows), _dp(idx),
                           _dp(Kg), _dp(Vg), wsp, wsb, _stream(stream)))
 
 
@@ -233,7 +241,7 @@ def tca_prefill(prm, Q, q_pos0, n_queries, K, V, kv_stride, idx, Kg, Vg, offs, n
     offs = _host(offs, np.int64)
     wsp, wsb = _ws_args(ws)
     _check(lib.tca_prefill(C.byref(prm), _dp(Q), q_pos0, n_queries, _dp(K), _dp(V), kv_stride, _dp(idx),
-                           _dp(Kg), _dp(Vg), offs.ctypes.data_as(_i64_p), _dp(n_rows), _dp(O), _dp(lse),
+                           _dp(Kg), _dp(Vg), _np(offs), _dp(n_rows), _dp(O), _dp(lse),
                            wsp, wsb, _stream(stream)))
 
 
@@ -241,7 +249,7 @@ def tca_prefill_part(prm, part, Q, q_pos0, n_queries, K, V, kv_stride, idx, Kg, 
     offs = _host(offs, np.int64)
     wsp, wsb = _ws_args(ws)
     _check(lib.tca_prefill_part(C.byref(prm), part, _dp(Q), q_pos0, n_queries, _dp(K), _dp(V), kv_stride, _dp(idx),
-                                _dp(Kg), _dp(Vg), offs.ctypes.data_as(_i64_p), _dp(n_rows), _dp(O), _dp(lse),
+                                _dp(Kg), _dp(Vg), _np(offs), _dp(n_rows), _dp(O), _dp(lse),
                                 wsp, wsb, _stream(stream)))
 
 
@@ -257,7 +265,7 @@ def tca_select_prefill_overlapped(prm, q_last, Q, K, V, kv_stride, pos0, n_token
     wsp, wsb = _ws_args(ws_select)
     wpp, wpb = _ws_args(ws_prefill)
     _check(lib.tca_select_prefill_overlapped(C.byref(prm), _dp(q_last), _dp(Q), _dp(K), _dp(V), kv_stride, pos0,
-                                             n_tokens, p.ctypes.data_as(_dbl_p), offs.ctypes.data_as(_i64_p),
+                                             n_tokens, _np(p), _np(offs),
                                              _dp(n_rows), _dp(idx), _dp(Kg), _dp(Vg), _dp(O), _dp(O_part),
                                              _dp(lse_parts), wsp, wsb, wpp, wpb, _stream(stream),
                                              C.c_void_p(int(side_stream))))
@@ -279,15 +287,15 @@ def tca_cache_load_window(prm, cache, seq, K, V, kv_stride, L, stream=None):
 def tca_cache_load_global(prm, cache, seq, idx, Kg, Vg, offs, n_rows, stream=None):
     offs = _host(offs, np.int64)
     _check(lib.tca_cache_load_global(C.byref(prm), C.byref(cache), seq, _dp(idx), _dp(Kg), _dp(Vg),
-                                     offs.ctypes.data_as(_i64_p), _dp(n_rows), _stream(stream)))
+                                     _np(offs), _dp(n_rows), _stream(stream)))
 
 
 def tca_decode(prm, cache, offs, q, k_new, v_new, p, O, ws, stream=None):
     p = _host(p, np.float64)
     offs = _host(offs, np.int64)
     wsp, wsb = _ws_args(ws)
-    _check(lib.tca_decode(C.byref(prm), C.byref(cache), offs.ctypes.data_as(_i64_p), _dp(q), _dp(k_new),
-                          _dp(v_new), p.ctypes.data_as(_dbl_p), _dp(O), wsp, wsb, _stream(stream)))
+    _check(lib.tca_decode(C.byref(prm), C.byref(cache), _np(offs), _dp(q), _dp(k_new),
+                          _dp(v_new), _np(p), _dp(O), wsp, wsb, _stream(stream)))
 
 
 TCA_DECODE_STATIC_BYTES = 32 << 20
@@ -296,8 +304,8 @@ TCA_DECODE_STATIC_BYTES = 32 << 20
 def tca_decode_static(prm, cache, offs, q, k_new, v_new, p, O, stream=None):
     p = _host(p, np.float64)
     offs = _host(offs, np.int64)
-    _check(lib.tca_decode_static(C.byref(prm), C.byref(cache), offs.ctypes.data_as(_i64_p), _dp(q), _dp(k_new),
-                                 _dp(v_new), p.ctypes.data_as(_dbl_p), _dp(O), _stream(stream)))
+    _check(lib.tca_decode_static(C.byref(prm), C.byref(cache), _np(offs), _dp(q), _dp(k_new),
+                                 _dp(v_new), _np(p), _dp(O), _stream(stream)))
 
 
 def tca_calibrate_budgets(prm, Qcal, Kcal, L_cal, M, sigma, tau, ws, stream=None):
@@ -310,9 +318,9 @@ def tca_calibrate_budgets(prm, Qcal, Kcal, L_cal, M, sigma, tau, ws, stream=None
     fb = np.empty(Hq, np.int32)
     wsp, wsb = _ws_args(ws)
     _check(lib.tca_calibrate_budgets(C.byref(prm), _dp(Qcal), _dp(Kcal), L_cal, M, sigma, tau,
-                                     p_star.ctypes.data_as(_dbl_p), cand.ctypes.data_as(_i32_p),
-                                     a.ctypes.data_as(_dbl_p), n.ctypes.data_as(_i64_p),
-                                     fb.ctypes.data_as(_i32_p), wsp, wsb, _stream(stream)))
+                                     _np(p_star), _np(cand),
+                                     _np(a), _np(n),
+                                     _np(fb), wsp, wsb, _stream(stream)))
     return {"p_star": p_star, "cand_idx": cand, "a": a, "n": n, "fallback": fb}
 
 
@@ -329,8 +337,8 @@ def tca_calibrate_layers(prm, Qcals, Kcals, L_cal, M, sigma, tau, ws, stream=Non
     fb = np.empty((nl, Hs), np.int32)
     wsp, wsb = _ws_args(ws)
     _check(lib.tca_calibrate_layers(C.byref(prm), nl, qp, kp, L_cal, M, sigma, tau,
-                                    p_star.ctypes.data_as(_dbl_p), cand.ctypes.data_as(_i32_p),
-                                    a.ctypes.data_as(_dbl_p), n.ctypes.data_as(_i64_p), fb.ctypes.data_as(_i32_p),
+                                    _np(p_star), _np(cand),
+                                    _np(a), _np(n), _np(fb),
                                     wsp, wsb, _stream(stream)))
     return {"p_star": p_star, "cand_idx": cand, "a": a, "n": n, "fallback": fb}
 
@@ -372,8 +380,8 @@ def tca_diag_prefill_xcd_plan(prm, offs, q_pos0: int, n_queries: int, part: int 
     """Returns (start[9], workgroups): the ranges of the (head, query tile) sequence the eight XCDs take."""
     offs = np.ascontiguousarray(offs, dtype=np.int64)
     start = np.zeros(9, dtype=np.int32)
-    n = lib.tca_diag_prefill_xcd_plan(C.byref(prm), offs.ctypes.data_as(C.c_void_p), q_pos0, n_queries, part,
-                                      int(bool(gather_free)), start.ctypes.data_as(C.c_void_p))
+    n = lib.tca_diag_prefill_xcd_plan(C.byref(prm), _np(offs), q_pos0, n_queries, part,
+                                      int(bool(gather_free)), _np(start))
     if n < 0:
         raise ValueError("tca_diag_prefill_xcd_plan: not a bf16 call with a head count that is a multiple of 8")
     return start, int(n)
@@ -385,8 +393,8 @@ def tca_diag_prefill_walk(prm, offs, q_pos0: int, n_queries: int, ws_bytes: int,
     offs = np.ascontiguousarray(offs, dtype=np.int64)
     heads = np.zeros(prm.n_q_heads, dtype=np.int32)
     chunks = C.c_int64(-1)
-    order = lib.tca_diag_prefill_walk(C.byref(prm), offs.ctypes.data_as(C.c_void_p), q_pos0, n_queries, part,
-                                      int(bool(gather_free)), ws_bytes, heads.ctypes.data_as(C.c_void_p), C.byref(chunks))
+    order = lib.tca_diag_prefill_walk(C.byref(prm), _np(offs), q_pos0, n_queries, part,
+                                      int(bool(gather_free)), ws_bytes, _np(heads), C.byref(chunks))
     if order < 0 and chunks.value < 0:
         raise ValueError("tca_diag_prefill_walk: not a bf16 call, or invalid sizes")
     return int(order), heads, int(chunks.value)
