@@ -17,15 +17,18 @@
 //                  keys of ONE query per 32-key sub-tile: the softmax max/sum are
 //                  in-register reductions plus one exchange between the two halves.
 //   O^T = V^T P^T: B = P^T taken straight from the C registers of S^T (registers
-//                  8g..8g+7 -> one bf16x8), A = V^T (d = c, the same 8 keys).  V^T
-//                  tiles are produced once per call by a transposing pre-pass into
-//                  the workspace, with the 64 keys of a tile stored in the order
-//                  the C registers hold them, so the A operand is one 16-byte LDS read.
+//                  8g..8g+7 -> one bf16x8), A = V^T (d = c, the same 8 keys: 4 hh .. 4 hh + 3 and
+//                  the four 8 further on).  Four waves: V lies in LDS as it does in memory, a row per
+//                  key, and ds_read_b64_tr_b16 transposes on the way out: 16 lanes address 4 keys x 16
+//                  columns, and lane i receives column i of the four keys, half an operand.  Eight waves:
+//                  V^T tiles are produced once per call by a transposing pre-pass into the workspace, the 64
+//                  keys of a tile in the order the C registers hold them, so that the operand is one
+//                  16-byte LDS read (uses_transposed_v).
 //   O^T accumulators: C[d = 32*s + 8*(r/4)+4*hh+r%4][query = c]: every register of
 //                  a lane belongs to the same query, so rescaling is a per-lane scalar.
 //
-// LDS holds a ring of K tiles [64][D] and a ring of V^T tiles [D][64] (two tiles each; three
-// in the two-blocks-per-wave shape) with XOR-swizzled 16-byte chunks (conflict-free b128
+// LDS holds a ring of K tiles [64][D] and a ring of V ([64][D]) or V^T ([D][64]) tiles (two tiles each; three
+// in the two-blocks-per-wave shape) with XOR-swizzled 16-byte chunks (conflict-free
 // reads without padding), filled by direct global -> LDS loads.  The loop is
 // software-pipelined by one tile (see the kernel); one barrier per tile.
 //
@@ -64,6 +67,13 @@ struct PrefillHeads {
 
 struct NoSplit {};
 
+// Where the V^T operand comes from.  The transposing reads take twice the instructions of plain ones, and the eight-wave
+// step, whose order is pinned to the instruction, pays for them: 3.7 % more cycles, 72.7 -> 73.7 ms at 128K tokens with
+// the pre-pass (0.31 ms) already taken off, 16.20 -> 16.15 for 8192 tokens behind 112K (64 heads), 550 -> 546 us at 5446
+// tokens.  The four-wave shapes take the calls of few query tiles, which read a tile a few times: there the pre-pass is a
+// launch and two passes over V for nothing (413 tokens behind 64K: 231 -> 193 us, 41 of them the pre-pass).
+constexpr bool uses_transposed_v(int nw) { return nw == 8; }
+
 // position p (0..63) inside a stored V^T tile -> key (0..63) of the tile
 __host__ __device__ inline int vt_key_of_pos(int p) {
   const int sub = p >> 5, q = p & 31;
@@ -89,10 +99,9 @@ __global__ __launch_bounds__(256) void transpose_tiles_kernel(
     const uint16_t* __restrict__ Vg, const uint16_t* __restrict__ V, int64_t kv_stride, const int32_t* __restrict__ n_rows,
     const int32_t* __restrict__ gather_idx, int sel_per_kv, int Hs, int region_tiles, int tiles, int tiles_per_group,
     int64_t first_row, int64_t valid_all, uint16_t* __restrict__ region_dst, uint16_t* __restrict__ dense_dst,
-    PrefillHeads ph, unsigned long long* clk) {
+    PrefillHeads ph) {
   constexpr int TPT = D;                           // threads per tile: 8 chunks of keys x D / 8 chunks of columns
   const int tid = threadIdx.x;
-  if (clk && blockIdx.x == 0 && tid < 4) clk[tid] = 0;       // the attention kernel that follows accumulates here
   const int t = __builtin_amdgcn_readfirstlane(blockIdx.x * (256 / TPT) + tid / TPT);      // uniform: a wave has one tile
   if (t >= tiles) return;
   const int in = tid % TPT;
@@ -150,6 +159,9 @@ __global__ __launch_bounds__(256) void transpose_tiles_kernel(
     *reinterpret_cast<uint4*>(o + kBN) = hi;
   }
 }
+
+// The cycle counters of a call (diagnostics only), cleared in front of the kernel that adds to them.
+__global__ void clear_clocks_kernel(unsigned long long* clk) { clk[threadIdx.x] = 0; }
 
 // ------------------------------------------------------------- main kernel --
 __device__ __forceinline__ int64_t i64min(int64_t a, int64_t b) { return a < b ? a : b; }
@@ -222,12 +234,15 @@ __device__ __forceinline__ float half_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// LDS byte offset of 16-byte chunk `ch` of K row r / V^T row dd (XOR swizzle, no padding)
-template <int D> __device__ __forceinline__ int k_off(int r, int ch) {
-  const int swz = (D / 8 == 16) ? (r & 15) : ((r >> 1) & 7);
-  return r * (D * 2) + ((ch ^ swz) << 4);
-}
-__device__ __forceinline__ int v_off(int dd, int ch) { return dd * (kBN * 2) + ((ch ^ ((dd >> 1) & 7)) << 4); }
+// XOR swizzle of a row's 16-byte chunks.  K, V^T: the 32 lanes of a half read one chunk column of 32 rows.  V: a half of a
+// transposing read takes 64 bytes, four chunks, of rows 0 .. 3 or 4 .. 7, which fill the 64 banks once if the four chunks
+// move together by the row (by two at a time, so that eight rows of 32 bytes fill them, every read took twice as long:
+// SQ_LDS_BANK_CONFLICT).
+template <int D> __device__ __forceinline__ int k_swz(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
+template <int D> __device__ __forceinline__ int v_swz(int r) { return D == 128 ? (r & 3) << 2 : ((r >> 1) & 1) << 2; }
+// LDS byte offset of 16-byte chunk `ch` of K row r, of V^T row dd
+template <int D> __device__ __forceinline__ int k_off(int r, int ch) { return r * (D * 2) + ((ch ^ k_swz<D>(r)) << 4); }
+__device__ __forceinline__ int vt_off(int dd, int ch) { return dd * (kBN * 2) + ((ch ^ ((dd >> 1) & 7)) << 4); }
 
 // Tile copies go global -> LDS directly (buffer loads with the LDS modifier: no
 // staging registers, no ds_write).  Every lane of a wave-load deposits 16 bytes at
@@ -235,24 +250,34 @@ __device__ __forceinline__ int v_off(int dd, int ch) { return dd * (kBN * 2) + (
 // fetches the global chunk the XOR swizzle assigns to p: a per-lane byte offset
 // inside the tile that never changes.  The tile itself is selected by the scalar
 // offset of the load, and rows past the end of a buffer read as zero (range check of
-// the buffer descriptor), so a copy costs no vector ALU work at all.  A K tile is CPR
-// wave-loads, a V^T tile D/8; each wave issues its share one load at a time, spread
+// the buffer descriptor), so a copy costs no vector ALU work at all.  A K or V tile is
+// CPR wave-loads; each wave issues its share one load at a time, spread
 // between the MFMAs instead of queueing up behind the barrier.
+// Four keys of this lane's column (see vfa).  Without the __restrict__ the compiler takes the read for one that may meet
+// the tile copies in flight and waits for them first, in the middle of every step (128K tokens: 7 % more cycles).
+__device__ __forceinline__ bf16x4_t read_transposed(const unsigned char* __restrict__ lds_src) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4_t*)lds_src);
+}
+
 template <int D, int NW>
 struct TileCopy {
   static constexpr int CPR = D / 8;
   static constexpr int NK = CPR / NW;               // K wave-loads per wave
-  static constexpr int NV = D / 8 / NW;             // V^T wave-loads per wave
+  static constexpr int NV = CPR / NW;               // V wave-loads per wave
   static constexpr int N = NK + NV;
   static_assert(NK >= 1 && NV >= 1 && N <= D / 16, "too many or too few waves for this tile");
   // byte offset inside a K tile of the chunk this lane fetches in wave-load q
   static __device__ __forceinline__ int k_lane_offset(int q, int lane) {
     const int cid = q * 64 + lane;                  // 16-byte chunk of the LDS tile this lane fills
     const int r = cid / CPR, pch = cid % CPR;
-    const int swz = (CPR == 16) ? (r & 15) : ((r >> 1) & 7);
-    return (r * D + (pch ^ swz) * 8) * 2;
+    return (r * D + (pch ^ k_swz<D>(r)) * 8) * 2;
   }
   static __device__ __forceinline__ int v_lane_offset(int q, int lane) {
+    const int cid = q * 64 + lane;
+    const int r = cid / CPR, pch = cid % CPR;
+    return (r * D + (pch ^ v_swz<D>(r)) * 8) * 2;
+  }
+  static __device__ __forceinline__ int vt_lane_offset(int q, int lane) {
     const int cid = q * 64 + lane;
     const int dd = cid >> 3, pch = cid & 7;
     return (dd * kBN + (pch ^ ((dd >> 1) & 7)) * 8) * 2;
@@ -278,34 +303,38 @@ __device__ __forceinline__ void copy16_to_lds(__amdgpu_buffer_rsrc_t rsrc, int l
 // one block's exponentials, neither depending on the other:
 //   slot A :  S_a(t+1), S_b(t+1)           (MFMA)  |  P_a(t)   from S_a(t)     (VALU)
 //   slot B :  O_a += V(t)^T P_a(t), O_b += V(t)^T P_b(t)  |  P_b(t+1) from S_b(t+1)
-// K(t+RING) and V^T(t+RING-1) are copied global -> LDS during iteration t, into the places
-// of K(t) and V^T(t-1); the rings hold RING = 2 or 3 tiles each; one barrier per iteration.
+// K(t+RING) and V(t+RING-1) are copied global -> LDS during iteration t, into the places
+// of K(t) and V(t-1); the rings hold RING = 2 or 3 tiles each; one barrier per iteration.
 // Positions and byte offsets are 32-bit here: the host checks (q_pos0 + n_queries) * D * 2 < 2^31.
-// GATHER: no compacted K exists; the K rows of a region tile are fetched from the dense K through
-// idx (the position of every row is read one iteration ahead and becomes the lane's offset of the
-// tile copy); the V^T tiles were built through idx by the pre-pass.
+// GATHER: no compacted copy exists; the K and V rows of a region tile are fetched from the dense K and V
+// through idx (the position of every row is read one iteration ahead and becomes the lane's offset of the
+// tile copies: V's tile is the one whose K was copied an iteration before, its positions are still there;
+// V^T tiles were built through idx by the pre-pass).
 // SPLIT: the workgroup walks one chunk of the item's tiles and leaves its accumulators, m and l to the merge.
 template <int D, int NW, int QB, bool GATHER, bool SPLIT = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2 / QB, 2 / QB)))
 void prefill_mfma_kernel(
     const uint16_t* __restrict__ Q, int64_t q_pos0, int64_t n_queries, const uint16_t* __restrict__ K,
-    int64_t kv_stride, const int32_t* __restrict__ idx, const uint16_t* __restrict__ Kg,
-    const int32_t* __restrict__ n_rows, const uint16_t* __restrict__ Vgt, const uint16_t* __restrict__ Vt,
+    const uint16_t* __restrict__ V, int64_t kv_stride, const int32_t* __restrict__ idx,
+    const uint16_t* __restrict__ Kg, const uint16_t* __restrict__ Vg, const int32_t* __restrict__ n_rows,
     int64_t dense_tile0, int dense_tiles, PrefillHeads ph, int Hq, int G, int GS, int w, float scale,
     uint16_t* __restrict__ O, float* __restrict__ lse, unsigned long long* __restrict__ clk, int part,
     std::conditional_t<SPLIT, SplitPlan, NoSplit> sp) {
   // part: TCA_PART_ALL, or one of the two key subsets alone (TCA_PART_WINDOW: the dense window;
   // TCA_PART_GLOBAL: the region), each normalised by itself, to be merged through lse
+  // V, Vg: the rows as the caller has them, or (uses_transposed_v) the pre-pass's tiles: of the dense rows from tile
+  // dense_tile0 on, dense_tiles per KV head, and of the regions
+  constexpr bool VT = uses_transposed_v(NW);
   constexpr int KK = D / 16;             // MFMA k-steps over the head dimension
   constexpr int DS = D / 32;             // 32-row slices of O^T
   constexpr int WQ = QB * 32;            // queries per wave
   constexpr int BM = NW * WQ;            // queries per workgroup
   const unsigned long long clk_c0 = __builtin_readcyclecounter(), clk_r0 = __builtin_amdgcn_s_memrealtime();
   constexpr int KBYTES = kBN * D * 2;    // K tile
-  constexpr int VBYTES = D * kBN * 2;    // V^T tile
+  constexpr int VBYTES = kBN * D * 2;    // V tile
   // Rows are not padded; the 16-byte chunk index is XOR-swizzled with the row so that
   // the b128 reads of 16 consecutive rows at one chunk column fall into distinct banks.
-  // Tiles in flight: rings of two K and two V^T tiles, a copy has one iteration to arrive (with two
+  // Tiles in flight: rings of two K and two V tiles, a copy has one iteration to arrive (with two
   // waves per SIMD a third tile measured no faster); the one-wave-per-SIMD shape, where nothing else
   // covers a late copy, keeps three.
   constexpr int RING = QB == 2 ? 3 : 2;
@@ -463,29 +492,33 @@ void prefill_mfma_kernel(
       (void*)(GATHER ? K : Kg + (size_t)base * D), 0, GATHER ? 0 : nr * (D * 2), kRsrcFlags);   // GATHER: never read
   const __amdgpu_buffer_rsrc_t krs_d = __builtin_amdgcn_make_buffer_rsrc(
       (void*)(K + (size_t)kvh * kv_stride * D), 0, (last_pos + 1) * (D * 2), kRsrcFlags);
+  constexpr bool VGATHER = GATHER && !VT;
   const __amdgpu_buffer_rsrc_t vrs_g = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(Vgt + (size_t)ph.tile_off[hs] * (D * kBN)), 0, n_gt * VBYTES, kRsrcFlags);
+      (void*)(VT ? Vg + (size_t)ph.tile_off[hs] * (D * kBN) : VGATHER ? V : Vg + (size_t)base * D), 0,
+      VT ? n_gt * VBYTES : VGATHER ? 0 : nr * (D * 2), kRsrcFlags);
   const __amdgpu_buffer_rsrc_t vrs_d = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(Vt + (size_t)kvh * dense_tiles * (D * kBN)), 0, dense_tiles * VBYTES, kRsrcFlags);
-  const int vdshift = dshift - (int)dense_tile0;   // tile t >= n_gt is tile t + vdshift of the dense V^T buffer
+      (void*)(V + (VT ? (size_t)kvh * dense_tiles * (D * kBN) : (size_t)kvh * kv_stride * D)), 0,
+      VT ? dense_tiles * VBYTES : (last_pos + 1) * (D * 2), kRsrcFlags);
+  const int vdshift = VT ? dshift - (int)dense_tile0 : dshift;       // tile t >= n_gt is tile t + vdshift of the dense V or V^T buffer
   int klo[Copy::NK], vlo[Copy::NV];                // this lane's byte offsets inside a tile, per wave-load
-  int krow[Copy::NK];                              // the tile row this lane copies a chunk of, per K wave-load
+  int krow[Copy::NK];                              // the tile row this lane copies a chunk of, per wave-load of K or V
 #pragma unroll
   for (int j = 0; j < Copy::NK; ++j) {
     klo[j] = Copy::k_lane_offset(wv * Copy::NK + j, lane);
     krow[j] = ((wv * Copy::NK + j) * 64 + lane) / Copy::CPR;
   }
 #pragma unroll
-  for (int j = 0; j < Copy::NV; ++j) vlo[j] = Copy::v_lane_offset(wv * Copy::NV + j, lane);
-  // One K tile and one V^T tile to copy: descriptors and scalar offsets chosen once, then
-  // load(j) issues wave-load j of the K tile (j < NK) or of the V^T tile (j >= NK)
+  for (int j = 0; j < Copy::NV; ++j)
+    vlo[j] = VT ? Copy::vt_lane_offset(wv * Copy::NV + j, lane) : Copy::v_lane_offset(wv * Copy::NV + j, lane);
+  // One K tile and one V tile to copy: descriptors and scalar offsets chosen once, then
+  // load(j) issues wave-load j of the K tile (j < NK) or of the V tile (j >= NK)
   struct CopyJob {
     __amdgpu_buffer_rsrc_t krs, vrs;
     int koff, voff;
     unsigned char* kdst;
     unsigned char* vdst;
-    bool k_through_idx;              // GATHER: a region tile, its rows fetched from the dense K
-    int kgo[Copy::NK];               // GATHER: this lane's byte offset into the dense K, per wave-load
+    bool k_through_idx, v_through_idx;       // GATHER: a region tile, its rows fetched from the dense K, V
+    int kgo[Copy::NK], vgo[VGATHER ? Copy::NV : 1];  // GATHER: this lane's byte offset into the dense K, V, per wave-load
   };
   // GATHER: positions of the rows this lane copies from region tile t (rows past the region's end get
   // an offset beyond the buffer, which the descriptor's range check turns into zeros)
@@ -499,20 +532,25 @@ void prefill_mfma_kernel(
     }
     return tr;
   };
-  auto copy_job = [&](int tk, int tv, unsigned char* kstage, unsigned char* vstage, const TileRows& rows_k) {
+  auto copy_job = [&](int tk, int tv, unsigned char* kstage, unsigned char* vstage, const TileRows& rows_k,
+                      const TileRows& rows_v) {
     CopyJob j;
     const bool kg = tk < n_gt, vg = tv < n_gt;
     j.krs = (kg && !GATHER) ? krs_g : krs_d;
-    j.vrs = vg ? vrs_g : vrs_d;
+    j.vrs = (vg && !VGATHER) ? vrs_g : vrs_d;
     j.koff = (tk + (kg ? 0 : dshift)) * KBYTES;
     j.voff = (tv + (vg ? 0 : vdshift)) * VBYTES;
     j.kdst = kstage + wv * (Copy::NK * 1024);
     j.vdst = vstage + wv * (Copy::NV * 1024);
     j.k_through_idx = GATHER && kg;
+    j.v_through_idx = VGATHER && vg;
     if constexpr (GATHER) {
+      static_assert(Copy::NK == Copy::NV, "a lane copies the same rows of K and of V");
 #pragma unroll
-      for (int q = 0; q < Copy::NK; ++q)       // the chunk inside the row stays the swizzled one of klo
+      for (int q = 0; q < Copy::NK; ++q) {     // the chunk inside the row stays the swizzled one of klo, vlo
         j.kgo[q] = rows_k.pos[q] >= 0 ? rows_k.pos[q] * (D * 2) + (klo[q] - krow[q] * (D * 2)) : 0x7FFFFFF0;
+        if constexpr (VGATHER) j.vgo[q] = rows_v.pos[q] >= 0 ? rows_v.pos[q] * (D * 2) + (vlo[q] - krow[q] * (D * 2)) : 0x7FFFFFF0;
+      }
     }
     return j;
   };
@@ -521,7 +559,8 @@ void prefill_mfma_kernel(
       if (GATHER && job.k_through_idx) copy16_to_lds(job.krs, job.kgo[j], 0, job.kdst + j * 1024);
       else copy16_to_lds(job.krs, klo[j], job.koff, job.kdst + j * 1024);
     } else {
-      copy16_to_lds(job.vrs, vlo[j - Copy::NK], job.voff, job.vdst + (j - Copy::NK) * 1024);
+      if (VGATHER && job.v_through_idx) copy16_to_lds(job.vrs, job.vgo[j - Copy::NK], 0, job.vdst + (j - Copy::NK) * 1024);
+      else copy16_to_lds(job.vrs, vlo[j - Copy::NK], job.voff, job.vdst + (j - Copy::NK) * 1024);
     }
   };
 
@@ -539,13 +578,20 @@ void prefill_mfma_kernel(
   }
 
   // per-lane LDS byte offsets of the MFMA fragments inside a tile (the rest is compile-time constant):
-  // K fragment (sub, kk) sits at kfa[kk] + sub * 32 rows, V^T fragment (sl, sg) at vfa[sg] + sl * 32 rows;
-  // the swizzles depend on the row only through c
+  // K fragment (sub, kk) sits at kfa[kk] + sub * 32 rows; V^T fragment (sl, sg) at vfa[sg] + sl * 32 rows, or its halves in
+  // V at vfa[sl] + sg * 16 rows and 8 rows behind; the swizzles depend on the row only through c (K, V^T), vr (V)
   int kfa[KK], vfa[4];
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) kfa[kk] = k_off<D>(c, 2 * kk + hh);
+  if constexpr (VT) {
 #pragma unroll
-  for (int sg = 0; sg < 4; ++sg) vfa[sg] = v_off(c, 2 * sg + hh);
+    for (int sg = 0; sg < 4; ++sg) vfa[sg] = vt_off(c, 2 * sg + hh);
+  } else {
+    const int vr = 4 * hh + ((c >> 2) & 3);        // what a lane addresses: 4 columns of a key; what it receives: a column of 4 keys
+#pragma unroll
+    for (int sl = 0; sl < DS; ++sl)
+      vfa[sl] = vr * (D * 2) + (((4 * sl + 2 * (c >> 4) + ((c >> 1) & 1)) ^ v_swz<D>(vr)) << 4) + (c & 1) * 8;
+  }
 
   // S^T = K Q^T for the 64 keys of the tile at kb and every query block of the wave (two 32-key
   // sub-tiles per block = 2 QB accumulation chains that alternate; fragments read kFragAhead
@@ -717,7 +763,7 @@ void prefill_mfma_kernel(
 
   int rpos = 0;                          // it % RING of the step about to run
   float mx_pre = -INFINITY;              // QB = 1: unmasked maximum of the scores the next step starts from
-  TileRows rows_ahead = {};              // GATHER: row positions of tile it + RING, read during step it - 1
+  TileRows rows_ahead = {}, rows_before = {};        // GATHER: row positions of tile it + RING, read during step it - 1, and of it + RING - 1
   static_assert((RING - 2) * Copy::N < 16, "the wait below encodes its count in four bits");
 
   // One pipeline step: tile `it` (scores in sc; with QB = 2 those of block 1 are already in pf[1])
@@ -726,9 +772,9 @@ void prefill_mfma_kernel(
   // stretches of the loop below where no tile needs a mask), which saves the test per step
   auto step = [&](int it, f32x16_t (&sc)[QB][2], f32x16_t (&sn)[QB][2], auto clear_tag) {
     constexpr bool kKnownClear = decltype(clear_tag)::value;
-    // K(it+1) and V^T(it) have landed for this wave (only the copies of the previous step may still
+    // K(it+1) and V(it) have landed for this wave (only the copies of the previous step may still
     // be on their way when the rings hold three tiles); after the barrier for every wave, and every
-    // wave is done reading K(it) and V^T(it-1).  With one block per wave this wait and barrier sit
+    // wave is done reading K(it) and V(it-1).  With one block per wave this wait and barrier sit
     // inside the previous step, before its last P V MFMAs (see there).
     if constexpr (QB != 1) {
       __builtin_amdgcn_s_waitcnt(0x0F70 | ((RING - 2) * Copy::N));     // vmcnt((RING - 2) * N)
@@ -740,10 +786,13 @@ void prefill_mfma_kernel(
     const int r_cur = RING == 2 ? (it & 1) : rpos;
     const int r_next = RING == 2 ? ((it + 1) & 1) : (rpos + 1 == RING ? 0 : rpos + 1);
     const int r_prev = RING == 2 ? r_next : (rpos == 0 ? RING - 1 : rpos - 1);
-    const CopyJob job = copy_job(tk, tv, kring + r_cur * KBYTES, vring + r_prev * VBYTES, rows_ahead);
+    const CopyJob job = copy_job(tk, tv, kring + r_cur * KBYTES, vring + r_prev * VBYTES, rows_ahead, rows_before);
     // GATHER: the positions for the copies of the next step are requested before this step's copies,
     // so that the wait at the top of the next step, which lets only the newest copies pass, covers them
-    if constexpr (GATHER) rows_ahead = load_tile_rows(it + 1 + RING < last ? it + 1 + RING : last);
+    if constexpr (GATHER) {
+      rows_before = rows_ahead;
+      rows_ahead = load_tile_rows(it + 1 + RING < last ? it + 1 + RING : last);
+    }
     const unsigned char* kb = kring + r_next * KBYTES;
     const unsigned char* vb = vring + r_cur * VBYTES;
     if constexpr (RING != 2) rpos = r_next;
@@ -755,7 +804,10 @@ void prefill_mfma_kernel(
       if ((i & 1) && (kk * Copy::N) % KK == 0 && kk * Copy::N / KK < Copy::N) copy_load(job, kk * Copy::N / KK);
     };
     auto vfrag = [&](int j) {
-      return *reinterpret_cast<const bf16x8_t*>(vb + vfa[j / DS] + (j % DS) * (32 * kBN * 2));
+      if constexpr (VT) return *reinterpret_cast<const bf16x8_t*>(vb + vfa[j / DS] + (j % DS) * (32 * kBN * 2));
+      const unsigned char* at = vb + vfa[j % DS] + (j / DS) * (16 * D * 2);
+      const bf16x4_t lo = read_transposed(at), hi = read_transposed(at + 8 * D * 2);
+      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     };
     bf16x8_t vfr[kFragAhead];
     if constexpr (QB == 1) {
@@ -816,11 +868,11 @@ void prefill_mfma_kernel(
     for (int j = 0; j < 4 * DS; ++j) {
       const int sl = j % DS, sg = j / DS;           // sg = sub*2 + g: 16 keys
       if constexpr (QB == 1) {
-        // The barrier of the next step, taken as soon as the last V^T fragment of this tile has been
+        // The barrier of the next step, taken as soon as the last V fragment of this tile has been
         // requested (the reads run kFragAhead ahead): the MFMAs still to come work from registers and
         // cover the first fragment reads of the next tile, which cannot start before the barrier.
         if (j == 4 * DS - kFragAhead) {
-          __builtin_amdgcn_s_waitcnt(0x0F70);          // this wave's copies of K(it+2), V^T(it+1) have landed
+          __builtin_amdgcn_s_waitcnt(0x0F70);          // this wave's copies of K(it+2), V(it+1) have landed
           __syncthreads();
         }
       }
@@ -842,12 +894,14 @@ void prefill_mfma_kernel(
       // one of P V tried: within 1 % of each other).  Pinning the exponentials or the scalar
       // instructions as well measured 8 % slower.
       constexpr int kMfma = 0x008, kValu = 0x002, kDsRead = 0x100, kVmemRead = 0x020;
+      constexpr int kVReads = VT ? 1 : 2;              // of a V^T fragment
       constexpr int VA = 384 / D, VB = 640 / D;        // plain vector ALU instructions behind an MFMA of S, of P V
       __builtin_amdgcn_sched_group_barrier(kDsRead, kFragAhead, 0);
 #pragma unroll
       for (int i = 0; i < 2 * KK; ++i) {
         __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
         __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
+        if (!VT && i >= 2 * KK - kFragAhead) __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
         if ((i & 1) && ((i >> 1) * Copy::N) % KK == 0 && (i >> 1) * Copy::N / KK < Copy::N)
           __builtin_amdgcn_sched_group_barrier(kVmemRead, 1, 0);
         __builtin_amdgcn_sched_group_barrier(kValu, VA, 0);
@@ -855,7 +909,7 @@ void prefill_mfma_kernel(
 #pragma unroll
       for (int j = 0; j < 4 * DS; ++j) {
         __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
-        if (j + kFragAhead < 4 * DS) __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
+        if (j + kFragAhead < 4 * DS) __builtin_amdgcn_sched_group_barrier(kDsRead, kVReads, 0);
         __builtin_amdgcn_sched_group_barrier(kValu, VB, 0);
       }
     }
@@ -871,25 +925,29 @@ void prefill_mfma_kernel(
     }
   };
 
-  // ---- prologue: everything the steps do not copy themselves - K(0) .. K(RING-1), V^T(0) ..
-  // V^T(RING-2) - is requested here, oldest first; S(0) is formed as soon as K(0) is in
+  // ---- prologue: everything the steps do not copy themselves - K(0) .. K(RING-1), V(0) ..
+  // V(RING-2) - is requested here, oldest first; S(0) is formed as soon as K(0) is in
   f32x16_t sa[QB][2], sb[QB][2];
   {
     auto tile_or_last = [&](int t) { return t < last ? t : last; };
-    const CopyJob first = copy_job(t_first, t_first, kring, vring, load_tile_rows(t_first));
+    const TileRows rows_first = load_tile_rows(t_first), rows_second = load_tile_rows(tile_or_last(t_first + 1));
+    const CopyJob first = copy_job(t_first, t_first, kring, vring, rows_first, rows_first);
 #pragma unroll
     for (int j = 0; j < Copy::N; ++j) copy_load(first, j);
-    const CopyJob second = copy_job(tile_or_last(t_first + 1), 0, kring + KBYTES, vring, load_tile_rows(tile_or_last(t_first + 1)));
+    const CopyJob second = copy_job(tile_or_last(t_first + 1), 0, kring + KBYTES, vring, rows_second, rows_first);
 #pragma unroll
     for (int j = 0; j < Copy::NK; ++j) copy_load(second, j);
     if constexpr (RING == 3) {
       const CopyJob third = copy_job(tile_or_last(2), tile_or_last(1), kring + 2 * KBYTES, vring + VBYTES,
-                                     load_tile_rows(tile_or_last(2)));
+                                     load_tile_rows(tile_or_last(2)), rows_second);
 #pragma unroll
       for (int j = 0; j < Copy::N; ++j) copy_load(third, j);
     }
-    if constexpr (GATHER) rows_ahead = load_tile_rows(tile_or_last(t_first + RING));    // for the copies of step 0
-    // K(0), V^T(0) are in (GATHER: the positions just requested count among the newest as well)
+    if constexpr (GATHER) {                        // for the copies of step 0
+      rows_before = rows_second;
+      rows_ahead = load_tile_rows(tile_or_last(t_first + RING));
+    }
+    // K(0), V(0) are in (GATHER: the positions just requested count among the newest as well)
     __builtin_amdgcn_s_waitcnt(0x0F70 | (Copy::NK + (RING - 2) * Copy::N + (GATHER ? Copy::NK : 0)));
     __syncthreads();
     s_tile(kring, sa, [&](int) {});
@@ -1023,7 +1081,7 @@ static MfmaWs carve_mfma_ws(void* ws, const tca_params* prm, int64_t g_tiles, in
   size_t off = 0;
   const size_t tile_bytes = (size_t)prm->head_dim * kBN * 2;
   m.clk = (unsigned long long*)(b + off); off = align_up(off + 4 * sizeof(unsigned long long), 256);
-  m.Vgt = (uint16_t*)(b + off); off = align_up(off + (size_t)g_tiles * tile_bytes, 256);
+  m.Vgt = (uint16_t*)(b + off); off = align_up(off + (size_t)g_tiles * tile_bytes, 256);      // (room a four-wave call leaves alone)
   m.Vt = (uint16_t*)(b + off);  off = align_up(off + (size_t)prm->n_kv_heads * d_tiles * tile_bytes, 256);
   m.need = off;
   m.part = (float*)(b + off);
@@ -1303,33 +1361,16 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
   const int Hq = prm->n_q_heads, Hkv = prm->n_kv_heads, Hs = sel_heads(prm), w = prm->window;
   PrefillHeads ph;
   int32_t run = 0;
-  for (int h = 0; h < Hs; ++h) {
+  for (int h = 0; h <= Hs; ++h) {
     ph.offs[h] = offs[h];
     ph.tile_off[h] = run;
-    const int nt = (int)((offs[h + 1] - offs[h] + kBN - 1) / kBN);
-    run += nt;
+    if (h < Hs) run += (int32_t)((offs[h + 1] - offs[h] + kBN - 1) / kBN);
   }
-  ph.offs[Hs] = offs[Hs];
-  ph.tile_off[Hs] = run;
-  const int64_t win_lo = q_pos0 - w + 1 > 0 ? q_pos0 - w + 1 : 0;
-  const int64_t dt0 = win_lo / kBN, dt1 = (q_pos0 + n_queries - 1) / kBN;
-  const int d_tiles = (int)(dt1 - dt0 + 1);
   MfmaWs mw = mfma_ws(ws, prm, n_queries, offs[Hs]);
-  // cycle counters only when asked for (and not for a part: two parts may run side by side on one workspace,
-  // where the window part touches only the dense V^T tiles and the global part only the regions')
+  // cycle counters only when asked for (and not for a part: two parts may run side by side on one workspace)
   unsigned long long* clk = diag_prefill_clocks() && part == TCA_PART_ALL ? mw.clk : nullptr;
-
-  // gather-free call (no compacted copy of the kept rows): V^T tiles of the regions are built from the
-  // dense V through idx, and the attention kernel fetches the K rows of its region tiles the same way
-  const bool gather = Kg == nullptr;
-  {
-    const int region_tiles = part == TCA_PART_WINDOW ? 0 : run;
-    const int tiles = region_tiles + (part == TCA_PART_GLOBAL ? 0 : d_tiles * Hkv);
-    if (tiles > 0)
-      hipLaunchKernelGGL((transpose_tiles_kernel<D>), dim3((unsigned)((tiles + 256 / D - 1) / (256 / D))), dim3(256), 0, st, Vg, V,
-                         kv_stride, n_rows, gather ? idx : (const int32_t*)nullptr, Hs / Hkv, Hs, region_tiles, tiles, d_tiles,
-                         dt0 * kBN, q_pos0 + n_queries, mw.Vgt, mw.Vt, ph, clk);
-  }
+  if (clk) hipLaunchKernelGGL(clear_clocks_kernel, dim3(1), dim3(4), 0, st, clk);
+  const bool gather = Kg == nullptr;               // no compacted copy of the kept rows
 
   // Shape of a workgroup.  Long calls: eight waves of 32 queries (256 queries, one workgroup per CU,
   // two waves per SIMD).  Calls with few query tiles: four waves of 32 queries
@@ -1345,8 +1386,8 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
       sp.part = mw.part;
       auto launch_split = [&](auto gather_tag) {
         hipLaunchKernelGGL((prefill_mfma_kernel<D, 4, 1, decltype(gather_tag)::value, true>), dim3(8u * sp.run * (unsigned)((n_wg + 8 * sp.run - 1) / (8 * sp.run))),
-                           dim3(256), 0, st, Q, q_pos0, n_queries, K, kv_stride, idx, Kg, n_rows, mw.Vgt, mw.Vt, dt0,
-                           d_tiles, ph, Hq, Hq / Hkv, sel_group(prm), w, (float)logit_scale(prm), O, lse, clk, part, sp);
+                           dim3(256), 0, st, Q, q_pos0, n_queries, K, V, kv_stride, idx, Kg, Vg, n_rows,
+                           0, 0, ph, Hq, Hq / Hkv, sel_group(prm), w, (float)logit_scale(prm), O, lse, clk, part, sp);
       };
       if (gather) launch_split(std::true_type{});
       else launch_split(std::false_type{});
@@ -1360,9 +1401,22 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
     const int n_qt = (int)((n_queries + NW * QB * 32 - 1) / (NW * QB * 32));
     const unsigned n_wg = (Hq & 7) == 0 ? 8u * (unsigned)plan_xcds(ph, prm, offs, q_pos0, n_queries, NW * QB * 32, part, xcd_slots(sh))
                                         : (unsigned)n_qt * Hq;
+    const uint16_t *v = V, *vg = Vg;
+    const int64_t dt0 = (q_pos0 - w + 1 > 0 ? q_pos0 - w + 1 : 0) / kBN;         // the dense tiles any query's window meets
+    const int d_tiles = (int)((q_pos0 + n_queries - 1) / kBN - dt0 + 1);
+    if constexpr (uses_transposed_v(NW)) {
+      const int region_tiles = part == TCA_PART_WINDOW ? 0 : run;
+      const int tiles = region_tiles + (part == TCA_PART_GLOBAL ? 0 : d_tiles * Hkv);
+      if (tiles > 0)
+        hipLaunchKernelGGL((transpose_tiles_kernel<D>), dim3((unsigned)((tiles + 256 / D - 1) / (256 / D))), dim3(256), 0, st, Vg, V,
+                           kv_stride, n_rows, GATHER ? idx : (const int32_t*)nullptr, Hs / Hkv, Hs, region_tiles, tiles, d_tiles,
+                           dt0 * kBN, q_pos0 + n_queries, mw.Vgt, mw.Vt, ph);
+      v = mw.Vt;
+      vg = mw.Vgt;
+    }
     hipLaunchKernelGGL((prefill_mfma_kernel<D, NW, QB, GATHER>), dim3(n_wg), dim3(NW * 64), 0, st, Q,
-                       q_pos0, n_queries, K, kv_stride, idx, Kg, n_rows, mw.Vgt, mw.Vt, dt0, d_tiles, ph, Hq,
-                       Hq / Hkv, sel_group(prm), w, (float)logit_scale(prm), O, lse, clk, part, NoSplit{});
+                       q_pos0, n_queries, K, v, kv_stride, idx, Kg, vg, n_rows, dt0, d_tiles, ph, Hq, Hq / Hkv,
+                       sel_group(prm), w, (float)logit_scale(prm), O, lse, clk, part, NoSplit{});
   };
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2>;

@@ -708,6 +708,57 @@ def test_few_queries_behind_a_long_context(tb, bufs, case):
     assert np.abs(outs[0][0] - outs[1][0]).max() <= 2 * H.TOL["bf16"]
 
 
+V_EDGE_CASES = [
+    # Hq, Hkv, d, queries, rows kept per head, gather-free
+    (8, 2, 128, 1, 1, False),
+    (8, 2, 64, 65, 63, False),
+    (3, 1, 128, 129, 64, False),
+    (3, 1, 64, 200, 65, True),
+    (8, 8, 128, 128, 129, True),
+]
+
+
+@pytest.mark.parametrize("case", V_EDGE_CASES, ids=lambda c: f"Hq{c[0]}-Hkv{c[1]}-d{c[2]}-n{c[3]}-rows{c[4]}-free{c[5]}")
+def test_v_tiles_end_where_the_rows_do(tb, bufs, case):
+    """The last tile of V, of a region and of the dense rows, ends at the last row: what lies behind (NaN here) is read as
+    zero by the four-wave shapes, which take V as it lies, as by the eight-wave one, which transposes it first."""
+    Hq, Hkv, d, n, kept, free = case
+    print("case", case, flush=True)
+    L, w = 700, 128
+    x = wl.prefill_inputs("lowrank", Hq, Hkv, d, L, "bf16", 95)
+    prm = H.params_for(tb, Hq, Hkv, d, 32, w, "bf16")
+    rng = np.random.default_rng(96)
+    S = [np.sort(rng.choice(400, size=kept, replace=False)) for _ in range(Hq)]
+    Qd, Kx, Vx = (bufs.to_device(x[k]) for k in ("Q", "K", "V"))
+    Kd, Vd = (torch.full((Hkv, L + 70, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    Kd[:, :L], Vd[:, :L] = Kx, Vx
+    gb = bufs.GlobalBuffers(prm, np.full(Hq, kept + 67))
+    gb.Kg.fill_(float("nan"))
+    gb.Vg.fill_(float("nan"))
+    for h, s in enumerate(S):
+        o, at = int(gb.offs[h]), torch.from_numpy(s).cuda()
+        gb.idx[o:o + kept] = at.to(torch.int32)
+        gb.Kg[o:o + kept], gb.Vg[o:o + kept] = Kd[h // (Hq // Hkv), at], Vd[h // (Hq // Hkv), at]
+        gb.n_rows[h] = kept
+    Qt = Qd[:, L - n:].contiguous()
+    ws = bufs.workspace(tb.tca_prefill_workspace_bytes(prm, n, int(gb.offs[-1])))
+    rows = sorted({0, n // 2, n - 1})
+    ref = H.oracle_rows(x, None, {"w": w}, S, np.array([L - n + r for r in rows]))
+    for variant in (0, 1, 3):
+        O = torch.full_like(Qt, float("nan"))
+        tb.tca_diag_prefill_variant(variant)
+        try:
+            tb.tca_prefill(prm, Qt, L - n, n, Kd, Vd, L + 70, gb.idx, None if free else gb.Kg, None if free else gb.Vg,
+                           gb.offs, gb.n_rows, O, None, ws)
+            torch.cuda.synchronize()
+        finally:
+            tb.tca_diag_prefill_variant(0)
+        got = bufs.to_host_f64(O)
+        assert not np.isnan(got).any(), f"variant {variant}"
+        for h in range(Hq):
+            assert np.abs(got[h][rows] - ref[h]).max() <= H.TOL["bf16"], f"variant {variant}, head {h}"
+
+
 F32_CASES = [
     # Hq, Hkv, d, L, q0, w, share, gather-free: both key splits of the fp32 kernel, at the edges of its tiles
     (4, 1, 64, 1300, 1283, 128, False, False),     # 17 queries: a second tile of one row, keys dealt to four waves
