@@ -500,7 +500,7 @@ void prefill_mfma_kernel(
       (void*)(V + (VT ? (size_t)kvh * dense_tiles * (D * kBN) : (size_t)kvh * kv_stride * D)), 0,
       VT ? dense_tiles * VBYTES : (last_pos + 1) * (D * 2), kRsrcFlags);
   const int vdshift = VT ? dshift - (int)dense_tile0 : dshift;       // tile t >= n_gt is tile t + vdshift of the dense V or V^T buffer
-  int klo[Copy::NK], vlo[Copy::NV];                // this lane's byte offsets inside a tile, per wave-load
+  int klo[Copy::NK], vlo[VT ? Copy::NV : 1];       // this lane's byte offsets inside a tile, per wave-load (V: 1024 more for the next)
   int krow[Copy::NK];                              // the tile row this lane copies a chunk of, per wave-load of K or V
 #pragma unroll
   for (int j = 0; j < Copy::NK; ++j) {
@@ -508,7 +508,7 @@ void prefill_mfma_kernel(
     krow[j] = ((wv * Copy::NK + j) * 64 + lane) / Copy::CPR;
   }
 #pragma unroll
-  for (int j = 0; j < Copy::NV; ++j)
+  for (int j = 0; j < (VT ? Copy::NV : 1); ++j)
     vlo[j] = VT ? Copy::vt_lane_offset(wv * Copy::NV + j, lane) : Copy::v_lane_offset(wv * Copy::NV + j, lane);
   // One K tile and one V tile to copy: descriptors and scalar offsets chosen once, then
   // load(j) issues wave-load j of the K tile (j < NK) or of the V tile (j >= NK)
@@ -549,7 +549,7 @@ void prefill_mfma_kernel(
 #pragma unroll
       for (int q = 0; q < Copy::NK; ++q) {     // the chunk inside the row stays the swizzled one of klo, vlo
         j.kgo[q] = rows_k.pos[q] >= 0 ? rows_k.pos[q] * (D * 2) + (klo[q] - krow[q] * (D * 2)) : 0x7FFFFFF0;
-        if constexpr (VGATHER) j.vgo[q] = rows_v.pos[q] >= 0 ? rows_v.pos[q] * (D * 2) + (vlo[q] - krow[q] * (D * 2)) : 0x7FFFFFF0;
+        if constexpr (VGATHER) j.vgo[q] = rows_v.pos[q] >= 0 ? rows_v.pos[q] * (D * 2) + (vlo[0] + q * 1024 - krow[q] * (D * 2)) : 0x7FFFFFF0;
       }
     }
     return j;
@@ -560,7 +560,8 @@ void prefill_mfma_kernel(
       else copy16_to_lds(job.krs, klo[j], job.koff, job.kdst + j * 1024);
     } else {
       if (VGATHER && job.v_through_idx) copy16_to_lds(job.vrs, job.vgo[j - Copy::NK], 0, job.vdst + (j - Copy::NK) * 1024);
-      else copy16_to_lds(job.vrs, vlo[j - Copy::NK], job.voff, job.vdst + (j - Copy::NK) * 1024);
+      else if (VT) copy16_to_lds(job.vrs, vlo[VT ? j - Copy::NK : 0], job.voff, job.vdst + (j - Copy::NK) * 1024);
+      else copy16_to_lds(job.vrs, vlo[0], job.voff + (j - Copy::NK) * 1024, job.vdst + (j - Copy::NK) * 1024);
     }
   };
 
@@ -700,6 +701,28 @@ void prefill_mfma_kernel(
     }
   };
 
+  // And for the four-wave shape, whose steps the scheduler gives up ordering by itself (all exponentials between the MFMAs of S
+  // and those of P V): one slot of it behind every MFMA of the step (t = 0 .. 2 KK - 1: of S, from 2 KK on: of P V), the order
+  // written out and fenced.  Exponentials at an even pace, done two slots before the last of them are needed (the last
+  // quarter of P V), rounded and summed one slot behind; the terms' sum in the order of exp_tile.  413 tokens behind 64K: 193
+  // -> 183.6 us.  The eight-wave shape is 1.1 % slower this way than in the order pinned below, and with rows fetched through
+  // idx there are no registers left for it.
+  constexpr bool kFenced = NW == 4 && QB == 1 && !GATHER;
+  constexpr int kSlots = 2 * KK + 4 * DS;
+  auto exp_slot = [&](int t, const f32x16_t (&s)[2], float mb, bf16x8_t (&pf)[2][2], float (&ls)[4], float (&p)[32]) {
+    auto done = [](int u) {                          // elements formed by the end of slot u
+      constexpr int span = kSlots * 13 / 16;
+      const int n = u < 0 ? 0 : ((u + 1) * 16 + span - 1) / span * 2;
+      return n < 32 ? n : 32;
+    };
+    for (int n = done(t - 2); n < done(t - 1); ++n) {
+      pf[n >> 4][(n >> 3) & 1][n & 7] = (__bf16)p[n];
+      ls[n & 3] += p[n];
+      asm volatile("" : "+v"(ls[n & 3]));            // added here: left to itself the compiler keeps all 32 terms to the end
+    }
+    for (int n = done(t - 1); n < done(t); ++n) p[n] = __builtin_amdgcn_exp2f(fmaf(s[n >> 4][n & 15], sl2e, -mb));
+  };
+
   // Does every query of the wave see every key of tile t?  (wave-uniform)
   auto mask_tile_is_clear = [&](int t) {
     const bool is_glob = t < n_gt;
@@ -810,6 +833,7 @@ void prefill_mfma_kernel(
       return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     };
     bf16x8_t vfr[kFragAhead];
+    float ls_slot[4] = {0.f, 0.f, 0.f, 0.f}, p_slot[32], m2[2], mb_slot = 0.f;
     if constexpr (QB == 1) {
       // One block per wave, two waves per SIMD: the reference is the running maximum of the visible
       // scores.  The maximum of this tile was taken under the previous step's P V MFMAs (again after
@@ -832,8 +856,19 @@ void prefill_mfma_kernel(
           for (int r = 0; r < 16; ++r) o[0][sl][r] *= alpha;
         m[0] = m_new;
       }
-      s_tile(kb, sn, issue_copies);
-      l[0] += exp_tile(sc[0], (m_new == -INFINITY) ? 0.f : m_new * sl2e, pf[0]);
+      const float mb = mb_slot = (m_new == -INFINITY) ? 0.f : m_new * sl2e;
+      if constexpr (kFenced) {
+        __builtin_amdgcn_sched_barrier(0);
+        s_tile(kb, sn, [&](int i) {
+          issue_copies(i);
+          if (i >= 2 * KK - kFragAhead) vfr[i - (2 * KK - kFragAhead)] = vfrag(i - (2 * KK - kFragAhead));
+          exp_slot(i, sc[0], mb, pf[0], ls_slot, p_slot);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      } else {
+        s_tile(kb, sn, issue_copies);
+        l[0] += exp_tile(sc[0], mb, pf[0]);
+      }
     } else {
       const bool sees = mask_tile(it, 0, sc[0]);
       const bool cold = m[0] == -INFINITY;          // no reference yet: no key seen so far
@@ -862,8 +897,10 @@ void prefill_mfma_kernel(
       mb1 = cold1 ? 0.f : m[1] * sl2e;
       __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (!kFenced) {
 #pragma unroll
-    for (int j = 0; j < kFragAhead; ++j) vfr[j] = vfrag(j);
+      for (int j = 0; j < kFragAhead; ++j) vfr[j] = vfrag(j);
+    }
 #pragma unroll
     for (int j = 0; j < 4 * DS; ++j) {
       const int sl = j % DS, sg = j / DS;           // sg = sub*2 + g: 16 keys
@@ -879,13 +916,26 @@ void prefill_mfma_kernel(
 #pragma unroll
       for (int blk = 0; blk < QB; ++blk) pv_mfma<QB == 2>(o[blk][sl], vfr[j % kFragAhead], pf[blk][sg >> 1][sg & 1]);
       if (j + kFragAhead < 4 * DS) vfr[j % kFragAhead] = vfrag(j + kFragAhead);
+      if constexpr (kFenced) {
+        exp_slot(2 * KK + j, sc[0], mb_slot, pf[0], ls_slot, p_slot);
+        const int r = 2 * (j - (4 * DS - 8) / 2);    // the next tile's maximum over the lane's keys
+        if (r >= 0 && r < 16) {
+          m2[0] = fmaxf(fmaxf(r ? m2[0] : sn[0][0][0], sn[0][0][r]), sn[0][0][r + 1]);
+          m2[1] = fmaxf(fmaxf(r ? m2[1] : sn[0][1][0], sn[0][1][r]), sn[0][1][r + 1]);
+          asm volatile("" : "+v"(m2[0]), "+v"(m2[1]));         // formed here, as the sums
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
       if constexpr (QB == 2) {
         exp_piece(j, sn[1], mb1, pn, ls1, pend1);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if constexpr (QB == 1) mx_pre = lane_max(sn[0]);    // vector ALU work for the shadow of the MFMAs above
-    if constexpr (QB == 1) {
+    if constexpr (kFenced) {
+      l[0] += (ls_slot[0] + ls_slot[1]) + (ls_slot[2] + ls_slot[3]);
+      mx_pre = half_max(fmaxf(m2[0], m2[1]));
+    } else if constexpr (QB == 1) {
+      mx_pre = lane_max(sn[0]);                        // vector ALU work for the shadow of the MFMAs above
       // The order of the step's instructions, spelled out for the scheduler (the step is one scheduling
       // region): behind every MFMA one fragment read and an even share of the plain vector ALU work, the
       // exponentials left to fall where they may, which is two per MFMA of the S half.  Left to itself the
