@@ -111,6 +111,42 @@ def test_fp8_cache_bytes_and_decode_match_oracle(tb, bufs, case):
         assert np.array_equal(got, ocache.K[kvh][ocache.S[n]]), f"head {n} rows after decoding"
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_handover_codes_are_those_of_the_divisions(tb, bufs, d):
+    """Codes and scales of rows over the range of bf16, bit for bit: every pair of mantissas of an element and its row's
+    largest one, zeros of both signs, rows too small or too large for the quotient without a division, one with an infinity."""
+    rng = np.random.default_rng(97)
+    w, Hkv = 512, 2
+    mant = np.arange(128, dtype=np.uint32)
+    bits = np.zeros((Hkv, w, d), np.uint32)
+    exps = np.concatenate([rng.integers(100, 150, w - 64), rng.integers(1, 70, 32), rng.integers(190, 255, 32)])
+    for r in range(w):
+        e = int(exps[r])
+        # element 0 is the row's largest; the others lie 1 .. 20 octaves below it and run through the mantissas
+        bits[:, r, 0] = e << 7 | mant[r % 128]
+        below = np.maximum(e - rng.integers(1, 21, (Hkv, d - 1)), 0)
+        bits[:, r, 1:] = below << 7 | mant[(np.arange(d - 1) + r // 128 * 32 + np.arange(Hkv)[:, None] * 64) % 128]
+    bits |= rng.integers(0, 2, bits.shape).astype(np.uint32) << 15
+    bits[:, :, 3] &= 0x8000                                          # zeros, of either sign
+    K = (bits << 16).view(np.float32)
+    K[0, 7, 5] = np.inf
+    Kd = torch.from_numpy(K).cuda().to(torch.bfloat16)
+    prm = H.params_for(tb, Hkv, Hkv, d, 16, w, "bf16")
+    cache = bufs.DecodeCache(prm, 1, np.full(Hkv, 16), kv_format=tb.TCA_KV_FP8)
+    tb.tca_cache_load_window(prm, cache.view, 0, Kd, Kd.flip(0).contiguous(), w, w)
+    torch.cuda.synchronize()
+    for kvh in range(Hkv):
+        amax = np.abs(K[kvh]).max(1)
+        with np.errstate(over="ignore", invalid="ignore"):
+            scale = np.where(amax > 0, amax / np.float32(448), np.float32(1)).astype(np.float32)
+            quot = np.clip(K[kvh] / scale[:, None], np.float32(-448), np.float32(448))
+        want = torch.from_numpy(quot).to(torch.float8_e4m3fn).view(torch.uint8).numpy()
+        finite = np.isfinite(K[kvh] / scale[:, None])
+        for ring, sc in ((cache.ringK[0, kvh], cache.ringK_scale[0, kvh]), (cache.ringV[0, 1 - kvh], cache.ringV_scale[0, 1 - kvh])):
+            assert np.array_equal(sc.cpu().numpy().reshape(-1), scale)
+            assert np.array_equal(ring.cpu().numpy().reshape(w, d)[finite], want[finite])
+
+
 def test_load_global_with_the_native_format_is_a_copy_and_checks_its_arguments(tb, bufs):
     Hq, Hkv, d, L, b, w = 4, 2, 64, 600, 16, 64
     x = wl.prefill_inputs("lowrank", Hq, Hkv, d, L, "bf16", 66)
