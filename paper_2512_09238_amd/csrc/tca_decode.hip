@@ -399,7 +399,7 @@ __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const
   merge_partials<D, NQ>(m, l, acc, out, out_head, red);
 }
 
-// The same for bf16 rows of 128 elements and NQ > 1 queries, with q.k on the matrix cores.
+// The same for bf16 and FP8 rows of 128 elements and NQ > 1 queries, with q.k on the matrix cores.
 // A wave takes 16 rows per iteration (its 16-lane group kb the rows 4kb .. 4kb+3).  K rows go
 // from registers into a wave-private LDS tile and come back in MFMA operand order (lane
 // (n, kb) = 8 consecutive elements of row n), so that four 16x16x32 MFMAs against the queries
@@ -409,14 +409,15 @@ __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const
 // as before.  The reference m[g] is common to the wave and lazy (raised only when a score
 // exceeds it by more than kSlack, decided by a wave-wide vote).  Against partial_rows this
 // removes, per (row, query), the dot products, the 16-lane reductions and 15 of the 16 copies
-// of the exponential.  tiles: LDS, kMfmaTileBytes per wave, then 256 bytes per query.
+// of the exponential.  FP8 rows come this way too (8 sequences of 30K tokens, the rings' rows scored against 4 queries: the
+// step 89.0 -> 85.6 us).  tiles: LDS, kMfmaTileBytes per wave, then 256 bytes per query.
 constexpr int kMfmaTileBytes = 16 * 256 + 16 * 8 * 4;
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 dec_bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float dec_f32x4_t;
 
-template <int NQ, typename Visible>
-__device__ __forceinline__ void partial_rows_mfma(const bf16_t* __restrict__ kbase, const bf16_t* __restrict__ vbase,
-                                                  int r_begin, int r_cap, Visible visible, const bf16_t* __restrict__ q0, double scale,
+template <typename KV, int NQ, typename Visible>
+__device__ __forceinline__ void partial_rows_mfma(const KV* __restrict__ kbase, const KV* __restrict__ vbase,
+                                                  const float* __restrict__ kscale, const float* __restrict__ vscale, int r_begin, int r_cap, Visible visible, const bf16_t* __restrict__ q0, double scale,
                                                   float* __restrict__ out, size_t out_head, float* red,
                                                   unsigned char* tiles) {
   constexpr int D = 128, EL = 8;
@@ -451,8 +452,12 @@ __device__ __forceinline__ void partial_rows_mfma(const bf16_t* __restrict__ kba
 
   // K rows are requested one iteration ahead (they are needed first, for the tile); V rows at the
   // end of the iteration before, so that they travel while the next scores are formed.
-  using Raw = RawSlice<bf16_t, EL>;
+  // FP8 rows: the codes are bf16 numbers, so the products on the matrix cores are those of the codes; the K row's scale
+  // multiplies the score, the V row's the term (both in the lanes of group kb, whose rows they are).
+  constexpr bool kFp8 = sizeof(KV) == 1;
+  using Raw = RawSlice<KV, EL>;
   Raw kn[4], vn[4];
+  float ks[4], ksn[4], vs[4];
   bool okk[4], okv[4];
   auto fetch_k = [&](int r0) {
 #pragma unroll
@@ -460,6 +465,7 @@ __device__ __forceinline__ void partial_rows_mfma(const bf16_t* __restrict__ kba
       const int r = r0 + 16 * wv + 4 * kb + u;
       okk[u] = r < r_end;                              // nothing is loaded past r_end
       if (okk[u]) kn[u].load(kbase + (size_t)r * D + n * EL);
+      if constexpr (kFp8) ksn[u] = okk[u] ? kscale[r] : 0.f;
     }
   };
   auto fetch_v = [&](int r0) {
@@ -468,6 +474,7 @@ __device__ __forceinline__ void partial_rows_mfma(const bf16_t* __restrict__ kba
       const int r = r0 + 16 * wv + 4 * kb + u;
       okv[u] = r < r_end;
       if (okv[u]) vn[u].load(vbase + (size_t)r * D + n * EL);
+      if constexpr (kFp8) vs[u] = okv[u] ? vscale[r] : 0.f;
     }
   };
   fetch_k(r_begin);
@@ -484,8 +491,17 @@ __device__ __forceinline__ void partial_rows_mfma(const bf16_t* __restrict__ kba
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int row = 4 * kb + u;
-      if (okk[u])
-        *reinterpret_cast<uint4*>(kt + row * 256 + ((n ^ row) & 15) * 16) = make_uint4(kn[u].w[0], kn[u].w[1], kn[u].w[2], kn[u].w[3]);
+      uint4 chunk;
+      if constexpr (kFp8) {
+        float x[EL];
+        kn[u].widen(x);
+        auto pair = [&](int i) { return __builtin_amdgcn_perm(__float_as_uint(x[i + 1]), __float_as_uint(x[i]), 0x07060302u); };
+        chunk = make_uint4(pair(0), pair(2), pair(4), pair(6));
+        ks[u] = ksn[u];
+      } else {
+        chunk = make_uint4(kn[u].w[0], kn[u].w[1], kn[u].w[2], kn[u].w[3]);
+      }
+      if (okk[u]) *reinterpret_cast<uint4*>(kt + row * 256 + ((n ^ row) & 15) * 16) = chunk;
     }
     fetch_k(r0 + 16 * kPartWaves);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -505,7 +521,7 @@ __device__ __forceinline__ void partial_rows_mfma(const bf16_t* __restrict__ kba
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const bool valid = r0 + 16 * wv + 4 * kb + i < r_end;      // rows past the end hold stale tile data
-      s2[i] = valid ? sv[i] * factor : -INFINITY;
+      s2[i] = valid ? (kFp8 ? sv[i] * factor * ks[i] : sv[i] * factor) : -INFINITY;
       raise |= holder && s2[i] > m_mine + kSlack;
     }
     if (__any(raise)) {
@@ -546,7 +562,7 @@ __device__ __forceinline__ void partial_rows_mfma(const bf16_t* __restrict__ kba
     }
     if (holder) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) pt[(4 * kb + i) * 8 + n] = p[i];
+      for (int i = 0; i < 4; ++i) pt[(4 * kb + i) * 8 + n] = kFp8 ? p[i] * vs[i] : p[i];
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 
@@ -590,7 +606,7 @@ __global__ __launch_bounds__(kPartThreads, sizeof(KV) == 1 && D == 128 && GW == 
   constexpr int EL = D / 16;
   constexpr int NMAX = GQ > GW ? GQ : GW;
   __shared__ float red[kPartWaves * 16 * NMAX * (EL + 2)];
-  constexpr bool kMfma = sizeof(KV) == 2 && D == 128;  // rows that partial_rows_mfma takes
+  constexpr bool kMfma = sizeof(KV) <= 2 && D == 128;  // rows that partial_rows_mfma takes
   __shared__ __attribute__((aligned(16))) unsigned char tiles[kMfma && NMAX > 1 ? kPartWaves * kMfmaTileBytes + NMAX * 256 : 16];
   const int id = blockIdx.x, s = blockIdx.y;
   const int Hs = Hq / GQ;
@@ -629,8 +645,8 @@ __global__ __launch_bounds__(kPartThreads, sizeof(KV) == 1 && D == 128 && GW == 
     const size_t out_head = (size_t)ns * (D + 2);
     const T* q0 = q + ((size_t)s * Hq + hs * GQ) * D;
     if constexpr (kMfma && GQ > 1)
-      partial_rows_mfma<GQ>((const T*)c.Kg + base * D, (const T*)c.Vg + base * D, r_begin, r_begin + len, visible, q0, scale, out,
-                            out_head, red, tiles);
+      partial_rows_mfma<KV, GQ>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base, c.Vg_scale + base,
+                                r_begin, r_begin + len, visible, q0, scale, out, out_head, red, tiles);
     else
       partial_rows<T, KV, D, GQ>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base,
                                  c.Vg_scale + base, r_begin, r_begin + len, visible, q0, scale, out, out_head, red);
@@ -650,8 +666,8 @@ __global__ __launch_bounds__(kPartThreads, sizeof(KV) == 1 && D == 128 && GW == 
     const size_t out_head = (size_t)dh.ring_units * (D + 2);
     const T* q0 = q + ((size_t)s * Hq + h0) * D;
     if constexpr (kMfma && GW > 1)
-      partial_rows_mfma<GW>((const T*)c.ringK + base * D, (const T*)c.ringV + base * D, r_begin, r_end, visible, q0, scale,
-                            out, out_head, red, tiles);
+      partial_rows_mfma<KV, GW>((const KV*)c.ringK + base * D, (const KV*)c.ringV + base * D, c.ringK_scale + base,
+                                c.ringV_scale + base, r_begin, r_end, visible, q0, scale, out, out_head, red, tiles);
     else
       partial_rows<T, KV, D, GW>((const KV*)c.ringK + base * D, (const KV*)c.ringV + base * D, c.ringK_scale + base,
                                  c.ringV_scale + base, r_begin, r_end, visible, q0, scale, out, out_head, red);
