@@ -1301,7 +1301,11 @@ static int64_t plan_xcds(PrefillHeads& ph, const tca_params* prm, const int64_t*
 
 // Whether a call's items are cut into chunks, and how long: fills sp (all but part) and returns the number of
 // workgroups, or 0 for the plain launch.  plain_steps: when the plain launch would end, in tile steps (each slot
-// of the chip taken: with 256 workgroups or fewer a step takes 0.6 of the time).  Measured, whole and in chunks: 413
+// of the chip taken: a workgroup alone on its CU takes 0.6 of the time for a step.  With 256 workgroups or fewer all are;
+// with up to 512 the longest meets a short one on its CU (pair_up) and is alone from there on, unless the heads share a
+// selection, are equally long and lie on one XCD.  Reckoned as if a second one were there to the end, calls were cut that are
+// faster whole: 2048 queries behind 30K, 32 heads, 432 us and 384 whole; 1000 of 64 heads 447 and 402; 16384 tokens of 4
+// heads, d = 64, 155 and 130; with a shared selection 2048 behind 64K 672 and 846).  Measured, whole and in chunks: 413
 // queries behind 64K tokens (32 heads) 539 -> 218 us, behind 112K 949 -> 344 us; 128 behind 16K 164 -> 62 us; 2048
 // behind 30K (4 heads, d = 64) 304 -> 93 us; from 512 items of equal length on nothing is gained.
 static int64_t plan_split(SplitPlan& sp, const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries,
@@ -1334,8 +1338,12 @@ static int64_t plan_split(SplitPlan& sp, const tca_params* prm, const int64_t* o
   // 128) or 1.1 us (64) with the chip full, 0.6 of that half full; the merge a launch, 0.3 us per chunk of an item, and
   // the partial results written and read at 4 TB/s.
   const double step = prm->head_dim == 128 ? 1.8 : 1.1;
-  const double occ_plain = n_items <= kSplitSlots / 2 ? 0.6 : 1.0;
-  const double plain = plain_steps * occ_plain * step;
+  double beside = 0.0;                             // steps of the longest workgroup with another one on its CU
+  if (n_items > kSplitSlots / 2) {
+    beside = (double)plain_steps;
+    if (n_items <= kSplitSlots && GS == 1) beside = std::max(0.0, std::min(beside, 2.0 * (total / (double)n_items + kFixedSteps) - plain_steps));
+  }
+  const double plain = (0.6 * plain_steps + 0.4 * beside) * step;
   double best = 0.9 * plain;
   int64_t best_items = 0, best_chunk = 0;
   for (const int64_t room : {(int64_t)kSplitSlots / 2, (int64_t)kSplitSlots, (int64_t)2 * kSplitSlots}) {
@@ -1376,7 +1384,13 @@ struct WgShape { int nw, qb; };
 static int xcd_slots(WgShape sh) { return sh.nw == 8 || sh.qb == 2 ? 32 : 64; }
 static WgShape choose_shape(const tca_params* prm, int64_t n_queries, bool gather) {
   const int variant = prefill_variant();
-  const bool many = ((n_queries + 255) / 256) * prm->n_q_heads >= 1024;
+  // With rows fetched through idx eight waves from 1024 items of 256 queries on.  Otherwise the pre-pass (uses_transposed_v)
+  // must be worth it too: the query tiles that read a tile of V^T must be many.  Four waves against eight, 22 tiles (5446
+  // tokens): 64 heads 551 / 579 us, with a shared selection 549 / 565; 16 tiles (4096 tokens, 64 heads) 345 / 351, behind
+  // 64K 2216 / 2218 and 2502 / 2582 shared; 32 tiles (8192 tokens): 32 heads 514 / 513, behind 30K 1250 / 1222, behind 112K
+  // 3116 / 3011; 64 tiles 2462 / 2452 with 64 heads.
+  const int64_t tiles = (n_queries + 255) / 256;
+  const bool many = tiles * prm->n_q_heads >= 1024 && (gather || tiles >= 24);
   if (gather) return {variant == 3 || (variant != 1 && many) ? 8 : 4, 1};
   if (variant == 3 || (variant == 0 && many)) return {8, 1};
   if (variant == 2) return {4, 2};
