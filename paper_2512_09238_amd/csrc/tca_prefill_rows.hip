@@ -13,9 +13,9 @@
 // 16 bytes at a time (chunk index xor row, conflict-free); in the second, row i of block s is element
 // (D / 16) i + s, so that V is too, and a lane ends up with D / 4 consecutive elements of its query.
 //
-// KG = 1: four waves (64 queries) share tiles of 16 keys.  KG = 4: the four waves take the same 16 queries and
-// every fourth tile each, and are merged at the end: four times the workgroups, for calls that would not
-// fill the chip.
+// KG = 1: four waves (64 queries) share tiles of 16 keys.  KG = 4, 8: four or eight waves take the same 16 queries and
+// every fourth or eighth tile each, and are merged at the end: four times the workgroups, and a chain of tiles a
+// fourth or an eighth as long, for calls that would not fill the chip.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -26,13 +26,13 @@
 
 namespace tca {
 
-constexpr int kRowThreads = 256;
+constexpr int row_threads(int kg) { return kg == 8 ? 512 : 256; }
 
 struct HeadOffs { int64_t offs[TCA_MAX_HEADS + 1]; };
 
-// grid (query tiles * Hq), longest query tiles first, heads inside; block 256
+// grid (query tiles * Hq), longest query tiles first, heads inside; block 256, 512 with KG = 8
 template <int D, int KG>
-__global__ __launch_bounds__(kRowThreads, D == 64 && KG == 1 ? 4 : 2) void prefill_f32_kernel(
+__global__ __launch_bounds__(row_threads(KG), D == 64 && KG == 1 ? 4 : 2) void prefill_f32_kernel(
     const float* __restrict__ Q, int64_t q_pos0, int64_t n_queries, const float* __restrict__ K,
     const float* __restrict__ V, int64_t kv_stride, const int32_t* __restrict__ idx,
     const float* __restrict__ Kg, const float* __restrict__ Vg, HeadOffs ho,
@@ -41,12 +41,12 @@ __global__ __launch_bounds__(kRowThreads, D == 64 && KG == 1 ? 4 : 2) void prefi
   typedef double f64x4_t __attribute__((ext_vector_type(4)));
   typedef float f32x4_t __attribute__((ext_vector_type(4)));
   constexpr int TK = 16;                           // keys per tile
-  constexpr int GW = 4 / KG, GT = GW * 64;         // waves, threads that share a tile
+  constexpr int GW = row_threads(KG) / 64 / KG, GT = GW * 64;      // waves, threads that share a tile
   constexpr int QT = GW * 16;                      // queries per workgroup
   constexpr int C4 = D / 4;                        // 16-byte chunks of a row
   constexpr int SB = D / 16;                       // blocks of O^T; chunks of a quarter row
   constexpr int NL = TK * C4 / GT;                 // chunks a thread stages, of K and of V
-  // KG = 4 shares nothing of V: at d = 128, where the registers are short, V goes from memory to its operands (at d = 64
+  // KG > 1 shares nothing of V: at d = 128, where the registers are short, V goes from memory to its operands (at d = 64
   // requesting it a tile ahead and keeping it in LDS is faster: 1024 tokens, 4 heads, 23 against 28 us).
   constexpr bool kStageV = KG == 1 || D == 64;
   __shared__ f32x4_t kt[KG][TK][C4], vt[kStageV ? KG : 1][TK][C4];
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(kRowThreads, D == 64 && KG == 1 ? 4 : 2) void prefi
   for (int s = 0; s < SB; ++s)
 #pragma unroll
     for (int e = 0; e < 4; ++e) odd = fmaf(o[s][e], 0.f, odd);
-  // (a wave of KG = 4 shares nothing with the others; with KG = 1 the barriers of the walk are the whole workgroup's)
+  // (a wave of KG > 1 shares nothing with the others; with KG = 1 the barriers of the walk are the whole workgroup's)
   if (__builtin_expect(KG == 1 ? __syncthreads_or(odd != 0.f) : __any(odd != 0.f), 0)) walk(std::false_type{});
   l += __shfl_xor(l, 16, kWave);
   l += __shfl_xor(l, 32, kWave);
@@ -279,28 +279,29 @@ __global__ __launch_bounds__(kRowThreads, D == 64 && KG == 1 ? 4 : 2) void prefi
     if (kb == 0) { ms[wv][c] = m; ls[wv][c] = l; }
     __syncthreads();
     const int qi = tid >> 4, sub = tid & 15;       // 16 threads per query, D / 16 elements each
-    if (r0 + qi >= n_queries) return;
+    if (qi >= 16 || r0 + qi >= n_queries) return;
     double M = ms[0][qi];
 #pragma unroll
     for (int g = 1; g < KG; ++g) M = fmax(M, ms[g][qi]);
-    float L = 0.f, a[SB];
+    // (in fp64: eight parts added in fp32 put the error at 1.2e-7 where four left 1.1e-7)
+    double L = 0.0, a[SB];
 #pragma unroll
-    for (int e = 0; e < SB; ++e) a[e] = 0.f;
+    for (int e = 0; e < SB; ++e) a[e] = 0.0;
 #pragma unroll
     for (int g = 0; g < KG; ++g) {
-      const float wgt = ms[g][qi] == -INFINITY ? 0.f : expf((float)(ms[g][qi] - M));      // no keys: a sum of 0 (or of NaN, which stays)
-      L += ls[g][qi] * wgt;
+      const double wgt = ms[g][qi] == -INFINITY ? 0.0 : exp(ms[g][qi] - M);      // no keys: a sum of 0 (or of NaN, which stays)
+      L += (double)ls[g][qi] * wgt;
 #pragma unroll
-      for (int e = 0; e < SB; ++e) a[e] += po[(g * 16 + qi) * D + sub * SB + e] * wgt;
+      for (int e = 0; e < SB; ++e) a[e] += (double)po[(g * 16 + qi) * D + sub * SB + e] * wgt;
     }
-    const float inv = L > 0.f ? 1.f / L : 0.f;
+    const double inv = L > 0.0 ? 1.0 / L : 0.0;
     float* orow = O + ((size_t)h * n_queries + r0 + qi) * D + sub * SB;
 #pragma unroll
     for (int u = 0; u < SB / 4; ++u) {
-      const f32x4_t v = {a[4 * u] * inv, a[4 * u + 1] * inv, a[4 * u + 2] * inv, a[4 * u + 3] * inv};
+      const f32x4_t v = {(float)(a[4 * u] * inv), (float)(a[4 * u + 1] * inv), (float)(a[4 * u + 2] * inv), (float)(a[4 * u + 3] * inv)};
       *reinterpret_cast<f32x4_t*>(orow + 4 * u) = v;
     }
-    if (lse && sub == 0) lse[(size_t)h * n_queries + r0 + qi] = L > 0.f ? (float)(M + log((double)L)) : -INFINITY;
+    if (lse && sub == 0) lse[(size_t)h * n_queries + r0 + qi] = L > 0.0 ? (float)(M + log(L)) : -INFINITY;
   }
 }
 
@@ -318,12 +319,22 @@ int launch_prefill_f32(const tca_params* prm, const float* Q, int64_t q_pos0, in
   const bool few = (n_queries + 63) / 64 * Hq < 400;
   const int64_t n_wg = (n_queries + (few ? 15 : 63)) / (few ? 16 : 64) * Hq;
   if (n_wg > INT32_MAX) return fail(TCA_ERR_UNSUPPORTED, "tca_prefill (fp32): %lld queries", (long long)n_queries);
-  auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)n_wg), dim3(kRowThreads), 0, st, Q, q_pos0, n_queries, K, V, kv_stride, idx,
+  // And of those, few enough that twice the waves all find a place at once: eight share the walk.  us with four / with
+  // eight: 4 heads, d = 64, 256 tokens 51.5 / 42.2, 1024 tokens (256 workgroups) 59.4 / 47.9, 2048 tokens (512) 86.5 / 73.2,
+  // 512 behind 4096 110.6 / 83.6; 32 heads, d = 128 (two waves of 256 registers fill a SIMD), 256 tokens (512) 55.4 / 57.5.
+  const bool fewest = few && n_wg <= (prm->head_dim == 64 ? 512 : 256);
+  auto launch = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n_wg), dim3(threads), 0, st, Q, q_pos0, n_queries, K, V, kv_stride, idx,
                        Kg, Vg, ho, n_rows, Hq, Hq / prm->n_kv_heads, sel_group(prm), prm->window, scale, O, lse, part);
   };
-  if (prm->head_dim == 128) { if (few) launch(prefill_f32_kernel<128, 4>); else launch(prefill_f32_kernel<128, 1>); }
-  else { if (few) launch(prefill_f32_kernel<64, 4>); else launch(prefill_f32_kernel<64, 1>); }
+  auto choose = [&](auto d_tag) {
+    constexpr int D = decltype(d_tag)::value;
+    if (fewest) launch(prefill_f32_kernel<D, 8>, row_threads(8));
+    else if (few) launch(prefill_f32_kernel<D, 4>, row_threads(4));
+    else launch(prefill_f32_kernel<D, 1>, row_threads(1));
+  };
+  if (prm->head_dim == 128) choose(std::integral_constant<int, 128>{});
+  else choose(std::integral_constant<int, 64>{});
   return TCA_OK;
 }
 

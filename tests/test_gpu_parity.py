@@ -766,9 +766,16 @@ F32_CASES = [
     (16, 2, 64, 1700, 1, 96, True, False),         # 64 queries per workgroup (27 tiles x 16 heads), shared selection
     (24, 3, 128, 1100, 3, 512, False, False),
 ]
+F32_WAVES_CASES = [
+    # eight waves a query tile: fewer tiles of keys than waves; 128 elements a row; four waves: more than 512 query tiles
+    (4, 1, 64, 40, 0, 32, False, False),
+    (4, 1, 64, 1040, 1000, 32, True, False),
+    (8, 2, 128, 333, 0, 64, False, False),
+    (32, 4, 64, 300, 0, 32, False, True),
+]
 
 
-@pytest.mark.parametrize("case", F32_CASES, ids=lambda c: f"Hq{c[0]}-Hkv{c[1]}-d{c[2]}-L{c[3]}-q{c[4]}-w{c[5]}-share{c[6]}-free{c[7]}")
+@pytest.mark.parametrize("case", F32_CASES + F32_WAVES_CASES, ids=lambda c: f"Hq{c[0]}-Hkv{c[1]}-d{c[2]}-L{c[3]}-q{c[4]}-w{c[5]}-share{c[6]}-free{c[7]}")
 def test_fp32_prefill_both_key_splits(tb, bufs, case):
     """Against the oracle on rows at the tiles' edges.  The bound is fp32's: the terms and the weighted sum of up to L
     of them carry 2^-24 each against values of up to ~5, so 1e-5 absolute leaves a factor of ten."""
