@@ -139,9 +139,9 @@ def test_handover_codes_are_those_of_the_divisions(tb, bufs, d):
         amax = np.abs(K[kvh]).max(1)
         with np.errstate(over="ignore", invalid="ignore"):
             scale = np.where(amax > 0, amax / np.float32(448), np.float32(1)).astype(np.float32)
+            finite = np.isfinite(K[kvh] / scale[:, None])
             quot = np.clip(K[kvh] / scale[:, None], np.float32(-448), np.float32(448))
         want = torch.from_numpy(quot).to(torch.float8_e4m3fn).view(torch.uint8).numpy()
-        finite = np.isfinite(K[kvh] / scale[:, None])
         for ring, sc in ((cache.ringK[0, kvh], cache.ringK_scale[0, kvh]), (cache.ringV[0, 1 - kvh], cache.ringV_scale[0, 1 - kvh])):
             assert np.array_equal(sc.cpu().numpy().reshape(-1), scale)
             assert np.array_equal(ring.cpu().numpy().reshape(w, d)[finite], want[finite])
@@ -168,3 +168,42 @@ def test_load_global_with_the_native_format_is_a_copy_and_checks_its_arguments(t
     with pytest.raises(tb.TcaError) as e:                                                         # FP8 rows need bf16 inputs
         tb.tca_cache_load_global(prm32, c8.view, 0, gb.idx, gb.Kg, gb.Vg, gb.offs, gb.n_rows)
     assert e.value.code == tb.TCA_ERR_UNSUPPORTED
+
+
+REGION_CASES = [
+    # Hq = Hkv, capacities of the heads' regions, rows filled of each
+    (4, (0, 33, 0, 64), (0, 33, 0, 40)),             # empty regions between; a workgroup's rows in two heads, and in one
+    (2, (32, 32), (32, 1)),                          # regions that end where a workgroup does
+    (70, tuple(7 * h % 45 for h in range(70)), tuple(7 * h % 45 // 2 for h in range(70))),       # more heads than lanes
+]
+
+
+@pytest.mark.parametrize("case", REGION_CASES, ids=lambda c: f"H{c[0]}")
+@pytest.mark.parametrize("kv", ["native", "fp8"])
+def test_load_global_copies_the_filled_rows_of_every_region(tb, bufs, case, kv):
+    """Rows below each region's count arrive (FP8: as codes and scales of the same rows), what lies behind is left alone."""
+    Hn, cap, rows = case
+    print("case", Hn, kv, flush=True)
+    d, fp8 = 64, kv == "fp8"
+    prm = H.params_for(tb, Hn, Hn, d, 16, 32, "bf16")
+    gb = bufs.GlobalBuffers(prm, np.array(cap))
+    total = int(gb.offs[-1])
+    g = torch.Generator(device="cuda").manual_seed(98)
+    for t in (gb.Kg, gb.Vg):
+        t.copy_(torch.randn(total, d, generator=g, device="cuda"))
+    gb.idx.copy_(torch.arange(total, device="cuda"))
+    gb.n_rows.copy_(torch.tensor(rows, dtype=torch.int32))
+    cache = bufs.DecodeCache(prm, 2, np.array(cap), kv_format=tb.TCA_KV_FP8 if fp8 else tb.TCA_KV_NATIVE)
+    cache.idx.fill_(-7)
+    tb.tca_cache_load_global(prm, cache.view, 1, gb.idx, gb.Kg, gb.Vg, gb.offs, gb.n_rows)
+    torch.cuda.synchronize()
+    full = np.concatenate([np.arange(c) < r for c, r in zip(cap, rows)])
+    assert np.array_equal(cache.idx[1].cpu().numpy(), np.where(full, np.arange(total), -7))
+    assert (cache.idx[0] == -7).all() and np.array_equal(cache.n_rows[1].cpu().numpy(), rows)
+    at = torch.from_numpy(full).cuda()
+    for src, dst, scale in ((gb.Kg, cache.Kg, getattr(cache, "Kg_scale", None)), (gb.Vg, cache.Vg, getattr(cache, "Vg_scale", None))):
+        if fp8:
+            codes, sc = orc.quantize_rows_fp8(src[at].double().cpu().numpy())
+            assert np.array_equal(dst[1][at].cpu().numpy(), codes) and np.array_equal(scale[1][at].cpu().numpy().ravel(), np.ravel(sc))
+        else:
+            assert torch.equal(dst[1][at], src[at])
