@@ -283,25 +283,31 @@ __global__ __launch_bounds__(row_threads(KG), D == 64 && KG == 1 ? 4 : 2) void p
     double M = ms[0][qi];
 #pragma unroll
     for (int g = 1; g < KG; ++g) M = fmax(M, ms[g][qi]);
-    // (in fp64: eight parts added in fp32 put the error at 1.2e-7 where four left 1.1e-7)
-    double L = 0.0, a[SB];
+    // Eight parts in fp64: added in fp32 they put the error against 64 bits at 1.2e-7 where four leave 1.1e-7; in fp64 it is
+    // 9e-8 (and costs calls of four parts 0.5 us in 70, which have no need of it).
+    using sum_t = std::conditional_t<KG == 8, double, float>;
+    sum_t L = 0, a[SB];
 #pragma unroll
-    for (int e = 0; e < SB; ++e) a[e] = 0.0;
+    for (int e = 0; e < SB; ++e) a[e] = 0;
 #pragma unroll
     for (int g = 0; g < KG; ++g) {
-      const double wgt = ms[g][qi] == -INFINITY ? 0.0 : exp(ms[g][qi] - M);      // no keys: a sum of 0 (or of NaN, which stays)
-      L += (double)ls[g][qi] * wgt;
+      sum_t wgt = 0;                               // no keys: a sum of 0 (or of NaN, which stays)
+      if (ms[g][qi] != -INFINITY) {
+        if constexpr (KG == 8) wgt = exp(ms[g][qi] - M);
+        else wgt = expf((float)(ms[g][qi] - M));
+      }
+      L += ls[g][qi] * wgt;
 #pragma unroll
-      for (int e = 0; e < SB; ++e) a[e] += (double)po[(g * 16 + qi) * D + sub * SB + e] * wgt;
+      for (int e = 0; e < SB; ++e) a[e] += po[(g * 16 + qi) * D + sub * SB + e] * wgt;
     }
-    const double inv = L > 0.0 ? 1.0 / L : 0.0;
+    const sum_t inv = L > 0 ? 1 / L : 0;
     float* orow = O + ((size_t)h * n_queries + r0 + qi) * D + sub * SB;
 #pragma unroll
     for (int u = 0; u < SB / 4; ++u) {
       const f32x4_t v = {(float)(a[4 * u] * inv), (float)(a[4 * u + 1] * inv), (float)(a[4 * u + 2] * inv), (float)(a[4 * u + 3] * inv)};
       *reinterpret_cast<f32x4_t*>(orow + 4 * u) = v;
     }
-    if (lse && sub == 0) lse[(size_t)h * n_queries + r0 + qi] = L > 0.0 ? (float)(M + log(L)) : -INFINITY;
+    if (lse && sub == 0) lse[(size_t)h * n_queries + r0 + qi] = L > 0 ? (float)(M + log((double)L)) : -INFINITY;
   }
 }
 
