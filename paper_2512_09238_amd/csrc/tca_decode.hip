@@ -272,7 +272,8 @@ __device__ __forceinline__ void merge_partials(float (&m)[NQ], float (&l)[NQ], f
 // kPartWaves * 16 * NQ * (D/16 + 2) floats.  Called by a whole workgroup.
 // T: type of the queries; KV: storage type of the rows (T itself, or fp8_t with one float scale per
 // row in kscale / vscale, indexed like the rows).
-template <typename T, typename KV, int D, int NQ, typename Visible>
+// UNR: rows a group has requested ahead and as many it works on.
+template <typename T, typename KV, int D, int NQ, int UNR, typename Visible>
 __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const KV* __restrict__ vbase,
                                              const float* __restrict__ kscale, const float* __restrict__ vscale,
                                              int r_begin, int r_cap, Visible visible, const T* __restrict__ q0, double scale,
@@ -319,7 +320,7 @@ __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const
   constexpr float kSlack = 8.f;
   // Rows are fetched one iteration ahead of their use (kUnr rows of K and of V per group,
   // kept as loaded until then), so that a lane has 2*kUnr loads in flight while it computes.
-  constexpr int kUnr = 2;                              // (4 for the FP8 rows, half the bytes each, measured no faster)
+  constexpr int kUnr = UNR;
   using Raw = RawSlice<KV, EL>;
   Raw kr[kUnr], vr[kUnr];
   float ksc[kUnr], vsc[kUnr];                          // row scales (FP8 rows only)
@@ -608,6 +609,11 @@ __global__ __launch_bounds__(kPartThreads, sizeof(KV) == 1 && D == 128 && GW == 
   __shared__ float red[kPartWaves * 16 * NMAX * (EL + 2)];
   constexpr bool kMfma = sizeof(KV) <= 2 && D == 128;  // rows that partial_rows_mfma takes
   __shared__ __attribute__((aligned(16))) unsigned char tiles[kMfma && NMAX > 1 ? kPartWaves * kMfmaTileBytes + NMAX * 256 : 16];
+  // FP8 rows are 8 bytes a lane: where the rings' body leaves fewer than four waves a SIMD (groups of more than 4 queries), four
+  // rows ahead make up for the missing waves' loads.  us with two / with four: 64 heads, 2 x 32000 tokens 47.5 / 45.5, 16 x
+  // 60000 571.7 / 553.0; with four waves (32 heads) 8 x 30011 87.4 / 86.7, 16 x 60000 279.6 / 280.8; 4 heads of 64 elements 16
+  // x 60000 41.8 / 42.9.
+  constexpr int kRegionUnr = sizeof(KV) == 1 && D == 128 && GQ == 1 && GW > 4 ? 4 : 2;
   const int id = blockIdx.x, s = blockIdx.y;
   const int Hs = Hq / GQ;
   const int64_t Tpos = c.length[s];
@@ -648,7 +654,7 @@ __global__ __launch_bounds__(kPartThreads, sizeof(KV) == 1 && D == 128 && GW == 
       partial_rows_mfma<KV, GQ>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base, c.Vg_scale + base,
                                 r_begin, r_begin + len, visible, q0, scale, out, out_head, red, tiles);
     else
-      partial_rows<T, KV, D, GQ>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base,
+      partial_rows<T, KV, D, GQ, kRegionUnr>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base,
                                  c.Vg_scale + base, r_begin, r_begin + len, visible, q0, scale, out, out_head, red);
   } else {
     const int kvh = id / dh.ring_units, slot = id - kvh * dh.ring_units, h0 = kvh * GW;
@@ -669,7 +675,7 @@ __global__ __launch_bounds__(kPartThreads, sizeof(KV) == 1 && D == 128 && GW == 
       partial_rows_mfma<KV, GW>((const KV*)c.ringK + base * D, (const KV*)c.ringV + base * D, c.ringK_scale + base,
                                 c.ringV_scale + base, r_begin, r_end, visible, q0, scale, out, out_head, red, tiles);
     else
-      partial_rows<T, KV, D, GW>((const KV*)c.ringK + base * D, (const KV*)c.ringV + base * D, c.ringK_scale + base,
+      partial_rows<T, KV, D, GW, 2>((const KV*)c.ringK + base * D, (const KV*)c.ringV + base * D, c.ringK_scale + base,
                                  c.ringV_scale + base, r_begin, r_end, visible, q0, scale, out, out_head, red);
   }
 }

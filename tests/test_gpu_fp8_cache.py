@@ -50,7 +50,14 @@ FP8_CASES = [
 ]
 
 
-@pytest.mark.parametrize("case", FP8_CASES, ids=lambda c: f"Hq{c[0]}-Hkv{c[1]}-d{c[2]}-L{c[3]}-b{c[4]}-w{c[5]}-n{c[6]}{'-shared' if c[7] else ''}")
+FP8_WIDE_CASES = [
+    (8, 1, 128, 700, 32, 128, 40, False, 67),         # groups of more than four: four region rows a lane group ahead, ragged ends
+    (5, 1, 128, 395, 16, 64, 20, False, 68),
+    (8, 1, 128, 600, 32, 96, 40, True, 69),
+]
+
+
+@pytest.mark.parametrize("case", FP8_CASES + FP8_WIDE_CASES, ids=lambda c: f"Hq{c[0]}-Hkv{c[1]}-d{c[2]}-L{c[3]}-b{c[4]}-w{c[5]}-n{c[6]}{'-shared' if c[7] else ''}")
 def test_fp8_cache_bytes_and_decode_match_oracle(tb, bufs, case):
     Hq, Hkv, d, L, b, w, steps, share, seed = case
     print("case", case, flush=True)
