@@ -557,8 +557,8 @@ __device__ __forceinline__ void partial_rows_mfma(const KV* __restrict__ kbase, 
     }
     float p[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      p[i] = (holder && s2[i] > -INFINITY) ? __builtin_amdgcn_exp2f(s2[i] - m_mine) : 0.f;
+    for (int i = 0; i < 4; ++i) {                    // (a score that is NaN has a term, NaN: only those of -inf, rows past the end among them, have none)
+      p[i] = (holder && s2[i] != -INFINITY) ? __builtin_amdgcn_exp2f(s2[i] - m_mine) : 0.f;
       l_mine += p[i];
     }
     if (holder) {

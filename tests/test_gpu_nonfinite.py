@@ -221,3 +221,99 @@ def test_calibration_shows_a_nan_key(tb, bufs, dtype, d, L):
     for name in ("a", "cand_idx", "p_star", "fallback"):
         assert np.array_equal(got[name][2:], clean[name][2:]), name
     assert np.array_equal(got["n"], clean["n"])
+
+
+DECODE_CASES = [
+    # Hq, Hkv, d, shared, rows: every body a step's rows go through, by their type, their length and the queries they meet
+    (8, 2, 128, False, "bf16"),
+    (8, 2, 128, True, "bf16"),
+    (8, 2, 128, False, "fp8"),
+    (8, 1, 128, False, "fp8"),
+    (6, 2, 128, True, "fp8"),
+    (4, 4, 128, False, "fp8"),
+    (6, 2, 64, False, "bf16"),
+    (4, 2, 64, True, "fp8"),
+    (4, 1, 64, False, "f32"),
+]
+DECODE_L, DECODE_W, DECODE_ROWS = 2003, 160, 300
+
+
+def decode_setup(tb, bufs, case):
+    """A cache of two sequences of DECODE_L tokens, DECODE_ROWS rows a region (the last 20 still inside the window), and one
+    step's queries, equal for all heads so that a key row can be set against all of them at once."""
+    Hq, Hkv, d, share, rows = case
+    fp8 = rows == "fp8"
+    prm = H.params_for(tb, Hq, Hkv, d, 16, DECODE_W, "f32" if rows == "f32" else "bf16", share=share)
+    Hs = tb.tca_selection_heads(prm)
+    g = torch.Generator(device="cuda").manual_seed(67)
+    c = bufs.DecodeCache(prm, 2, np.full(Hs, DECODE_ROWS + 5), kv_format=tb.TCA_KV_FP8 if fp8 else tb.TCA_KV_NATIVE)
+    for t in (c.Kg, c.Vg, c.ringK, c.ringV):
+        if fp8:                                                      # codes of finite numbers
+            t.copy_(torch.randint(0, 0x78, t.shape, generator=g, device="cuda") | torch.randint(0, 2, t.shape, generator=g, device="cuda") << 7)
+        else:
+            t.copy_(torch.randn(t.shape, generator=g, device="cuda"))
+    for t in (c.Kg_scale, c.Vg_scale, c.ringK_scale, c.ringV_scale):
+        if fp8:
+            t.copy_(torch.rand(t.shape, generator=g, device="cuda") * 0.01 + 0.001)
+    c.length.fill_(DECODE_L)
+    c.n_rows.fill_(DECODE_ROWS)
+    rng = np.random.default_rng(68)
+    for s in range(2):
+        for n in range(Hs):
+            o = int(c.offs[n])
+            old = np.sort(rng.choice(DECODE_L - DECODE_W, DECODE_ROWS - 20, replace=False))
+            new = np.sort(rng.choice(np.arange(DECODE_L - DECODE_W + 1, DECODE_L), 20, replace=False))
+            c.idx[s, o:o + DECODE_ROWS] = torch.from_numpy(np.append(old, new).astype(np.int32)).cuda()
+    dt = torch.float32 if rows == "f32" else torch.bfloat16
+    q = torch.randn(2, 1, d, generator=g, device="cuda").expand(2, Hq, d).to(dt).contiguous()
+    q = torch.where(q == 0, torch.ones_like(q), q)
+    kn, vn = (torch.randn(2, Hkv, d, generator=g, device="cuda").to(dt) for _ in range(2))
+    P = np.stack([tb.tca_config_from_budget(16, 1.0, 0.4)] * Hs)
+
+    def step():
+        c.length.fill_(DECODE_L)                                     # (no block ends at this position: the regions stay)
+        O = torch.full_like(q, 7.0)
+        tb.tca_decode(prm, c.view, c.offs, q, kn, vn, P, O, bufs.workspace(tb.tca_decode_workspace_bytes(prm, 2, c.max_head_rows)))
+        torch.cuda.synchronize()
+        return O
+    return c, q, step
+
+
+def decode_row(c, case, where, row):
+    """Row `row` of KV head 0's ring or of the first region, of sequence 1: K, its scale (FP8), and which heads see it."""
+    Hq, Hkv, d, share, rows = case
+    bad = torch.zeros(2, Hq, dtype=torch.bool)
+    G = Hq // Hkv
+    if where == "ring":
+        bad[1, :G] = True
+        return c.ringK[1, 0, row], None if c.ringK_scale is None else c.ringK_scale[1, 0], bad
+    bad[1, :G if share else 1] = row < DECODE_ROWS - 20
+    return c.Kg[1, row], None if c.Kg_scale is None else c.Kg_scale[1], bad
+
+
+# rows at the start, inside and at the end of a chunk; the last one of a region is still inside the window, where nobody sees it
+DECODE_AT = [("ring", 0), ("ring", 77), ("ring", 159), ("region", 0), ("region", 130), ("region", 279), ("region", 290)]
+
+
+@pytest.mark.parametrize("at", DECODE_AT, ids=lambda a: f"{a[0]}{a[1]}")
+@pytest.mark.parametrize("case", DECODE_CASES, ids=lambda c: f"Hq{c[0]}-Hkv{c[1]}-d{c[2]}-share{c[3]}-{c[4]}")
+def test_decode_shows_a_nan_key_where_it_is_seen(tb, bufs, case, at):
+    """A NaN in a key row of the ring or of a region (FP8: a NaN code, or a NaN scale) makes the outputs of the heads that see
+    the row NaN; every other head keeps every bit."""
+    print("case", case, at, flush=True)
+    c, _, step = decode_setup(tb, bufs, case)
+    clean = step()
+    assert torch.isfinite(clean).all()
+    k, scale, bad = decode_row(c, case, *at)
+    kept = k.clone()
+    for what in ("element", "scale"):
+        if what == "element":
+            k[5] = 0x7F if scale is not None else float("nan")
+        elif scale is None:
+            break
+        else:
+            k.copy_(kept)
+            scale[at[1]] = float("nan")
+        O = step().cpu()
+        assert O[bad].isnan().all(), what
+        assert torch.equal(O[~bad], clean.cpu()[~bad]), what
