@@ -27,6 +27,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cfloat>
 #include <functional>
 #include <type_traits>
 
@@ -307,7 +308,7 @@ __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const
   float m[NQ], l[NQ], acc[NQ][EL];
 #pragma unroll
   for (int g = 0; g < NQ; ++g) {
-    m[g] = -INFINITY;
+    m[g] = -FLT_MAX;                                   // finite: a first logit of -inf has the term 0, not NaN
     l[g] = 0.f;
 #pragma unroll
     for (int e = 0; e < EL; ++e) acc[g][e] = 0.f;
@@ -380,7 +381,7 @@ __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const
         if (ok[u]) {
           if (sc > (logit_t)m[g] + (logit_t)kSlack) {
             const float m_new = sizeof(KV) == 4 ? ceilf((float)sc) : (float)sc;
-            const float corr = __builtin_amdgcn_exp2f(m[g] - m_new);    // 0 on the first row (m = -inf)
+            const float corr = __builtin_amdgcn_exp2f(m[g] - m_new);    // 0 on the first row (m = -FLT_MAX)
             l[g] *= corr;
 #pragma unroll
             for (int e = 0; e < EL; ++e) acc[g][e] *= corr;

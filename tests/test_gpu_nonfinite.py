@@ -317,3 +317,18 @@ def test_decode_shows_a_nan_key_where_it_is_seen(tb, bufs, case, at):
         O = step().cpu()
         assert O[bad].isnan().all(), what
         assert torch.equal(O[~bad], clean.cpu()[~bad]), what
+
+
+@pytest.mark.parametrize("at", [("ring", 0), ("ring", 77), ("region", 0), ("region", 130)], ids=lambda a: f"{a[0]}{a[1]}")
+@pytest.mark.parametrize("case", [c for c in DECODE_CASES if c[4] != "fp8"], ids=lambda c: f"Hq{c[0]}-Hkv{c[1]}-d{c[2]}-share{c[3]}-{c[4]}")
+def test_decode_gives_a_logit_of_minus_infinity_no_weight(tb, bufs, case, at):
+    """Wherever in a chunk the row lies: every output is, bit for bit, that of a logit so small that its term is zero."""
+    print("case", case, at, flush=True)
+    c, q, step = decode_setup(tb, bufs, case)
+    k, _, bad = decode_row(c, case, *at)
+    outs = []
+    for far in (1e3, float("inf")):
+        k.copy_(-torch.sign(q[1, 0]) * far)
+        outs.append(step())
+    assert bad.any() and torch.isfinite(outs[0]).all()
+    assert torch.equal(outs[0], outs[1])
