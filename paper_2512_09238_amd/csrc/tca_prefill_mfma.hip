@@ -1382,7 +1382,11 @@ static int64_t plan_split(SplitPlan& sp, const tca_params* prm, const int64_t* o
 struct WgShape { int nw, qb; };
 // workgroups of it an XCD runs at a time: 32 CUs, one eight-wave workgroup, one of four waves with a SIMD each, or two of four waves
 static int xcd_slots(WgShape sh) { return sh.nw == 8 || sh.qb == 2 ? 32 : 64; }
-static WgShape choose_shape(const tca_params* prm, int64_t n_queries, bool gather) {
+// v_aligned: V and Vg are 16-byte aligned.  Where they are not (the entry points take any element for a start) the direct
+// copies into LDS cannot be relied on, which the four-wave shapes make of V itself: such a call takes eight waves, whose
+// pre-pass reads V with plain loads.
+static WgShape choose_shape(const tca_params* prm, int64_t n_queries, bool gather, bool v_aligned) {
+  if (!v_aligned) return {8, 1};
   const int variant = prefill_variant();
   // With rows fetched through idx eight waves from 1024 items of 256 queries on.  Otherwise the pre-pass (uses_transposed_v)
   // must be worth it too: the query tiles that read a tile of V^T must be many.  Four waves against eight, 22 tiles (5446
@@ -1442,7 +1446,7 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
   // queries (one wave per SIMD, every LDS fragment feeds two MFMAs, half the LDS reads) stay
   // selectable through the diagnostics switch: measured 5-8 % slower on 128K tokens, because a
   // lone wave cannot issue its vector, LDS and scalar instructions fast enough beside the MFMAs.
-  const WgShape sh = choose_shape(prm, n_queries, gather);
+  const WgShape sh = choose_shape(prm, n_queries, gather, (((uintptr_t)V | (uintptr_t)Vg) & 15) == 0);
   SplitPlan sp;
   {
     const int64_t n_wg = choose_split(sp, prm, offs, q_pos0, n_queries, part, sh, ws_bytes > mw.need ? ws_bytes - mw.need : 0);
@@ -1497,7 +1501,7 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
 int64_t prefill_mfma_xcd_plan(const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries, int part,
                               bool gather, int32_t* start_out) {
   if ((prm->n_q_heads & 7) != 0) return -1;
-  const WgShape sh = choose_shape(prm, n_queries, gather);
+  const WgShape sh = choose_shape(prm, n_queries, gather, true);
   PrefillHeads ph;
   const int64_t longest = plan_xcds(ph, prm, offs, q_pos0, n_queries, sh.nw * sh.qb * 32, part, xcd_slots(sh));
   for (int x = 0; x <= 8; ++x) start_out[x] = ph.xcd_start[x];
@@ -1506,7 +1510,7 @@ int64_t prefill_mfma_xcd_plan(const tca_params* prm, const int64_t* offs, int64_
 
 int prefill_mfma_walk(const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries, int part, bool gather,
                       size_t ws_bytes, int32_t* heads_out, int64_t* chunks_out) {
-  const WgShape sh = choose_shape(prm, n_queries, gather);
+  const WgShape sh = choose_shape(prm, n_queries, gather, true);
   const size_t need = prefill_mfma_workspace_need(prm, n_queries, offs[sel_heads(prm)]);
   SplitPlan sp;
   const int64_t chunks = choose_split(sp, prm, offs, q_pos0, n_queries, part, sh, ws_bytes > need ? ws_bytes - need : 0);

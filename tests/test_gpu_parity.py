@@ -759,6 +759,56 @@ def test_v_tiles_end_where_the_rows_do(tb, bufs, case):
             assert np.abs(got[h][rows] - ref[h]).max() <= H.TOL["bf16"], f"variant {variant}, head {h}"
 
 
+V_START_CASES = [
+    # Hq, Hkv, d, tokens, first query, gather-free: whole, and few queries behind a context (which an aligned call cuts into chunks)
+    (8, 2, 128, 700, 0, False),
+    (8, 2, 64, 3000, 2900, False),
+    (3, 1, 128, 900, 850, True),
+]
+
+
+@pytest.mark.parametrize("off", [1, 4], ids=lambda o: f"element{o}")
+@pytest.mark.parametrize("case", V_START_CASES, ids=lambda c: f"Hq{c[0]}-Hkv{c[1]}-d{c[2]}-L{c[3]}-q{c[4]}-free{c[5]}")
+def test_v_may_start_at_any_element(tb, bufs, case, off):
+    """V, Vg or both at an address that is no multiple of 16: what the eight-wave shape, which reads V with plain loads, makes
+    of the same rows at one that is, bit for bit."""
+    Hq, Hkv, d, L, q0, free = case
+    print("case", case, off, flush=True)
+    w, kept = 128, 300
+    x = wl.prefill_inputs("lowrank", Hq, Hkv, d, L, "bf16", 99)
+    prm = H.params_for(tb, Hq, Hkv, d, 32, w, "bf16")
+    rng = np.random.default_rng(100)
+    Qd, Kd, Vd = (bufs.to_device(x[k]) for k in ("Q", "K", "V"))
+    gb = bufs.GlobalBuffers(prm, np.full(Hq, kept))
+    for h in range(Hq):
+        o, at = int(gb.offs[h]), torch.from_numpy(np.sort(rng.choice(L - w, kept, replace=False))).cuda()
+        gb.idx[o:o + kept] = at.to(torch.int32)
+        gb.Kg[o:o + kept], gb.Vg[o:o + kept] = Kd[h // (Hq // Hkv), at], Vd[h // (Hq // Hkv), at]
+        gb.n_rows[h] = kept
+
+    def moved(t):
+        room = torch.zeros(t.numel() + off, dtype=t.dtype, device="cuda")
+        room[off:] = t.reshape(-1)
+        return room[off:].view(t.shape)
+    Qt = Qd[:, q0:].contiguous()
+    ws = bufs.workspace(tb.tca_prefill_workspace_bytes(prm, L - q0, int(gb.offs[-1])))
+
+    def call(V, Vg):
+        O = torch.full_like(Qt, float("nan"))
+        tb.tca_prefill(prm, Qt, q0, L - q0, Kd, V, L, gb.idx, None if free else gb.Kg, None if free else Vg, gb.offs, gb.n_rows,
+                       O, None, ws)
+        torch.cuda.synchronize()
+        return O
+    tb.tca_diag_prefill_variant(3)
+    try:
+        want = call(Vd, gb.Vg)
+    finally:
+        tb.tca_diag_prefill_variant(0)
+    assert torch.isfinite(want).all()
+    for V, Vg in ((moved(Vd), gb.Vg), (Vd, moved(gb.Vg)), (moved(Vd), moved(gb.Vg)))[:1 if free else 3]:
+        assert torch.equal(call(V, Vg), want)
+
+
 F32_CASES = [
     # Hq, Hkv, d, L, q0, w, share, gather-free: both key splits of the fp32 kernel, at the edges of its tiles
     (4, 1, 64, 1300, 1283, 128, False, False),     # 17 queries: a second tile of one row, keys dealt to four waves
