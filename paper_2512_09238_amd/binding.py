@@ -58,50 +58,47 @@ class tca_cache(C.Structure):
 
 _P = C.POINTER
 _dbl_p, _i64_p, _i32_p = _P(C.c_double), _P(C.c_int64), _P(C.c_int32)
-# How host arrays are declared below: an address (see _np), which costs half a microsecond less to make than a typed
-# pointer; typed pointers and byref() are taken as well.
-_dbls = _i64s = _i32s = C.c_void_p
 
 EXPORTS = {
     "tca_selection_heads": (C.c_int, [_P(tca_params)]),
     "tca_num_counts": (C.c_int, [C.c_int]),
-    "tca_make_candidates": (C.c_int, [C.c_int, C.c_int, C.c_double, _dbls]),
-    "tca_config_from_budget": (C.c_int, [C.c_int, C.c_double, C.c_double, _dbls]),
-    "tca_psi_counts": (C.c_int, [C.c_int, C.c_int64, _dbls, _i64s]),
-    "tca_select_rows": (C.c_int64, [_P(tca_params), C.c_int64, _dbls, _i64s]),
-    "tca_decode_budget": (C.c_int, [C.c_int, _dbls]),
+    "tca_make_candidates": (C.c_int, [C.c_int, C.c_int, C.c_double, _dbl_p]),
+    "tca_config_from_budget": (C.c_int, [C.c_int, C.c_double, C.c_double, _dbl_p]),
+    "tca_psi_counts": (C.c_int, [C.c_int, C.c_int64, _dbl_p, _i64_p]),
+    "tca_select_rows": (C.c_int64, [_P(tca_params), C.c_int64, _dbl_p, _i64_p]),
+    "tca_decode_budget": (C.c_int, [C.c_int, _dbl_p]),
     "tca_select_workspace_bytes": (C.c_size_t, [_P(tca_params), C.c_int64]),
     "tca_prefill_workspace_bytes": (C.c_size_t, [_P(tca_params), C.c_int64, C.c_int64]),
     "tca_decode_workspace_bytes": (C.c_size_t, [_P(tca_params), C.c_int, C.c_int64]),
     "tca_calibrate_workspace_bytes": (C.c_size_t, [_P(tca_params), C.c_int64, C.c_int]),
     "tca_probe_workspace_bytes": (C.c_size_t, []),
-    "tca_probe_mfma": (C.c_int, [C.c_int, C.c_int, _dbls, _dbls, C.c_void_p, C.c_size_t, C.c_void_p]),
+    "tca_probe_mfma": (C.c_int, [C.c_int, C.c_int, _dbl_p, _dbl_p, C.c_void_p, C.c_size_t, C.c_void_p]),
     "tca_select": (C.c_int, [_P(tca_params), C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_int64,
-                             C.c_int64, _dbls, _i64s, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
+                             C.c_int64, _dbl_p, _i64_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                              C.c_void_p, C.c_size_t, C.c_void_p]),
     "tca_prefill": (C.c_int, [_P(tca_params), C.c_void_p, C.c_int64, C.c_int64, C.c_void_p, C.c_void_p,
-                              C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, _i64s, C.c_void_p,
+                              C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, _i64_p, C.c_void_p,
                               C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
     "tca_prefill_part": (C.c_int, [_P(tca_params), C.c_int, C.c_void_p, C.c_int64, C.c_int64, C.c_void_p, C.c_void_p,
-                                   C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, _i64s, C.c_void_p,
+                                   C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, _i64_p, C.c_void_p,
                                    C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
     "tca_prefill_merge": (C.c_int, [_P(tca_params), C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                                     C.c_void_p, C.c_void_p]),
     "tca_select_prefill_overlapped": (C.c_int, [_P(tca_params), C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
-                                                C.c_int64, C.c_int64, C.c_int64, _dbls, _i64s, C.c_void_p,
+                                                C.c_int64, C.c_int64, C.c_int64, _dbl_p, _i64_p, C.c_void_p,
                                                 C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                                                 C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p, C.c_size_t,
                                                 C.c_void_p, C.c_void_p]),
     "tca_cache_load_window": (C.c_int, [_P(tca_params), _P(tca_cache), C.c_int, C.c_void_p, C.c_void_p,
                                         C.c_int64, C.c_int64, C.c_void_p]),
     "tca_cache_load_global": (C.c_int, [_P(tca_params), _P(tca_cache), C.c_int, C.c_void_p, C.c_void_p, C.c_void_p,
-                                        _i64s, C.c_void_p, C.c_void_p]),
-    "tca_decode": (C.c_int, [_P(tca_params), _P(tca_cache), _i64s, C.c_void_p, C.c_void_p, C.c_void_p,
-                             _dbls, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
-    "tca_decode_static": (C.c_int, [_P(tca_params), _P(tca_cache), _i64s, C.c_void_p, C.c_void_p, C.c_void_p,
-                                    _dbls, C.c_void_p, C.c_void_p]),
+                                        _i64_p, C.c_void_p, C.c_void_p]),
+    "tca_decode": (C.c_int, [_P(tca_params), _P(tca_cache), _i64_p, C.c_void_p, C.c_void_p, C.c_void_p,
+                             _dbl_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
+    "tca_decode_static": (C.c_int, [_P(tca_params), _P(tca_cache), _i64_p, C.c_void_p, C.c_void_p, C.c_void_p,
+                                    _dbl_p, C.c_void_p, C.c_void_p]),
     "tca_calibrate_budgets": (C.c_int, [_P(tca_params), C.c_void_p, C.c_void_p, C.c_int64, C.c_int,
-                                        C.c_double, C.c_double, _dbls, _i32s, _dbls, _i64s, _i32s,
+                                        C.c_double, C.c_double, _dbl_p, _i32_p, _dbl_p, _i64_p, _i32_p,
                                         C.c_void_p, C.c_size_t, C.c_void_p]),
     "tca_diag_prefill_clocks": (None, [C.c_int]),
     "tca_diag_prefill_variant": (C.c_int, [C.c_int]),
@@ -109,7 +106,7 @@ EXPORTS = {
     "tca_diag_prefill_walk": (C.c_int, [_P(tca_params), C.c_void_p, C.c_int64, C.c_int64, C.c_int, C.c_int, C.c_size_t,
                                         C.c_void_p, C.c_void_p]),
     "tca_calibrate_layers": (C.c_int, [_P(tca_params), C.c_int, _P(C.c_void_p), _P(C.c_void_p), C.c_int64, C.c_int,
-                                       C.c_double, C.c_double, _dbls, _i32s, _dbls, _i64s, _i32s,
+                                       C.c_double, C.c_double, _dbl_p, _i32_p, _dbl_p, _i64_p, _i32_p,
                                        C.c_void_p, C.c_size_t, C.c_void_p]),
     "tca_rope": (C.c_int, [_P(tca_params), C.c_void_p, C.c_int, C.c_int64, C.c_int64, C.c_double, C.c_int, C.c_void_p]),
     "tca_qkv_project": (C.c_int, [_P(tca_params), C.c_void_p, C.c_int64, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p,
@@ -117,15 +114,21 @@ EXPORTS = {
     "tca_strerror": (C.c_char_p, [C.c_int]),
     "tca_last_error": (C.c_char_p, []),
 }
+# The same functions twice: `lib` takes host arrays as typed pointers and refuses those of another type; the wrappers
+# below, which have converted their arrays, go through `_lib`, which takes addresses (see _np): a typed pointer costs half a
+# microsecond more to make, on every array of every call of a decoding step.
+_lib = C.CDLL(LIB_PATH)
 for _name, (_res, _args) in EXPORTS.items():
     _f = getattr(lib, _name)
     _f.restype, _f.argtypes = _res, _args
+    _f = getattr(_lib, _name)
+    _f.restype, _f.argtypes = _res, [C.c_void_p if _a in (_dbl_p, _i64_p, _i32_p) else _a for _a in _args]
 
 
 class TcaError(RuntimeError):
     def __init__(self, code: int):
         self.code = code
-        super().__init__(f"{lib.tca_strerror(code).decode()} ({code}): {lib.tca_last_error().decode()}")
+        super().__init__(f"{_lib.tca_strerror(code).decode()} ({code}): {_lib.tca_last_error().decode()}")
 
 
 def _check(rc: int) -> int:
@@ -167,58 +170,58 @@ def make_params(n_q_heads, n_kv_heads, head_dim, block, window, dtype, alpha=0.5
 
 # ---------------------------------------------------------------- host --
 def tca_selection_heads(prm: tca_params) -> int:
-    return _check(lib.tca_selection_heads(C.byref(prm)))
+    return _check(_lib.tca_selection_heads(C.byref(prm)))
 
 
 def tca_num_counts(b: int) -> int:
-    return _check(lib.tca_num_counts(b))
+    return _check(_lib.tca_num_counts(b))
 
 
 def tca_make_candidates(b: int, M: int, sigma: float) -> np.ndarray:
     out = np.empty((M, tca_num_counts(b)), np.float64)
-    _check(lib.tca_make_candidates(b, M, sigma, _np(out)))
+    _check(_lib.tca_make_candidates(b, M, sigma, _np(out)))
     return out
 
 
 def tca_config_from_budget(b: int, sigma: float, frac: float) -> np.ndarray:
     out = np.empty(tca_num_counts(b), np.float64)
-    _check(lib.tca_config_from_budget(b, sigma, frac, _np(out)))
+    _check(_lib.tca_config_from_budget(b, sigma, frac, _np(out)))
     return out
 
 
 def tca_psi_counts(b: int, m: int, p) -> np.ndarray:
     p = _host(p, np.float64)
     out = np.empty(tca_num_counts(b), np.int64)
-    _check(lib.tca_psi_counts(b, m, _np(p), _np(out)))
+    _check(_lib.tca_psi_counts(b, m, _np(p), _np(out)))
     return out
 
 
 def tca_select_rows(prm: tca_params, n_blocks: int, p):
     p = _host(p, np.float64)
     rows = np.empty(tca_selection_heads(prm), np.int64)
-    total = _check(lib.tca_select_rows(C.byref(prm), n_blocks, _np(p), _np(rows)))
+    total = _check(_lib.tca_select_rows(C.byref(prm), n_blocks, _np(p), _np(rows)))
     return total, rows
 
 
 def tca_decode_budget(b: int, p) -> int:
     p = _host(p, np.float64)
-    return _check(lib.tca_decode_budget(b, _np(p)))
+    return _check(_lib.tca_decode_budget(b, _np(p)))
 
 
 def tca_select_workspace_bytes(prm, n_tokens: int) -> int:
-    return int(lib.tca_select_workspace_bytes(C.byref(prm), n_tokens))
+    return int(_lib.tca_select_workspace_bytes(C.byref(prm), n_tokens))
 
 
 def tca_prefill_workspace_bytes(prm, n_queries: int, cap_rows: int) -> int:
-    return int(lib.tca_prefill_workspace_bytes(C.byref(prm), n_queries, cap_rows))
+    return int(_lib.tca_prefill_workspace_bytes(C.byref(prm), n_queries, cap_rows))
 
 
 def tca_decode_workspace_bytes(prm, batch: int, max_head_rows: int) -> int:
-    return int(lib.tca_decode_workspace_bytes(C.byref(prm), batch, max_head_rows))
+    return int(_lib.tca_decode_workspace_bytes(C.byref(prm), batch, max_head_rows))
 
 
 def tca_calibrate_workspace_bytes(prm, L_cal: int, M: int) -> int:
-    return int(lib.tca_calibrate_workspace_bytes(C.byref(prm), L_cal, M))
+    return int(_lib.tca_calibrate_workspace_bytes(C.byref(prm), L_cal, M))
 
 
 # -------------------------------------------------------------- device --
@@ -232,7 +235,7 @@ def tca_select(prm, q_last, K, V, kv_stride, pos0, n_tokens, p, offs, n_rows, id
     p = _host(p, np.float64)
     offs = _host(offs, np.int64)
     wsp, wsb = _ws_args(ws)
-    _check(lib.tca_select(C.byref(prm), _dp(q_last), _dp(K), _dp(V), kv_stride, pos0, n_tokens,
+    _check(_lib.tca_select(C.byref(prm), _dp(q_last), _dp(K), _dp(V), kv_stride, pos0, n_tokens,
                           _np(p), _np(offs), _dp(n_rows), _dp(idx),
                           _dp(Kg), _dp(Vg), wsp, wsb, _stream(stream)))
 
@@ -240,7 +243,7 @@ def tca_select(prm, q_last, K, V, kv_stride, pos0, n_tokens, p, offs, n_rows, id
 def tca_prefill(prm, Q, q_pos0, n_queries, K, V, kv_stride, idx, Kg, Vg, offs, n_rows, O, lse, ws, stream=None):
     offs = _host(offs, np.int64)
     wsp, wsb = _ws_args(ws)
-    _check(lib.tca_prefill(C.byref(prm), _dp(Q), q_pos0, n_queries, _dp(K), _dp(V), kv_stride, _dp(idx),
+    _check(_lib.tca_prefill(C.byref(prm), _dp(Q), q_pos0, n_queries, _dp(K), _dp(V), kv_stride, _dp(idx),
                            _dp(Kg), _dp(Vg), _np(offs), _dp(n_rows), _dp(O), _dp(lse),
                            wsp, wsb, _stream(stream)))
 
@@ -248,13 +251,13 @@ def tca_prefill(prm, Q, q_pos0, n_queries, K, V, kv_stride, idx, Kg, Vg, offs, n
 def tca_prefill_part(prm, part, Q, q_pos0, n_queries, K, V, kv_stride, idx, Kg, Vg, offs, n_rows, O, lse, ws, stream=None):
     offs = _host(offs, np.int64)
     wsp, wsb = _ws_args(ws)
-    _check(lib.tca_prefill_part(C.byref(prm), part, _dp(Q), q_pos0, n_queries, _dp(K), _dp(V), kv_stride, _dp(idx),
+    _check(_lib.tca_prefill_part(C.byref(prm), part, _dp(Q), q_pos0, n_queries, _dp(K), _dp(V), kv_stride, _dp(idx),
                                 _dp(Kg), _dp(Vg), _np(offs), _dp(n_rows), _dp(O), _dp(lse),
                                 wsp, wsb, _stream(stream)))
 
 
 def tca_prefill_merge(prm, n_queries, O_a, lse_a, O_b, lse_b, lse_out=None, stream=None):
-    _check(lib.tca_prefill_merge(C.byref(prm), n_queries, _dp(O_a), _dp(lse_a), _dp(O_b), _dp(lse_b), _dp(lse_out),
+    _check(_lib.tca_prefill_merge(C.byref(prm), n_queries, _dp(O_a), _dp(lse_a), _dp(O_b), _dp(lse_b), _dp(lse_out),
                                  _stream(stream)))
 
 
@@ -264,7 +267,7 @@ def tca_select_prefill_overlapped(prm, q_last, Q, K, V, kv_stride, pos0, n_token
     offs = _host(offs, np.int64)
     wsp, wsb = _ws_args(ws_select)
     wpp, wpb = _ws_args(ws_prefill)
-    _check(lib.tca_select_prefill_overlapped(C.byref(prm), _dp(q_last), _dp(Q), _dp(K), _dp(V), kv_stride, pos0,
+    _check(_lib.tca_select_prefill_overlapped(C.byref(prm), _dp(q_last), _dp(Q), _dp(K), _dp(V), kv_stride, pos0,
                                              n_tokens, _np(p), _np(offs),
                                              _dp(n_rows), _dp(idx), _dp(Kg), _dp(Vg), _dp(O), _dp(O_part),
                                              _dp(lse_parts), wsp, wsb, wpp, wpb, _stream(stream),
@@ -280,13 +283,13 @@ def make_cache(batch, cap_rows, idx, Kg, Vg, n_rows, ringK, ringV, length, kv_fo
 
 
 def tca_cache_load_window(prm, cache, seq, K, V, kv_stride, L, stream=None):
-    _check(lib.tca_cache_load_window(C.byref(prm), C.byref(cache), seq, _dp(K), _dp(V), kv_stride, L,
+    _check(_lib.tca_cache_load_window(C.byref(prm), C.byref(cache), seq, _dp(K), _dp(V), kv_stride, L,
                                      _stream(stream)))
 
 
 def tca_cache_load_global(prm, cache, seq, idx, Kg, Vg, offs, n_rows, stream=None):
     offs = _host(offs, np.int64)
-    _check(lib.tca_cache_load_global(C.byref(prm), C.byref(cache), seq, _dp(idx), _dp(Kg), _dp(Vg),
+    _check(_lib.tca_cache_load_global(C.byref(prm), C.byref(cache), seq, _dp(idx), _dp(Kg), _dp(Vg),
                                      _np(offs), _dp(n_rows), _stream(stream)))
 
 
@@ -294,7 +297,7 @@ def tca_decode(prm, cache, offs, q, k_new, v_new, p, O, ws, stream=None):
     p = _host(p, np.float64)
     offs = _host(offs, np.int64)
     wsp, wsb = _ws_args(ws)
-    _check(lib.tca_decode(C.byref(prm), C.byref(cache), _np(offs), _dp(q), _dp(k_new),
+    _check(_lib.tca_decode(C.byref(prm), C.byref(cache), _np(offs), _dp(q), _dp(k_new),
                           _dp(v_new), _np(p), _dp(O), wsp, wsb, _stream(stream)))
 
 
@@ -304,7 +307,7 @@ TCA_DECODE_STATIC_BYTES = 32 << 20
 def tca_decode_static(prm, cache, offs, q, k_new, v_new, p, O, stream=None):
     p = _host(p, np.float64)
     offs = _host(offs, np.int64)
-    _check(lib.tca_decode_static(C.byref(prm), C.byref(cache), _np(offs), _dp(q), _dp(k_new),
+    _check(_lib.tca_decode_static(C.byref(prm), C.byref(cache), _np(offs), _dp(q), _dp(k_new),
                                  _dp(v_new), _np(p), _dp(O), _stream(stream)))
 
 
@@ -317,7 +320,7 @@ def tca_calibrate_budgets(prm, Qcal, Kcal, L_cal, M, sigma, tau, ws, stream=None
     n = np.empty((Hq, M), np.int64)
     fb = np.empty(Hq, np.int32)
     wsp, wsb = _ws_args(ws)
-    _check(lib.tca_calibrate_budgets(C.byref(prm), _dp(Qcal), _dp(Kcal), L_cal, M, sigma, tau,
+    _check(_lib.tca_calibrate_budgets(C.byref(prm), _dp(Qcal), _dp(Kcal), L_cal, M, sigma, tau,
                                      _np(p_star), _np(cand),
                                      _np(a), _np(n),
                                      _np(fb), wsp, wsb, _stream(stream)))
@@ -336,7 +339,7 @@ def tca_calibrate_layers(prm, Qcals, Kcals, L_cal, M, sigma, tau, ws, stream=Non
     n = np.empty((nl, Hs, M), np.int64)
     fb = np.empty((nl, Hs), np.int32)
     wsp, wsb = _ws_args(ws)
-    _check(lib.tca_calibrate_layers(C.byref(prm), nl, qp, kp, L_cal, M, sigma, tau,
+    _check(_lib.tca_calibrate_layers(C.byref(prm), nl, qp, kp, L_cal, M, sigma, tau,
                                     _np(p_star), _np(cand),
                                     _np(a), _np(n), _np(fb),
                                     wsp, wsb, _stream(stream)))
@@ -344,43 +347,43 @@ def tca_calibrate_layers(prm, Qcals, Kcals, L_cal, M, sigma, tau, ws, stream=Non
 
 
 def tca_rope(prm, X, n_heads, n_rows, pos0, base=10000.0, pairing=TCA_ROPE_HALF, stream=None):
-    _check(lib.tca_rope(C.byref(prm), _dp(X), n_heads, n_rows, pos0, base, pairing, _stream(stream)))
+    _check(_lib.tca_rope(C.byref(prm), _dp(X), n_heads, n_rows, pos0, base, pairing, _stream(stream)))
 
 
 def tca_qkv_project(prm, X, n_tokens, hidden, W, bias, Q, q_token_stride, q_head_stride, K, V, kv_token_stride,
                     kv_head_stride, stream=None):
-    _check(lib.tca_qkv_project(C.byref(prm), _dp(X), n_tokens, hidden, _dp(W), _dp(bias) if bias is not None else None,
+    _check(_lib.tca_qkv_project(C.byref(prm), _dp(X), n_tokens, hidden, _dp(W), _dp(bias) if bias is not None else None,
                                _dp(Q), q_token_stride, q_head_stride, _dp(K), _dp(V), kv_token_stride,
                                kv_head_stride, _stream(stream)))
 
 
 # --------------------------------------------------------- diagnostics --
 def tca_probe_workspace_bytes() -> int:
-    return int(lib.tca_probe_workspace_bytes())
+    return int(_lib.tca_probe_workspace_bytes())
 
 
 def tca_probe_mfma(random_operands: bool, iters: int, ws, stream=None):
     """Returns (TFLOP/s reached by a register-only bf16 MFMA loop, shader clock in GHz)."""
     tf, ghz = C.c_double(0.0), C.c_double(0.0)
     wsp, wsb = _ws_args(ws)
-    _check(lib.tca_probe_mfma(int(bool(random_operands)), int(iters), C.byref(tf), C.byref(ghz), wsp, wsb,
+    _check(_lib.tca_probe_mfma(int(bool(random_operands)), int(iters), C.byref(tf), C.byref(ghz), wsp, wsb,
                               _stream(stream)))
     return tf.value, ghz.value
 
 
 def tca_diag_prefill_clocks(enable: bool) -> None:
-    lib.tca_diag_prefill_clocks(int(bool(enable)))
+    _lib.tca_diag_prefill_clocks(int(bool(enable)))
 
 
 def tca_diag_prefill_variant(variant: int) -> None:
-    _check(lib.tca_diag_prefill_variant(int(variant)))
+    _check(_lib.tca_diag_prefill_variant(int(variant)))
 
 
 def tca_diag_prefill_xcd_plan(prm, offs, q_pos0: int, n_queries: int, part: int = 0, gather_free: bool = False):
     """Returns (start[9], workgroups): the ranges of the (head, query tile) sequence the eight XCDs take."""
     offs = np.ascontiguousarray(offs, dtype=np.int64)
     start = np.zeros(9, dtype=np.int32)
-    n = lib.tca_diag_prefill_xcd_plan(C.byref(prm), _np(offs), q_pos0, n_queries, part,
+    n = _lib.tca_diag_prefill_xcd_plan(C.byref(prm), _np(offs), q_pos0, n_queries, part,
                                       int(bool(gather_free)), _np(start))
     if n < 0:
         raise ValueError("tca_diag_prefill_xcd_plan: not a bf16 call with a head count that is a multiple of 8")
@@ -393,7 +396,7 @@ def tca_diag_prefill_walk(prm, offs, q_pos0: int, n_queries: int, ws_bytes: int,
     offs = np.ascontiguousarray(offs, dtype=np.int64)
     heads = np.zeros(prm.n_q_heads, dtype=np.int32)
     chunks = C.c_int64(-1)
-    order = lib.tca_diag_prefill_walk(C.byref(prm), _np(offs), q_pos0, n_queries, part,
+    order = _lib.tca_diag_prefill_walk(C.byref(prm), _np(offs), q_pos0, n_queries, part,
                                       int(bool(gather_free)), ws_bytes, _np(heads), C.byref(chunks))
     if order < 0 and chunks.value < 0:
         raise ValueError("tca_diag_prefill_walk: not a bf16 call, or invalid sizes")

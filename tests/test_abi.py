@@ -98,6 +98,22 @@ def test_argument_errors_are_codes_not_crashes():
     assert tb.tca_select_workspace_bytes(ok, 131072) > 4 * 131072
 
 
+def test_exports_refuse_host_arrays_of_another_type():
+    """The exports take their host arrays as pointers of the declared type: one of another type is refused by the binding
+    instead of being read as what it is not."""
+    import paper_2512_09238_amd.binding as tb
+    prm = tb.make_params(4, 2, 128, 128, 512, tb.TCA_BF16)
+    p, rows = np.full((4, 8), 1 / 8), np.zeros(4, np.int64)
+    as_f32, as_i32 = p.astype(np.float32), rows.astype(np.int32)
+    good_p, good_rows = p.ctypes.data_as(tb._dbl_p), rows.ctypes.data_as(tb._i64_p)
+    for pp, rr in ((as_f32.ctypes.data_as(ctypes.POINTER(ctypes.c_float)), good_rows), (good_p, as_i32.ctypes.data_as(tb._i32_p)),
+                   (p.ctypes.data, good_rows), (good_p, ctypes.byref(ctypes.c_int32(0)))):
+        with pytest.raises(ctypes.ArgumentError):
+            tb.lib.tca_select_rows(ctypes.byref(prm), 4, pp, rr)
+    assert tb.lib.tca_select_rows(ctypes.byref(prm), 4, good_p, good_rows) == rows.sum() > 0
+    assert np.array_equal(tb.tca_select_rows(prm, 4, as_f32)[1], rows)          # the wrappers convert
+
+
 def test_probe_rejects_bad_arguments_without_a_gpu():
     import paper_2512_09238_amd.binding as tb
     assert tb.tca_probe_workspace_bytes() >= 1024 * 24
