@@ -157,10 +157,12 @@ def _np(a):
 
 def _stream(stream):
     """The stream handle to launch on: the given one, or torch's current one.  The handle is asked for directly: a
-    torch.cuda.Stream object around it costs 3 us, as much as a launch, on every call of a decoding step."""
+    torch.cuda.Stream object around it costs 3 us, as much as a launch, on every call of a decoding step.  The function is
+    no public one of torch's: where there is none, the object's handle."""
     if stream is not None:
         return int(stream)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
 
 
 def make_params(n_q_heads, n_kv_heads, head_dim, block, window, dtype, alpha=0.5, scale=0.0,

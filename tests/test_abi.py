@@ -114,6 +114,20 @@ def test_exports_refuse_host_arrays_of_another_type():
     assert np.array_equal(tb.tca_select_rows(prm, 4, as_f32)[1], rows)          # the wrappers convert
 
 
+def test_current_stream_without_the_direct_query(monkeypatch):
+    import types
+
+    import torch
+
+    import paper_2512_09238_amd.binding as tb
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda dev: 100 + dev, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    assert tb._stream(None) == 103 and tb._stream(5) == 5
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert tb._stream(None) == 77 and tb._stream(5) == 5
+
+
 def test_probe_rejects_bad_arguments_without_a_gpu():
     import paper_2512_09238_amd.binding as tb
     assert tb.tca_probe_workspace_bytes() >= 1024 * 24
