@@ -401,7 +401,7 @@ __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const
   merge_partials<D, NQ>(m, l, acc, out, out_head, red);
 }
 
-// The same for bf16 and FP8 rows of 128 elements and NQ > 1 queries, with q.k on the matrix cores.
+// The same for bf16 rows of 128 elements and NQ > 1 queries, and FP8 rows and NQ > 2, with q.k on the matrix cores.
 // A wave takes 16 rows per iteration (its 16-lane group kb the rows 4kb .. 4kb+3).  K rows go
 // from registers into a wave-private LDS tile and come back in MFMA operand order (lane
 // (n, kb) = 8 consecutive elements of row n), so that four 16x16x32 MFMAs against the queries
@@ -419,8 +419,9 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float dec_f32x4_t;
 
 template <typename KV, int NQ, typename Visible>
 __device__ __forceinline__ void partial_rows_mfma(const KV* __restrict__ kbase, const KV* __restrict__ vbase,
-                                                  const float* __restrict__ kscale, const float* __restrict__ vscale, int r_begin, int r_cap, Visible visible, const bf16_t* __restrict__ q0, double scale,
-                                                  float* __restrict__ out, size_t out_head, float* red,
+                                                  const float* __restrict__ kscale, const float* __restrict__ vscale,
+                                                  int r_begin, int r_cap, Visible visible, const bf16_t* __restrict__ q0,
+                                                  double scale, float* __restrict__ out, size_t out_head, float* red,
                                                   unsigned char* tiles) {
   constexpr int D = 128, EL = 8;
   constexpr float kLog2e = 1.4426950408889634f;
@@ -608,7 +609,10 @@ __global__ __launch_bounds__(kPartThreads, sizeof(KV) == 1 && D == 128 && GW == 
   constexpr int EL = D / 16;
   constexpr int NMAX = GQ > GW ? GQ : GW;
   __shared__ float red[kPartWaves * 16 * NMAX * (EL + 2)];
-  constexpr bool kMfma = sizeof(KV) <= 2 && D == 128;  // rows that partial_rows_mfma takes
+  // Rows that partial_rows_mfma takes.  FP8 rows that meet two queries are faster without: us on vector units / on the matrix cores,
+  // rings only 1 x 8000 tokens 14.4 / 14.6, 4 x 12000 26.2 / 27.9, 8 x 30000 85.8 / 89.7, shared selection 1 x 100000 32.3 /
+  // 36.8, 8 x 30000 51.4 / 53.2, 16 x 60000 180 / 178; three queries, shared, 8 x 30000 67.5 / 56.6.
+  constexpr bool kMfma = D == 128 && (sizeof(KV) == 2 || (sizeof(KV) == 1 && GW > 2));
   __shared__ __attribute__((aligned(16))) unsigned char tiles[kMfma && NMAX > 1 ? kPartWaves * kMfmaTileBytes + NMAX * 256 : 16];
   // FP8 rows are 8 bytes a lane: where the rings' body leaves fewer than four waves a SIMD (groups of more than 4 queries), four
   // rows ahead make up for the missing waves' loads.  us with two / with four: 64 heads, 2 x 32000 tokens 47.5 / 45.5, 16 x

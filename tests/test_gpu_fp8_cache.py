@@ -54,6 +54,9 @@ FP8_WIDE_CASES = [
     (8, 1, 128, 700, 32, 128, 40, False, 67),         # groups of more than four: four region rows a lane group ahead, ragged ends
     (5, 1, 128, 395, 16, 64, 20, False, 68),
     (8, 1, 128, 600, 32, 96, 40, True, 69),
+    (4, 2, 128, 500, 16, 96, 30, False, 70),          # two queries a row: rows of 128 elements on vector units
+    (4, 2, 128, 700, 32, 128, 40, True, 71),
+    (6, 2, 128, 600, 32, 96, 40, True, 72),           # three: on the matrix cores
 ]
 
 
