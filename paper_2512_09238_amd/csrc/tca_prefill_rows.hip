@@ -18,6 +18,7 @@
 // fourth or an eighth as long, for calls that would not fill the chip.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "tca_common.h"
@@ -325,10 +326,19 @@ int launch_prefill_f32(const tca_params* prm, const float* Q, int64_t q_pos0, in
   const bool few = (n_queries + 63) / 64 * Hq < 400;
   const int64_t n_wg = (n_queries + (few ? 15 : 63)) / (few ? 16 : 64) * Hq;
   if (n_wg > INT32_MAX) return fail(TCA_ERR_UNSUPPORTED, "tca_prefill (fp32): %lld queries", (long long)n_queries);
-  // And of those, few enough that twice the waves all find a place at once: eight share the walk.  us with four / with
-  // eight: 4 heads, d = 64, 256 tokens 51.5 / 42.2, 1024 tokens (256 workgroups) 59.4 / 47.9, 2048 tokens (512) 86.5 / 73.2,
-  // 512 behind 4096 110.6 / 83.6; 32 heads, d = 128 (two waves of 256 registers fill a SIMD), 256 tokens (512) 55.4 / 57.5.
-  const bool fewest = few && n_wg <= (prm->head_dim == 64 ? 512 : 256);
+  // And of those, few enough that twice the waves all find a place at once, and with keys for all of them: eight share the
+  // walk.  us with four / with eight, on inputs in the caches and not: 4 heads, d = 64, 64 tokens (4 tiles of keys) 8.3 / 9.5 and
+  // 10.8 / 11.8, 96 (6) 10.7 / 10.6 and 15.4 / 13.1, 1024 32.3 / 25.7 and 49.8 / 34.2, 2048 (512 workgroups) 56.8 / 48.8 and
+  // 90 / 63, 1024 behind 8192 190 / 130 and 351 / 193; 32 heads, d = 128 (two waves of 256 registers fill a SIMD), 128 tokens
+  // (8 tiles) 17.2 / 17.7 and 25 / 21.8, 64 behind 200 29.3 / 25.6 and 46 / 35, 64 behind 4096 411 / 240 and 534 / 293.  With two
+  // workgroups to a CU the matrix units are the bound, and of a shared selection, whose rows the heads find in L2, nothing is
+  // left to hide: 1500 tokens of 4 heads behind 4096 65.8 / 69.8.
+  int64_t region = 0;                              // keys the last query may see
+  for (int h = 0; h < sel_heads(prm); ++h) region = std::max(region, offs[h + 1] - offs[h]);
+  const int64_t seen = q_pos0 + n_queries, old = std::max<int64_t>(0, seen - prm->window);
+  const int64_t keys = (part == TCA_PART_GLOBAL ? 0 : seen - old) + (part == TCA_PART_WINDOW ? 0 : std::min(region, old));
+  const bool d64 = prm->head_dim == 64;
+  const bool fewest = few && n_wg <= (d64 && sel_group(prm) == 1 ? 512 : 256) && keys > (d64 ? 4 : 8) * 16;
   auto launch = [&](auto kernel, int threads) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)n_wg), dim3(threads), 0, st, Q, q_pos0, n_queries, K, V, kv_stride, idx,
                        Kg, Vg, ho, n_rows, Hq, Hq / prm->n_kv_heads, sel_group(prm), prm->window, scale, O, lse, part);

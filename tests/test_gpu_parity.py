@@ -822,6 +822,13 @@ F32_WAVES_CASES = [
     (4, 1, 64, 1040, 1000, 32, True, False),
     (8, 2, 128, 333, 0, 64, False, False),
     (32, 4, 64, 300, 0, 32, False, True),
+    # and where the choice between four and eight turns: 64 and 65 keys, 128 and 129; 256 query tiles of a shared selection, and more
+    (4, 1, 64, 64, 0, 128, False, False),
+    (4, 1, 64, 65, 0, 128, True, False),
+    (8, 2, 128, 128, 0, 128, False, False),
+    (8, 2, 128, 129, 0, 128, False, True),
+    (16, 4, 64, 256, 0, 64, True, False),
+    (16, 4, 64, 257, 0, 64, True, False),
 ]
 
 
