@@ -69,8 +69,7 @@ struct NoSplit {};
 
 // Where the V^T operand comes from.  The transposing reads take twice the instructions of plain ones, and the eight-wave
 // step, whose order is pinned to the instruction, pays for them: 3.7 % more cycles, 72.7 -> 73.7 ms at 128K tokens with
-// the pre-pass (0.31 ms) already taken off, 16.20 -> 16.15 for 8192 tokens behind 112K (64 heads), 550 -> 546 us at 5446
-// tokens.  The four-wave shapes take the calls of few query tiles, which read a tile a few times: there the pre-pass is a
+// the pre-pass (0.31 ms) already taken off, 16.20 -> 16.15 for 8192 tokens behind 112K (64 heads).  The four-wave shapes take the calls of few query tiles, which read a tile a few times: there the pre-pass is a
 // launch and two passes over V for nothing (413 tokens behind 64K: 231 -> 193 us, 41 of them the pre-pass).
 constexpr bool uses_transposed_v(int nw) { return nw == 8; }
 
@@ -1385,16 +1384,25 @@ static int xcd_slots(WgShape sh) { return sh.nw == 8 || sh.qb == 2 ? 32 : 64; }
 // v_aligned: V and Vg are 16-byte aligned.  Where they are not (the entry points take any element for a start) the direct
 // copies into LDS cannot be relied on, which the four-wave shapes make of V itself: such a call takes eight waves, whose
 // pre-pass reads V with plain loads.
-static WgShape choose_shape(const tca_params* prm, int64_t n_queries, bool gather, bool v_aligned) {
+static WgShape choose_shape(const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries, bool gather, bool v_aligned) {
   if (!v_aligned) return {8, 1};
   const int variant = prefill_variant();
-  // With rows fetched through idx eight waves from 1024 items of 256 queries on.  Otherwise the pre-pass (uses_transposed_v)
-  // must be worth it too: the query tiles that read a tile of V^T must be many.  Four waves against eight, 22 tiles (5446
-  // tokens): 64 heads 551 / 579 us, with a shared selection 549 / 565; 16 tiles (4096 tokens, 64 heads) 345 / 351, behind
-  // 64K 2216 / 2218 and 2502 / 2582 shared; 32 tiles (8192 tokens): 32 heads 514 / 513, behind 30K 1250 / 1222, behind 112K
-  // 3116 / 3011; 64 tiles 2462 / 2452 with 64 heads.
+  // With rows fetched through idx eight waves from 1024 items of 256 queries on.  Otherwise they must also pay for the pre-pass
+  // (uses_transposed_v), for their coarser last round of workgroups and for prologues that nothing covers: by many query tiles, or by
+  // a long walk of each.  us with four / with eight, 64 heads, region rows 0.2 to 0.5 of the tokens: 4096 tokens 291 / 300, 5446
+  // 476 / 503, 6144 (24 tiles) 593 / 589, 6656 672 / 658, 7900 917 / 871; 4096 behind 8192 (about 110 steps an item) 792 / 820,
+  // behind 16384 (150) 1119 / 1131, behind 30000 (220) 1680 / 1657, behind 64K (430) 3050 / 2998; 5446 behind 6000 1000 / 1061;
+  // 5888 behind 30000 2477 / 2412, behind 64K 4490 / 4380.  With a shared selection 5446 tokens 471 / 487, 6656 661 / 651, 4096
+  // behind 8192 796 / 809, behind 16384 1150 / 1150 and 1170 / 1127, behind 64K 3156 / 3118.  On inputs that are not in the caches the same within 1 %.
   const int64_t tiles = (n_queries + 255) / 256;
-  const bool many = tiles * prm->n_q_heads >= 1024 && (gather || tiles >= 24);
+  bool many = tiles * prm->n_q_heads >= 1024;
+  if (many && !gather && tiles < 24) {
+    int64_t steps = 0;
+    for (int h = 0; h < sel_heads(prm); ++h)
+      for (int64_t qt = 0; qt < tiles; ++qt)
+        steps += tile_steps(prm, offs[h + 1] - offs[h], q_pos0, n_queries, 256, qt, TCA_PART_ALL);
+    many = steps >= 130 * tiles * sel_heads(prm);
+  }
   if (gather) return {variant == 3 || (variant != 1 && many) ? 8 : 4, 1};
   if (variant == 3 || (variant == 0 && many)) return {8, 1};
   if (variant == 2) return {4, 2};
@@ -1446,7 +1454,7 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
   // queries (one wave per SIMD, every LDS fragment feeds two MFMAs, half the LDS reads) stay
   // selectable through the diagnostics switch: measured 5-8 % slower on 128K tokens, because a
   // lone wave cannot issue its vector, LDS and scalar instructions fast enough beside the MFMAs.
-  const WgShape sh = choose_shape(prm, n_queries, gather, (((uintptr_t)V | (uintptr_t)Vg) & 15) == 0);
+  const WgShape sh = choose_shape(prm, offs, q_pos0, n_queries, gather, (((uintptr_t)V | (uintptr_t)Vg) & 15) == 0);
   SplitPlan sp;
   {
     const int64_t n_wg = choose_split(sp, prm, offs, q_pos0, n_queries, part, sh, ws_bytes > mw.need ? ws_bytes - mw.need : 0);
@@ -1501,7 +1509,7 @@ static void run_mfma(const tca_params* prm, const uint16_t* Q, int64_t q_pos0, i
 int64_t prefill_mfma_xcd_plan(const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries, int part,
                               bool gather, int32_t* start_out) {
   if ((prm->n_q_heads & 7) != 0) return -1;
-  const WgShape sh = choose_shape(prm, n_queries, gather, true);
+  const WgShape sh = choose_shape(prm, offs, q_pos0, n_queries, gather, true);
   PrefillHeads ph;
   const int64_t longest = plan_xcds(ph, prm, offs, q_pos0, n_queries, sh.nw * sh.qb * 32, part, xcd_slots(sh));
   for (int x = 0; x <= 8; ++x) start_out[x] = ph.xcd_start[x];
@@ -1510,7 +1518,7 @@ int64_t prefill_mfma_xcd_plan(const tca_params* prm, const int64_t* offs, int64_
 
 int prefill_mfma_walk(const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries, int part, bool gather,
                       size_t ws_bytes, int32_t* heads_out, int64_t* chunks_out) {
-  const WgShape sh = choose_shape(prm, n_queries, gather, true);
+  const WgShape sh = choose_shape(prm, offs, q_pos0, n_queries, gather, true);
   const size_t need = prefill_mfma_workspace_need(prm, n_queries, offs[sel_heads(prm)]);
   SplitPlan sp;
   const int64_t chunks = choose_split(sp, prm, offs, q_pos0, n_queries, part, sh, ws_bytes > need ? ws_bytes - need : 0);

@@ -98,6 +98,23 @@ def test_argument_errors_are_codes_not_crashes():
     assert tb.tca_select_workspace_bytes(ok, 131072) > 4 * 131072
 
 
+def test_prefill_query_tiles_by_the_length_of_the_walk():
+    """Host logic of the bf16 prefill launch: 256 queries a workgroup in calls of many query tiles, and of fewer (1024 in all
+    at least) where each walks a long context; otherwise 128, and rows fetched through their positions do not ask for it."""
+    import paper_2512_09238_amd.binding as tb
+    wide = tb.make_params(64, 8, 128, 128, 4096, tb.TCA_BF16, 0.5, 0.0)
+    shared = tb.make_params(64, 8, 128, 128, 4096, tb.TCA_BF16, 0.5, 0.0, share=tb.TCA_SHARE_GROUP)
+    layer = tb.make_params(32, 8, 128, 128, 4096, tb.TCA_BF16, 0.5, 0.0)
+    for prm, pos0, n, free, want in ((wide, 0, 4096, False, 128), (wide, 0, 4096, True, 256), (wide, 8192, 4096, False, 128),
+                                     (wide, 16384, 4096, False, 256), (wide, 65536, 5000, False, 256), (shared, 65536, 4096, False, 256),
+                                     (shared, 0, 5446, False, 128), (wide, 0, 6144, False, 256), (wide, 65536, 2048, False, 128),
+                                     (layer, 65536, 4096, False, 128), (layer, 0, 8192, False, 256)):
+        Hs = tb.tca_selection_heads(prm)
+        offs = np.arange(Hs + 1, dtype=np.int64) * int(0.35 * (pos0 + n))
+        start, _ = tb.tca_diag_prefill_xcd_plan(prm, offs, pos0, n, gather_free=free)
+        assert start[8] == prm.n_q_heads * -(-n // want), (pos0, n, free)
+
+
 def test_exports_refuse_host_arrays_of_another_type():
     """The exports take their host arrays as pointers of the declared type: one of another type is refused by the binding
     instead of being read as what it is not."""
