@@ -42,6 +42,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <vector>
 
@@ -218,7 +219,7 @@ __device__ __forceinline__ void settle_acc(f32x16_t (&o)[N]) {
 
 // Two four-wave workgroups share a CU, and an XCD deals its ids to its 32 CUs in turn: every second run of 32 ids is
 // taken backwards, so that of a sequence sorted by length the longest and the shortest meet on a CU.
-__device__ __forceinline__ int pair_up(int u, int n) {
+__host__ __device__ __forceinline__ int pair_up(int u, int n) {
   const int b = u & ~31, len = n - b < 32 ? n - b : 32;
   return (u & 32) ? b + len - 1 - (u - b) : u;
 }
@@ -1298,17 +1299,53 @@ static int64_t plan_xcds(PrefillHeads& ph, const tca_params* prm, const int64_t*
   return longest;
 }
 
+// What a tile step takes, us with the chip full (two four-wave workgroups to a CU), and of that with one workgroup to a CU:
+// measured over calls of 257 to 512 workgroups, whole and in chunks (4 to 64 heads behind 0 to 64K tokens).
+static double step_us(const tca_params* prm) { return prm->head_dim == 128 ? 1.8 : 1.25; }
+static double alone(const tca_params* prm) { return prm->head_dim == 128 ? 0.6 : 0.69; }
+
+// When a call of up to kSplitSlots four-wave workgroups, all resident at once, would end, in full steps: that of the CU whose
+// two (by the ids of prefill_mfma_kernel, an XCD's 32 CUs served in turn) take longest, the longer one alone once the other
+// has ended.  A call whose long heads meet on a CU runs to the end at the full chip's pace: 6363 queries of 8 heads (d = 64,
+// one to an XCD) behind 64K 587 us whole and 467 in chunks, 4187 of 12 heads 842 and 758; one whose long heads meet short ones
+// does not: 859 of 64 heads 796 and 880.  (A call cut for 5 % is still worth it: in chunks two workgroups to a CU hide each
+// other's waits for inputs that are not in the caches.  8192 queries of 4 heads, d = 64, behind 4096: 91 us whole, 74 in
+// chunks; 111 and 77 on such inputs.)
+static double whole_steps(const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries, int part) {
+  const int Hq = prm->n_q_heads, GS = sel_group(prm), nh = Hq / 8;
+  const int n_qt = (int)((n_queries + 127) / 128), n_items = Hq * n_qt;
+  auto cost = [&](int h, int qt) {
+    return (double)(kFixedSteps + tile_steps(prm, offs[h / GS + 1] - offs[h / GS], q_pos0, n_queries, 128, qt, part));
+  };
+  double end = 0.0;
+  if (n_items <= kSplitSlots / 2) {                // nobody shares a CU: the longest, a head's last query tile
+    for (int h = 0; h < Hq; h += GS) end = std::max(end, alone(prm) * cost(h, n_qt - 1));
+    return end;
+  }
+  PrefillHeads ph;
+  if ((Hq & 7) == 0) plan_xcds(ph, prm, offs, q_pos0, n_queries, 128, part, 64);
+  for (int x = 0; x < 8; ++x) {
+    const int mine = (Hq & 7) == 0 ? nh * n_qt : (n_items - x + 7) >> 3;
+    auto item = [&](int u) {
+      const int v = pair_up(u, mine);
+      if ((Hq & 7) == 0) return cost(ph.perm[x * nh + v % nh], n_qt - 1 - v / nh);
+      const int g = v * 8 + x, k = g / Hq, period = 8 / ((Hq & 1) ? 1 : (Hq & 2) ? 2 : 4);
+      return cost((g - k * Hq + k / period) % Hq, n_qt - 1 - k);
+    };
+    for (int u = 0; u < 32 && u < mine; ++u) {
+      const double a = item(u), b = u + 32 < mine ? item(u + 32) : 0.0;
+      end = std::max(end, alone(prm) * std::fabs(a - b) + std::min(a, b));
+    }
+  }
+  return end;
+}
+
 // Whether a call's items are cut into chunks, and how long: fills sp (all but part) and returns the number of
-// workgroups, or 0 for the plain launch.  plain_steps: when the plain launch would end, in tile steps (each slot
-// of the chip taken: a workgroup alone on its CU takes 0.6 of the time for a step.  With 256 workgroups or fewer all are;
-// with up to 512 the longest meets a short one on its CU (pair_up) and is alone from there on, unless the heads share a
-// selection, are equally long and lie on one XCD.  Reckoned as if a second one were there to the end, calls were cut that are
-// faster whole: 2048 queries behind 30K, 32 heads, 432 us and 384 whole; 1000 of 64 heads 447 and 402; 16384 tokens of 4
-// heads, d = 64, 155 and 130; with a shared selection 2048 behind 64K 672 and 846).  Measured, whole and in chunks: 413
-// queries behind 64K tokens (32 heads) 539 -> 218 us, behind 112K 949 -> 344 us; 128 behind 16K 164 -> 62 us; 2048
-// behind 30K (4 heads, d = 64) 304 -> 93 us; from 512 items of equal length on nothing is gained.
+// workgroups, or 0 for the plain launch.  plain_steps: when the plain launch would end, in tile steps of the full chip.
+// Measured, whole and in chunks: 413 queries behind 64K tokens (32 heads) 539 -> 218 us, behind 112K 949 -> 344 us; 128 behind
+// 16K 164 -> 62 us; 2048 behind 30K (4 heads, d = 64) 304 -> 93 us; from 512 items of equal length on nothing is gained.
 static int64_t plan_split(SplitPlan& sp, const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries,
-                          size_t ws_left, int64_t plain_steps) {
+                          size_t ws_left, double plain_steps) {
   const int Hq = prm->n_q_heads, GS = sel_group(prm);
   const int64_t n_qt = (n_queries + 127) / 128, n_items = Hq * n_qt;
   const size_t item_bytes = (prm->head_dim == 128 ? split_floats<128>() : split_floats<64>()) * sizeof(float);
@@ -1333,17 +1370,10 @@ static int64_t plan_split(SplitPlan& sp, const tca_params* prm, const int64_t* o
     }
     if (bound[h] > longest) longest = bound[h];
   }
-  // Chunk lengths: the shortest that keeps one round of the chip, and two.  Their cost in us: a step takes 1.8 us (d =
-  // 128) or 1.1 us (64) with the chip full, 0.6 of that half full; the merge a launch, 0.3 us per chunk of an item, and
-  // the partial results written and read at 4 TB/s.
-  const double step = prm->head_dim == 128 ? 1.8 : 1.1;
-  double beside = 0.0;                             // steps of the longest workgroup with another one on its CU
-  if (n_items > kSplitSlots / 2) {
-    beside = (double)plain_steps;
-    if (n_items <= kSplitSlots && GS == 1) beside = std::max(0.0, std::min(beside, 2.0 * (total / (double)n_items + kFixedSteps) - plain_steps));
-  }
-  const double plain = (0.6 * plain_steps + 0.4 * beside) * step;
-  double best = 0.9 * plain;
+  // Chunk lengths: the shortest that keeps one round of the chip, and two.  Their cost in us: the steps; the merge a launch,
+  // 0.3 us per chunk of an item, and the partial results written and read at 4 TB/s.
+  const double step = step_us(prm);
+  double best = 0.95 * plain_steps * step;
   int64_t best_items = 0, best_chunk = 0;
   for (const int64_t room : {(int64_t)kSplitSlots / 2, (int64_t)kSplitSlots, (int64_t)2 * kSplitSlots}) {
     const int64_t lim = room < most ? room : most;
@@ -1355,7 +1385,7 @@ static int64_t plan_split(SplitPlan& sp, const tca_params* prm, const int64_t* o
       for (int h = 0; h < Hq; ++h) items += n_qt * ((bound[h] + chunk - 1) / chunk);
       if (items <= lim) break;
     }
-    const double walk = items <= kSplitSlots / 2 ? 0.6 * (chunk + kFixedSteps)
+    const double walk = items <= kSplitSlots / 2 ? alone(prm) * (chunk + kFixedSteps)
                         : items <= kSplitSlots   ? (double)(chunk + kFixedSteps)
                                                  : 1.1 * (total + kFixedSteps * items) / kSplitSlots + 0.3 * chunk;
     const double t = walk * step + 5.0 + 0.3 * ((longest + chunk - 1) / chunk) + items * (double)item_bytes * 2e-6 / 4.0;
@@ -1416,15 +1446,18 @@ static int64_t choose_split(SplitPlan& sp, const tca_params* prm, const int64_t*
   const int Hq = prm->n_q_heads, GS = sel_group(prm);
   const int64_t n_qt = (n_queries + 127) / 128;
   if (sh.nw != 4 || sh.qb != 1 || part != TCA_PART_ALL || prefill_variant() != 0 || n_qt * Hq >= 2 * kSplitSlots) return 0;
-  // when the plain launch would end: its longest item if it is all resident at once, else what the plan says
-  int64_t plain = 0;
-  if (n_qt * Hq > kSplitSlots && (Hq & 7) == 0) {
+  // when the plain launch would end
+  double plain = 0.0;
+  if (n_qt * Hq <= kSplitSlots) {
+    plain = whole_steps(prm, offs, q_pos0, n_queries, part);
+  } else if ((Hq & 7) == 0) {
     PrefillHeads ph;
-    plan_xcds(ph, prm, offs, q_pos0, n_queries, 128, part, 64, &plain);
-  } else {
+    int64_t makespan = 0;
+    plan_xcds(ph, prm, offs, q_pos0, n_queries, 128, part, 64, &makespan);
+    plain = (double)makespan;
+  } else {                                         // no plan for such head counts: what the longest takes alone, at least
     for (int h = 0; h < Hq; h += GS)
-      plain = std::max(plain, kFixedSteps + tile_steps(prm, offs[h / GS + 1] - offs[h / GS], q_pos0, n_queries, 128, n_qt - 1, part));
-    if (n_qt * Hq > kSplitSlots) plain = plain * 6 / 10;           // no plan for such head counts: what the longest takes alone, at least
+      plain = std::max(plain, 0.6 * (kFixedSteps + tile_steps(prm, offs[h / GS + 1] - offs[h / GS], q_pos0, n_queries, 128, n_qt - 1, part)));
   }
   return plan_split(sp, prm, offs, q_pos0, n_queries, ws_left, plain);
 }

@@ -115,6 +115,21 @@ def test_prefill_query_tiles_by_the_length_of_the_walk():
         assert start[8] == prm.n_q_heads * -(-n // want), (pos0, n, free)
 
 
+def test_prefill_cut_into_chunks_where_long_heads_share_a_cu():
+    """Host logic of the bf16 prefill launch, calls of 257 to 512 workgroups whose heads keep 20 to 50 % of the rows: cut into
+    chunks of keys where the long heads' workgroups meet on a CU, whole where they meet short ones."""
+    import paper_2512_09238_amd.binding as tb
+    for (Hq, Hkv, d, w), pos0, n, cut in (((4, 1, 64, 128), 32768, 12763, True), ((8, 2, 64, 1024), 65536, 6363, True),
+                                          ((28, 4, 64, 1024), 65536, 1755, True), ((12, 4, 128, 4096), 65536, 4187, True),
+                                          ((16, 4, 128, 4096), 65536, 3163, False), ((32, 8, 128, 4096), 65536, 1499, False),
+                                          ((64, 8, 128, 4096), 65536, 859, False), ((12, 4, 128, 4096), 0, 4187, False)):
+        prm = tb.make_params(Hq, Hkv, d, 32, w, tb.TCA_BF16, 0.5, 0.0)
+        kept = np.linspace(0.2, 0.5, Hq)[np.random.default_rng(5).permutation(Hq)] * (pos0 + n)
+        offs = np.concatenate([[0], np.cumsum(kept.astype(np.int64))])
+        ws = tb.tca_prefill_workspace_bytes(prm, n, int(offs[-1]))
+        assert (tb.tca_diag_prefill_walk(prm, offs, pos0, n, ws)[2] > 0) == cut, (Hq, pos0, n)
+
+
 def test_exports_refuse_host_arrays_of_another_type():
     """The exports take their host arrays as pointers of the declared type: one of another type is refused by the binding
     instead of being read as what it is not."""
