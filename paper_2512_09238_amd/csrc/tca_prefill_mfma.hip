@@ -706,8 +706,10 @@ void prefill_mfma_kernel(
   // written out and fenced.  Exponentials at an even pace, done two slots before the last of them are needed (the last
   // quarter of P V), rounded and summed one slot behind; the terms' sum in the order of exp_tile.  413 tokens behind 64K: 193
   // -> 183.6 us.  The eight-wave shape is 1.1 % slower this way than in the order pinned below, and with rows fetched through
-  // idx there are no registers left for it.
-  constexpr bool kFenced = NW == 4 && QB == 1 && !GATHER;
+  // idx there are no registers left for it.  With 64 elements only chunks take it (us pinned / fenced: 8192 tokens of 4 heads
+  // 64.3 / 60.0, 6363 of 8 heads behind 64K 510 / 467); calls that walk their tiles whole are as fast or faster in the pinned
+  // order: 4 heads, 12000 tokens 82 / 90, 20000 on inputs that are not in the caches 144 / 168, 40000 behind 64K 1693 / 1790.
+  constexpr bool kFenced = NW == 4 && QB == 1 && !GATHER && (D == 128 || SPLIT);
   constexpr int kSlots = 2 * KK + 4 * DS;
   auto exp_slot = [&](int t, const f32x16_t (&s)[2], float mb, bf16x8_t (&pf)[2][2], float (&ls)[4], float (&p)[32]) {
     auto done = [](int u) {                          // elements formed by the end of slot u
@@ -822,9 +824,13 @@ void prefill_mfma_kernel(
 
     // ---- slot A: scores of the next tile (MFMA) under the exponentials of this one (VALU), taken
     // against the reference as it stands
+    // With 64 elements, whose steps are short, V is asked for before K: the step's end waits for both.  us K / V first, pinned
+    // steps, 4 heads: 20000 tokens on inputs that are not in the caches 144 / 141, 40000 behind 64K 1693 / 1618; with 128
+    // elements neither is better.
+    constexpr bool kVFirst = D == 64 && NW == 4 && QB == 1 && !GATHER;
     auto issue_copies = [&](int i) {     // copies spread as evenly as the counts allow: load j after fragment pair j * KK / N
-      const int kk = i >> 1;
-      if ((i & 1) && (kk * Copy::N) % KK == 0 && kk * Copy::N / KK < Copy::N) copy_load(job, kk * Copy::N / KK);
+      const int kk = i >> 1, j = kk * Copy::N / KK;
+      if ((i & 1) && (kk * Copy::N) % KK == 0 && j < Copy::N) copy_load(job, kVFirst ? (j + Copy::NK) % Copy::N : j);
     };
     auto vfrag = [&](int j) {
       if constexpr (VT) return *reinterpret_cast<const bf16x8_t*>(vb + vfa[j / DS] + (j % DS) * (32 * kBN * 2));

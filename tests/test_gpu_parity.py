@@ -715,6 +715,7 @@ V_EDGE_CASES = [
     (3, 1, 128, 129, 64, False),
     (3, 1, 64, 200, 65, True),
     (8, 8, 128, 128, 129, True),
+    (4, 1, 64, 257, 200, False),
 ]
 
 
@@ -744,7 +745,7 @@ def test_v_tiles_end_where_the_rows_do(tb, bufs, case):
     ws = bufs.workspace(tb.tca_prefill_workspace_bytes(prm, n, int(gb.offs[-1])))
     rows = sorted({0, n // 2, n - 1})
     ref = H.oracle_rows(x, None, {"w": w}, S, np.array([L - n + r for r in rows]))
-    for variant in (0, 1, 3):
+    for variant in (0, 1, 2, 3):
         O = torch.full_like(Qt, float("nan"))
         tb.tca_diag_prefill_variant(variant)
         try:
