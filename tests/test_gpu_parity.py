@@ -935,6 +935,40 @@ def test_decode_units_at_their_edges(tb, bufs, case):
                 assert (Ox[s, h] - ref).abs().max().item() <= H.TOL[dtype], (s, h)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_decode_fp32_sums_keep_small_chunks_beside_a_large_one(tb, bufs, d):
+    """The first chunk of a region has logits of 0 and values of 0, all other rows base-2 logits of -25 and values of 1: every
+    partial is exact, and a chunk's 2^-18 is half of what an fp32 sum of 128 keeps.  What is left is one rounding of the
+    result (2^-24, twice that allowed)."""
+    w, n = 128, 32768
+    prm = tb.make_params(2, 2, d, 16, w, tb.TCA_F32)
+    c = bufs.DecodeCache(prm, 1, [n, n])
+    far = -25.0 * np.log(2.0) * np.sqrt(d)
+    key = torch.zeros(d, device="cuda")
+    key[0] = float(np.float32(far))
+    key[1] = far - float(np.float32(far))
+    for K, V in ((c.Kg, c.Vg), (c.ringK, c.ringV)):
+        K[:] = key
+        V[:] = 1.0
+    for h in range(2):
+        c.idx[0, h * n:(h + 1) * n] = torch.arange(n, device="cuda")
+        c.Kg[0, h * n:h * n + 128] = 0.0
+        c.Vg[0, h * n:h * n + 128] = 0.0
+    c.n_rows.fill_(n)
+    c.length.fill_(n + w)
+    q = torch.zeros(1, 2, d, device="cuda")
+    q[..., :2] = 1.0
+    kv = torch.ones(1, 2, d, device="cuda")
+    O = torch.empty_like(q)
+    tb.tca_decode(prm, c.view, c.offs, q, key * kv, kv, np.stack([tb.tca_config_from_budget(16, 1.0, 0.4)] * 2), O,
+                  bufs.workspace(tb.tca_decode_workspace_bytes(prm, 1, c.max_head_rows)))
+    torch.cuda.synchronize()
+    small = (n - 128 + w) * 2.0 ** -25
+    err = np.abs(bufs.to_host_f64(O) / (small / (128 + small)) - 1).max()
+    print("relative error", err, flush=True)
+    assert err <= 2.0 ** -23
+
+
 ROOMY_CASES = [
     # Hq, Hkv, d, dtype, share: more heads than a wave has lanes, a number of heads that is odd, one head, units of one length
     (128, 16, 64, "bf16", False),
