@@ -42,7 +42,7 @@ constexpr int kChunk = 4 * kPartThreads;          // rows per split-K unit of a 
 constexpr int kChunkShared = 2048;                // the same when every row is scored against a group of queries (1024: 507, 2048: 480, 4096: 540 us per step)
 constexpr int kMinChunk = 128;                    // of a short step: see choose_chunk
 constexpr int kDecThreads = 256;                  // the other kernels
-constexpr int kMaxSlots = 4096;       // split-K units per head the merge kernel can weigh (4M rows per head)
+constexpr int kMaxSlots = 4096;       // split-K units per head that a step is taken for (4M rows per head): far inside the 24 bits order_units has for them
 
 struct DecodeHeads {
   int64_t offs[TCA_MAX_HEADS + 1];
@@ -600,10 +600,8 @@ __device__ __forceinline__ void partial_rows_mfma(const KV* __restrict__ kbase, 
 // empty ones follow.  (Head after head, the first chunks of all heads may be on one or two XCDs.  us per step of 32 heads with
 // room for 40000 rows each, head after head / this: 4 sequences of 1500 rows 91 / 53, 16 of 1500 286 / 162, 16 of 10000 618 /
 // 518, 16 of 3000 with a shared selection 222 / 135; full caches, 16 x 128K tokens 1088 / 1066, 5 x 112K 790 / 768.)
-// (The bound on the FP8 rows of 128 and groups of 4, which sit at 128 registers: with 132, a wave fewer per SIMD, 93.5 against
-// 92.4 us at 8 sequences of 30K tokens.)
 template <typename T, typename KV, int D, int GQ, int GW>
-__global__ __launch_bounds__(kPartThreads, sizeof(KV) == 1 && D == 128 && GW == 4 ? 4 : 1) void decode_partial_kernel(
+__global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
     tca_cache c, DecodeHeads dh, int Hq, int Hkv, int w, double scale, const T* __restrict__ q,
     const T* __restrict__ k_new, const T* __restrict__ v_new, uint32_t* __restrict__ pos, float* __restrict__ part) {
   constexpr int EL = D / 16;
@@ -880,9 +878,9 @@ __global__ __launch_bounds__(kDecThreads) void decode_merge_kernel(
 }
 
 // Both handover kernels are HBM-bound copies: one 16-lane group per row, kCopyRows (kWinRows) rows of K and of V per
-// group requested before the first is stored.  32768 tokens, 32 heads, into the FP8 cache (147 MB): 47.5 -> 44.7 us for the
-// two kernels; with bf16 rows, which went two bytes per lane, 62 -> 42 us.
-// (Four rows of the regions: 40 and 37 us against 36 and 35; of the window, of which there is little: 10.8 against 8.3.)
+// group requested before the first is stored.  The two launches of a sequence of 32768 tokens and 32 heads that keeps a third of
+// its rows, into the FP8 cache, take 54.6 us (58.5 on rows that are not in the caches); with four rows of the regions at a time
+// 56.8 (63.4), two of the window 54.7 (58.7).  8192 tokens 22.1; 24.6 and 23.1.
 constexpr int kCopyRows = 2, kWinRows = 1;
 
 // grid (ceil(rows / (16 kWinRows)), Hkv); block 256

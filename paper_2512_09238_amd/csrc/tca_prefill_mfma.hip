@@ -70,8 +70,10 @@ struct NoSplit {};
 
 // Where the V^T operand comes from.  The transposing reads take twice the instructions of plain ones, and the eight-wave
 // step, whose order is pinned to the instruction, pays for them: 3.7 % more cycles, 72.7 -> 73.7 ms at 128K tokens with
-// the pre-pass (0.31 ms) already taken off, 16.20 -> 16.15 for 8192 tokens behind 112K (64 heads).  The four-wave shapes take the calls of few query tiles, which read a tile a few times: there the pre-pass is a
-// launch and two passes over V for nothing (413 tokens behind 64K: 231 -> 193 us, 41 of them the pre-pass).
+// the pre-pass (0.31 ms) already taken off, 16.20 -> 16.15 for 8192 tokens behind 112K (64 heads).  The four-wave shapes take
+// the calls of few query tiles, which read a tile a few times: there the pre-pass is a launch and two passes over V for
+// nothing (413 tokens behind 64K: 231 -> 193 us, 41 of them the pre-pass; on inputs that are not in the caches 330 -> 251
+// together with the fenced order of the steps).
 constexpr bool uses_transposed_v(int nw) { return nw == 8; }
 
 // position p (0..63) inside a stored V^T tile -> key (0..63) of the tile
@@ -244,6 +246,14 @@ template <int D> __device__ __forceinline__ int v_swz(int r) { return D == 128 ?
 template <int D> __device__ __forceinline__ int k_off(int r, int ch) { return r * (D * 2) + ((ch ^ k_swz<D>(r)) << 4); }
 __device__ __forceinline__ int vt_off(int dd, int ch) { return dd * (kBN * 2) + ((ch ^ ((dd >> 1) & 7)) << 4); }
 
+// Four keys of this lane's column (see vfa).  Without the __restrict__ the compiler takes the read for one that may meet
+// the tile copies in flight and waits for them first, in the middle of every step (128K tokens: 7 % more cycles).  No such wait
+// is needed: the tile read has landed by the wait and the barrier of the step before, and the copies in flight go to
+// other places of the ring.
+__device__ __forceinline__ bf16x4_t read_transposed(const unsigned char* __restrict__ lds_src) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4_t*)lds_src);
+}
+
 // Tile copies go global -> LDS directly (buffer loads with the LDS modifier: no
 // staging registers, no ds_write).  Every lane of a wave-load deposits 16 bytes at
 // consecutive LDS addresses, so the lane that fills LDS chunk position p of a row
@@ -253,12 +263,6 @@ __device__ __forceinline__ int vt_off(int dd, int ch) { return dd * (kBN * 2) + 
 // the buffer descriptor), so a copy costs no vector ALU work at all.  A K or V tile is
 // CPR wave-loads; each wave issues its share one load at a time, spread
 // between the MFMAs instead of queueing up behind the barrier.
-// Four keys of this lane's column (see vfa).  Without the __restrict__ the compiler takes the read for one that may meet
-// the tile copies in flight and waits for them first, in the middle of every step (128K tokens: 7 % more cycles).
-__device__ __forceinline__ bf16x4_t read_transposed(const unsigned char* __restrict__ lds_src) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4_t*)lds_src);
-}
-
 template <int D, int NW>
 struct TileCopy {
   static constexpr int CPR = D / 8;
@@ -1424,12 +1428,13 @@ static WgShape choose_shape(const tca_params* prm, const int64_t* offs, int64_t 
   if (!v_aligned) return {8, 1};
   const int variant = prefill_variant();
   // With rows fetched through idx eight waves from 1024 items of 256 queries on.  Otherwise they must also pay for the pre-pass
-  // (uses_transposed_v), for their coarser last round of workgroups and for prologues that nothing covers: by many query tiles, or by
-  // a long walk of each.  us with four / with eight, 64 heads, region rows 0.2 to 0.5 of the tokens: 4096 tokens 291 / 300, 5446
-  // 476 / 503, 6144 (24 tiles) 593 / 589, 6656 672 / 658, 7900 917 / 871; 4096 behind 8192 (about 110 steps an item) 792 / 820,
-  // behind 16384 (150) 1119 / 1131, behind 30000 (220) 1680 / 1657, behind 64K (430) 3050 / 2998; 5446 behind 6000 1000 / 1061;
-  // 5888 behind 30000 2477 / 2412, behind 64K 4490 / 4380.  With a shared selection 5446 tokens 471 / 487, 6656 661 / 651, 4096
-  // behind 8192 796 / 809, behind 16384 1150 / 1150 and 1170 / 1127, behind 64K 3156 / 3118.  On inputs that are not in the caches the same within 1 %.
+  // (uses_transposed_v), for their coarser last round of workgroups and for prologues that nothing covers: by many query
+  // tiles, or by a long walk of each.  us with four / with eight, the attention alone, 64 heads, region rows 0.2 to 0.5 of the
+  // tokens: 4096 tokens 291 / 300, 5446 476 / 503, 6144 (24 tiles) 593 / 589, 6656 672 / 658, 7900 917 / 871; 4096 behind 8192
+  // (about 110 steps an item) 792 / 820, behind 16384 (150) 1119 / 1131, behind 30000 (220) 1680 / 1657, behind 64K (430)
+  // 3050 / 2998; 5446 behind 6000 1000 / 1061; 5888 behind 30000 2477 / 2412, behind 64K 4490 / 4380.  With a shared selection
+  // 5446 tokens 471 / 487, 6656 661 / 651, 4096 behind 8192 796 / 809, behind 16384 1150 / 1150 and 1170 / 1127, behind 64K
+  // 3156 / 3118.  On inputs that are not in the caches the same within 1 %.
   const int64_t tiles = (n_queries + 255) / 256;
   bool many = tiles * prm->n_q_heads >= 1024;
   if (many && !gather && tiles < 24) {
