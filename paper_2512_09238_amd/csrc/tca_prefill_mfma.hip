@@ -1174,25 +1174,28 @@ static int64_t tile_steps(const tca_params* prm, int64_t cap, int64_t q_pos0, in
   return c;
 }
 
-// When the slowest of `slots` workgroup places of one XCD ends, items taken in order by the first free place.
-template <typename Cost>
-static int64_t play(int64_t n, int slots, Cost cost) {
-  int64_t heap[64], worst = 0;                     // when each place is free, a binary heap, smallest on top
-  for (int i = 0; i < slots; ++i) heap[i] = 0;
-  for (int64_t u = 0; u < n; ++u) {
-    const int64_t t = heap[0] + cost(u);
-    if (t > worst) worst = t;
-    int i = 0;
-    for (int k = 1; k < slots; k = 2 * i + 1) {
-      if (k + 1 < slots && heap[k + 1] < heap[k]) ++k;
-      if (heap[k] >= t) break;
-      heap[i] = heap[k];
-      i = k;
-    }
-    heap[i] = t;
+// The workgroup places of one XCD, items taken in order by the first free one: when the slowest ends.  A tournament over the
+// times the places are free: an item costs one path to the root and no branch.  The XCDs are played side by side (plan_xcds), so
+// that their paths, each a chain of a dozen dependent instructions, overlap: 3.6 ns an item (64 places), a binary heap 19.
+template <int SLOTS>
+struct Places {
+  int32_t worst = 0, node[2 * SLOTS];              // 64 time + place; node[1] the earliest, node[SLOTS + i] place i
+  Places() {
+    for (int i = 0; i < SLOTS; ++i) node[SLOTS + i] = i;
+    for (int i = SLOTS - 1; i > 0; --i) node[i] = std::min(node[2 * i], node[2 * i + 1]);
   }
-  return worst;
-}
+  void take(int32_t cost) {                        // (times stay below 2^25: 16 rounds of an item's steps, which are 2^18 at most)
+    int32_t k = node[1] + (cost << 6);
+    int i = SLOTS + (k & 63);
+    worst = std::max(worst, k >> 6);
+    node[i] = k;
+    for (int level = 1; level < SLOTS; level *= 2) {
+      k = std::min(k, node[i ^ 1]);
+      i >>= 1;
+      node[i] = k;
+    }
+  }
+};
 
 // Chooses which items an XCD takes and in which order (PrefillHeads: xcd_start, order, perm), and returns the
 // length of the longest range.  *makespan: the estimated end of the call in tile steps.
@@ -1271,25 +1274,59 @@ static int64_t plan_xcds(PrefillHeads& ph, const tca_params* prm, const int64_t*
   while (x < 8) by_work[++x] = (int32_t)n_items;
   const int32_t* best = by_work;
   if (few_rounds) {
+    auto played = [&](auto walk) {                 // walk(take): take(xcd, cost) in every XCD's order
+      auto with = [&](auto slots_tag) {
+        Places<decltype(slots_tag)::value> pl[8];
+        walk([&](int xc, int32_t cost) { pl[xc].take(cost); });
+        int32_t t = 0;
+        for (const auto& p : pl) t = std::max(t, p.worst);
+        return (int64_t)t;
+      };
+      return slots == 64 ? with(std::integral_constant<int, 64>{}) : with(std::integral_constant<int, 32>{});      // (xcd_slots)
+    };
     auto ranges = [&](const int32_t* st) {
-      int64_t t = 0;
-      for (int xc = 0; xc < 8; ++xc) {
-        const int64_t s = st[xc], e = st[xc + 1], he = e / n_qt * n_qt, len_e = he > s ? e - he : 0;
-        t = std::max(t, play(e - s, slots, [&](int64_t u) { return c[u < len_e ? he + u : s + (u - len_e)]; }));
-      }
-      return t;
+      return played([&](auto take) {
+        int32_t at[8], most = 0;                   // an XCD takes the piece of the head its range ends in first
+        for (int xc = 0; xc < 8; ++xc) {
+          at[xc] = std::max(st[xc], st[xc + 1] / (int32_t)n_qt * (int32_t)n_qt);
+          most = std::max(most, st[xc + 1] - st[xc]);
+        }
+        for (int32_t u = 0; u < most; ++u)
+          for (int xc = 0; xc < 8; ++xc)
+            if (u < st[xc + 1] - st[xc]) {
+              if (at[xc] == st[xc + 1]) at[xc] = st[xc];
+              take(xc, c[at[xc]++]);
+            }
+      });
     };
     auto dealt = [&](int order) {
-      int64_t t = 0;
-      for (int xc = 0; xc < 8; ++xc) {
-        const uint8_t* p = ph.perm + xc * nh;
-        t = std::max(t, play(nh * n_qt, slots, [&](int64_t u) {
-          return order == 1 ? c[p[u % nh] * n_qt + u / nh] : c[p[u / n_qt] * n_qt + u % n_qt];
-        }));
-      }
-      return t;
+      return played([&](auto take) {
+        auto all = [&](int i, int64_t qt) {
+          for (int xc = 0; xc < 8; ++xc) take(xc, c[ph.perm[xc * nh + i] * n_qt + qt]);
+        };
+        if (order == 1) {
+          for (int64_t qt = 0; qt < n_qt; ++qt)
+            for (int i = 0; i < nh; ++i) all(i, qt);
+        } else {
+          for (int i = 0; i < nh; ++i)
+            for (int64_t qt = 0; qt < n_qt; ++qt) all(i, qt);
+        }
+      });
     };
-    const int64_t t_head = ranges(by_head), t_work = ranges(by_work), t_one = dealt(1), t_two = dealt(2);
+    // (what the sum of its fullest XCD rules out is not played)
+    int64_t sum_head = 0, sum_dealt = 0;
+    for (int xc = 0; xc < 8; ++xc) {
+      int64_t a = 0, b = 0;
+      for (int i = xc * nh; i < (xc + 1) * nh; ++i) {
+        a += head_cost[i];
+        b += head_cost[ph.perm[i]];
+      }
+      sum_head = std::max(sum_head, a / slots);
+      sum_dealt = std::max(sum_dealt, b / slots);
+    }
+    const int64_t t_work = ranges(by_work), t_head = sum_head > t_work ? sum_head : ranges(by_head);
+    const bool too_full = sum_dealt >= std::min(t_head, t_work);
+    const int64_t t_one = too_full ? sum_dealt : dealt(1), t_two = too_full ? sum_dealt : dealt(2);
     int64_t t = std::min(t_head, t_work);
     best = t_head <= t_work ? by_head : by_work;
     if (t_two * 40 < t * 39) {
@@ -1324,26 +1361,38 @@ static double alone(const tca_params* prm) { return prm->head_dim == 128 ? 0.6 :
 static double whole_steps(const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries, int part) {
   const int Hq = prm->n_q_heads, GS = sel_group(prm), nh = Hq / 8;
   const int n_qt = (int)((n_queries + 127) / 128), n_items = Hq * n_qt;
-  auto cost = [&](int h, int qt) {
-    return (double)(kFixedSteps + tile_steps(prm, offs[h / GS + 1] - offs[h / GS], q_pos0, n_queries, 128, qt, part));
+  double share[kSplitSlots], window[kSplitSlots];  // of a query tile: of a region's rows, in tiles, and its steps without them
+  for (int qt = 0; qt < n_qt; ++qt) {
+    const int64_t lastq = std::min<int64_t>(q_pos0 + 128 * qt + 127, q_pos0 + n_queries - 1);
+    window[qt] = (double)(kFixedSteps + tile_steps(prm, 0, q_pos0, n_queries, 128, qt, part));
+    share[qt] = part == TCA_PART_WINDOW || lastq < prm->window ? 0.0 : (double)(lastq - prm->window + 1) / (double)((q_pos0 + n_queries) * kBN);
+  }
+  double cap[TCA_MAX_HEADS];
+  for (int h = 0; h < Hq; ++h) cap[h] = (double)(offs[h / GS + 1] - offs[h / GS]);
+  auto cost = [&](int h, int qt) {                 // as tile_steps, which divides for every item
+    return window[qt] + (double)(int32_t)(cap[h] * share[qt] + (kBN - 1.0) / kBN);
   };
   double end = 0.0;
   if (n_items <= kSplitSlots / 2) {                // nobody shares a CU: the longest, a head's last query tile
     for (int h = 0; h < Hq; h += GS) end = std::max(end, alone(prm) * cost(h, n_qt - 1));
     return end;
   }
-  PrefillHeads ph;
-  if ((Hq & 7) == 0) plan_xcds(ph, prm, offs, q_pos0, n_queries, 128, part, 64);
+  double c[8][kSplitSlots / 8];                    // of the XCDs' items, in the order in which prefill_mfma_kernel counts them
+  if ((Hq & 7) == 0) {
+    PrefillHeads ph;
+    plan_xcds(ph, prm, offs, q_pos0, n_queries, 128, part, 64);
+    for (int x = 0; x < 8; ++x)
+      for (int k = 0, v = 0; k < n_qt; ++k)
+        for (int i = 0; i < nh; ++i) c[x][v++] = cost(ph.perm[x * nh + i], n_qt - 1 - k);
+  } else {
+    const int period = 8 / ((Hq & 1) ? 1 : (Hq & 2) ? 2 : 4);
+    for (int k = 0, g = 0; k < n_qt; ++k)
+      for (int i = 0, h = k / period % Hq; i < Hq; ++i, ++g, h = h + 1 < Hq ? h + 1 : 0) c[g & 7][g >> 3] = cost(h, n_qt - 1 - k);
+  }
   for (int x = 0; x < 8; ++x) {
     const int mine = (Hq & 7) == 0 ? nh * n_qt : (n_items - x + 7) >> 3;
-    auto item = [&](int u) {
-      const int v = pair_up(u, mine);
-      if ((Hq & 7) == 0) return cost(ph.perm[x * nh + v % nh], n_qt - 1 - v / nh);
-      const int g = v * 8 + x, k = g / Hq, period = 8 / ((Hq & 1) ? 1 : (Hq & 2) ? 2 : 4);
-      return cost((g - k * Hq + k / period) % Hq, n_qt - 1 - k);
-    };
     for (int u = 0; u < 32 && u < mine; ++u) {
-      const double a = item(u), b = u + 32 < mine ? item(u + 32) : 0.0;
+      const double a = c[x][pair_up(u, mine)], b = u + 32 < mine ? c[x][pair_up(u + 32, mine)] : 0.0;
       end = std::max(end, alone(prm) * std::fabs(a - b) + std::min(a, b));
     }
   }
@@ -1438,11 +1487,14 @@ static WgShape choose_shape(const tca_params* prm, const int64_t* offs, int64_t 
   const int64_t tiles = (n_queries + 255) / 256;
   bool many = tiles * prm->n_q_heads >= 1024;
   if (many && !gather && tiles < 24) {
-    int64_t steps = 0;
-    for (int h = 0; h < sel_heads(prm); ++h)
-      for (int64_t qt = 0; qt < tiles; ++qt)
-        steps += tile_steps(prm, offs[h + 1] - offs[h], q_pos0, n_queries, 256, qt, TCA_PART_ALL);
-    many = steps >= 130 * tiles * sel_heads(prm);
+    const int Hs = sel_heads(prm);
+    int64_t steps = 0, most = 0;                   // of all query tiles; of a head's last, and what another may have more of the window
+    for (int h = 0; h < Hs; ++h) most += 6 + tile_steps(prm, offs[h + 1] - offs[h], q_pos0, n_queries, 256, tiles - 1, TCA_PART_ALL);
+    if (most >= 130 * Hs)
+      for (int h = 0; h < Hs; ++h)
+        for (int64_t qt = 0; qt < tiles; ++qt)
+          steps += tile_steps(prm, offs[h + 1] - offs[h], q_pos0, n_queries, 256, qt, TCA_PART_ALL);
+    many = steps >= 130 * tiles * Hs;
   }
   if (gather) return {variant == 3 || (variant != 1 && many) ? 8 : 4, 1};
   if (variant == 3 || (variant == 0 && many)) return {8, 1};

@@ -224,6 +224,69 @@ def test_prefill_work_split_over_the_xcds():
         tb.tca_diag_prefill_xcd_plan(prm12, np.arange(13, dtype=np.int64) * 1000, 0, 4096)
 
 
+@pytest.mark.parametrize("hq,hkv,share,pos0,n", [
+    (8, 8, False, 0, 17000), (16, 4, False, 30000, 9001), (64, 8, False, 0, 5446), (64, 8, True, 0, 5446), (32, 8, False, 65536, 3000),
+    (32, 8, False, 114688, 8192), (64, 8, True, 65536, 6000), (64, 8, False, 0, 13000), (40, 8, False, 5000, 7777), (24, 8, False, 0, 12345)])
+def test_prefill_plan_is_that_of_a_plain_replay(hq, hkv, share, pos0, n):
+    """Order and ranges of calls of more than a round and fewer than sixteen against the same rule played through here, every
+    candidate, with a heap: what the plan leaves out cannot change its choice."""
+    import heapq
+
+    import paper_2512_09238_amd.binding as tb
+    w, GS, nh = 4096, hq // hkv if share else 1, hq // 8
+    prm = tb.make_params(hq, hkv, 128, 128, w, tb.TCA_BF16, share=tb.TCA_SHARE_GROUP if share else tb.TCA_SHARE_HEAD)
+    eight = -(-n // 256) * hq >= 1024                         # rows fetched through idx: the number of items alone decides
+    BM, slots = (256, 32) if eight else (128, 64)
+    n_qt, end = -(-n // BM), pos0 + n
+    assert 8 * slots < hq * n_qt < 8 * slots * 16
+    for seed in range(3):
+        cap = np.random.default_rng(seed).integers(0, int(0.5 * end), hq // GS)
+        offs = np.concatenate([[0], np.cumsum(cap)]).astype(np.int64)
+        first = pos0 + BM * np.arange(n_qt)[::-1]
+        last = np.minimum(first + BM - 1, end - 1)
+        dense = last // 64 - np.maximum(first - w + 1, 0) // 64 + 1
+        cost = [4 + dense + np.where(last >= w, (int(cap[h // GS]) * np.maximum(last - w + 1, 0) // end + 63) // 64, 0) for h in range(hq)]
+        flat = np.concatenate(cost)
+
+        def ends(xcds):
+            worst = 0
+            for items in xcds:
+                places = [0] * slots
+                for c in items:
+                    worst = max(worst, places[0] + int(c))
+                    heapq.heapreplace(places, places[0] + int(c))
+            return worst
+
+        def ranges(st):
+            cut = [max(a, b // n_qt * n_qt) for a, b in zip(st[:-1], st[1:])]
+            return ends([np.concatenate([flat[m:b], flat[a:m]]) for a, m, b in zip(st[:-1], cut, st[1:])])
+
+        by_head = [x * nh * n_qt for x in range(9)]
+        acc = np.cumsum(flat)
+        by_work = [0] + [int(np.argmax(acc * 8 >= acc[-1] * x)) + 1 for x in range(1, 8)] + [len(flat)]
+        order, heads, _ = tb.tca_diag_prefill_walk(prm, offs, pos0, n, 0, gather_free=True)
+        start, _ = tb.tca_diag_prefill_xcd_plan(prm, offs, pos0, n, gather_free=True)
+        deal = np.asarray(heads).reshape(8, nh) if order else None
+        if deal is None:                                      # dealt out by the last query tile's cost, the costliest first
+            deal, have, total = [[] for _ in range(8)], range(8), [0] * 8
+            for h in sorted(range(hq), key=lambda h: -cost[h][0]):
+                x = min((x for x in have if len(deal[x]) < nh), key=lambda x: (total[x], x))
+                deal[x].append(h)
+                total[x] += int(cost[h][0])
+            deal = np.arange(hq).reshape(8, nh) if share else np.asarray(deal)
+        one = ends([np.stack([cost[h] for h in d], 1).ravel() for d in deal])
+        two = ends([np.concatenate([cost[h] for h in d]) for d in deal])
+        t = min(ranges(by_head), ranges(by_work))
+        expected = 0
+        if two * 40 < t * 39:
+            t, expected = two, 2
+        if one * 20 < t * 19:
+            expected = 1
+        assert order == expected
+        if not expected:
+            assert list(start) == (by_head if ranges(by_head) <= ranges(by_work) else by_work)
+
+
 def test_prefill_of_ten_rounds_keeps_a_head_at_a_time():
     """Ten rounds of workgroups, heads of 4 % to 25 %: ranges of equal work, a head at a time.  Taking the heads of an XCD
     side by side, in whole heads, promises an end 4 % earlier and was 10 % later (all stream through one L2)."""
