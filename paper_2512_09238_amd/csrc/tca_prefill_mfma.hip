@@ -1354,10 +1354,10 @@ static double alone(const tca_params* prm) { return prm->head_dim == 128 ? 0.6 :
 // When a call of up to kSplitSlots four-wave workgroups, all resident at once, would end, in full steps: that of the CU whose
 // two (by the ids of prefill_mfma_kernel, an XCD's 32 CUs served in turn) take longest, the longer one alone once the other
 // has ended.  A call whose long heads meet on a CU runs to the end at the full chip's pace: 6363 queries of 8 heads (d = 64,
-// one to an XCD) behind 64K 587 us whole and 467 in chunks, 4187 of 12 heads 842 and 758; one whose long heads meet short ones
-// does not: 859 of 64 heads 796 and 880.  (A call cut for 5 % is still worth it: in chunks two workgroups to a CU hide each
-// other's waits for inputs that are not in the caches.  8192 queries of 4 heads, d = 64, behind 4096: 91 us whole, 74 in
-// chunks; 111 and 77 on such inputs.)
+// one to an XCD) behind 64K 562 us whole and 474 in chunks, 4000 of 12 heads behind 32768 293 and 250; one whose long heads
+// meet short ones does not: 859 of 64 heads (d = 128) 796 and 880.  (A call cut for 5 % is still worth it: in chunks two
+// workgroups to a CU hide each other's waits for inputs that are not in the caches.  8192 queries of 4 heads, d = 64, behind
+// 32768 236 us whole, 218 in chunks; 249 and 205 on such inputs.)
 static double whole_steps(const tca_params* prm, const int64_t* offs, int64_t q_pos0, int64_t n_queries, int part) {
   const int Hq = prm->n_q_heads, GS = sel_group(prm), nh = Hq / 8;
   const int n_qt = (int)((n_queries + 127) / 128), n_items = Hq * n_qt;
