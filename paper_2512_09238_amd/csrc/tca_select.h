@@ -31,4 +31,8 @@ void select_assign_stage(const tca_params* prm, int64_t n_tokens, const double* 
                          const double* stats, int32_t* n_rows, int32_t* blk_t, int32_t* blk_dst,
                          hipStream_t st);
 
+// The same for n configurations, each of which every selection head takes: blk_t, blk_dst [n][Hs][nb], n_rows [n][Hs]; p: [n][nk].
+void select_assign_all(const tca_params* prm, int64_t n_tokens, int n, const double* p, const double* stats, int32_t* n_rows,
+                       int32_t* blk_t, int32_t* blk_dst, hipStream_t st);
+
 }  // namespace tca

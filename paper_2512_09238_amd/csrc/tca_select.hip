@@ -319,12 +319,13 @@ __device__ __forceinline__ double block_reduce(double v, double* red) {
 // does (ha, ja) come after (hb, jb) in the order: ascending h, ties by lower block
 __device__ __forceinline__ bool comes_after(double ha, int ja, double hb, int jb) { return ha > hb || (ha == hb && ja > jb); }
 
-// grid (heads in this launch); block NT, R blocks per thread, m <= NT * R.  Everything is latency: the sort keeps its
+// grid (heads in this launch, or, heads_each > 0, configurations in this launch x heads_each heads that share one); block NT, R
+// blocks per thread, m <= NT * R.  Everything is latency: the sort keeps its
 // pairs in registers, exchanges at distances below 64 are lane shuffles, those between waves go through LDS
 // (barriers), those at NT and beyond stay inside the thread.
 template <int NT, int R>
 __global__ __launch_bounds__(NT) void assign_kernel(
-    AssignArgs args, int head0, int nk, int m, int nbt, int b, double alpha, int metric,
+    AssignArgs args, int head0, int heads_each, int nk, int m, int nbt, int b, double alpha, int metric,
     const double* __restrict__ stats, int32_t* __restrict__ n_rows,
     int32_t* __restrict__ blk_t, int32_t* __restrict__ blk_dst) {
   constexpr int P = NT * R;
@@ -334,8 +335,8 @@ __global__ __launch_bounds__(NT) void assign_kernel(
   __shared__ double red[NT / kWave];
   __shared__ int32_t wave_sum[NT / kWave];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int hl = blockIdx.x, h = head0 + hl;
-  const double* st = stats + (size_t)h * nbt * kBlockStats;
+  const int h = head0 + blockIdx.x, hl = heads_each ? blockIdx.x / heads_each : blockIdx.x;
+  const double* st = stats + (size_t)(heads_each ? h % heads_each : h) * nbt * kBlockStats;
   const int32_t fill = n_rows[h];
 
   // the statistics of this thread's blocks (block j = tid + k * NT, tail block included), read once
@@ -653,34 +654,55 @@ void select_score_stage(const tca_params* prm, const void* q_last, const void* K
   }
 }
 
+// One wave where it can hold all blocks (no barrier at all), then four, then sixteen, whose threads take four blocks
+// each at most.  us per launch, 32 heads: 64 blocks 12.5 -> 8.6, 3 blocks 8.5 -> 5.3, 1024 blocks 28.3 -> 20.3
+// (one shape of 1024 threads, the sort and the scan in LDS, before).
+static void launch_assign(const tca_params* prm, const AssignArgs& aa, int grid, int head0, int heads_each, int64_t n_tokens,
+                          const double* stats, int32_t* n_rows, int32_t* blk_t, int32_t* blk_dst, hipStream_t st) {
+  const int b = prm->block, nk = block_log2(b) + 1;
+  const int64_t nb = n_tokens / b, nbt = (n_tokens + b - 1) / b;
+  auto launch = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, aa, head0, heads_each, nk, (int)nb, (int)nbt, b, prm->alpha,
+                       prm->metric, stats, n_rows, blk_t, blk_dst);
+  };
+  if (nb <= 64) launch(assign_kernel<64, 1>, 64);
+  else if (nb <= 256) launch(assign_kernel<256, 1>, 256);
+  else if (nb <= 1024) launch(assign_kernel<1024, 1>, 1024);
+  else launch(assign_kernel<1024, 4>, 1024);
+}
+
+static void fill_cum(AssignArgs& aa, int i, int nk, int64_t nb, const double* p, int64_t cap) {
+  int64_t c[TCA_MAX_COUNTS], run = 0;
+  psi_counts(nk, nb, p, c);
+  for (int e = 0; e < nk; ++e) aa.cum[i][e] = (int32_t)(run += c[e]);
+  aa.cap[i] = cap;
+}
+
 // Stage 2: block metric, ranking and budgets for one configuration per selection head.
 // blk_t / blk_dst: [Hs][nb]; n_rows: [Hs] fill counters (in/out); cap: per-head capacity.
 void select_assign_stage(const tca_params* prm, int64_t n_tokens, const double* p, const int64_t* cap,
                          const double* stats, int32_t* n_rows, int32_t* blk_t, int32_t* blk_dst,
                          hipStream_t st) {
-  const int Hs = sel_heads(prm), b = prm->block, nk = block_log2(b) + 1;
-  const int64_t nb = n_tokens / b, nbt = (n_tokens + b - 1) / b;
+  const int Hs = sel_heads(prm), nk = block_log2(prm->block) + 1;
   for (int h0 = 0; h0 < Hs; h0 += kHeadsPerLaunch) {
     const int nh = Hs - h0 < kHeadsPerLaunch ? Hs - h0 : kHeadsPerLaunch;
     AssignArgs aa;
-    for (int hl = 0; hl < nh; ++hl) {
-      int64_t c[TCA_MAX_COUNTS];
-      psi_counts(nk, nb, p + (size_t)(h0 + hl) * nk, c);
-      int64_t run = 0;
-      for (int e = 0; e < nk; ++e) { run += c[e]; aa.cum[hl][e] = (int32_t)run; }
-      aa.cap[hl] = cap[h0 + hl];
-    }
-    // One wave where it can hold all blocks (no barrier at all), then four, then sixteen, whose threads take four blocks
-    // each at most.  us per launch, 32 heads: 64 blocks 12.5 -> 8.6, 3 blocks 8.5 -> 5.3, 1024 blocks 28.3 -> 20.3
-    // (one shape of 1024 threads, the sort and the scan in LDS, before).
-    auto launch = [&](auto kernel, int threads) {
-      hipLaunchKernelGGL(kernel, dim3(nh), dim3(threads), 0, st, aa, h0, nk, (int)nb, (int)nbt, b, prm->alpha, prm->metric,
-                         stats, n_rows, blk_t, blk_dst);
-    };
-    if (nb <= 64) launch(assign_kernel<64, 1>, 64);
-    else if (nb <= 256) launch(assign_kernel<256, 1>, 256);
-    else if (nb <= 1024) launch(assign_kernel<1024, 1>, 1024);
-    else launch(assign_kernel<1024, 4>, 1024);
+    for (int hl = 0; hl < nh; ++hl) fill_cum(aa, hl, nk, n_tokens / prm->block, p + (size_t)(h0 + hl) * nk, cap[h0 + hl]);
+    launch_assign(prm, aa, nh, h0, 0, n_tokens, stats, n_rows, blk_t, blk_dst, st);
+  }
+}
+
+// One launch for up to 32 of calibration's candidates (14 launches of 7 us before, 9 us now, 32 heads and 64 blocks).
+void select_assign_all(const tca_params* prm, int64_t n_tokens, int n, const double* p, const double* stats, int32_t* n_rows,
+                       int32_t* blk_t, int32_t* blk_dst, hipStream_t st) {
+  const int Hs = sel_heads(prm), nk = block_log2(prm->block) + 1;
+  for (int i0 = 0; i0 < n; i0 += kHeadsPerLaunch) {
+    const int ni = n - i0 < kHeadsPerLaunch ? n - i0 : kHeadsPerLaunch;
+    AssignArgs aa;
+    for (int i = 0; i < ni; ++i) fill_cum(aa, i, nk, n_tokens / prm->block, p + (size_t)(i0 + i) * nk, INT32_MAX);
+    const size_t off = (size_t)i0 * Hs;
+    launch_assign(prm, aa, ni * Hs, 0, Hs, n_tokens, stats, n_rows + off, blk_t + off * (n_tokens / prm->block),
+                  blk_dst + off * (n_tokens / prm->block), st);
   }
 }
 

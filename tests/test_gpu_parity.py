@@ -1029,6 +1029,48 @@ def test_calibrate_at_the_edges_of_its_tiles(tb, bufs, case):
     test_calibrate_budgets_matches_oracle(tb, bufs, case)
 
 
+# What the elements of a bf16 sample are to each other decides how its products are formed: (of 16 rows that share an exponent)
+# with a lowest digit, with one element left out (of K, of Q, of both at one column), with several, with logits in the thousands
+CALIB_ELEMENTS = ["plain", "low", "rest_k", "rest_q", "rest_both", "odd_k", "odd_q", "far", "far_rows"]
+
+
+@pytest.mark.parametrize("d,L", [(128, 333), (64, 160)])
+@pytest.mark.parametrize("kind", CALIB_ELEMENTS)
+def test_calibrate_whatever_the_elements_span(tb, bufs, kind, d, L):
+    """fp64 throughout: L sums and logits x of 2^-53 relative each, 1e-13 with x of tens, 1e-11 with thousands.  A workspace
+    without room for the digits takes the fp64 products, within the same bound."""
+    print("case", kind, d, L, flush=True)
+    Hq, Hkv, b, M = 4, 2, 16, 5
+    x = wl.prefill_inputs("lowrank", Hq, Hkv, d, L, "bf16", 81)
+    Q, K = wl.to_f64(x["Q"]), wl.to_f64(x["K"])
+    tiny = 3 * 2.0 ** -31                                            # of elements around one
+    if kind == "low":
+        K[:, :, ::3] *= 2.0 ** -17
+        Q[:, ::5, ::4] *= 2.0 ** -18
+    if kind in ("rest_k", "rest_both"):
+        K[:, 37, d - 5] = tiny
+    if kind in ("rest_q", "rest_both"):
+        Q[:, 101, d - 5] = -tiny
+    if kind == "odd_k":
+        K[:, 64:96, 7] = tiny
+    if kind == "odd_q":
+        Q[:, 64:67, 9] = tiny
+    if kind == "far":
+        Q *= 1024.0
+    if kind == "far_rows":                                           # the references of a few queries, far below the others'
+        Q[:, 70:75] *= -4096.0
+    Qb, Kb = (torch.from_numpy(v).to(torch.bfloat16) for v in (Q, K))
+    Qf, Kf = Qb.double().numpy(), Kb.double().numpy()
+    prm = H.params_for(tb, Hq, Hkv, d, b, b, "bf16")
+    ref = orc.calibrate(Qf, Kf, b, M, 1.0, 0.0, 0.5)
+    size = tb.tca_calibrate_workspace_bytes(prm, L, M)
+    for ws in (bufs.workspace(size), bufs.workspace(size)[:size - 256]):
+        ws.fill_(0xFF)
+        got = tb.tca_calibrate_budgets(prm, Qb.cuda(), Kb.cuda(), L, M, 1.0, 0.0, ws)
+        np.testing.assert_allclose(got["a"], np.stack([c.a for c in ref]), rtol=1e-11 if kind.startswith("far") else 1e-13, atol=0)
+        assert np.array_equal(got["n"], np.stack([c.n for c in ref]))
+
+
 @pytest.mark.parametrize("case", [(2, 1, 64, 300, 32, 40), (16, 4, 128, 1700, 96, 150)], ids=["16-queries", "64-queries"])
 def test_fp32_prefill_counts_a_position_held_more_than_once(tb, bufs, case):
     """Positions ascend but need not be distinct: a row held `times` times has that many keys, hidden from the first
