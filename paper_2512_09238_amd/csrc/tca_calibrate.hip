@@ -5,12 +5,14 @@
 //   rows      : per query row j, max and sum of exp of the causal logits        (softmax denominators)
 //   columns   : per key column k, sum_{j>=k} exp(x_jk - max_j) / sum_j, divided
 //               by the structural column count L-k                              (Eq. 4 inner term)
-// Both are passes of one kernel over Q K^T on the matrix cores (v_mfma_f64_16x16x4_f64, operands widened in
+// Samples in bf16 take their products in int8 digits (below).  fp32 samples, and calls whose workspace has no room for the
+// digits: both are passes of one kernel over Q K^T on the matrix cores (v_mfma_f64_16x16x4_f64, operands widened in
 // registers): a wave keeps 32 rows of one operand (the queries of its row statistics, the keys of its column sums) in
 // registers and streams the other through LDS.  The order of the head's elements inside a product is free as long as
 // both operands agree: lane kb takes the kb-th quarter of a row, so that LDS is read 16 bytes at a time (chunk index
-// xor row, conflict-free).  The bound is the fp64 matrix product, 64 cycles per 16 x 16 x 4 block and SIMD: 8192 tokens,
-// 32 heads, 3.6 ms per pass at 2.4 GHz, measured 5.1 and 4.9 ms; on the vector ALU (dot products of 16 lanes and a
+// xor row, conflict-free).  The bound is the fp64 matrix product, 64 cycles per 16 x 16 x 4 block and SIMD, and the exponentials
+// (24 fp64 instructions) on top of it: fp64 instructions of the vector ALU do not run beside it (8 multiply-adds and one block
+// 102 cycles, 36 and 64 alone).  8192 tokens, 32 heads, bf16: 3.6 ms of products per pass at 2.4 GHz, measured 5.1 and 4.9 ms; on the vector ALU (dot products of 16 lanes and a
 // butterfly) the passes took 16.5 and 18.9 ms.
 // The selection of every candidate reuses the online-selection stages (scores
 // and in-block ranks once, budgets per candidate); cand_score sums the column
@@ -286,6 +288,13 @@ __global__ __launch_bounds__(256) void cal_digits_kernel(const bf16_t* __restric
 // Where no logit can be further than kFar from zero (by the norms, Cauchy and Schwarz) any reference as near will do, and
 // nothing can leave its range: adding kMagic rounds, and the whole number lies in the lower half of the sum.  Elsewhere and on
 // the diagonal the reference follows the maximum, step by step.
+//
+// 8192 tokens, 32 heads, d = 128: 1.38 and 1.46 ms, where the passes above take 5.05 and 4.92.  The bound is instruction issue: per
+// 16 x 16 block 18 products of 16 cycles (32 with a lowest digit), 7 (10) instructions an element to put the sums together, 11
+// for the exponential, at 4 to 5.4 cycles each; the matrix cores are busy 40 % of the time.  Three waves a SIMD, although some
+// registers of the uncommon paths spill for it, against two: 1.38 / 1.48.  A tile's two halves are written out in one block so that
+// the second's products run under the first's exponentials.  One element left out of a group: with its products in fp64
+// instead the few workgroups that have one end last, 1.83 ms.
 template <int D, bool COL>
 __global__ __launch_bounds__(kCalThreads, 3) void cal_digit_pass_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const i32x4_t* __restrict__ Qd, const i32x4_t* __restrict__ Kd,
@@ -608,7 +617,7 @@ __global__ __launch_bounds__(kCalThreads) void cal_cand_score_kernel(
   const uint8_t* tr = tokrank + (size_t)h * (nb * b);
   double acc = 0.0;
   long long cnt = 0;
-  // (loads without regard to the rank, several tokens ahead: 26 -> 12 us for 14 candidates of 32 heads and 8192 tokens)
+  // (loads without regard to the rank, several tokens ahead: 26 -> 16 us for 14 candidates of 32 heads and 8192 tokens)
   const int lb = __builtin_ctz(b);
 #pragma unroll 4
   for (int64_t k = tid; k < nb * b; k += kCalThreads) {
