@@ -192,6 +192,24 @@ template <typename V> __device__ __forceinline__ V group_max(V v, int width) {
   return v;
 }
 
+// The butterflies over a whole wave for doubles (xor 32, 16, 8 .. 1, every lane has the result, bit for bit group_sum's), on
+// the vector ALU: lane swaps, then DPP.  Six exchanges of two shuffles each through LDS take about 1500 cycles, these 250.
+constexpr int kDppRor8 = 0x128, kDppRor4 = 0x124;       // xor 8; xor 4 once lanes i and i ^ 8 hold the same
+template <typename OP> __device__ __forceinline__ double wave_reduce(double v, OP op) {
+  auto swapped = [&](auto swap) {
+    const auto lo = swap((unsigned)__double2loint(v)), hi = swap((unsigned)__double2hiint(v));
+    return op(__hiloint2double((int)hi[0], (int)lo[0]), __hiloint2double((int)hi[1], (int)lo[1]));
+  };
+  v = swapped([](unsigned x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
+  v = swapped([](unsigned x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
+  v = op(v, dpp_f64<kDppRor8>(v));
+  v = op(v, dpp_f64<kDppRor4>(v));
+  v = op(v, dpp_f64<kDppXor2>(v));
+  return op(v, dpp_f64<kDppXor1>(v));
+}
+__device__ __forceinline__ double wave_sum(double v) { return wave_reduce(v, [](double a, double b) { return a + b; }); }
+__device__ __forceinline__ double wave_max(double v) { return wave_reduce(v, [](double a, double b) { return fmax(a, b); }); }
+
 // Number of entries <= bound among the ascending idx[0..n), found by a whole wave: every
 // round probes the last element of up to 64 equal chunks of the open range, so 2^18 rows take
 // three dependent loads instead of eighteen.  Result in every lane.

@@ -18,7 +18,9 @@
 //   gather_kernel : one workgroup per (head, block).  Ranks the block's tokens by
 //                   counting over their keys (skipped when t_j = b), keeps those
 //                   with rank < t_j in position order and copies their K/V rows
-//                   and positions into the head's flat region (App. C).
+//                  and positions into the head's flat region (App. C).  With
+//                   few blocks its waves assign the budgets themselves, and
+//                   assign_kernel is not launched.
 // When the query heads of a group share one selection (an extension for GQA), the
 // scores of the group's heads have to be normalised before they can be averaged:
 // score_kernel then leaves the fp64 logits in the workspace, group_lse_kernel turns
@@ -26,6 +28,8 @@
 // merges the G logits of a token into one log-domain score and produces the block
 // statistics and ranking keys of that score; assign and gather run once per KV head.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "tca_common.h"
 #include "tca_device.h"
@@ -37,6 +41,10 @@ constexpr int kScoreThreads = 256;
 constexpr int kGatherThreads = 256;
 constexpr int kGatherRows = 2;        // rows per thread in flight in the copy loop (4 measured the same)
 constexpr int kHeadsPerLaunch = 32;
+// Blocks, the tail included, that a wave holds one to a lane: up to there the launches between the scores and the copy, which
+// are all latency, go into the kernels behind them.  us of the kernels behind the scores, with launches of their own and without:
+// 1024 tokens of 4 heads (32 blocks of 32) 10.5 / 6.7; 413 of 32 heads 12.3 / 8.0; 5446 of a shared selection 28.0 / 20.1.
+constexpr int kFewBlocks = 64;
 constexpr int kBlockStats = 4;        // doubles per (head, block) in SelectWs::stats
 
 // the group's query heads are merged into one score only when there is more than one of them
@@ -103,7 +111,7 @@ __global__ __launch_bounds__(kScoreThreads) void score_kernel(
     const T* __restrict__ K, const T* __restrict__ q_last, int64_t kv_stride, int64_t pos0,
     int64_t n_tokens, int b, int64_t n_blocks, int64_t nbt, int Hq, double scale,
     uint8_t* __restrict__ tokrank, uint64_t* __restrict__ keys_out, double* __restrict__ stats,
-    double* __restrict__ xlog) {
+    double* __restrict__ xlog, const int32_t* __restrict__ n_rows, int32_t* __restrict__ fill) {
   constexpr bool RANK = EMIT == kEmitRanks;
   constexpr int EPL = Vec16<T>::N;            // elements per lane per load
   constexpr int LPR = D / EPL;                // lanes per row
@@ -120,6 +128,7 @@ __global__ __launch_bounds__(kScoreThreads) void score_kernel(
   const int64_t j = blockIdx.x;
   const int kvh = blockIdx.y;
   const int sub = lane % LPR, rsub = lane / LPR;
+  if (EMIT == kEmitKeys && fill && j == 0 && tid < G) fill[kvh * G + tid] = n_rows[kvh * G + tid];       // as group_score_kernel
 
   double qv[GP][EPL];
 #pragma unroll
@@ -170,7 +179,7 @@ __global__ __launch_bounds__(kScoreThreads) void score_kernel(
   for (int g = wv; g < G; g += kScoreThreads / kWave) {
     double mx = -INFINITY;
     for (int i = lane; i < b; i += kWave) mx = fmax(mx, xs[g][i]);
-    mx = group_max(mx, kWave);
+    mx = wave_max(mx);
     double e1 = 0.0, e2 = 0.0, e3 = 0.0;
     for (int i = lane; i < b; i += kWave) {
       const double dx = xs[g][i] - mx;
@@ -179,9 +188,9 @@ __global__ __launch_bounds__(kScoreThreads) void score_kernel(
       e2 += e * e;
       if (e > 0.0) e3 += e * dx;                         // 0 * (-inf) counts as 0
     }
-    e1 = group_sum(e1, kWave);
-    e2 = group_sum(e2, kWave);
-    e3 = group_sum(e3, kWave);
+    e1 = wave_sum(e1);
+    e2 = wave_sum(e2);
+    e3 = wave_sum(e3);
     if (lane == 0) {
       double* st = stats + ((size_t)(kvh * G + g) * nbt + j) * kBlockStats;
       st[0] = mx; st[1] = e1; st[2] = e2; st[3] = e3;
@@ -228,35 +237,53 @@ __global__ __launch_bounds__(256) void group_lse_kernel(const double* __restrict
   const double* st = stats + (size_t)blockIdx.x * nbt * kBlockStats;
   double mx = -INFINITY;
   for (int j = tid; j < nbt; j += 256) mx = fmax(mx, st[(size_t)j * kBlockStats]);
-  mx = group_max(mx, kWave);
+  mx = wave_max(mx);
   if (lane == 0) red[wv] = mx;
   __syncthreads();
   mx = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
   __syncthreads();
   double z = 0.0;
   for (int j = tid; j < nbt; j += 256) z += st[(size_t)j * kBlockStats + 1] * exp(st[(size_t)j * kBlockStats] - mx);
-  z = group_sum(z, kWave);
+  z = wave_sum(z);
   if (lane == 0) red[wv] = z;
   __syncthreads();
   if (tid == 0) lse[blockIdx.x] = mx + log((red[0] + red[1]) + (red[2] + red[3]));
 }
 
 // grid (nbt, Hkv); block 256: thread i owns token i of the block.
+// lse == NULL (up to kFewBlocks blocks): the workgroup forms the normalisers of its heads itself, a wave a head and a lane a
+// block, the same sums as group_lse_kernel's.  fill != NULL: n_rows as it is before this selection, for gather_kernel.
 template <int G, bool RANK>
 __global__ __launch_bounds__(256) void group_score_kernel(
-    const double* __restrict__ xlog, const double* __restrict__ lse, int b, int64_t n_blocks, int64_t nbt,
-    uint8_t* __restrict__ tokrank, uint64_t* __restrict__ keys_out, double* __restrict__ gstats) {
+    const double* __restrict__ xlog, const double* __restrict__ lse, const double* __restrict__ stats, int b, int64_t n_blocks,
+    int64_t nbt, uint8_t* __restrict__ tokrank, uint64_t* __restrict__ keys_out, double* __restrict__ gstats,
+    const int32_t* __restrict__ n_rows, int32_t* __restrict__ fill) {
   __shared__ double red[4][3];
+  __shared__ double norm[G];
   __shared__ __attribute__((aligned(16))) uint64_t keys[256];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int64_t j = blockIdx.x;
   const int kvh = blockIdx.y;
+  if (fill && j == 0 && tid == 0) fill[kvh] = n_rows[kvh];
+  double a[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) a[g] = tid < b ? xlog[((size_t)(kvh * G + g) * nbt + j) * b + tid] : 0.0;
+  if (!lse) {
+    for (int g = wv; g < G; g += 4) {
+      const double* st = stats + ((size_t)(kvh * G + g) * nbt + lane) * kBlockStats;
+      const double bM = lane < nbt ? st[0] : -INFINITY, bE = lane < nbt ? st[1] : 0.0;
+      const double mx = wave_max(fmax(-INFINITY, bM));
+      const double z = wave_sum(lane < nbt ? bE * exp(bM - mx) : 0.0);
+      if (lane == 0) norm[g] = mx + log(z);
+    }
+    __syncthreads();
+  }
   double y = -INFINITY;
   if (tid < b) {
-    double a[G], top = -INFINITY;
+    double top = -INFINITY;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      a[g] = xlog[((size_t)(kvh * G + g) * nbt + j) * b + tid] - lse[kvh * G + g];
+      a[g] -= lse ? lse[kvh * G + g] : norm[g];
       top = fmax(top, a[g]);
     }
     if (top > -INFINITY) {                                 // a token past the end of the tail stays at -inf
@@ -266,15 +293,15 @@ __global__ __launch_bounds__(256) void group_score_kernel(
       y = top + log(sum);
     }
   }
-  double mx = group_max(y, kWave);
+  double mx = wave_max(y);
   if (lane == 0) red[wv][0] = mx;
   __syncthreads();
   mx = fmax(fmax(red[0][0], red[1][0]), fmax(red[2][0], red[3][0]));
   __syncthreads();
   const double dx = y - mx;
   const double e = y > -INFINITY ? exp(dx) : 0.0;
-  const double e1 = group_sum(e, kWave), e2 = group_sum(e * e, kWave);
-  const double e3 = group_sum(e > 0.0 ? e * dx : 0.0, kWave);
+  const double e1 = wave_sum(e), e2 = wave_sum(e * e);
+  const double e3 = wave_sum(e > 0.0 ? e * dx : 0.0);
   if (lane == 0) { red[wv][0] = e1; red[wv][1] = e2; red[wv][2] = e3; }
   __syncthreads();
   if (tid == 0) {
@@ -304,7 +331,7 @@ struct AssignArgs {
 // max / sum over the NT threads of the workgroup, result in every thread; red: one double per wave
 template <int NT, bool MAX>
 __device__ __forceinline__ double block_reduce(double v, double* red) {
-  v = MAX ? group_max(v, kWave) : group_sum(v, kWave);
+  v = MAX ? wave_max(v) : wave_sum(v);
   if constexpr (NT > kWave) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     __syncthreads();
@@ -314,6 +341,16 @@ __device__ __forceinline__ double block_reduce(double v, double* red) {
     for (int i = 1; i < NT / kWave; ++i) v = MAX ? fmax(v, red[i]) : v + red[i];
   }
   return v;
+}
+
+// Eq. 6: h of a block from its mass in the whole and its statistics (s2: the one that the chosen index needs).  HHI of the
+// block, or the entropy of the scores renormalised inside it: t_i = e_i / E1  =>  -sum t_i ln t_i = ln E1 - (sum e_i (x_i - M)) / E1
+// A row that is not finite makes every h of its head NaN.  Both sides of a pair decide for themselves in the sort, which
+// leaves the blocks a permutation only in a total order: NaN takes the last place, ties by block as ever.
+__device__ __forceinline__ double block_index(double mass, double e1, double s2, int b, double alpha, int metric) {
+  const double spread = metric == TCA_METRIC_ENTROPY ? (log(e1) - s2 / e1) / log((double)b) : 1.0 - s2 / (e1 * e1);
+  const double hj = (1.0 - alpha) * mass + alpha * spread;
+  return hj == hj ? hj : INFINITY;
 }
 
 // does (ha, ja) come after (hb, jb) in the order: ascending h, ties by lower block
@@ -371,18 +408,7 @@ __global__ __launch_bounds__(NT) void assign_kernel(
     const int j = tid + k * NT;
     key[k] = INFINITY;                                 // padding sorts last
     blk[k] = j;
-    if (j < m) {
-      const double mass = bM[k] / z;
-      // HHI of the block (Eq. 6), or the entropy of the scores renormalised inside it:
-      // t_i = e_i / E1  =>  -sum t_i ln t_i = ln E1 - (sum e_i (x_i - M)) / E1
-      const double spread = metric == TCA_METRIC_ENTROPY
-                                ? (log(bE1[k]) - bE2[k] / bE1[k]) / log((double)b)
-                                : 1.0 - bE2[k] / (bE1[k] * bE1[k]);
-      const double hj = (1.0 - alpha) * mass + alpha * spread;
-      // A row that is not finite makes every h of its head NaN.  Both sides of a pair decide for themselves below, which
-      // leaves the blocks a permutation only in a total order: NaN takes the last place, ties by block as ever.
-      if (hj == hj) key[k] = hj;
-    }
+    if (j < m) key[k] = block_index(bM[k] / z, bE1[k], bE2[k], b, alpha, metric);
   }
 
   // order the blocks by ascending h (ties: lower block first) with a bitonic sort of (h, block) pairs,
@@ -486,17 +512,28 @@ __global__ __launch_bounds__(NT) void assign_kernel(
 // ----------------------------------------------------------------- gather --
 // offsets of the heads' regions travel in the kernel's argument block: no copy, no extra launch
 struct OffsArgs { int64_t offs[TCA_MAX_HEADS + 1]; };
+struct NoFew {};
+struct FewArgs {                                 // assign_kernel's, for up to kFewBlocks blocks
+  uint64_t cum[TCA_MAX_HEADS];                   // byte i: how many blocks get 2^i tokens or fewer
+  int nk, nbt, metric;
+  double alpha;
+  const double* stats;
+  const int32_t* fill;                           // n_rows as it was
+  int32_t* n_rows;
+};
 
 // grid (n_blocks * selection heads); block 256.  G: selection heads per KV head.
 // Workgroup ids go round-robin over the 8 XCDs.  The G selection heads of a KV head keep
 // overlapping subsets of the same block's rows, so their workgroups are given ids 8 apart:
 // same XCD, consecutive in time, and the rows a later one needs are mostly in that L2 already.
-template <typename T, int D>
+// FEW: every wave assigns its head's budgets for itself (the waves of a workgroup run side by side, which costs less than
+// sharing), a lane a block: the sums as assign_kernel forms them, a block's place by counting the blocks that precede it.
+template <typename T, int D, bool FEW>
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
     const T* __restrict__ K, const T* __restrict__ V, int64_t kv_stride, int64_t pos0, int b,
     int64_t n_blocks, int G, const uint64_t* __restrict__ keys,
     const int32_t* __restrict__ blk_t, const int32_t* __restrict__ blk_dst,
-    OffsArgs oa, int32_t* __restrict__ idx, T* __restrict__ Kg, T* __restrict__ Vg) {
+    OffsArgs oa, int32_t* __restrict__ idx, T* __restrict__ Kg, T* __restrict__ Vg, std::conditional_t<FEW, FewArgs, NoFew> few) {
   constexpr int EPL = Vec16<T>::N;
   constexpr int LPR = D / EPL;
   constexpr int RPI = kGatherThreads / LPR;
@@ -521,16 +558,47 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
       kvh = h / G;
     }
   }
-  const int t = min(blk_t[(size_t)h * n_blocks + j], b);               // sel below has room for b rows, whatever it is told
   const int64_t base = oa.offs[h], cap = oa.offs[h + 1] - base;
-  const int64_t dst0 = blk_dst[(size_t)h * n_blocks + j];
+  int t;
+  int64_t dst0;
+  uint64_t my_key = 0;
+  if constexpr (FEW) {
+    const double* st = few.stats + ((size_t)h * few.nbt + lane) * kBlockStats;
+    const bool in = lane < few.nbt;
+    const double bM = in ? st[0] : -INFINITY, bE1 = in ? st[1] : 0.0, bE2 = in ? st[few.metric == TCA_METRIC_ENTROPY ? 3 : 2] : 0.0;
+    const int32_t fill = few.fill[h];
+    if (tid < b) my_key = keys[(size_t)h * (n_blocks * b) + j * b + tid];
+    const double mx = wave_max(fmax(-INFINITY, bM));
+    const double own = in ? bE1 * exp(bM - mx) : 0.0, z = wave_sum(own);
+    const int m = (int)n_blocks;
+    const double hj = lane < m ? block_index(own / z, bE1, bE2, b, few.alpha, few.metric) : INFINITY;
+    int r = 0;
+    for (int i = 0; i < m; ++i) {
+      const double hi = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(hj), i), __builtin_amdgcn_readlane(__double2loint(hj), i));
+      r += comes_after(hj, lane, hi, i);
+    }
+    const uint64_t cum = few.cum[h];
+    int e = 0, before = 0, all = 0;
+    for (int i = 0; i < few.nk - 1; ++i) e += r >= (int)((cum >> (8 * i)) & 255);
+    for (int i = 0; i < few.nk; ++i) {             // tokens of the blocks before this one, and of all
+      const uint64_t who = __ballot(lane < m && e == i);
+      before += __popcll(who & ((1ull << j) - 1)) << i;
+      all += __popcll(who) << i;
+    }
+    t = min(1 << __builtin_amdgcn_readlane(e, (int)j), b);
+    dst0 = (int64_t)fill + before;
+    if (j == 0 && tid == 0) few.n_rows[h] = (int32_t)((int64_t)fill + all > cap ? cap : (int64_t)fill + all);
+  } else {
+    t = min(blk_t[(size_t)h * n_blocks + j], b);                       // sel below has room for b rows, whatever it is told
+    dst0 = blk_dst[(size_t)h * n_blocks + j];
+  }
 
   // Eq. 8: rank of every token inside the block, all 256 threads share the b*b comparisons;
   // nothing to rank when the whole block is kept
   bool keep = tid < b;
   if (t < b) {
     if (tid < b) {
-      bkeys[tid] = keys[(size_t)h * (n_blocks * b) + j * b + tid];
+      bkeys[tid] = FEW ? my_key : keys[(size_t)h * (n_blocks * b) + j * b + tid];
       rank[tid] = 0;
     }
     __syncthreads();
@@ -590,12 +658,12 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
 template <typename T, int D, int EMIT>
 static void launch_score(int G, dim3 grid, hipStream_t st, const T* K, const T* q, int64_t kv_stride,
                          int64_t pos0, int64_t n_tokens, int b, int64_t nb, int64_t nbt, int Hq,
-                         double scale, const SelectWs& w) {
+                         double scale, const SelectWs& w, const int32_t* n_rows, int32_t* fill) {
 #define TCA_SCORE_CASE(GG)                                                                           \
   case GG:                                                                                           \
     hipLaunchKernelGGL((score_kernel<T, D, GG, EMIT>), grid, dim3(kScoreThreads), 0, st, K, q,       \
                        kv_stride, pos0, n_tokens, b, nb, nbt, Hq, scale, w.tokrank, w.keys, w.stats, \
-                       w.xlog);                                                                      \
+                       w.xlog, n_rows, fill);                                                        \
     break;
   switch (G) {
     TCA_SCORE_CASE(1) TCA_SCORE_CASE(2) TCA_SCORE_CASE(3) TCA_SCORE_CASE(4)
@@ -606,13 +674,17 @@ static void launch_score(int G, dim3 grid, hipStream_t st, const T* K, const T* 
 
 template <bool RANK>
 static void launch_group_score(int G, int Hq, int Hkv, int b, int64_t nb, int64_t nbt, const SelectWs& w,
-                               hipStream_t st) {
-  hipLaunchKernelGGL(group_lse_kernel, dim3(Hq), dim3(256), 0, st, w.stats, (int)nbt, w.lse);
+                               const int32_t* n_rows, int32_t* fill, hipStream_t st) {
+  const double* lse = nullptr;
+  if (nbt > kFewBlocks) {
+    hipLaunchKernelGGL(group_lse_kernel, dim3(Hq), dim3(256), 0, st, w.stats, (int)nbt, w.lse);
+    lse = w.lse;
+  }
   const dim3 grid((unsigned)nbt, Hkv);
 #define TCA_GROUP_CASE(GG)                                                                              \
   case GG:                                                                                              \
-    hipLaunchKernelGGL((group_score_kernel<GG, RANK>), grid, dim3(256), 0, st, w.xlog, w.lse, b, nb, nbt, \
-                       w.tokrank, w.keys, w.sel_stats);                                                 \
+    hipLaunchKernelGGL((group_score_kernel<GG, RANK>), grid, dim3(256), 0, st, w.xlog, lse, w.stats, b, nb, nbt, \
+                       w.tokrank, w.keys, w.sel_stats, n_rows, fill);                                   \
     break;
   switch (G) {
     TCA_GROUP_CASE(2) TCA_GROUP_CASE(3) TCA_GROUP_CASE(4) TCA_GROUP_CASE(5)
@@ -622,20 +694,20 @@ static void launch_group_score(int G, int Hq, int Hkv, int b, int64_t nb, int64_
 }
 
 // Scores tokens [pos0, pos0 + n_tokens) for every selection head: block statistics in
-// w.sel_stats, and in-block ranks in w.tokrank (RANK) or ranking keys in w.keys.
+// w.sel_stats, and in-block ranks in w.tokrank (RANK) or ranking keys in w.keys.  fill: where the heads' n_rows go, or NULL.
 template <typename T, int D, bool RANK>
 static void score_stage(const tca_params* prm, const T* q_last, const T* K, int64_t kv_stride, int64_t pos0,
-                        int64_t n_tokens, const SelectWs& w, hipStream_t st) {
+                        int64_t n_tokens, const SelectWs& w, const int32_t* n_rows, int32_t* fill, hipStream_t st) {
   const int Hq = prm->n_q_heads, Hkv = prm->n_kv_heads, G = Hq / Hkv, b = prm->block;
   const int64_t nb = n_tokens / b, nbt = (n_tokens + b - 1) / b;
   const dim3 grid((unsigned)nbt, Hkv);
   const double sc = logit_scale(prm);
   if (grouped(prm)) {
-    launch_score<T, D, kEmitLogits>(G, grid, st, K, q_last, kv_stride, pos0, n_tokens, b, nb, nbt, Hq, sc, w);
-    launch_group_score<RANK>(G, Hq, Hkv, b, nb, nbt, w, st);
+    launch_score<T, D, kEmitLogits>(G, grid, st, K, q_last, kv_stride, pos0, n_tokens, b, nb, nbt, Hq, sc, w, nullptr, nullptr);
+    launch_group_score<RANK>(G, Hq, Hkv, b, nb, nbt, w, n_rows, fill, st);
   } else {
     launch_score<T, D, RANK ? kEmitRanks : kEmitKeys>(G, grid, st, K, q_last, kv_stride, pos0, n_tokens, b, nb,
-                                                      nbt, Hq, sc, w);
+                                                      nbt, Hq, sc, w, n_rows, fill);
   }
 }
 
@@ -645,12 +717,12 @@ void select_score_stage(const tca_params* prm, const void* q_last, const void* K
                         int64_t n_tokens, const SelectWs& w, hipStream_t st) {
   if (prm->dtype == TCA_BF16) {
     using T = bf16_t;
-    if (prm->head_dim == 128) score_stage<T, 128, true>(prm, (const T*)q_last, (const T*)K, kv_stride, 0, n_tokens, w, st);
-    else score_stage<T, 64, true>(prm, (const T*)q_last, (const T*)K, kv_stride, 0, n_tokens, w, st);
+    if (prm->head_dim == 128) score_stage<T, 128, true>(prm, (const T*)q_last, (const T*)K, kv_stride, 0, n_tokens, w, nullptr, nullptr, st);
+    else score_stage<T, 64, true>(prm, (const T*)q_last, (const T*)K, kv_stride, 0, n_tokens, w, nullptr, nullptr, st);
   } else {
     using T = float;
-    if (prm->head_dim == 128) score_stage<T, 128, true>(prm, (const T*)q_last, (const T*)K, kv_stride, 0, n_tokens, w, st);
-    else score_stage<T, 64, true>(prm, (const T*)q_last, (const T*)K, kv_stride, 0, n_tokens, w, st);
+    if (prm->head_dim == 128) score_stage<T, 128, true>(prm, (const T*)q_last, (const T*)K, kv_stride, 0, n_tokens, w, nullptr, nullptr, st);
+    else score_stage<T, 64, true>(prm, (const T*)q_last, (const T*)K, kv_stride, 0, n_tokens, w, nullptr, nullptr, st);
   }
 }
 
@@ -717,14 +789,38 @@ static int run_select(const tca_params* prm, const T* q_last, const T* K, const 
   OffsArgs oa;
   for (int h = 0; h <= Hs; ++h) oa.offs[h] = offs[h];
 
-  score_stage<T, D, false>(prm, q_last, K, kv_stride, pos0, n_tokens, w, st);
+  const bool few = nb > 0 && (n_tokens + b - 1) / b <= kFewBlocks;
+  int32_t* const fill = few ? w.blk_t : nullptr;                       // [Hs], in a place that such a call has no other use for
+  score_stage<T, D, false>(prm, q_last, K, kv_stride, pos0, n_tokens, w, n_rows, fill, st);
   if (nb == 0) return TCA_OK;
 
+  auto gather = [&](auto few_tag, const auto& args) {
+    hipLaunchKernelGGL((gather_kernel<T, D, decltype(few_tag)::value>), dim3((unsigned)(nb * Hs)), dim3(kGatherThreads), 0, st, K, V,
+                       kv_stride, pos0, b, nb, Hs / Hkv, w.keys, w.blk_t, w.blk_dst, oa, idx, Kg, Vg, args);
+  };
+  if (few) {
+    const int nk = block_log2(b) + 1;
+    FewArgs fa;
+    for (int h = 0; h < Hs; ++h) {
+      int64_t c[TCA_MAX_COUNTS], run = 0;
+      psi_counts(nk, nb, p + (size_t)h * nk, c);
+      fa.cum[h] = 0;
+      for (int e = 0; e < nk - 1; ++e) fa.cum[h] |= (uint64_t)(run += c[e]) << (8 * e);
+    }
+    fa.nk = nk;
+    fa.nbt = (int)((n_tokens + b - 1) / b);
+    fa.metric = prm->metric;
+    fa.alpha = prm->alpha;
+    fa.stats = w.sel_stats;
+    fa.fill = fill;
+    fa.n_rows = n_rows;
+    gather(std::true_type{}, fa);
+    return TCA_OK;
+  }
   int64_t cap[TCA_MAX_HEADS];
   for (int h = 0; h < Hs; ++h) cap[h] = offs[h + 1] - offs[h];
   select_assign_stage(prm, n_tokens, p, cap, w.sel_stats, n_rows, w.blk_t, w.blk_dst, st);
-  hipLaunchKernelGGL((gather_kernel<T, D>), dim3((unsigned)(nb * Hs)), dim3(kGatherThreads), 0, st, K, V,
-                     kv_stride, pos0, b, nb, Hs / Hkv, w.keys, w.blk_t, w.blk_dst, oa, idx, Kg, Vg);
+  gather(std::false_type{}, NoFew{});
   return TCA_OK;
 }
 

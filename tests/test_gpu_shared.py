@@ -66,6 +66,37 @@ def test_shared_select_matches_oracle(mods, case, metric):
         assert differs, "the shared sets equal the first head's own sets: the group mean is not exercised"
 
 
+@pytest.mark.parametrize("share", [False, True])
+@pytest.mark.parametrize("blocks,tail", [(1, 0), (1, 3), (63, 5), (64, 0), (64, 1), (65, 0)], ids=lambda v: str(v))
+def test_selections_of_few_blocks_go_on_where_the_fill_stood(mods, share, blocks, tail):
+    """Up to 64 blocks, the tail included, the waves of the copy assign the budgets themselves: the sets of a chunk behind rows
+    that are there already, the fill advanced once, and cut off at the region's end (the first head has room for three rows less)."""
+    tb, bufs, _ = mods
+    Hq, Hkv, d, b, pos0 = 6, 2, 64, 16, 48
+    L = pos0 + blocks * b + tail
+    x = wl.prefill_inputs("lowrank", Hq, Hkv, d, L, "bf16", 118)
+    Hs = Hkv if share else Hq
+    P_gpu, P_orc = configs(tb, b, wl.budget_fractions(119, Hs))
+    prm = H.params_for(tb, Hq, Hkv, d, b, 32, "bf16", share=share)
+    _, rows = tb.tca_select_rows(prm, blocks, P_gpu)
+    first = np.arange(Hs) + 2
+    gb = bufs.GlobalBuffers(prm, rows + first - 3 * (np.arange(Hs) == 0))
+    gb.idx.fill_(-7)
+    gb.n_rows.copy_(torch.from_numpy(first.astype(np.int32)))
+    H.gpu_select(tb, bufs, prm, x, P_gpu, pos0=pos0, gb=gb)
+    q, K = wl.to_f64(x["Q"][:, L - 1]), wl.to_f64(x["K"])[:, pos0:]
+    sels = (orc.select_all_groups if share else orc.select_all_heads)(q, K, b, P_orc, 0.5)
+    for h in range(Hs):
+        got = H.head_indices(gb, h)
+        cap = int(gb.offs[h + 1] - gb.offs[h])
+        assert len(got) == cap == first[h] + rows[h] - (3 if h == 0 else 0)
+        assert (got[:first[h]] == -7).all()
+        if h:
+            H.assert_selection(sels[h], got[first[h]:] - pos0, b, P_orc[h], tag=f"head {h}")
+        else:
+            assert np.array_equal(got[first[h]:] - pos0, sels[h].S[:len(got) - first[h]])
+
+
 PREFILL_CASES = [
     ("centroid", 4, 1, 64, 1024, "f32", 32, 128, 1001),
     ("lowrank", 8, 2, 128, 1500, "bf16", 128, 256, 131),
