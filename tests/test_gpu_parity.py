@@ -861,6 +861,23 @@ def test_fp32_prefill_both_key_splits(tb, bufs, case):
     assert worst <= 1e-5
 
 
+F32_SEARCH_CASES = [
+    # 64 queries per workgroup (640 workgroups of them and more), with more rows to search than one round of loads; the same for
+    # 16 queries, four waves and eight; a window almost as long as the context; few queries
+    (64, 8, 64, 1500, 700, 64, False, False),
+    (64, 8, 128, 900, 259, 32, True, True),
+    (8, 2, 64, 6000, 5400, 64, False, False),
+    (4, 1, 128, 6000, 5950, 64, False, True),
+    (4, 1, 64, 700, 690, 672, False, False),
+    (2, 1, 64, 900, 896, 32, False, False),
+]
+
+
+@pytest.mark.parametrize("case", F32_SEARCH_CASES, ids=lambda c: f"Hq{c[0]}-Hkv{c[1]}-d{c[2]}-L{c[3]}-q{c[4]}-w{c[5]}-share{c[6]}-free{c[7]}")
+def test_fp32_prefill_finds_its_rows(tb, bufs, case):
+    test_fp32_prefill_both_key_splits(tb, bufs, case)
+
+
 CHUNK_CASES = [
     # Hq, Hkv, d, dtype, w, rows of the heads' regions, tokens seen, share, kv
     (4, 2, 128, "bf16", 256, (0, 1, 128, 129), 700, False, "native"),        # no unit, one row, a full unit, one more
