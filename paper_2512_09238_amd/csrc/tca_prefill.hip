@@ -54,6 +54,8 @@ __global__ __launch_bounds__(256) void merge_split_kernel(SplitPlan sp, int64_t 
   const float* base = sp.part + (size_t)(sp.item_start[h] + qtile) * split_floats<D>();
   const float sl2e = scale * 1.4426950408889634f;
   const int q = wv * 32 + c;
+  const int64_t r = (int64_t)qtile * 128 + q;
+  if (r >= n_queries) return;
   float M = -INFINITY;
 #pragma unroll 8
   for (int s = 0; s < n_ch; ++s) M = fmaxf(M, base[s * stride + 128 * D + q]);
@@ -74,8 +76,6 @@ __global__ __launch_bounds__(256) void merge_split_kernel(SplitPlan sp, int64_t 
       for (int j = 0; j < 4; ++j) acc[q4][j] += l != 0.f ? v[j] * wgt : 0.f;     // an empty chunk's accumulators were never written
     }
   }
-  const int64_t r = (int64_t)qtile * 128 + q;
-  if (r >= n_queries) return;
   const float inv = L != 0.f ? 1.f / L : 0.f;
   uint16_t* orow = O + ((size_t)h * n_queries + r) * D;
 #pragma unroll

@@ -708,6 +708,20 @@ def test_few_queries_behind_a_long_context(tb, bufs, case):
     assert np.abs(outs[0][0] - outs[1][0]).max() <= 2 * H.TOL["bf16"]
 
 
+IDLE_CASES = [
+    # a last query tile of which one wave, two, three have no query, and none: in chunks and whole, rows through idx as well
+    (8, 2, 128, 96, "spread", False, False),
+    (8, 2, 128, 193, "spread", False, True),
+    (4, 1, 64, 31, "spread", True, True),
+    (8, 2, 64, 225, "front", False, False),
+]
+
+
+@pytest.mark.parametrize("case", IDLE_CASES, ids=lambda c: f"Hq{c[0]}-Hkv{c[1]}-d{c[2]}-n{c[3]}-{c[4]}-share{c[5]}-free{c[6]}")
+def test_waves_without_a_query(tb, bufs, case):
+    test_few_queries_behind_a_long_context(tb, bufs, case)
+
+
 V_EDGE_CASES = [
     # Hq, Hkv, d, queries, rows kept per head, gather-free
     (8, 2, 128, 1, 1, False),
