@@ -109,6 +109,18 @@ __device__ __forceinline__ float row16_max(float v) {
   return v;
 }
 
+// sum over the 16 lanes of a row, or over each half of them
+template <int LPR, typename V> __device__ __forceinline__ V row_sum(V v) {
+  if constexpr (LPR == 16) {
+    return row16_sum(v);
+  } else {
+    static_assert(LPR == 8 && sizeof(V) == 4, "");
+    v += dpp_f32<kDppXor1>(v);
+    v += dpp_f32<kDppXor2>(v);
+    return v + dpp_f32<kDppHalfMirror>(v);
+  }
+}
+
 // Scale of an FP8 row from the largest magnitude of its elements, and its reciprocal use: the codes are
 // RNE_e4m3(x / scale) with both divisions in float32 (the rule stated with TCA_KV_FP8).
 __device__ __forceinline__ float fp8_row_scale(float amax) { return amax > 0.f ? amax / 448.f : 1.f; }
@@ -215,20 +227,20 @@ __device__ __forceinline__ void store_new_row(const tca_cache& c, size_t row, co
   __syncthreads();
 }
 
-// Tail of the split-K kernels: every 16-lane group of the workgroup holds, for each of NQ
+// Tail of the split-K kernels: every group of LPR lanes of the workgroup holds, for each of NQ
 // queries, an online-softmax state (reference m in base-2 units, sum l, acc over the lane's
-// slice of d).  Merges the 4 groups of each wave, then the 4 waves through LDS, and writes one
+// slice of d).  Merges the groups of each wave, then the 4 waves through LDS, and writes one
 // (reference, sum, acc[D]) partial per query at out + g * out_head, the reference still in
 // base-2 units (integer references, as the fp32 path keeps them, stay exact through every merge).
-template <int D, int NQ>
-__device__ __forceinline__ void merge_partials(float (&m)[NQ], float (&l)[NQ], float (&acc)[NQ][D / 16],
+template <int D, int NQ, int LPR>
+__device__ __forceinline__ void merge_partials(float (&m)[NQ], float (&l)[NQ], float (&acc)[NQ][D / LPR],
                                                float* __restrict__ out, size_t out_head, float* red) {
-  constexpr int EL = D / 16;
+  constexpr int EL = D / LPR;
   constexpr int PW = EL + 2;                          // floats of one lane's share of a partial
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
 #pragma unroll
   for (int g = 0; g < NQ; ++g) {
-    for (int o = 16; o < 64; o <<= 1) {
+    for (int o = LPR; o < 64; o <<= 1) {
       const float mo = __shfl_xor(m[g], o, kWave), lo = __shfl_xor(l[g], o, kWave);
       const float mn = fmaxf(m[g], mo);
       const float ca = (m[g] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m[g] - mn);
@@ -238,27 +250,27 @@ __device__ __forceinline__ void merge_partials(float (&m)[NQ], float (&l)[NQ], f
       for (int e = 0; e < EL; ++e) acc[g][e] = acc[g][e] * ca + __shfl_xor(acc[g][e], o, kWave) * cb;
       m[g] = mn;
     }
-    if (lane < 16) {
-      red[(wv * 16 + lane) * (NQ * PW) + g * PW] = m[g];
-      red[(wv * 16 + lane) * (NQ * PW) + g * PW + 1] = l[g];
+    if (lane < LPR) {
+      red[(wv * LPR + lane) * (NQ * PW) + g * PW] = m[g];
+      red[(wv * LPR + lane) * (NQ * PW) + g * PW + 1] = l[g];
 #pragma unroll
-      for (int e = 0; e < EL; ++e) red[(wv * 16 + lane) * (NQ * PW) + g * PW + 2 + e] = acc[g][e];
+      for (int e = 0; e < EL; ++e) red[(wv * LPR + lane) * (NQ * PW) + g * PW + 2 + e] = acc[g][e];
     }
   }
   __syncthreads();
-  for (int pi = tid; pi < 16 * NQ; pi += kPartThreads) {
-    const int g = pi >> 4, ln = pi & 15;
+  for (int pi = tid; pi < LPR * NQ; pi += kPartThreads) {
+    const int g = pi / LPR, ln = pi % LPR;
     float M = -INFINITY;
-    for (int x = 0; x < kPartWaves; ++x) M = fmaxf(M, red[(x * 16 + ln) * (NQ * PW) + g * PW]);
+    for (int x = 0; x < kPartWaves; ++x) M = fmaxf(M, red[(x * LPR + ln) * (NQ * PW) + g * PW]);
     float L = 0.f, a[EL];
 #pragma unroll
     for (int e = 0; e < EL; ++e) a[e] = 0.f;
     for (int x = 0; x < kPartWaves; ++x) {
-      const float mx = red[(x * 16 + ln) * (NQ * PW) + g * PW];
+      const float mx = red[(x * LPR + ln) * (NQ * PW) + g * PW];
       const float cf = (mx == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mx - M);
-      L += red[(x * 16 + ln) * (NQ * PW) + g * PW + 1] * cf;
+      L += red[(x * LPR + ln) * (NQ * PW) + g * PW + 1] * cf;
 #pragma unroll
-      for (int e = 0; e < EL; ++e) a[e] += red[(x * 16 + ln) * (NQ * PW) + g * PW + 2 + e] * cf;
+      for (int e = 0; e < EL; ++e) a[e] += red[(x * LPR + ln) * (NQ * PW) + g * PW + 2 + e] * cf;
     }
     float* og = out + g * out_head;
     if (ln == 0) { og[0] = M; og[1] = L; }
@@ -270,18 +282,18 @@ __device__ __forceinline__ void merge_partials(float (&m)[NQ], float (&l)[NQ], f
 // Split-K attention of NQ queries (consecutive heads, q0 = the first one's row) over rows
 // [r_begin, r_end) of one K/V buffer: every row is read once and scored against all NQ queries.
 // Writes one (max, sum, acc[D]) partial per query at out + g * out_head.  red: LDS scratch of
-// kPartWaves * 16 * NQ * (D/16 + 2) floats.  Called by a whole workgroup.
+// kPartWaves * LPR * NQ * (D/LPR + 2) floats.  Called by a whole workgroup.
 // T: type of the queries; KV: storage type of the rows (T itself, or fp8_t with one float scale per
 // row in kscale / vscale, indexed like the rows).
-// UNR: rows a group has requested ahead and as many it works on.
-template <typename T, typename KV, int D, int NQ, int UNR, typename Visible>
+// UNR: rows a group has requested ahead and as many it works on.  LPR: lanes that share a row, with 16 or 8 bytes each (FP8).
+template <typename T, typename KV, int D, int NQ, int UNR, int LPR, typename Visible>
 __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const KV* __restrict__ vbase,
                                              const float* __restrict__ kscale, const float* __restrict__ vscale,
                                              int r_begin, int r_cap, Visible visible, const T* __restrict__ q0, double scale,
                                              float* __restrict__ out, size_t out_head, float* red) {
-  constexpr int EL = D / 16;
+  constexpr int EL = D / LPR, GROUPS = kPartThreads / LPR;
   const int tid = threadIdx.x;
-  const int grp = tid >> 4, sub = tid & 15;           // groups of 16 lanes
+  const int grp = tid / LPR, sub = tid % LPR;
   int r_end = r_cap;                                  // until the first rows are requested
   // logits are carried in base-2 units (scale * log2 e) so that the exponential is one v_exp_f32.
   // bf16 storage: q.k over a lane's slice is EL/2 two-element bf16 dot products with fp32
@@ -301,8 +313,13 @@ __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const
   RawSlice<T, EL> qraw[kDot2 ? NQ : 1];
 #pragma unroll
   for (int g = 0; g < NQ; ++g) {
-    if constexpr (kDot2) qraw[g].load(q0 + (size_t)g * D + sub * EL);
-    else load_slice<T, EL>(q0 + (size_t)g * D + sub * EL, qv[g]);
+    if constexpr (kDot2) {
+      qraw[g].load(q0 + (size_t)g * D + sub * EL);
+    } else {
+      constexpr int E = EL < 8 ? EL : 8;
+#pragma unroll
+      for (int e = 0; e < EL; e += E) load_slice<T, E>(q0 + (size_t)g * D + sub * EL + e, *reinterpret_cast<float(*)[E]>(&qv[g][e]));
+    }
   }
 
   float m[NQ], l[NQ], acc[NQ][EL];
@@ -329,7 +346,7 @@ __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const
   auto fetch = [&](int r0, Raw (&kk)[kUnr], Raw (&vq)[kUnr], float (&ks)[kUnr], float (&vs)[kUnr], bool (&okk)[kUnr]) {
 #pragma unroll
     for (int u = 0; u < kUnr; ++u) {
-      const int r = r0 + u * (kPartThreads / 16) + grp;
+      const int r = r0 + u * GROUPS + grp;
       okk[u] = r < r_end;
       ks[u] = vs[u] = 1.f;
       if (okk[u]) {
@@ -346,12 +363,12 @@ __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const
     return;
   }
 #pragma unroll
-  for (int u = 0; u < kUnr; ++u) ok[u] = r_begin + u * (kPartThreads / 16) + grp < r_end;
-  for (int r0 = r_begin; r0 < r_end; r0 += (kPartThreads / 16) * kUnr) {
+  for (int u = 0; u < kUnr; ++u) ok[u] = r_begin + u * GROUPS + grp < r_end;
+  for (int r0 = r_begin; r0 < r_end; r0 += GROUPS * kUnr) {
     Raw kn[kUnr], vn[kUnr];
     float ksn[kUnr], vsn[kUnr];
     bool okn[kUnr];
-    fetch(r0 + (kPartThreads / 16) * kUnr, kn, vn, ksn, vsn, okn);          // nothing is loaded past r_end
+    fetch(r0 + GROUPS * kUnr, kn, vn, ksn, vsn, okn);          // nothing is loaded past r_end
 #pragma unroll
     for (int u = 0; u < kUnr; ++u) {
       float kv[EL], vv[EL];
@@ -376,7 +393,7 @@ __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const
             }
           }
         }
-        sc = row16_sum(sc) * qk_factor;
+        sc = row_sum<LPR>(sc) * qk_factor;
         if constexpr (kFp8) sc *= ksc[u];
         if (ok[u]) {
           if (sc > (logit_t)m[g] + (logit_t)kSlack) {
@@ -398,7 +415,7 @@ __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const
 #pragma unroll
     for (int u = 0; u < kUnr; ++u) { kr[u] = kn[u]; vr[u] = vn[u]; ksc[u] = ksn[u]; vsc[u] = vsn[u]; ok[u] = okn[u]; }
   }
-  merge_partials<D, NQ>(m, l, acc, out, out_head, red);
+  merge_partials<D, NQ, LPR>(m, l, acc, out, out_head, red);
 }
 
 // The same for bf16 rows of 128 elements and NQ > 1 queries, and FP8 rows and NQ > 2, with q.k on the matrix cores.
@@ -590,7 +607,7 @@ __device__ __forceinline__ void partial_rows_mfma(const KV* __restrict__ kbase, 
   // the sum of query g over this group's rows sits in lane g of the group
 #pragma unroll
   for (int g = 0; g < NQ; ++g) l[g] = __shfl(l_mine, (lane & 48) + g, kWave);
-  merge_partials<D, NQ>(m, l, acc, out, out_head, red);
+  merge_partials<D, NQ, 16>(m, l, acc, out, out_head, red);
 }
 
 // grid (units, B); block kPartThreads.  Selection head hs serves the GQ query heads hs*GQ .. hs*GQ+GQ-1 (GQ = 1: one
@@ -616,6 +633,10 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
   // rows ahead make up for the missing waves' loads.  us with two / with four: 64 heads, 2 x 32000 tokens 47.5 / 45.5, 16 x
   // 60000 571.7 / 553.0; with four waves (32 heads) 8 x 30011 87.4 / 86.7, 16 x 60000 279.6 / 280.8; 4 heads of 64 elements 16
   // x 60000 41.8 / 42.9.
+  // FP8 rows of 128 elements, one query: eight lanes a row, 16 bytes each, which halves the reductions and exponentials per
+  // byte.  us of the step, with sixteen lanes / with eight: 32 heads, 2 x 100000 tokens 73.0 / 66.4, 16 x 60000 285 / 280, 8 x 30011
+  // 87.5 / 86.6 (three or four rows ahead instead of two: 89 / 88).
+  constexpr int kLpr = sizeof(KV) == 1 && D == 128 && GQ == 1 ? 8 : 16;
   constexpr int kRegionUnr = sizeof(KV) == 1 && D == 128 && GQ == 1 && GW > 4 ? 4 : 2;
   const int id = blockIdx.x, s = blockIdx.y;
   const int Hs = Hq / GQ;
@@ -657,7 +678,7 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
       partial_rows_mfma<KV, GQ>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base, c.Vg_scale + base,
                                 r_begin, r_begin + len, visible, q0, scale, out, out_head, red, tiles);
     else
-      partial_rows<T, KV, D, GQ, kRegionUnr>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base,
+      partial_rows<T, KV, D, GQ, kRegionUnr, kLpr>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base,
                                  c.Vg_scale + base, r_begin, r_begin + len, visible, q0, scale, out, out_head, red);
   } else {
     const int kvh = id / dh.ring_units, slot = id - kvh * dh.ring_units, h0 = kvh * GW;
@@ -678,7 +699,7 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
       partial_rows_mfma<KV, GW>((const KV*)c.ringK + base * D, (const KV*)c.ringV + base * D, c.ringK_scale + base,
                                 c.ringV_scale + base, r_begin, r_end, visible, q0, scale, out, out_head, red, tiles);
     else
-      partial_rows<T, KV, D, GW, 2>((const KV*)c.ringK + base * D, (const KV*)c.ringV + base * D, c.ringK_scale + base,
+      partial_rows<T, KV, D, GW, 2, 16>((const KV*)c.ringK + base * D, (const KV*)c.ringV + base * D, c.ringK_scale + base,
                                  c.ringV_scale + base, r_begin, r_end, visible, q0, scale, out, out_head, red);
   }
 }

@@ -217,3 +217,51 @@ def test_load_global_copies_the_filled_rows_of_every_region(tb, bufs, case, kv):
             assert np.array_equal(dst[1][at].cpu().numpy(), codes) and np.array_equal(scale[1][at].cpu().numpy().ravel(), np.ravel(sc))
         else:
             assert torch.equal(dst[1][at], src[at])
+
+
+@pytest.mark.parametrize("rows", [0, 1, 31, 33, 130])
+@pytest.mark.parametrize("share", [False, True])
+def test_fp8_decode_reads_regions_from_any_eight_bytes(tb, bufs, rows, share):
+    """Region rows are read 16 bytes a lane where a row meets one query, 8 bytes elsewhere: buffers that start 8 bytes off a
+    16-byte boundary give the same bits.  Three sequences, region counts at the edges of a wave's rows, and no region at all."""
+    Hq, Hkv, d, b, w, B = 8, 2, 128, 16, 64, 3
+    prm = H.params_for(tb, Hq, Hkv, d, b, w, "bf16", share=share)
+    Hs = Hkv if share else Hq
+    P = np.stack([tb.tca_config_from_budget(b, 1.0, 0.3)] * Hs)
+    g = torch.Generator(device="cuda").manual_seed(99)
+    q, k, v = (torch.randn(B, n, d, generator=g, device="cuda").bfloat16() for n in (Hq, Hkv, Hkv))
+    cap = np.full(Hs, rows)
+    fill = [torch.randint(0, 0x78, (B, max(Hs * rows, 1), d), generator=g, device="cuda", dtype=torch.uint8) for _ in range(2)]
+    ring = [torch.randint(0, 0x78, (B, Hkv, w, d), generator=g, device="cuda", dtype=torch.uint8) for _ in range(2)]
+    outs = []
+    for off in (0, 8):
+        c = bufs.DecodeCache(prm, B, cap, kv_format=tb.TCA_KV_FP8)
+        moved = []
+        for t in (c.Kg, c.Vg):
+            big = torch.empty(t.numel() + 16, dtype=torch.uint8, device="cuda")
+            moved.append(big[off:off + t.numel()].view(t.shape))
+        moved[0].copy_(fill[0]); moved[1].copy_(fill[1]); c.ringK.copy_(ring[0]); c.ringV.copy_(ring[1])
+        for t in (c.Kg_scale, c.Vg_scale, c.ringK_scale, c.ringV_scale):
+            t.fill_(0.01)
+        c.length.copy_(torch.tensor([2000, 40, 1999]))
+        c.n_rows.fill_(rows)
+        if rows:
+            c.idx.copy_((torch.arange(rows, device="cuda") * 3).repeat(Hs)[None].expand(B, -1))
+        view = tb.make_cache(B, c.cap_rows, c.idx, moved[0], moved[1], c.n_rows, c.ringK, c.ringV, c.length, tb.TCA_KV_FP8, c.Kg_scale,
+                             c.Vg_scale, c.ringK_scale, c.ringV_scale)
+        O = torch.full_like(q, float("nan"))
+        tb.tca_decode(prm, view, c.offs, q, k, v, P, O, bufs.workspace(tb.tca_decode_workspace_bytes(prm, B, c.max_head_rows)))
+        torch.cuda.synchronize()
+        outs.append(O)
+        for s, T in enumerate((2000, 40, 1999)):
+            for h in range(Hq):
+                hs, kvh = h * Hs // Hq, h * Hkv // Hq
+                n = int((np.arange(rows) * 3 <= T - w).sum())
+                o, live = hs * rows, min(T + 1, w)
+                keys = torch.cat([m[s, o:o + n] if i == 0 else m[s, kvh, :live] for i, m in ((0, moved[0]), (1, c.ringK))]).view(torch.float8_e4m3fn).double()
+                vals = torch.cat([m[s, o:o + n] if i == 0 else m[s, kvh, :live] for i, m in ((0, moved[1]), (1, c.ringV))]).view(torch.float8_e4m3fn).double()
+                ks = torch.cat([c.Kg_scale[s, o:o + n], c.ringK_scale[s, kvh, :live]]).double()
+                vs = torch.cat([c.Vg_scale[s, o:o + n], c.ringV_scale[s, kvh, :live]]).double()
+                p = torch.softmax((keys @ q[s, h].double()) * ks / d ** 0.5, 0)
+                assert (O[s, h].double() - (p * vs) @ vals).abs().max().item() <= H.TOL["bf16"], (s, h)
+    assert torch.equal(outs[0], outs[1])
