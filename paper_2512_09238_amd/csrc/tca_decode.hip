@@ -610,9 +610,11 @@ __device__ __forceinline__ void partial_rows_mfma(const KV* __restrict__ kbase, 
   merge_partials<D, NQ, 16>(m, l, acc, out, out_head, red);
 }
 
-// grid (units, B); block kPartThreads.  Selection head hs serves the GQ query heads hs*GQ .. hs*GQ+GQ-1 (GQ = 1: one
+// grid (units * B); block kPartThreads.  Selection head hs serves the GQ query heads hs*GQ .. hs*GQ+GQ-1 (GQ = 1: one
 // selection per query head).  The ring belongs to the KV head, so its units score each row against all GW query heads of
-// the group.  The rings' units come first, then the regions', all heads' first chunks, then all heads' second ones, ..: in
+// the group.  The rings' units of all sequences come first, which take the longest (FP8, four queries a row: 32 us where a
+// region's takes 18; with each sequence's rings in front of its regions the last one's ended 15 us behind everything else: 8 x 30011 tokens 85.4 / 80.5 us, 64 heads 172 / 154).
+// Then the regions', sequence by sequence, all heads' first chunks, then all heads' second ones, ..: in
 // a cache with room to spare those that hold rows are neighbours, which the chip deals to its XCDs and CUs in turn, and the
 // empty ones follow.  (Head after head, the first chunks of all heads may be on one or two XCDs.  us per step of 32 heads with
 // room for 40000 rows each, head after head / this: 4 sequences of 1500 rows 91 / 53, 16 of 1500 286 / 162, 16 of 10000 618 /
@@ -638,10 +640,17 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
   // 87.5 / 86.6 (three or four rows ahead instead of two: 89 / 88).
   constexpr int kLpr = sizeof(KV) == 1 && D == 128 && GQ == 1 ? 8 : 16;
   constexpr int kRegionUnr = sizeof(KV) == 1 && D == 128 && GQ == 1 && GW > 4 ? 4 : 2;
-  const int id = blockIdx.x, s = blockIdx.y;
   const int Hs = Hq / GQ;
-  const int64_t Tpos = c.length[s];
   const int region_units = dh.unit0[Hs], all_ring_units = Hkv * dh.ring_units;
+  int id = blockIdx.x - c.batch * all_ring_units, s;
+  if (id >= 0) {
+    s = id / region_units;
+    id += all_ring_units - s * region_units;
+  } else {
+    s = (int)blockIdx.x / all_ring_units;
+    id = (int)blockIdx.x - s * all_ring_units;
+  }
+  const int64_t Tpos = c.length[s];
   float* const seq_part = part + (size_t)s * ((size_t)GQ * region_units + (size_t)Hq * dh.ring_units) * (D + 2);
   if (id == 0 && threadIdx.x == 0) pos[s] = (uint32_t)Tpos;      // for the merge that follows
 
@@ -1061,10 +1070,10 @@ static int run_decode(const tca_params* prm, const tca_cache* c, const DecodeHea
 #define TCA_PARTIAL_CASE(GG)                                                                                    \
   case GG:                                                                                                      \
     if (GS > 1)                                                                                                 \
-      hipLaunchKernelGGL((decode_partial_kernel<T, KV, D, GG, GG>), dim3((unsigned)units, B), dim3(kPartThreads), 0, st, \
+      hipLaunchKernelGGL((decode_partial_kernel<T, KV, D, GG, GG>), dim3((unsigned)(units * B)), dim3(kPartThreads), 0, st, \
                          *c, dh, Hq, Hkv, w, sc, q, k_new, v_new, dw.pos, dw.part);                             \
     else                                                                                                        \
-      hipLaunchKernelGGL((decode_partial_kernel<T, KV, D, 1, GG>), dim3((unsigned)units, B), dim3(kPartThreads), 0, st, \
+      hipLaunchKernelGGL((decode_partial_kernel<T, KV, D, 1, GG>), dim3((unsigned)(units * B)), dim3(kPartThreads), 0, st, \
                          *c, dh, Hq, Hkv, w, sc, q, k_new, v_new, dw.pos, dw.part);                             \
     break;
   switch (G) {
