@@ -240,16 +240,25 @@ __device__ __forceinline__ void merge_partials(float (&m)[NQ], float (&l)[NQ], f
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
 #pragma unroll
   for (int g = 0; g < NQ; ++g) {
-    for (int o = LPR; o < 64; o <<= 1) {
-      const float mo = __shfl_xor(m[g], o, kWave), lo = __shfl_xor(l[g], o, kWave);
-      const float mn = fmaxf(m[g], mo);
-      const float ca = (m[g] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m[g] - mn);
-      const float cb = (mo == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mo - mn);
-      l[g] = l[g] * ca + lo * cb;
+    auto across = [&](auto o_tag) {                   // (through LDS these exchanges took a fourth of a short unit)
+      constexpr int O = decltype(o_tag)::value;
+      float ma, mb, x, y;
+      lane_pair<O>(m[g], ma, mb);
+      const float mn = fmaxf(ma, mb);
+      const float ca = (ma == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ma - mn);
+      const float cb = (mb == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mb - mn);
+      lane_pair<O>(l[g], x, y);
+      l[g] = x * ca + y * cb;
 #pragma unroll
-      for (int e = 0; e < EL; ++e) acc[g][e] = acc[g][e] * ca + __shfl_xor(acc[g][e], o, kWave) * cb;
+      for (int e = 0; e < EL; ++e) {
+        lane_pair<O>(acc[g][e], x, y);
+        acc[g][e] = x * ca + y * cb;
+      }
       m[g] = mn;
-    }
+    };
+    if constexpr (LPR == 8) across(std::integral_constant<int, 8>{});
+    across(std::integral_constant<int, 16>{});
+    across(std::integral_constant<int, 32>{});
     if (lane < LPR) {
       red[(wv * LPR + lane) * (NQ * PW) + g * PW] = m[g];
       red[(wv * LPR + lane) * (NQ * PW) + g * PW + 1] = l[g];
@@ -453,11 +462,9 @@ __device__ __forceinline__ void partial_rows_mfma(const KV* __restrict__ kbase, 
   // The queries sit in LDS (chunk index xor query, like the K tile) and are read as operand B
   // of MFMA j (elements (4j + kb) * 8 .. + 7 of query n) every iteration: 4 registers instead of 16.
   unsigned char* qt = tiles + kPartWaves * kMfmaTileBytes;       // [NQ][16 chunks of 16 B]
-  for (int ci = tid; ci < NQ * 16; ci += kPartThreads) {
-    const int g = ci >> 4, ch = ci & 15;
-    *reinterpret_cast<uint4*>(qt + g * 256 + ((ch ^ g) & 15) * 16) = *reinterpret_cast<const uint4*>(q0 + (size_t)g * D + ch * 8);
-  }
-  __syncthreads();
+  static_assert(NQ * 16 <= kPartThreads, "one chunk a thread");
+  uint4 q_chunk;
+  if (tid < NQ * 16) q_chunk = *reinterpret_cast<const uint4*>(q0 + (size_t)(tid >> 4) * D + (tid & 15) * 8);
   const float factor = (float)(scale * (double)kLog2e);
 
   float m[NQ], l[NQ], acc[NQ][EL];
@@ -499,6 +506,8 @@ __device__ __forceinline__ void partial_rows_mfma(const KV* __restrict__ kbase, 
   };
   fetch_k(r_begin);
   fetch_v(r_begin);
+  if (tid < NQ * 16) *reinterpret_cast<uint4*>(qt + (tid >> 4) * 256 + (((tid & 15) ^ (tid >> 4)) & 15) * 16) = q_chunk;
+  __syncthreads();
   r_end = visible();
   if (r_begin >= r_end) {
     if (tid < NQ) { out[tid * out_head] = -INFINITY; out[tid * out_head + 1] = 0.f; }
@@ -546,25 +555,13 @@ __device__ __forceinline__ void partial_rows_mfma(const KV* __restrict__ kbase, 
     }
     if (__any(raise)) {
       // raise the references: every lane learns the largest score of each query over the 16 rows
-      if (holder) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) pt[(4 * kb + i) * 8 + n] = s2[i];
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      float mxs[8];
-#pragma unroll
-      for (int g = 0; g < 8; ++g) mxs[g] = -INFINITY;
-#pragma unroll 2
-      for (int x = 0; x < 16; ++x) {
-        float t[8];
-        *reinterpret_cast<float4*>(&t[0]) = *reinterpret_cast<const float4*>(pt + x * 8);
-        if constexpr (NQ > 4) *reinterpret_cast<float4*>(&t[4]) = *reinterpret_cast<const float4*>(pt + x * 8 + 4);
-#pragma unroll
-        for (int g = 0; g < NQ; ++g) mxs[g] = fmaxf(mxs[g], t[g]);
-      }
+      float top = fmaxf(fmaxf(s2[0], s2[1]), fmaxf(s2[2], s2[3])), x, y;
+      lane_pair<16>(top, x, y);
+      lane_pair<32>(fmaxf(x, y), x, y);
+      top = fmaxf(x, y);
 #pragma unroll
       for (int g = 0; g < NQ; ++g) {
-        const float mx = mxs[g];
+        const float mx = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(top), g));
         const float m_new = fmaxf(m[g], mx);
         const float corr = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m[g] - m_new);   // 0 while m[g] = -inf
 #pragma unroll
@@ -572,7 +569,6 @@ __device__ __forceinline__ void partial_rows_mfma(const KV* __restrict__ kbase, 
         if (n == g) { l_mine *= corr; m_mine = m_new; }
         m[g] = m_new;
       }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
     float p[4];
 #pragma unroll

@@ -210,6 +210,22 @@ template <typename OP> __device__ __forceinline__ double wave_reduce(double v, O
 __device__ __forceinline__ double wave_sum(double v) { return wave_reduce(v, [](double a, double b) { return a + b; }); }
 __device__ __forceinline__ double wave_max(double v) { return wave_reduce(v, [](double a, double b) { return fmax(a, b); }); }
 
+// The values of a lane and of the one O (8, 16, 32) lanes across, in the same order in both.
+template <int O> __device__ __forceinline__ void lane_pair(float v, float& a, float& b) {
+  if constexpr (O == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
+  } else if constexpr (O == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
+  } else {
+    static_assert(O == 8, "");
+    const float o = dpp_f32<kDppRor8>(v);
+    const bool upper = (threadIdx.x & 8) != 0;
+    a = upper ? o : v; b = upper ? v : o;
+  }
+}
+
 // Number of entries <= bound among the ascending idx[0..n), found by a whole wave: every
 // round probes the last element of up to 64 equal chunks of the open range, so 2^18 rows take
 // three dependent loads instead of eighteen.  Result in every lane.
