@@ -606,10 +606,54 @@ __device__ __forceinline__ void partial_rows_mfma(const KV* __restrict__ kbase, 
   merge_partials<D, NQ, 16>(m, l, acc, out, out_head, red);
 }
 
+// Unit u of all sequences' rings (Hkv * ring_units each): those that hold rows first, sequence by sequence and ring by ring,
+// then the empty ones.  Uniform; called by whole waves.
+struct RingUnit { int s, kvh, slot; };
+__device__ __forceinline__ RingUnit ring_unit(int u, const int64_t* __restrict__ length, int batch, int Hkv, int ring_units, int chunk, int w) {
+  const int lane = threadIdx.x & 63;
+  if (batch == 1) {                                  // nothing to look through: 0.3 us of a small step
+    const int64_t T = length[0];
+    const int live = T >= w ? ring_units : min(ring_units, (int)T / chunk + 1), empty = u - Hkv * live;
+    const int per = empty < 0 ? live : ring_units - live, in = empty < 0 ? u : empty, kvh = in / per;
+    return {0, kvh, in - kvh * per + (empty < 0 ? 0 : live)};
+  }
+  for (int part = 0; part < 2; ++part) {             // with rows; without
+    for (int s0 = 0; s0 < batch; s0 += kWave) {
+      int n = 0;                                     // lane's sequence: slots of a ring in this part
+      if (s0 + lane < batch) {
+        const int64_t T = length[s0 + lane];
+        const int live = T >= w ? ring_units : min(ring_units, (int)T / chunk + 1);
+        n = part ? ring_units - live : live;
+      }
+      int incl = n * Hkv;
+      if (__all(n == ring_units || s0 + lane >= batch)) {            // the common case: no sum to form
+        incl *= lane + 1;
+      } else {
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+          const int v = __shfl_up(incl, o, kWave);
+          if (lane >= o) incl += v;
+        }
+      }
+      const int last = min(batch - s0, kWave) - 1, all = __builtin_amdgcn_readlane(incl, last);
+      if (u < all) {
+        const int k = __popcll(__ballot(lane <= last && incl <= u));
+        const int per = __builtin_amdgcn_readlane(n, k), in = u - (k ? __builtin_amdgcn_readlane(incl, k - 1) : 0);
+        const int kvh = in / per;
+        return {s0 + k, kvh, in - kvh * per + (part ? ring_units - per : 0)};
+      }
+      u -= all;
+    }
+  }
+  return {0, 0, 0};                                  // (not reached)
+}
+
 // grid (units * B); block kPartThreads.  Selection head hs serves the GQ query heads hs*GQ .. hs*GQ+GQ-1 (GQ = 1: one
 // selection per query head).  The ring belongs to the KV head, so its units score each row against all GW query heads of
-// the group.  The rings' units of all sequences come first, which take the longest (FP8, four queries a row: 32 us where a
-// region's takes 18; with each sequence's rings in front of its regions the last one's ended 15 us behind everything else: 8 x 30011 tokens 85.4 / 80.5 us, 64 heads 172 / 154).
+// the group.  The rings' units of all sequences come first, those without rows last: they take the longest (FP8, four
+// queries a row: 32 us where a region's takes 18), and with each sequence's in front of its regions the last one's ended 15 us
+// behind everything else: FP8, 8 x 30011 tokens 85.4 / 80.5 us, 64 heads 172 / 154.  Rings that are half full, their empty units
+// among the others, left half of the CUs, which are served in turn, without work: 32 x 2000 66 / 47.
 // Then the regions', sequence by sequence, all heads' first chunks, then all heads' second ones, ..: in
 // a cache with room to spare those that hold rows are neighbours, which the chip deals to its XCDs and CUs in turn, and the
 // empty ones follow.  (Head after head, the first chunks of all heads may be on one or two XCDs.  us per step of 32 heads with
@@ -638,22 +682,18 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
   constexpr int kRegionUnr = sizeof(KV) == 1 && D == 128 && GQ == 1 && GW > 4 ? 4 : 2;
   const int Hs = Hq / GQ;
   const int region_units = dh.unit0[Hs], all_ring_units = Hkv * dh.ring_units;
-  int id = blockIdx.x - c.batch * all_ring_units, s;
-  if (id >= 0) {
-    s = id / region_units;
-    id += all_ring_units - s * region_units;
-  } else {
-    s = (int)blockIdx.x / all_ring_units;
-    id = (int)blockIdx.x - s * all_ring_units;
-  }
+  const int id = blockIdx.x - c.batch * all_ring_units;               // < 0: a ring's
+  RingUnit ru = {};
+  if (id < 0) ru = ring_unit(blockIdx.x, c.length, c.batch, Hkv, dh.ring_units, dh.chunk, w);
+  const int s = id >= 0 ? id / region_units : ru.s;
   const int64_t Tpos = c.length[s];
   float* const seq_part = part + (size_t)s * ((size_t)GQ * region_units + (size_t)Hq * dh.ring_units) * (D + 2);
-  if (id == 0 && threadIdx.x == 0) pos[s] = (uint32_t)Tpos;      // for the merge that follows
+  if (id < 0 && ru.kvh == 0 && ru.slot == 0 && threadIdx.x == 0) pos[s] = (uint32_t)Tpos;       // for the merge that follows
 
-  if (id >= all_ring_units) {
+  if (id >= 0) {
     // The lanes read the tables at once and they are looked up in registers: in memory, one lookup behind the other and each
     // line a miss at first, it cost the smallest steps 0.6 us of 17.
-    const int r = id - all_ring_units, lane = threadIdx.x & 63;
+    const int r = id - s * region_units, lane = threadIdx.x & 63;
     auto in_regs = [&](auto table) {
       const int lo = lane < Hs ? table(lane) : INT32_MAX, hi = lane + 64 < Hs ? table(lane + 64) : INT32_MAX;
       return [=](int i) { return i < 64 ? __builtin_amdgcn_readlane(lo, i) : __builtin_amdgcn_readlane(hi, i - 64); };
@@ -686,7 +726,7 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
       partial_rows<T, KV, D, GQ, kRegionUnr, kLpr>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base,
                                  c.Vg_scale + base, r_begin, r_begin + len, visible, q0, scale, out, out_head, red);
   } else {
-    const int kvh = id / dh.ring_units, slot = id - kvh * dh.ring_units, h0 = kvh * GW;
+    const int kvh = ru.kvh, slot = ru.slot, h0 = kvh * GW;
     const int r_begin = slot * dh.chunk;
     const size_t base = ((size_t)s * Hkv + kvh) * w;
     // Slot r of the ring holds the latest position congruent to r mod w that is <= Tpos.  Once

@@ -265,3 +265,30 @@ def test_fp8_decode_reads_regions_from_any_eight_bytes(tb, bufs, rows, share):
                 p = torch.softmax((keys @ q[s, h].double()) * ks / d ** 0.5, 0)
                 assert (O[s, h].double() - (p * vs) @ vals).abs().max().item() <= H.TOL["bf16"], (s, h)
     assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("lengths", [(0,), (700,), (0, 5000, 255, 256, 700, 40), tuple(range(0, 1400, 20))], ids=["empty", "part", "mixed", "70"])
+def test_rings_of_any_fill_are_read_once(tb, bufs, lengths):
+    """The units of all rings, those with rows first: sequences that have just begun, part of a window, all of it, more of them
+    than lanes; every ring row below the fill counts once."""
+    Hq, Hkv, d, b, w, B = 4, 2, 128, 16, 1024, len(lengths)
+    prm = H.params_for(tb, Hq, Hkv, d, b, w, "bf16")
+    P = np.stack([tb.tca_config_from_budget(b, 1.0, 0.3)] * Hq)
+    g = torch.Generator(device="cuda").manual_seed(100)
+    q, k, v = (torch.randn(B, n, d, generator=g, device="cuda").bfloat16() for n in (Hq, Hkv, Hkv))
+    c = bufs.DecodeCache(prm, B, np.zeros(Hq, np.int64))
+    c.ringK.copy_(torch.randn(c.ringK.shape, generator=g, device="cuda"))
+    c.ringV.copy_(torch.randn(c.ringV.shape, generator=g, device="cuda"))
+    c.length.copy_(torch.tensor(lengths))
+    O = torch.full_like(q, float("nan"))
+    ws = bufs.workspace(tb.tca_decode_workspace_bytes(prm, B, 0))
+    ws.fill_(0xFF)
+    tb.tca_decode(prm, c.view, c.offs, q, k, v, P, O, ws)
+    torch.cuda.synchronize()
+    assert c.length.tolist() == [T + 1 for T in lengths]
+    for s, T in enumerate(lengths):
+        live = min(T + 1, w)
+        for h in range(Hq):
+            keys, vals = c.ringK[s, h // 2, :live].double(), c.ringV[s, h // 2, :live].double()
+            ref = torch.softmax((keys @ q[s, h].double()) / d ** 0.5, 0) @ vals
+            assert (O[s, h].double() - ref).abs().max().item() <= H.TOL["bf16"], (s, h)
