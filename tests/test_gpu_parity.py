@@ -722,6 +722,42 @@ def test_waves_without_a_query(tb, bufs, case):
     test_few_queries_behind_a_long_context(tb, bufs, case)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("tiles", [8, 24, 31, 32, 34, 63, 66, 95, 98, 130])
+def test_any_number_of_chunks_is_merged(tb, bufs, tiles, d):
+    """The chunks of an item, 4 to 17 of them here, are read four at a time, two rounds ahead, and their references eight
+    at a time: the output and the log-sum-exp against the oracle on either side of each of these."""
+    print("case", tiles, d, flush=True)
+    Hq, Hkv, n, b, w = 2, 1, 33, 64, 64 * tiles
+    L = w + 64 + n
+    x = wl.prefill_inputs("lowrank", Hq, Hkv, d, L, "bf16", 93)
+    prm = H.params_for(tb, Hq, Hkv, d, b, w, "bf16")
+    gb = bufs.GlobalBuffers(prm, np.array([0, 64]))
+    Qd, Kd, Vd = (bufs.to_device(x[k]) for k in ("Q", "K", "V"))
+    S = [np.arange(0), np.arange(64)]
+    gb.idx[:64] = torch.arange(64, device="cuda", dtype=torch.int32)
+    gb.Kg[:64], gb.Vg[:64] = Kd[0, :64], Vd[0, :64]
+    gb.n_rows[0], gb.n_rows[1] = 0, 64
+    Qt = Qd[:, L - n:].contiguous()
+    full = tb.tca_prefill_workspace_bytes(prm, n, int(gb.offs[-1]))
+    chunks = tb.tca_diag_prefill_walk(prm, gb.offs, L - n, n, full)[2]
+    O = torch.full_like(Qt, float("nan"))
+    lse = torch.full((Hq, n), float("nan"), dtype=torch.float32, device="cuda")
+    tb.tca_prefill(prm, Qt, L - n, n, Kd, Vd, L, gb.idx, gb.Kg, gb.Vg, gb.offs, gb.n_rows, O, lse, bufs.workspace(full))
+    torch.cuda.synchronize()
+    print("chunks", chunks, flush=True)
+    assert chunks > 0 or tiles < 24, "this call is not cut into chunks"
+    rows = [0, n // 2, n - 1]
+    ref = H.oracle_rows(x, None, {"w": w}, S, np.array([L - n + r for r in rows]))
+    Qf, Kf = wl.to_f64(x["Q"]), wl.to_f64(x["K"])
+    got, gl = bufs.to_host_f64(O), lse.cpu().numpy()
+    assert not np.isnan(got).any() and not np.isnan(gl).any(), "some output rows were never written"
+    for h in range(Hq):
+        assert np.abs(got[h][rows] - ref[h]).max() <= H.TOL["bf16"], f"head {h}"
+        T = orc.visible_keys(L - 1, S[h], w)
+        assert abs(gl[h, n - 1] - np.log(np.exp(Kf[0][T] @ Qf[h, L - 1] / np.sqrt(d)).sum())) <= 5e-2
+
+
 V_EDGE_CASES = [
     # Hq, Hkv, d, queries, rows kept per head, gather-free
     (8, 2, 128, 1, 1, False),
