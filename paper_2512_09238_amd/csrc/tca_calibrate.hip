@@ -588,8 +588,10 @@ __global__ __launch_bounds__(kCalThreads, 3) void cal_digit_pass_kernel(
       if constexpr (COL) {
         l[b] += lo;
       } else {
-        const double mo = __shfl_xor(m[b], o, kWave), mn = fmax(m[b], mo);
-        l[b] = ldexp(l[b], (int)fmax((m[b] - mn) * 0x1p-8, -4096.0)) + ldexp(lo, (int)fmax((mo - mn) * 0x1p-8, -4096.0));
+        // A lane that has seen no key (of the first queries) has no say in the reference: its zero may lie far above the others'.
+        const double mo = __shfl_xor(m[b], o, kWave), mn = l[b] == 0.0 ? mo : lo == 0.0 ? m[b] : fmax(m[b], mo);
+        auto scaled = [&](double sum, double ref) { return ldexp(sum, (int)fmax(fmin((ref - mn) * 0x1p-8, 0.0), -4096.0)); };
+        l[b] = scaled(l[b], m[b]) + scaled(lo, mo);
         m[b] = mn;
       }
     }

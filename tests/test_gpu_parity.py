@@ -1098,7 +1098,7 @@ def test_calibrate_at_the_edges_of_its_tiles(tb, bufs, case):
 
 # What the elements of a bf16 sample are to each other decides how its products are formed: (of 16 rows that share an exponent)
 # with a lowest digit, with one element left out (of K, of Q, of both at one column), with several, with logits in the thousands
-CALIB_ELEMENTS = ["plain", "low", "rest_k", "rest_q", "rest_both", "odd_k", "odd_q", "far", "far_rows"]
+CALIB_ELEMENTS = ["plain", "low", "rest_k", "rest_q", "rest_both", "odd_k", "odd_q", "far", "far_rows", "far_first"]
 
 
 @pytest.mark.parametrize("d,L", [(128, 333), (64, 160)])
@@ -1126,10 +1126,20 @@ def test_calibrate_whatever_the_elements_span(tb, bufs, kind, d, L):
         Q *= 1024.0
     if kind == "far_rows":                                           # the references of a few queries, far below the others'
         Q[:, 70:75] *= -4096.0
+    if kind == "far_first":                                          # the same where not every lane of a query has a key to see
+        K[:, :12] = 1.0 + 0.1 * K[:, :12]
+        Q[:, :12] = -1200.0 / d ** 0.5 + Q[:, :12]
+        Q[:, L - 1] = 8.0 / d ** 0.5                                 # (for the tokens to be kept)
     Qb, Kb = (torch.from_numpy(v).to(torch.bfloat16) for v in (Q, K))
     Qf, Kf = Qb.double().numpy(), Kb.double().numpy()
     prm = H.params_for(tb, Hq, Hkv, d, b, b, "bf16")
     ref = orc.calibrate(Qf, Kf, b, M, 1.0, 0.0, 0.5)
+    if kind == "far_first":
+        for h in range(Hq):
+            assert (Qf[h, :12] @ Kf[h // (Hq // Hkv), :12].T).max() / d ** 0.5 < -800.0
+            kept = [orc.select(Qf[h, L - 1], Kf[h // (Hq // Hkv)], b, p, 0.5).S for p in orc.candidates(b, M, 1.0)]
+            assert any(np.isin(np.arange(12), S).all() for S in kept), "no candidate keeps the first tokens"
+    assert all(np.isfinite(c.a).all() for c in ref)
     size = tb.tca_calibrate_workspace_bytes(prm, L, M)
     for ws in (bufs.workspace(size), bufs.workspace(size)[:size - 256]):
         ws.fill_(0xFF)
