@@ -648,9 +648,10 @@ __device__ __forceinline__ RingUnit ring_unit(int u, const int64_t* __restrict__
   return {0, 0, 0};                                  // (not reached)
 }
 
-// grid (units * B); block kPartThreads.  Selection head hs serves the GQ query heads hs*GQ .. hs*GQ+GQ-1 (GQ = 1: one
+// grid (units, B); block kPartThreads.  Selection head hs serves the GQ query heads hs*GQ .. hs*GQ+GQ-1 (GQ = 1: one
 // selection per query head).  The ring belongs to the KV head, so its units score each row against all GW query heads of
-// the group.  The rings' units of all sequences come first, those without rows last: they take the longest (FP8, four
+// the group.  Workgroups are numbered through (one dimension would leave them 2^24: 65535 sequences of 257), and in their order
+// the rings' units of all sequences come first, those without rows last: they take the longest (FP8, four
 // queries a row: 32 us where a region's takes 18), and with each sequence's in front of its regions the last one's ended 15 us
 // behind everything else: FP8, 8 x 30011 tokens 85.4 / 80.5 us, 64 heads 172 / 154.  Rings that are half full, their empty units
 // among the others, left half of the CUs, which are served in turn, without work: 32 x 2000 66 / 47.
@@ -682,9 +683,10 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
   constexpr int kRegionUnr = sizeof(KV) == 1 && D == 128 && GQ == 1 && GW > 4 ? 4 : 2;
   const int Hs = Hq / GQ;
   const int region_units = dh.unit0[Hs], all_ring_units = Hkv * dh.ring_units;
-  const int id = blockIdx.x - c.batch * all_ring_units;               // < 0: a ring's
+  const int number = blockIdx.y * gridDim.x + blockIdx.x;
+  const int id = number - c.batch * all_ring_units;                   // < 0: a ring's
   RingUnit ru = {};
-  if (id < 0) ru = ring_unit(blockIdx.x, c.length, c.batch, Hkv, dh.ring_units, dh.chunk, w);
+  if (id < 0) ru = ring_unit(number, c.length, c.batch, Hkv, dh.ring_units, dh.chunk, w);
   const int s = id >= 0 ? id / region_units : ru.s;
   const int64_t Tpos = c.length[s];
   float* const seq_part = part + (size_t)s * ((size_t)GQ * region_units + (size_t)Hq * dh.ring_units) * (D + 2);
@@ -1106,10 +1108,10 @@ static int run_decode(const tca_params* prm, const tca_cache* c, const DecodeHea
 #define TCA_PARTIAL_CASE(GG)                                                                                    \
   case GG:                                                                                                      \
     if (GS > 1)                                                                                                 \
-      hipLaunchKernelGGL((decode_partial_kernel<T, KV, D, GG, GG>), dim3((unsigned)(units * B)), dim3(kPartThreads), 0, st, \
+      hipLaunchKernelGGL((decode_partial_kernel<T, KV, D, GG, GG>), dim3((unsigned)units, B), dim3(kPartThreads), 0, st, \
                          *c, dh, Hq, Hkv, w, sc, q, k_new, v_new, dw.pos, dw.part);                             \
     else                                                                                                        \
-      hipLaunchKernelGGL((decode_partial_kernel<T, KV, D, 1, GG>), dim3((unsigned)(units * B)), dim3(kPartThreads), 0, st, \
+      hipLaunchKernelGGL((decode_partial_kernel<T, KV, D, 1, GG>), dim3((unsigned)units, B), dim3(kPartThreads), 0, st, \
                          *c, dh, Hq, Hkv, w, sc, q, k_new, v_new, dw.pos, dw.part);                             \
     break;
   switch (G) {
@@ -1238,7 +1240,8 @@ static int decode_step(const tca_params* prm, const tca_cache* cache, const int6
                 ws_bytes);
   const int64_t units = choose_chunk(dh, prm, cache->batch, ws_bytes);
   order_units(dh, Hs);
-  if (units > INT32_MAX || cache->batch > 65535) return fail(TCA_ERR_UNSUPPORTED, "%s: batch=%d", who, cache->batch);
+  // (a unit's partial takes 264 bytes or more: 2^31 of them have no place on a GPU)
+  if (units * cache->batch > INT32_MAX || cache->batch > 65535) return fail(TCA_ERR_UNSUPPORTED, "%s: batch=%d", who, cache->batch);
   hipStream_t st = (hipStream_t)stream;
 #define TCA_RUN_DECODE(TT, KK)                                                                                         \
   (prm->head_dim == 128                                                                                                \

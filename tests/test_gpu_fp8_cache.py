@@ -292,3 +292,39 @@ def test_rings_of_any_fill_are_read_once(tb, bufs, lengths):
             keys, vals = c.ringK[s, h // 2, :live].double(), c.ringV[s, h // 2, :live].double()
             ref = torch.softmax((keys @ q[s, h].double()) / d ** 0.5, 0) @ vals
             assert (O[s, h].double() - ref).abs().max().item() <= H.TOL["bf16"], (s, h)
+
+
+def test_more_workgroups_than_one_dimension_of_a_grid_holds(tb, bufs):
+    """65535 sequences of 128 heads, 257 units of a step each: 256 threads times 16.8 million are more than 2^32.  The first
+    sequence, the last and some between against float64; every output is written."""
+    Hq, d, b, w, B, rows = 128, 64, 2, 2, 65535, 1025
+    assert B * (2 * Hq + 1) * 256 >= 2 ** 32
+    prm = H.params_for(tb, Hq, Hq, d, b, w, "bf16")
+    P = np.stack([tb.tca_config_from_budget(b, 1.0, 0.5)] * Hq)
+    cap = np.where(np.arange(Hq) == 0, rows, 1)                      # two units, one for every other head
+    c = bufs.DecodeCache(prm, B, cap, kv_format=tb.TCA_KV_FP8)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    q, k, v = (torch.zeros(B, Hq, d, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    some = [0, 1, 33333, B - 1]
+    for s in some:
+        for t in (q, k, v):
+            t[s] = torch.randn(Hq, d, generator=g, device="cuda").bfloat16()
+        for t in (c.Kg, c.Vg, c.ringK, c.ringV):
+            t[s] = torch.randint(0, 0x78, t[s].shape, generator=g, device="cuda", dtype=torch.uint8)
+    for t in (c.Kg_scale, c.Vg_scale, c.ringK_scale, c.ringV_scale):
+        t.fill_(0.01)
+    c.length.fill_(6)                                                # no block completes
+    c.n_rows.copy_(torch.from_numpy(cap.astype(np.int32)))
+    O = torch.full_like(q, float("nan"))
+    tb.tca_decode(prm, c.view, c.offs, q, k, v, P, O, bufs.workspace(tb.tca_decode_workspace_bytes(prm, B, c.max_head_rows)))
+    torch.cuda.synchronize()
+    assert torch.isfinite(O).all() and (c.length == 7).all()
+    for s in some:
+        for h in range(Hq):
+            at = slice(int(c.offs[h]), int(c.offs[h + 1]))
+            code = lambda t: t.view(torch.float8_e4m3fn).double()
+            keys, vals = torch.cat([code(c.Kg[s, at]), code(c.ringK[s, h])]) * 0.01, torch.cat([code(c.Vg[s, at]), code(c.ringV[s, h])]) * 0.01
+            new = len(keys) - 2                                      # position 6 lies in the ring's row 0
+            keys[new], vals[new] = (code(t[s, h, 0]) * x[s, h, 0].double() for t, x in ((c.ringK, c.ringK_scale), (c.ringV, c.ringV_scale)))
+            ref = torch.softmax((keys @ q[s, h].double()) / d ** 0.5, 0) @ vals
+            assert (O[s, h].double() - ref).abs().max().item() <= H.TOL["bf16"], (s, h)
