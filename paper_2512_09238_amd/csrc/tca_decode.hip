@@ -606,55 +606,47 @@ __device__ __forceinline__ void partial_rows_mfma(const KV* __restrict__ kbase, 
   merge_partials<D, NQ, 16>(m, l, acc, out, out_head, red);
 }
 
-// Unit u of all sequences' rings (Hkv * ring_units each): those that hold rows first, sequence by sequence and ring by ring,
-// then the empty ones.  Uniform; called by whole waves.
-struct RingUnit { int s, kvh, slot; };
-__device__ __forceinline__ RingUnit ring_unit(int u, const int64_t* __restrict__ length, int batch, int Hkv, int ring_units, int chunk, int w) {
+// Unit u of all sequences' rings (Hkv * ring_units each), and the position of its sequence's step.  Where the first 64 sequences'
+// rings are full: sequence by sequence and ring by ring; else all rings' first units, then all their second ones, .., so that those
+// without rows come last.  Uniform; called by whole waves.
+// (The second order for full rings reads the same places of power-of-two strides at once: 8 x 12000 tokens 66.5 / 72.6.  The units
+// with rows of each sequence counted, and those without put behind them: one round of loads and a scan for every 64 sequences,
+// 4096 of them 111 us, now 94; 128 x 1000 190 / 153, 2 x 16000 29.5 / 29.3, 8 x 30011 141 / 140.)
+struct RingUnit {
+  int s, kvh, slot;
+  int64_t T;
+};
+__device__ __forceinline__ RingUnit ring_unit(int u, const int64_t* __restrict__ length, int batch, int Hkv, int ring_units, int w) {
+  if (batch == 1) {                                  // without vector loads: 0.3 us of a small step
+    const int64_t T1 = length[0];
+    if (T1 >= w) return {0, u / ring_units, u % ring_units, T1};
+    return {0, u % Hkv, u / Hkv, T1};
+  }
   const int lane = threadIdx.x & 63;
-  if (batch == 1) {                                  // nothing to look through: 0.3 us of a small step
-    const int64_t T = length[0];
-    const int live = T >= w ? ring_units : min(ring_units, (int)T / chunk + 1), empty = u - Hkv * live;
-    const int per = empty < 0 ? live : ring_units - live, in = empty < 0 ? u : empty, kvh = in / per;
-    return {0, kvh, in - kvh * per + (empty < 0 ? 0 : live)};
+  int64_t T = w;
+  if (lane < batch) T = length[lane];
+  // both, while the lengths are on their way
+  const int seq = Hkv * ring_units, s_f = u / seq, in_f = u - s_f * seq, kvh_f = in_f / ring_units;
+  const int turn = batch * Hkv, slot_p = u / turn, in_p = u - slot_p * turn, s_p = in_p / Hkv;
+  RingUnit r;
+  if (__all(T >= w)) r = {s_f, kvh_f, in_f - kvh_f * ring_units, 0};
+  else r = {s_p, in_p - s_p * Hkv, slot_p, 0};
+  if (r.s < kWave) {
+    const uint32_t lo = __builtin_amdgcn_readlane((int)T, r.s), hi = __builtin_amdgcn_readlane((int)(T >> 32), r.s);
+    r.T = (int64_t)((uint64_t)hi << 32 | lo);
+  } else {
+    r.T = length[r.s];
   }
-  for (int part = 0; part < 2; ++part) {             // with rows; without
-    for (int s0 = 0; s0 < batch; s0 += kWave) {
-      int n = 0;                                     // lane's sequence: slots of a ring in this part
-      if (s0 + lane < batch) {
-        const int64_t T = length[s0 + lane];
-        const int live = T >= w ? ring_units : min(ring_units, (int)T / chunk + 1);
-        n = part ? ring_units - live : live;
-      }
-      int incl = n * Hkv;
-      if (__all(n == ring_units || s0 + lane >= batch)) {            // the common case: no sum to form
-        incl *= lane + 1;
-      } else {
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-          const int v = __shfl_up(incl, o, kWave);
-          if (lane >= o) incl += v;
-        }
-      }
-      const int last = min(batch - s0, kWave) - 1, all = __builtin_amdgcn_readlane(incl, last);
-      if (u < all) {
-        const int k = __popcll(__ballot(lane <= last && incl <= u));
-        const int per = __builtin_amdgcn_readlane(n, k), in = u - (k ? __builtin_amdgcn_readlane(incl, k - 1) : 0);
-        const int kvh = in / per;
-        return {s0 + k, kvh, in - kvh * per + (part ? ring_units - per : 0)};
-      }
-      u -= all;
-    }
-  }
-  return {0, 0, 0};                                  // (not reached)
+  return r;
 }
 
 // grid (units, B); block kPartThreads.  Selection head hs serves the GQ query heads hs*GQ .. hs*GQ+GQ-1 (GQ = 1: one
 // selection per query head).  The ring belongs to the KV head, so its units score each row against all GW query heads of
 // the group.  Workgroups are numbered through (one dimension would leave them 2^24: 65535 sequences of 257), and in their order
-// the rings' units of all sequences come first, those without rows last: they take the longest (FP8, four
+// the rings' units of all sequences come first: they take the longest (FP8, four
 // queries a row: 32 us where a region's takes 18), and with each sequence's in front of its regions the last one's ended 15 us
-// behind everything else: FP8, 8 x 30011 tokens 85.4 / 80.5 us, 64 heads 172 / 154.  Rings that are half full, their empty units
-// among the others, left half of the CUs, which are served in turn, without work: 32 x 2000 66 / 47.
+// behind everything else: FP8, 8 x 30011 tokens 90 / 85 us, 64 heads 169 / 154.  Rings that are half full, their empty units
+// among the others, left half of the CUs, which are served in turn, without work: 32 x 2000 68 / 45.
 // Then the regions', sequence by sequence, all heads' first chunks, then all heads' second ones, ..: in
 // a cache with room to spare those that hold rows are neighbours, which the chip deals to its XCDs and CUs in turn, and the
 // empty ones follow.  (Head after head, the first chunks of all heads may be on one or two XCDs.  us per step of 32 heads with
@@ -686,9 +678,9 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
   const int number = blockIdx.y * gridDim.x + blockIdx.x;
   const int id = number - c.batch * all_ring_units;                   // < 0: a ring's
   RingUnit ru = {};
-  if (id < 0) ru = ring_unit(number, c.length, c.batch, Hkv, dh.ring_units, dh.chunk, w);
+  if (id < 0) ru = ring_unit(number, c.length, c.batch, Hkv, dh.ring_units, w);
   const int s = id >= 0 ? id / region_units : ru.s;
-  const int64_t Tpos = c.length[s];
+  const int64_t Tpos = id >= 0 ? c.length[s] : ru.T;
   float* const seq_part = part + (size_t)s * ((size_t)GQ * region_units + (size_t)Hq * dh.ring_units) * (D + 2);
   if (id < 0 && ru.kvh == 0 && ru.slot == 0 && threadIdx.x == 0) pos[s] = (uint32_t)Tpos;       // for the merge that follows
 

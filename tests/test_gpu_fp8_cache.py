@@ -267,10 +267,12 @@ def test_fp8_decode_reads_regions_from_any_eight_bytes(tb, bufs, rows, share):
     assert torch.equal(outs[0], outs[1])
 
 
-@pytest.mark.parametrize("lengths", [(0,), (700,), (0, 5000, 255, 256, 700, 40), tuple(range(0, 1400, 20))], ids=["empty", "part", "mixed", "70"])
+@pytest.mark.parametrize("lengths", [(0,), (700,), (0, 5000, 255, 256, 700, 40), tuple(range(0, 1400, 20)), (1024, 2000, 1500),
+                                     (1100,) * 64 + (3, 600, 1024, 0), (1100,) * 64 + (2000, 1024)],
+                         ids=["empty", "part", "mixed", "70", "full", "full-but-the-last", "66-full"])
 def test_rings_of_any_fill_are_read_once(tb, bufs, lengths):
-    """The units of all rings, those with rows first: sequences that have just begun, part of a window, all of it, more of them
-    than lanes; every ring row below the fill counts once."""
+    """The units of all rings, in the order for full ones and the other: sequences that have just begun, part of a window, all of
+    it, more of them than lanes, of which the first decide; every ring row below the fill counts once."""
     Hq, Hkv, d, b, w, B = 4, 2, 128, 16, 1024, len(lengths)
     prm = H.params_for(tb, Hq, Hkv, d, b, w, "bf16")
     P = np.stack([tb.tca_config_from_budget(b, 1.0, 0.3)] * Hq)
@@ -290,6 +292,8 @@ def test_rings_of_any_fill_are_read_once(tb, bufs, lengths):
         live = min(T + 1, w)
         for h in range(Hq):
             keys, vals = c.ringK[s, h // 2, :live].double(), c.ringV[s, h // 2, :live].double()
+            at = T % w                                               # (the step wrote it)
+            assert torch.equal(c.ringK[s, h // 2, at], k[s, h // 2]) and torch.equal(c.ringV[s, h // 2, at], v[s, h // 2])
             ref = torch.softmax((keys @ q[s, h].double()) / d ** 0.5, 0) @ vals
             assert (O[s, h].double() - ref).abs().max().item() <= H.TOL["bf16"], (s, h)
 
