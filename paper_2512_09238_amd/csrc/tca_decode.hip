@@ -240,18 +240,24 @@ __device__ __forceinline__ void merge_partials(float (&m)[NQ], float (&l)[NQ], f
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
 #pragma unroll
   for (int g = 0; g < NQ; ++g) {
-    auto across = [&](auto o_tag) {                   // (through LDS these exchanges took a fourth of a short unit)
+    // Through LDS these exchanges took a fourth of a short unit of 128 elements a row.  With 64 elements, where a unit has half as many
+    // lines to wait for, the swaps' instructions cost more: 4096 sequences of 200 tokens 90.7 us through LDS, 93.9 by swaps.
+    auto across = [&](auto o_tag) {
       constexpr int O = decltype(o_tag)::value;
+      auto pair = [&](float v, float& a, float& b) {
+        if constexpr (D == 64) { a = v; b = __shfl_xor(v, O, kWave); }
+        else lane_pair<O>(v, a, b);
+      };
       float ma, mb, x, y;
-      lane_pair<O>(m[g], ma, mb);
+      pair(m[g], ma, mb);
       const float mn = fmaxf(ma, mb);
       const float ca = (ma == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ma - mn);
       const float cb = (mb == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mb - mn);
-      lane_pair<O>(l[g], x, y);
+      pair(l[g], x, y);
       l[g] = x * ca + y * cb;
 #pragma unroll
       for (int e = 0; e < EL; ++e) {
-        lane_pair<O>(acc[g][e], x, y);
+        pair(acc[g][e], x, y);
         acc[g][e] = x * ca + y * cb;
       }
       m[g] = mn;
