@@ -300,8 +300,8 @@ __device__ __forceinline__ void merge_partials(float (&m)[NQ], float (&l)[NQ], f
 // kPartWaves * LPR * NQ * (D/LPR + 2) floats.  Called by a whole workgroup.
 // T: type of the queries; KV: storage type of the rows (T itself, or fp8_t with one float scale per
 // row in kscale / vscale, indexed like the rows).
-// UNR: rows a group has requested ahead and as many it works on.  LPR: lanes that share a row, with 16 or 8 bytes each (FP8).
-template <typename T, typename KV, int D, int NQ, int UNR, int LPR, typename Visible>
+// LPR: lanes that share a row, 16 or (FP8, 16 bytes each) 8: see kWideRows.
+template <typename T, typename KV, int D, int NQ, int LPR, typename Visible>
 __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const KV* __restrict__ vbase,
                                              const float* __restrict__ kscale, const float* __restrict__ vscale,
                                              int r_begin, int r_cap, Visible visible, const T* __restrict__ q0, double scale,
@@ -353,7 +353,7 @@ __device__ __forceinline__ void partial_rows(const KV* __restrict__ kbase, const
   constexpr float kSlack = 8.f;
   // Rows are fetched one iteration ahead of their use (kUnr rows of K and of V per group,
   // kept as loaded until then), so that a lane has 2*kUnr loads in flight while it computes.
-  constexpr int kUnr = UNR;
+  constexpr int kUnr = 2;
   using Raw = RawSlice<KV, EL>;
   Raw kr[kUnr], vr[kUnr];
   float ksc[kUnr], vsc[kUnr];                          // row scales (FP8 rows only)
@@ -658,7 +658,7 @@ __device__ __forceinline__ RingUnit ring_unit(int u, const int64_t* __restrict__
 // empty ones follow.  (Head after head, the first chunks of all heads may be on one or two XCDs.  us per step of 32 heads with
 // room for 40000 rows each, head after head / this: 4 sequences of 1500 rows 91 / 53, 16 of 1500 286 / 162, 16 of 10000 618 /
 // 518, 16 of 3000 with a shared selection 222 / 135; full caches, 16 x 128K tokens 1088 / 1066, 5 x 112K 790 / 768.)
-template <typename T, typename KV, int D, int GQ, int GW>
+template <typename T, typename KV, int D, int GQ, int GW, int LPR>
 __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
     tca_cache c, DecodeHeads dh, int Hq, int Hkv, int w, double scale, const T* __restrict__ q,
     const T* __restrict__ k_new, const T* __restrict__ v_new, uint32_t* __restrict__ pos, float* __restrict__ part) {
@@ -670,15 +670,6 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
   // 36.8, 8 x 30000 51.4 / 53.2, 16 x 60000 180 / 178; three queries, shared, 8 x 30000 67.5 / 56.6.
   constexpr bool kMfma = D == 128 && (sizeof(KV) == 2 || (sizeof(KV) == 1 && GW > 2));
   __shared__ __attribute__((aligned(16))) unsigned char tiles[kMfma && NMAX > 1 ? kPartWaves * kMfmaTileBytes + NMAX * 256 : 16];
-  // FP8 rows are 8 bytes a lane: where the rings' body leaves fewer than four waves a SIMD (groups of more than 4 queries), four
-  // rows ahead make up for the missing waves' loads.  us with two / with four: 64 heads, 2 x 32000 tokens 47.5 / 45.5, 16 x
-  // 60000 571.7 / 553.0; with four waves (32 heads) 8 x 30011 87.4 / 86.7, 16 x 60000 279.6 / 280.8; 4 heads of 64 elements 16
-  // x 60000 41.8 / 42.9.
-  // FP8 rows of 128 elements, one query: eight lanes a row, 16 bytes each, which halves the reductions and exponentials per
-  // byte.  us of the step, with sixteen lanes / with eight: 32 heads, 2 x 100000 tokens 73.0 / 66.4, 16 x 60000 285 / 280, 8 x 30011
-  // 87.5 / 86.6 (three or four rows ahead instead of two: 89 / 88).
-  constexpr int kLpr = sizeof(KV) == 1 && D == 128 && GQ == 1 ? 8 : 16;
-  constexpr int kRegionUnr = sizeof(KV) == 1 && D == 128 && GQ == 1 && GW > 4 ? 4 : 2;
   const int Hs = Hq / GQ;
   const int region_units = dh.unit0[Hs], all_ring_units = Hkv * dh.ring_units;
   const int number = blockIdx.y * gridDim.x + blockIdx.x;
@@ -723,7 +714,7 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
       partial_rows_mfma<KV, GQ>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base, c.Vg_scale + base,
                                 r_begin, r_begin + len, visible, q0, scale, out, out_head, red, tiles);
     else
-      partial_rows<T, KV, D, GQ, kRegionUnr, kLpr>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base,
+      partial_rows<T, KV, D, GQ, LPR>((const KV*)c.Kg + base * D, (const KV*)c.Vg + base * D, c.Kg_scale + base,
                                  c.Vg_scale + base, r_begin, r_begin + len, visible, q0, scale, out, out_head, red);
   } else {
     const int kvh = ru.kvh, slot = ru.slot, h0 = kvh * GW;
@@ -744,7 +735,7 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
       partial_rows_mfma<KV, GW>((const KV*)c.ringK + base * D, (const KV*)c.ringV + base * D, c.ringK_scale + base,
                                 c.ringV_scale + base, r_begin, r_end, visible, q0, scale, out, out_head, red, tiles);
     else
-      partial_rows<T, KV, D, GW, 2, 16>((const KV*)c.ringK + base * D, (const KV*)c.ringV + base * D, c.ringK_scale + base,
+      partial_rows<T, KV, D, GW, 16>((const KV*)c.ringK + base * D, (const KV*)c.ringV + base * D, c.ringK_scale + base,
                                  c.ringV_scale + base, r_begin, r_end, visible, q0, scale, out, out_head, red);
   }
 }
@@ -1094,6 +1085,15 @@ static void order_units(DecodeHeads& dh, int Hs) {
   }
 }
 
+// FP8 rows of 128 elements that meet one query: eight lanes a row, 16 bytes each, which halves the reductions and exponentials per
+// byte, where chunks are this long; in shorter ones, of two or four rounds of 64 rows, sixteen lanes of 8 bytes have twice the loads to start
+// with (and with groups of one or two queries six and five waves a SIMD instead of four).  us per step with sixteen / with eight, chunks of
+// 1024 rows: 32 heads, 16 x 60000 tokens 278 / 272; of 512: 2 x 100000 72.9 / 63.7, 8 x 30011 86.2 / 83.3, 64 heads 164 / 154, 16 KV heads
+// 104 / 96, 32 KV heads 123 / 119; of 256: 4 x 30000 43.1 / 43.4, 16 KV heads 44.0 / 46.3; of 128: 2 x 16000 23.9 / 24.6, 4 x 12000
+// 29.9 / 30.5, 16 KV heads 2 x 16000 25.1 / 26.6, 32 KV heads 2 x 8000 23.0 / 25.4.  (Two rows ahead in both.  Four with eight lanes: 64
+// heads, 8 x 8000 52.9 instead of 52.2, 4 x 12000 39.2 instead of 38.6; with sixteen, 2 x 16000 37.5 instead of 37.1.)
+constexpr int kWideRows = 512;
+
 template <typename T, typename KV, int D>
 static int run_decode(const tca_params* prm, const tca_cache* c, const DecodeHeads& dh, int64_t units, const T* q,
                       const T* k_new, const T* v_new, T* O, void* ws, hipStream_t st) {
@@ -1103,14 +1103,16 @@ static int run_decode(const tca_params* prm, const tca_cache* c, const DecodeHea
   const double sc = logit_scale(prm);
   // (queries per region row, queries per ring row): (G, G) for a shared selection, else (1, G)
   const int G = Hq / Hkv;
-#define TCA_PARTIAL_CASE(GG)                                                                                    \
-  case GG:                                                                                                      \
-    if (GS > 1)                                                                                                 \
-      hipLaunchKernelGGL((decode_partial_kernel<T, KV, D, GG, GG>), dim3((unsigned)units, B), dim3(kPartThreads), 0, st, \
-                         *c, dh, Hq, Hkv, w, sc, q, k_new, v_new, dw.pos, dw.part);                             \
-    else                                                                                                        \
-      hipLaunchKernelGGL((decode_partial_kernel<T, KV, D, 1, GG>), dim3((unsigned)units, B), dim3(kPartThreads), 0, st, \
-                         *c, dh, Hq, Hkv, w, sc, q, k_new, v_new, dw.pos, dw.part);                             \
+  constexpr int kWideLpr = sizeof(KV) == 1 && D == 128 ? 8 : 16;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)units, B), dim3(kPartThreads), 0, st, *c, dh, Hq, Hkv, w, sc, q, k_new, v_new,
+                       dw.pos, dw.part);
+  };
+#define TCA_PARTIAL_CASE(GG)                                                                  \
+  case GG:                                                                                    \
+    if (GS > 1) launch(decode_partial_kernel<T, KV, D, GG, GG, 16>);                          \
+    else if (dh.chunk >= kWideRows) launch(decode_partial_kernel<T, KV, D, 1, GG, kWideLpr>); \
+    else launch(decode_partial_kernel<T, KV, D, 1, GG, 16>);                                  \
     break;
   switch (G) {
     TCA_PARTIAL_CASE(1) TCA_PARTIAL_CASE(2) TCA_PARTIAL_CASE(3) TCA_PARTIAL_CASE(4)

@@ -221,10 +221,11 @@ def test_load_global_copies_the_filled_rows_of_every_region(tb, bufs, case, kv):
 
 @pytest.mark.parametrize("rows", [0, 1, 31, 33, 130])
 @pytest.mark.parametrize("share", [False, True])
-def test_fp8_decode_reads_regions_from_any_eight_bytes(tb, bufs, rows, share):
-    """Region rows are read 16 bytes a lane where a row meets one query, 8 bytes elsewhere: buffers that start 8 bytes off a
-    16-byte boundary give the same bits.  Three sequences, region counts at the edges of a wave's rows, and no region at all."""
-    Hq, Hkv, d, b, w, B = 8, 2, 128, 16, 64, 3
+@pytest.mark.parametrize("B", [3, 320])
+def test_fp8_decode_reads_regions_from_any_eight_bytes(tb, bufs, rows, share, B):
+    """Region rows are read 16 bytes a lane where a row meets one query and chunks are long (320 sequences), 8 bytes elsewhere: buffers
+    that start 8 bytes off a 16-byte boundary give the same bits.  Region counts at the edges of a wave's rows, and no region at all."""
+    Hq, Hkv, d, b, w = 8, 2, 128, 16, 64
     prm = H.params_for(tb, Hq, Hkv, d, b, w, "bf16", share=share)
     Hs = Hkv if share else Hq
     P = np.stack([tb.tca_config_from_budget(b, 1.0, 0.3)] * Hs)
@@ -243,7 +244,8 @@ def test_fp8_decode_reads_regions_from_any_eight_bytes(tb, bufs, rows, share):
         moved[0].copy_(fill[0]); moved[1].copy_(fill[1]); c.ringK.copy_(ring[0]); c.ringV.copy_(ring[1])
         for t in (c.Kg_scale, c.Vg_scale, c.ringK_scale, c.ringV_scale):
             t.fill_(0.01)
-        c.length.copy_(torch.tensor([2000, 40, 1999]))
+        c.length.fill_(50)
+        c.length[:3].copy_(torch.tensor([2000, 40, 1999]))
         c.n_rows.fill_(rows)
         if rows:
             c.idx.copy_((torch.arange(rows, device="cuda") * 3).repeat(Hs)[None].expand(B, -1))
