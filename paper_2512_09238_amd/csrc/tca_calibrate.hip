@@ -35,12 +35,12 @@ constexpr int kCalThreads = 256;
 // grid (ceil(L / 128) * Hq), the longest walks first, heads inside (head by head, the last head's longest walks start when
 // the others are done: 16.0 against 10.1 ms for both passes); block 256: wave = 32 fixed rows, lane (kb = lane / 16, c = lane % 16)
 // holds, of every 16 streamed rows, the logits of the rows kb + 4 r against the fixed rows c and c + 16.
-// COL = false: the queries are fixed, keys 0 .. j stream by, row_max / row_sum are written.  COL = true: the keys are
+// COL = false: the queries are fixed, keys 0 .. j stream by, stats are written.  COL = true: the keys are
 // fixed, queries k .. L-1 stream by, abar is written.
 template <typename T, int D, bool COL>
 __global__ __launch_bounds__(kCalThreads, 2) void cal_pass_kernel(
-    const T* __restrict__ Q, const T* __restrict__ K, int64_t L, int Hq, int G, double scale,
-    double* __restrict__ row_max, double* __restrict__ row_sum, double* __restrict__ abar) {
+    const T* __restrict__ Q, const T* __restrict__ K, int64_t L, int Hq, int G, double scale, double2* __restrict__ stats,
+    double* __restrict__ abar, const int32_t* __restrict__ only) {
   typedef double f64x4_t __attribute__((ext_vector_type(4)));
   constexpr int EPC = Vec16<T>::N;                 // elements of a 16-byte chunk
   constexpr int CPR = D / EPC, CPQ = CPR / 4;      // chunks of a row, of a quarter row
@@ -52,11 +52,11 @@ __global__ __launch_bounds__(kCalThreads, 2) void cal_pass_kernel(
   __shared__ double rmx[COL ? TS : 1], rinv[COL ? TS : 1];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, kb = lane >> 4, c = lane & 15;
   const int h = blockIdx.x % Hq, kvh = h / G, turn = blockIdx.x / Hq;
+  if (only && !only[h]) return;
   const int64_t f0 = (int64_t)(COL ? turn : gridDim.x / Hq - 1 - turn) * 128;
   const T* fixed = COL ? K + (size_t)kvh * L * D : Q + (size_t)h * L * D;
   const T* stream = COL ? Q + (size_t)h * L * D : K + (size_t)kvh * L * D;
-  const double* rm = row_max + (size_t)h * L;
-  const double* rs = row_sum + (size_t)h * L;
+  const double2* const rows = stats + (size_t)h * L;                 // (maximum, sum)
 
   int64_t frow[2];
   double f[2][D / 4];                              // elements kb D/4 .. of the fixed rows
@@ -83,8 +83,9 @@ __global__ __launch_bounds__(kCalThreads, 2) void cal_pass_kernel(
       if (s0 + r < s_end) nxt[i] = load_raw16(stream + (size_t)(s0 + r) * D + ch * EPC);
     }
     if (COL && tid < TS && s0 + tid < s_end) {
-      nrm = rm[s0 + tid];
-      nri = 1.0 / rs[s0 + tid];
+      const double2 st = rows[s0 + tid];
+      nrm = st.x;
+      nri = 1.0 / st.y;
     }
   };
   double m[2] = {-INFINITY, -INFINITY}, l[2] = {0.0, 0.0};          // COL: l alone, the sum
@@ -172,7 +173,7 @@ __global__ __launch_bounds__(kCalThreads, 2) void cal_pass_kernel(
     if (kb == 0 && frow[b] < L) {
       const size_t at = (size_t)h * L + frow[b];
       if constexpr (COL) abar[at] = l[b] / (double)(L - frow[b]);
-      else { row_max[at] = m[b]; row_sum[at] = l[b]; }
+      else stats[at] = make_double2(m[b], l[b]);
     }
   }
 }
@@ -203,16 +204,23 @@ struct ExpTable { uint64_t t[kExpTable]; };
 
 static int64_t digit_groups(int64_t L) { return (L + 127) / 128 * (128 / kGroupRows); }       // per head, whole workgroups of the passes
 
-// grid (groups of all heads / 4); block 256, a wave per group.  Lane (kb, c) holds of row c the elements 64 s + 16 kb .. + 15
+// grid (groups of all heads of Q, then of K, / 4); block 256, a wave per group.  Lane (kb, c) holds of row c the elements 64 s + 16 kb .. + 15
 // of every step s, which is its operand of v_mfma_i32_16x16x64_i8 either way round; a group lies as [digit][step][lane][16
 // bytes], lowest digit first.
 template <int D>
-__global__ __launch_bounds__(256) void cal_digits_kernel(const bf16_t* __restrict__ X, int64_t L, int64_t groups, int64_t all,
-                                                         i32x4_t* __restrict__ digits, GroupInfo* __restrict__ info) {
+__global__ __launch_bounds__(256) void cal_digits_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, int64_t L,
+                                                         int64_t groups, int64_t q_groups, int64_t all, i32x4_t* __restrict__ Qd,
+                                                         i32x4_t* __restrict__ Kd, GroupInfo* __restrict__ q_info,
+                                                         GroupInfo* __restrict__ k_info) {
   constexpr int KS = D / 64;
   const int lane = threadIdx.x & 63, kb = lane >> 4, c = lane & 15;
-  const int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (g >= all) return;
+  const bool of_k = g >= q_groups;
+  if (of_k) g -= q_groups;
+  const bf16_t* const X = of_k ? K : Q;
+  i32x4_t* const digits = of_k ? Kd : Qd;
+  GroupInfo* const info = of_k ? k_info : q_info;
   const int64_t row = (g % groups) * kGroupRows + c;
   const bf16_t* x = X + ((size_t)(g / groups) * L + row) * D + kb * 16;
   uint32_t w[KS][8];
@@ -299,7 +307,7 @@ template <int D, bool COL>
 __global__ __launch_bounds__(kCalThreads, 3) void cal_digit_pass_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const i32x4_t* __restrict__ Qd, const i32x4_t* __restrict__ Kd,
     GroupInfo* __restrict__ q_info, const GroupInfo* __restrict__ k_info, int64_t L, int64_t groups, int Hq, int G, double unit,
-    double2* __restrict__ stats, double* __restrict__ abar, ExpTable table) {
+    double2* __restrict__ stats, double* __restrict__ abar, const int32_t* __restrict__ fp64_head, ExpTable table) {
   typedef double f64x4_t __attribute__((ext_vector_type(4)));
   constexpr int KS = D / 64;
   constexpr int TS = 2 * kGroupRows;               // streamed rows per tile
@@ -314,6 +322,7 @@ __global__ __launch_bounds__(kCalThreads, 3) void cal_digit_pass_kernel(
   const int tid = threadIdx.x, lane = tid & 63, kb = lane >> 4, c = lane & 15;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.x % Hq, kvh = h / G, turn = blockIdx.x / Hq;
+  if (fp64_head[h]) return;
   const int64_t f0 = (int64_t)(COL ? turn : gridDim.x / Hq - 1 - turn) * 128;
   const int64_t wave0 = f0 + wv * 32;
   const bf16_t* const fixed = COL ? K + (size_t)kvh * L * D : Q + (size_t)h * L * D;
@@ -649,8 +658,7 @@ __global__ void cal_zero_kernel(int32_t* p, int64_t n) {
 
 struct CalWs {
   void* select_ws;      // tokrank + stats (+ one blk_t/blk_dst pair, unused here)
-  double* row_max;      // [Hq][L]
-  double* row_sum;      // [Hq][L]
+  double2* stats;       // [Hq][L] of a query's row: reference and sum, or (digits) its inverse
   double* abar;         // [Hq][L]
   int32_t* blk_t;       // [M][Hs][nb]   (Hs selection heads <= Hq; sized for Hq)
   int32_t* blk_dst;     // [M][Hs][nb]
@@ -672,8 +680,7 @@ static CalWs carve_cal_ws(void* ws, const tca_params* prm, int64_t L, int M) {
   const int64_t nb = L / prm->block;
   const size_t sel = carve_select_ws(nullptr, prm, L).bytes;
   c.select_ws = base + off;          off = align_up(off + sel, 256);
-  c.row_max = (double*)(base + off); off = align_up(off + (size_t)Hq * L * 8, 256);
-  c.row_sum = (double*)(base + off); off = align_up(off + (size_t)Hq * L * 8, 256);
+  c.stats = (double2*)(base + off);  off = align_up(align_up(off + (size_t)Hq * L * 8, 256) + (size_t)Hq * L * 8, 256);
   c.abar = (double*)(base + off);    off = align_up(off + (size_t)Hq * L * 8, 256);
   c.blk_t = (int32_t*)(base + off);  off = align_up(off + (size_t)M * Hq * nb * 4, 256);
   c.blk_dst = (int32_t*)(base + off); off = align_up(off + (size_t)M * Hq * nb * 4, 256);
@@ -693,14 +700,41 @@ static CalWs carve_cal_ws(void* ws, const tca_params* prm, int64_t L, int M) {
   return c;
 }
 
+// grid Hq; block 128
 template <typename T>
 __global__ void cal_gather_qlast_kernel(const T* __restrict__ Q, int64_t L, int D, T* __restrict__ out) {
   const int h = blockIdx.x;
   for (int e = threadIdx.x; e < D; e += blockDim.x) out[(size_t)h * D + e] = Q[((size_t)h * L + (L - 1)) * D + e];
 }
 
+// The same for bf16 samples, cal_zero_kernel's work, and which heads take the fp64 passes: those of whose pairs of groups more than half are not to be
+// had in digits.  Such a pair costs the digit passes 1.6 times what the fp64 ones take for it, any other a fourth.  8192 tokens, 32
+// heads, keys with channels 2^8, 2^12 and 2^16 times the others (a few, most, all of the pairs): ms with digits 4.8, 10.2 and 16.6, in
+// fp64 10.1.  grid Hq; block 256
+__global__ __launch_bounds__(256) void cal_heads_kernel(const bf16_t* __restrict__ Q, int64_t L, int D, bf16_t* __restrict__ out,
+                                                        int64_t groups, int G, const GroupInfo* __restrict__ q_info,
+                                                        const GroupInfo* __restrict__ k_info, int32_t* __restrict__ fp64_head,
+                                                        int32_t* __restrict__ zeros, int n_zeros) {
+  __shared__ int odd[2];
+  const int h = blockIdx.x, tid = threadIdx.x;
+  if (tid < 2) odd[tid] = 0;
+  for (int i = h * 256 + tid; i < n_zeros; i += gridDim.x * 256) zeros[i] = 0;
+  if (tid < D) out[(size_t)h * D + tid] = Q[((size_t)h * L + (L - 1)) * D + tid];
+  int q = 0, k = 0;
+#pragma unroll 4
+  for (int64_t g = tid; g < groups; g += 256) {
+    q += (q_info[(size_t)h * groups + g].word & kOddGroup) != 0;
+    k += (k_info[(size_t)(h / G) * groups + g].word & kOddGroup) != 0;
+  }
+  __syncthreads();
+  if (q) atomicAdd(&odd[0], q);
+  if (k) atomicAdd(&odd[1], k);
+  __syncthreads();
+  if (tid == 0) fp64_head[h] = 2 * (groups - odd[0]) * (groups - odd[1]) < groups * groups;
+}
+
 template <int D>
-static void run_digit_passes(const tca_params* prm, const bf16_t* Q, const bf16_t* K, int64_t L, const CalWs& c, hipStream_t st) {
+static void run_digit_passes(const tca_params* prm, const bf16_t* Q, const bf16_t* K, int64_t L, int M, const CalWs& c, hipStream_t st) {
   const int Hq = prm->n_q_heads, Hkv = prm->n_kv_heads;
   const int64_t groups = digit_groups(L);
   const dim3 grid((unsigned)((L + 127) / 128 * Hq));
@@ -714,34 +748,35 @@ static void run_digit_passes(const tca_params* prm, const bf16_t* Q, const bf16_
     return t;
   }();
   const double unit = (double)(logit_scale(prm) * (kExpTable * 1.44269504088896340735992468100189214L));
-  auto digits = [&](const bf16_t* x, int heads, i32x4_t* to, GroupInfo* info) {
-    const int64_t all = groups * heads;
-    hipLaunchKernelGGL((cal_digits_kernel<D>), dim3((unsigned)((all + 3) / 4)), dim3(256), 0, st, x, L, groups, all, to, info);
+  const int G = Hq / Hkv;
+  const int64_t q_groups = groups * Hq, all = q_groups + groups * Hkv;
+  hipLaunchKernelGGL((cal_digits_kernel<D>), dim3((unsigned)((all + 3) / 4)), dim3(256), 0, st, Q, K, L, groups, q_groups, all, c.Qd, c.Kd,
+                     c.q_info, c.k_info);
+  int32_t* const fp64_head = (int32_t*)c.n_dev;                      // [Hq], where the candidates' sizes come later
+  hipLaunchKernelGGL(cal_heads_kernel, dim3(Hq), dim3(256), 0, st, Q, L, D, (bf16_t*)c.q_last, groups, G, c.q_info, c.k_info, fp64_head,
+                     c.n_rows, M * sel_heads(prm));
+  auto pass = [&](auto kernel, auto fp64_kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kCalThreads), 0, st, Q, K, c.Qd, c.Kd, c.q_info, c.k_info, L, groups, Hq, G, unit, c.stats,
+                       c.abar, fp64_head, table);
+    hipLaunchKernelGGL(fp64_kernel, grid, dim3(kCalThreads), 0, st, Q, K, L, Hq, G, logit_scale(prm), c.stats, c.abar, fp64_head);
   };
-  digits(Q, Hq, c.Qd, c.q_info);
-  digits(K, Hkv, c.Kd, c.k_info);
-  auto pass = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(kCalThreads), 0, st, Q, K, c.Qd, c.Kd, c.q_info, c.k_info, L, groups, Hq, Hq / Hkv, unit,
-                       (double2*)c.row_max, c.abar, table);
-  };
-  pass(cal_digit_pass_kernel<D, false>);
-  pass(cal_digit_pass_kernel<D, true>);
+  pass(cal_digit_pass_kernel<D, false>, cal_pass_kernel<bf16_t, D, false>);
+  pass(cal_digit_pass_kernel<D, true>, cal_pass_kernel<bf16_t, D, true>);
 }
 
 template <typename T, int D>
-static void run_passes(const tca_params* prm, const T* Q, const T* K, int64_t L, const CalWs& c, bool digits, hipStream_t st) {
+static void run_passes(const tca_params* prm, const T* Q, const T* K, int64_t L, int M, const CalWs& c, bool digits, hipStream_t st) {
   const int Hq = prm->n_q_heads, G = Hq / prm->n_kv_heads;
   const dim3 grid((unsigned)((L + 127) / 128 * Hq));
   const double sc = logit_scale(prm);
   if constexpr (sizeof(T) == 2) {
     if (digits) {
-      run_digit_passes<D>(prm, Q, K, L, c, st);
-      hipLaunchKernelGGL((cal_gather_qlast_kernel<T>), dim3(Hq), dim3(128), 0, st, Q, L, D, (T*)c.q_last);
+      run_digit_passes<D>(prm, Q, K, L, M, c, st);
       return;
     }
   }
-  hipLaunchKernelGGL((cal_pass_kernel<T, D, false>), grid, dim3(kCalThreads), 0, st, Q, K, L, Hq, G, sc, c.row_max, c.row_sum, c.abar);
-  hipLaunchKernelGGL((cal_pass_kernel<T, D, true>), grid, dim3(kCalThreads), 0, st, Q, K, L, Hq, G, sc, c.row_max, c.row_sum, c.abar);
+  hipLaunchKernelGGL((cal_pass_kernel<T, D, false>), grid, dim3(kCalThreads), 0, st, Q, K, L, Hq, G, sc, c.stats, c.abar, nullptr);
+  hipLaunchKernelGGL((cal_pass_kernel<T, D, true>), grid, dim3(kCalThreads), 0, st, Q, K, L, Hq, G, sc, c.stats, c.abar, nullptr);
   hipLaunchKernelGGL((cal_gather_qlast_kernel<T>), dim3(Hq), dim3(128), 0, st, Q, L, D, (T*)c.q_last);
 }
 
@@ -774,7 +809,7 @@ extern "C" int tca_calibrate_budgets(const tca_params* prm, const void* Qcal, co
   if (ws_bytes < need || ((uintptr_t)ws & 255))
     return fail(TCA_ERR_WORKSPACE, "tca_calibrate_budgets: workspace needs %zu bytes, 256-byte aligned", need);
   hipStream_t st = (hipStream_t)stream;
-  const bool digits = ws_bytes >= c.bytes;
+  const bool digits = prm->dtype == TCA_BF16 && ws_bytes >= c.bytes;
 
   std::vector<double> cands((size_t)M * nk);
   rc = tca_make_candidates(b, M, sigma, cands.data());
@@ -783,12 +818,12 @@ extern "C" int tca_calibrate_budgets(const tca_params* prm, const void* Qcal, co
   // column means of the dense causal attention matrix (Alg. 1 line 1, Eq. 4)
   if (prm->dtype == TCA_BF16) {
     using T = bf16_t;
-    if (prm->head_dim == 128) run_passes<T, 128>(prm, (const T*)Qcal, (const T*)Kcal, L_cal, c, digits, st);
-    else run_passes<T, 64>(prm, (const T*)Qcal, (const T*)Kcal, L_cal, c, digits, st);
+    if (prm->head_dim == 128) run_passes<T, 128>(prm, (const T*)Qcal, (const T*)Kcal, L_cal, M, c, digits, st);
+    else run_passes<T, 64>(prm, (const T*)Qcal, (const T*)Kcal, L_cal, M, c, digits, st);
   } else {
     using T = float;
-    if (prm->head_dim == 128) run_passes<T, 128>(prm, (const T*)Qcal, (const T*)Kcal, L_cal, c, digits, st);
-    else run_passes<T, 64>(prm, (const T*)Qcal, (const T*)Kcal, L_cal, c, digits, st);
+    if (prm->head_dim == 128) run_passes<T, 128>(prm, (const T*)Qcal, (const T*)Kcal, L_cal, M, c, digits, st);
+    else run_passes<T, 64>(prm, (const T*)Qcal, (const T*)Kcal, L_cal, M, c, digits, st);
   }
 
   // selection of every candidate (Alg. 1 line 4): scores and ranks once, budgets per candidate
@@ -798,7 +833,7 @@ extern "C" int tca_calibrate_budgets(const tca_params* prm, const void* Qcal, co
   std::vector<int64_t> n_host((size_t)Hs * M, 0);
   if (nb > 0) {
     const int64_t nz = (int64_t)M * Hs;
-    hipLaunchKernelGGL(cal_zero_kernel, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, c.n_rows, nz);
+    if (!digits) hipLaunchKernelGGL(cal_zero_kernel, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, c.n_rows, nz);
     select_assign_all(prm, L_cal, M, cands.data(), sw.sel_stats, c.n_rows, c.blk_t, c.blk_dst, st);
     hipLaunchKernelGGL(cal_cand_score_kernel, dim3(M, Hs), dim3(kCalThreads), 0, st, sw.tokrank, c.blk_t, c.abar,
                        L_cal, b, nb, Hs, sel_group(prm), M, c.a_dev, c.n_dev);

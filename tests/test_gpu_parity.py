@@ -1098,7 +1098,7 @@ def test_calibrate_at_the_edges_of_its_tiles(tb, bufs, case):
 
 # What the elements of a bf16 sample are to each other decides how its products are formed: (of 16 rows that share an exponent)
 # with a lowest digit, with one element left out (of K, of Q, of both at one column), with several, with logits in the thousands
-CALIB_ELEMENTS = ["plain", "low", "rest_k", "rest_q", "rest_both", "odd_k", "odd_q", "far", "far_rows", "far_first"]
+CALIB_ELEMENTS = ["plain", "low", "rest_k", "rest_q", "rest_both", "odd_k", "odd_q", "far", "far_rows", "far_first", "odd_all", "odd_head"]
 
 
 @pytest.mark.parametrize("d,L", [(128, 333), (64, 160)])
@@ -1122,6 +1122,10 @@ def test_calibrate_whatever_the_elements_span(tb, bufs, kind, d, L):
         K[:, 64:96, 7] = tiny
     if kind == "odd_q":
         Q[:, 64:67, 9] = tiny
+    if kind in ("odd_all", "odd_head"):                              # outlier channels: most groups are odd, of all heads or of one KV head's
+        n = Hkv if kind == "odd_all" else 1
+        K[:n, :, [3, 40]] *= 2.0 ** 16
+        Q[:n * (Hq // Hkv), :, [3, 40]] *= 2.0 ** -16
     if kind == "far":
         Q *= 1024.0
     if kind == "far_rows":                                           # the references of a few queries, far below the others'
