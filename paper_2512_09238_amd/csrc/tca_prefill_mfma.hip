@@ -1027,11 +1027,7 @@ void prefill_mfma_kernel(
           __builtin_amdgcn_s_waitcnt(0x0F70);
           __syncthreads();
         }
-        if constexpr (SPLIT) {
-          float* const ml = sp.part + (size_t)item * split_floats<D>() + 128 * D;
-          if (hh == 0) { ml[wv * 32 + c] = -INFINITY; ml[128 + wv * 32 + c] = 0.f; }
-        }
-        return;
+        return;                                        // (the merge of chunks reads no row without a query)
       }
     }
     // K(0), V(0) are in (GATHER: the positions just requested count among the newest as well)
