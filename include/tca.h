@@ -141,8 +141,9 @@ size_t tca_select_workspace_bytes(const tca_params* prm, int64_t n_tokens);
 size_t tca_prefill_workspace_bytes(const tca_params* prm, int64_t n_queries, int64_t cap_rows);
 /* max_head_rows: the largest capacity of one head's region, max_h (offs[h+1]-offs[h]). */
 size_t tca_decode_workspace_bytes(const tca_params* prm, int batch, int64_t max_head_rows);
-/* TCA_BF16: includes 4 bytes per element of Qcal and Kcal (their digits).  A call with less than that, down to the size
- * without them, gives the same results in about three times the time. */
+/* TCA_BF16: includes the digits of Qcal and Kcal, 4 bytes per element and 16 per 16 rows of every head, rows rounded up to 128.
+ * A call with less than that, down to what the same parameters with dtype TCA_F32 ask for, gives the same results (within the
+ * rounding of fp64) in up to four times the time. */
 size_t tca_calibrate_workspace_bytes(const tca_params* prm, int64_t L_cal, int M);
 
 /* ---------------------------------------------------------------- device --*/

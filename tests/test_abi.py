@@ -98,6 +98,15 @@ def test_argument_errors_are_codes_not_crashes():
     assert tb.tca_select_workspace_bytes(ok, 131072) > 4 * 131072
 
 
+@pytest.mark.parametrize("L,d", [(1, 64), (333, 128), (8192, 128)])
+def test_calibration_workspace_without_the_digits(L, d):
+    """What a bf16 call asks for over the same call in fp32: 4 bytes per element, 16 per 16 rows, rows rounded up to 128."""
+    import paper_2512_09238_amd.binding as tb
+    bf16, f32 = (tb.tca_calibrate_workspace_bytes(tb.make_params(8, 2, d, 32, 64, t), L, 5) for t in (tb.TCA_BF16, tb.TCA_F32))
+    rows = (8 + 2) * (-(-L // 128) * 128)
+    assert 0 <= bf16 - f32 - (rows * d * 4 + rows // 16 * 16) < 4 * 256
+
+
 def test_prefill_query_tiles_by_the_length_of_the_walk():
     """Host logic of the bf16 prefill launch: 256 queries a workgroup in calls of many query tiles, and of fewer (1024 in all
     at least) where each walks a long context; otherwise 128, and rows fetched through their positions do not ask for it."""
