@@ -41,9 +41,11 @@ __global__ __launch_bounds__(256) void merge_parts_kernel(T* __restrict__ Oa, co
 // score units, as the kernel keeps them).  grid (query tiles, Hq, D / 32); block 256: wave = 32 queries, lane =
 // (half, query) with 4 x 4 of the D / 32 slice's columns, the layout the accumulators were left in: coalesced reads.
 // Bound by latency: 27 MB of parts for 413 queries of 32 heads behind 64K tokens (6 us at the copy
-// rate).  The references, eight at a time, and the first four chunks are requested together, four more ahead of every four; a
-// place behind the last chunk is the last one again with the weight zero, so that no chunk's loads wait for another's (a loop with a
-// remainder took 12.4 us there, now 8.8).  217 registers leave two waves a SIMD, which the grid seldom exceeds.
+// rate).  The references, eight at a time, and the first two chunks are requested together, two more ahead of every two; a
+// place behind the last chunk is the last one again with the weight zero, so that no chunk's loads wait for another's.  us, a loop with
+// a remainder and four chunks in flight / this / four at a time, whose 217 registers leave two waves a SIMD instead of three: there
+// 11.1 / 7.4 / 8.7; 413 of 64 heads 18.6 / 13.1 / 14.3; 9000 tokens of 4 heads of 64 elements (568 workgroups) 8.6 / 8.0 / 9.4; 1 behind
+// 8192, 32 heads, 9.5 / 4.9 / 4.7.
 // A chunk is empty if its sum l is 0; one whose sum is NaN (a key or a query that is not finite) takes part.  (The file of
 // the attention kernel is compiled without regard for NaN, this one is not.)
 template <int D>
@@ -60,7 +62,7 @@ __global__ __launch_bounds__(256) void merge_split_kernel(SplitPlan sp, int64_t 
   const int q = wv * 32 + c;
   const int64_t r = (int64_t)qtile * 128 + q;
   if (r >= n_queries) return;
-  constexpr int kAhead = 4, kRef = 8;
+  constexpr int kAhead = 2, kRef = 8;
   f32x4_t v[2][kAhead][4];
   float m[2][kAhead], l[2][kAhead], ref[kRef];
   auto load = [&](int b, int s0) {

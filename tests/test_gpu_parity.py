@@ -725,7 +725,7 @@ def test_waves_without_a_query(tb, bufs, case):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("tiles,count", [(8, 0), (24, 8), (31, 9), (32, 10), (34, 10), (63, 17), (66, 18), (95, 25), (98, 26), (130, 34)])
 def test_any_number_of_chunks_is_merged(tb, bufs, tiles, count, d):
-    """The chunks of an item are read four at a time, two rounds ahead, and their references eight at a time: the output and the
+    """The chunks of an item are read two at a time, two rounds ahead, and their references eight at a time: the output and the
     log-sum-exp against the oracle on either side of each of these.  Of the two heads one has a tile more than the other: count
     (of a call cut by the present rule) is of 4 and 4 chunks, 4 and 5, 5 and 5, 8 and 9, 9 and 9, 12 and 13, 13 and 13, 17 and 17."""
     print("case", tiles, d, flush=True)
