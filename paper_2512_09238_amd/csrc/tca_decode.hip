@@ -52,6 +52,7 @@ struct DecodeHeads {
   uint8_t by_units[TCA_MAX_HEADS];    // the heads, those with the most units first
   int32_t chunk;                      // rows per unit
   int32_t ring_units;                 // units of one ring
+  int32_t units;                      // of a sequence: those of its rings and regions
 };
 
 // Partials of a sequence: region [selection head][its query heads][its units], then ring [query head][ring_units];
@@ -671,8 +672,9 @@ __global__ __launch_bounds__(kPartThreads) void decode_partial_kernel(
   constexpr bool kMfma = D == 128 && (sizeof(KV) == 2 || (sizeof(KV) == 1 && GW > 2));
   __shared__ __attribute__((aligned(16))) unsigned char tiles[kMfma && NMAX > 1 ? kPartWaves * kMfmaTileBytes + NMAX * 256 : 16];
   const int Hs = Hq / GQ;
-  const int region_units = dh.unit0[Hs], all_ring_units = Hkv * dh.ring_units;
-  const int number = blockIdx.y * gridDim.x + blockIdx.x;
+  const int all_ring_units = Hkv * dh.ring_units, region_units = dh.units - all_ring_units;
+  // (dh.units, not gridDim.x or from unit0: those are lines of their own to wait for, 0.5 us of a step)
+  const int number = blockIdx.y * dh.units + blockIdx.x;
   const int id = number - c.batch * all_ring_units;                   // < 0: a ring's
   RingUnit ru = {};
   if (id < 0) ru = ring_unit(number, c.length, c.batch, Hkv, dh.ring_units, w);
@@ -1048,7 +1050,9 @@ static int64_t set_chunk(DecodeHeads& dh, const tca_params* prm, int chunk) {
   dh.unit0[Hs] = (int32_t)run;
   dh.chunk = chunk;
   dh.ring_units = (int32_t)chunks_of(prm->window, chunk);
-  return run + (int64_t)prm->n_kv_heads * dh.ring_units;
+  run += (int64_t)prm->n_kv_heads * dh.ring_units;
+  dh.units = (int32_t)run;
+  return run;
 }
 
 static size_t ws_of(const DecodeHeads& dh, const tca_params* prm, int batch) {
