@@ -183,7 +183,10 @@ __global__ __launch_bounds__(kCalThreads, 2) void cal_pass_kernel(
 // these four signed digits of 8 bits: a logit is then the sum of sixteen int8 matrix products, each exact (128 products of
 // 2^14, four sums of them: at most 2^23), added up by weight in fp64.  One int8 product takes a 64th of the fp64 one, and
 // the lowest digit is seldom there.  An element whose bits would fall off the end, below 2^-24 of the group's largest, is left
-// out of the digits and added by itself; a group with several, or with one that is not finite, has its products in fp64.
+// out of the digits and added by itself; a group with several, or with one that is not finite, has its products in fp64 (and a head
+// with many such groups takes the fp64 passes: cal_heads_kernel).  What the sample holds decides the time: 8192 tokens of 32 heads,
+// Gaussian elements 2.8 ms, with references far from zero 4.3, with channels 2^4, 2^8 and 2^12 times the others 4.3, 4.8 and 10.2, in
+// fp64 throughout 10.1.
 constexpr int kDigits = 4;
 constexpr int kGroupRows = 16;                     // rows that share an exponent
 constexpr int kDigitBias = 127 + 7 + 23;           // a group of exponent e holds its elements times 2^(kDigitBias - e)

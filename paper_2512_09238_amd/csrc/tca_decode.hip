@@ -2,16 +2,17 @@
 // completed while decoding (Sec. IV-B, "Online Token Selection in Decoding Stage").
 //
 // One step = two launches on the caller's stream:
-//   partial : split-K attention.  grid (unit, sequence); a unit is a chunk of rows of one
-//             head's global region, or of one KV head's ring, and there is one for every chunk
-//             of the region's capacity (heads keep different numbers of rows; a grid of heads x
-//             longest head had two workgroups of three find nothing to do).  The host does not know
+//   partial : split-K attention.  grid (units of a sequence, sequences), numbered through: the units of
+//             all rings first.  A unit is a chunk of rows of one head's global region, or of one KV
+//             head's ring, and there is one for every chunk of the region's capacity (heads keep
+//             different numbers of rows; a grid of heads x longest head had two workgroups of three
+//             find nothing to do).  The host does not know
 //             how full a region is: in a cache with room for far more than it holds, units behind
 //             the last row return at once, and the chunk length is chosen as for a full one.
 //             The rows that have left the window (idx <= T-w; idx is ascending, so a prefix of the
 //             chunk) are found by a 64-way search, one load as a rule.  The unit that holds the new
 //             row's ring slot writes the row there first.  The 256 threads form sixteen 16-lane
-//             groups, each streaming whole rows with 16-byte loads and keeping its own online
+//             groups (or 32 of eight: kWideRows), each streaming whole rows and keeping its own online
 //             softmax; groups are merged into one (max, sum, acc[D]) partial per unit and query head.
 //             HBM-bound: every K/V row is read once per selection head - once per query head,
 //             or, when the group shares one selection, once per KV head with every row scored
